@@ -1,12 +1,18 @@
-"""ctypes binding of libmc_kv.so: the same names as include/mc_kv.h, argument
-marshalling only.  Device buffers are torch tensors (or raw integer addresses);
-every step of the path runs in the library's HIP kernels.  There is no fallback:
-if the library is missing or a call fails, this raises."""
+"""Binding of libmc_kv.so: the same names as include/mc_kv.h, argument marshalling
+only.  Device buffers are torch tensors (or raw integer addresses); every step of
+the path runs in the library's HIP kernels.  There is no fallback: if the library
+is missing or a call fails, this raises.
+
+The calls an engine makes per layer or per request go through _calls.so
+(csrc/py_calls.cc), which turns their arguments into C values in native code; the
+rest, made once per pool or per plan, go through ctypes.  Both call the same C ABI."""
 import ctypes as C
+import importlib
 import os
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.path.join(HERE, "libmc_kv.so")
+CALLS_PATH = os.path.join(HERE, "_calls.so")
 
 MC_OK, MC_ERR_INVALID, MC_ERR_NO_PAGES, MC_ERR_RANGE, MC_ERR_ALIAS, MC_ERR_UNSUPPORTED, \
     MC_ERR_HIP = range(7)
@@ -42,6 +48,17 @@ class mc_pool_desc(C.Structure):
                 ("dtype", C.c_int32), ("skipped", C.c_void_p)]
 
 
+class _LazyCalls:
+    """Stands in for the native module until the first call that needs it."""
+
+    def __getattr__(self, name):
+        global _calls
+        lib()                        # builds what is missing; loads libmc_kv.so
+        _calls = importlib.import_module("._calls", __package__)
+        return getattr(_calls, name)
+
+
+_calls = _LazyCalls()
 _lib = None
 
 
@@ -50,7 +67,7 @@ def lib():
     global _lib
     if _lib is not None:
         return _lib
-    if not os.path.exists(LIB_PATH):
+    if not (os.path.exists(LIB_PATH) and os.path.exists(CALLS_PATH)):
         from . import build as _build
         _build.build()
     L = C.CDLL(LIB_PATH)
@@ -155,13 +172,13 @@ def mc_kv_allocator_destroy(alloc):
 
 
 def mc_kv_alloc_pages(alloc, n: int):
-    out = (C.c_int32 * max(n, 1))()
-    _check(lib().mc_kv_alloc_pages(alloc, n, out), "mc_kv_alloc_pages")
-    return list(out[:n])
+    st, pages = _calls.alloc_pages(alloc, n)
+    _check(st, "mc_kv_alloc_pages")
+    return pages
 
 
 def mc_kv_free_pages(alloc, pages):
-    _check(lib().mc_kv_free_pages(alloc, len(pages), _i32_array(pages)), "mc_kv_free_pages")
+    _check(_calls.free_pages(alloc, pages), "mc_kv_free_pages")
 
 
 def mc_kv_allocator_num_free(alloc) -> int:
@@ -172,7 +189,7 @@ def mc_kv_allocator_num_free(alloc) -> int:
 
 def mc_kv_check_page_table(pages, num_pages: int) -> int:
     """Returns the status code (MC_OK / MC_ERR_RANGE / MC_ERR_ALIAS) instead of raising."""
-    return lib().mc_kv_check_page_table(_i32_array(pages), len(pages), num_pages)
+    return _calls.check_page_table(pages, num_pages)
 
 
 # ---- device calls -------------------------------------------------------------
@@ -188,18 +205,16 @@ def mc_kv_copy_check(pool: mc_pool_desc, stream=None) -> int:
 
 def mc_kv_append(pool: mc_pool_desc, layer, k_new, v_new, batch, total_q, cu_q, begin,
                  page_table, cu_pages, stream=None):
-    _check(lib().mc_kv_append(C.byref(pool), layer, _ptr(k_new), _ptr(v_new), batch, total_q,
-                              _ptr(cu_q), _ptr(begin), _ptr(page_table), _ptr(cu_pages),
-                              _stream(stream)), "mc_kv_append")
+    _check(_calls.append(pool, layer, k_new, v_new, batch, total_q, cu_q, begin, page_table,
+                         cu_pages, stream), "mc_kv_append")
 
 
 def mc_kv_append_send(pool: mc_pool_desc, layer, k_new, v_new, batch, total_q, cu_q, begin,
                       page_table, cu_pages, send_layer_begin, s0, s1, buf_offset, sendbuf,
                       stream=None):
-    _check(lib().mc_kv_append_send(C.byref(pool), layer, _ptr(k_new), _ptr(v_new), batch, total_q,
-                                   _ptr(cu_q), _ptr(begin), _ptr(page_table), _ptr(cu_pages),
-                                   send_layer_begin, _ptr(s0), _ptr(s1), _ptr(buf_offset),
-                                   _ptr(sendbuf), _stream(stream)), "mc_kv_append_send")
+    _check(_calls.append_send(pool, layer, k_new, v_new, batch, total_q, cu_q, begin, page_table,
+                              cu_pages, send_layer_begin, s0, s1, buf_offset, sendbuf, stream),
+           "mc_kv_append_send")
 
 
 def mc_attn_workspace_size(batch, total_q, num_q_heads, num_kv_heads) -> int:
@@ -208,17 +223,14 @@ def mc_attn_workspace_size(batch, total_q, num_q_heads, num_kv_heads) -> int:
 
 def mc_attn_plan(pool: mc_pool_desc, num_q_heads, batch, total_q, cu_q, begin, page_table,
                  cu_pages, workspace, workspace_bytes, stream=None):
-    _check(lib().mc_attn_plan(C.byref(pool), num_q_heads, batch, total_q, _ptr(cu_q), _ptr(begin),
-                              _ptr(page_table), _ptr(cu_pages), _ptr(workspace), workspace_bytes,
-                              _stream(stream)), "mc_attn_plan")
+    _check(_calls.plan(pool, num_q_heads, batch, total_q, cu_q, begin, page_table, cu_pages, 0,
+                       workspace, workspace_bytes, stream), "mc_attn_plan")
 
 
 def mc_attn_plan_ahead(pool: mc_pool_desc, num_q_heads, batch, total_q, cu_q, begin, page_table,
                        cu_pages, ahead_tokens, workspace, workspace_bytes, stream=None):
-    _check(lib().mc_attn_plan_ahead(C.byref(pool), num_q_heads, batch, total_q, _ptr(cu_q),
-                                    _ptr(begin), _ptr(page_table), _ptr(cu_pages), ahead_tokens,
-                                    _ptr(workspace), workspace_bytes, _stream(stream)),
-           "mc_attn_plan_ahead")
+    _check(_calls.plan(pool, num_q_heads, batch, total_q, cu_q, begin, page_table, cu_pages,
+                       ahead_tokens, workspace, workspace_bytes, stream), "mc_attn_plan_ahead")
 
 
 def mc_attn_plan_check(workspace, stream=None):
@@ -228,78 +240,61 @@ def mc_attn_plan_check(workspace, stream=None):
 def mc_prefix_prefill_attn(pool: mc_pool_desc, layer, q, num_q_heads, batch, total_q, cu_q, begin,
                            page_table, cu_pages, sm_scale, out, lse, workspace, workspace_bytes,
                            stream=None):
-    _check(lib().mc_prefix_prefill_attn(C.byref(pool), layer, _ptr(q), num_q_heads, batch, total_q,
-                                        _ptr(cu_q), _ptr(begin), _ptr(page_table), _ptr(cu_pages),
-                                        float(sm_scale), _ptr(out), _ptr(lse), _ptr(workspace),
-                                        workspace_bytes, _stream(stream)),
+    _check(_calls.attn(pool, layer, q, num_q_heads, batch, total_q, cu_q, begin, page_table,
+                       cu_pages, sm_scale, out, lse, workspace, workspace_bytes, stream),
            "mc_prefix_prefill_attn")
 
 
 def mc_prefix_prefill_attn_noalloc(pool: mc_pool_desc, layer, q, num_q_heads, batch, total_q, cu_q,
                                    begin, page_table, cu_pages, sm_scale, out, lse, stream=None):
-    _check(lib().mc_prefix_prefill_attn_noalloc(C.byref(pool), layer, _ptr(q), num_q_heads, batch,
-                                                total_q, _ptr(cu_q), _ptr(begin),
-                                                _ptr(page_table), _ptr(cu_pages), float(sm_scale),
-                                                _ptr(out), _ptr(lse), _stream(stream)),
+    _check(_calls.attn_noalloc(pool, layer, q, num_q_heads, batch, total_q, cu_q, begin,
+                               page_table, cu_pages, sm_scale, out, lse, stream),
            "mc_prefix_prefill_attn_noalloc")
 
 
 def mc_kv_pack_range(pool: mc_pool_desc, layer_begin, layer_end, pages, n_table_pages, s0, s1,
                      sendbuf, stream=None):
-    _check(lib().mc_kv_pack_range(C.byref(pool), layer_begin, layer_end, _ptr(pages),
-                                  n_table_pages, s0, s1, _ptr(sendbuf), _stream(stream)),
-           "mc_kv_pack_range")
+    _check(_calls.pack_range(pool, layer_begin, layer_end, pages, n_table_pages, s0, s1, sendbuf,
+                             stream), "mc_kv_pack_range")
 
 
 def mc_kv_unpack_range(pool: mc_pool_desc, layer_begin, layer_end, pages, n_table_pages, s0, s1,
                        sendbuf, stream=None):
-    _check(lib().mc_kv_unpack_range(C.byref(pool), layer_begin, layer_end, _ptr(pages),
-                                    n_table_pages, s0, s1, _ptr(sendbuf), _stream(stream)),
-           "mc_kv_unpack_range")
+    _check(_calls.unpack_range(pool, layer_begin, layer_end, pages, n_table_pages, s0, s1, sendbuf,
+                               stream), "mc_kv_unpack_range")
 
 
 def mc_kv_pack_batch(pool: mc_pool_desc, layer_begin, layer_end, batch, page_table, cu_pages, s0,
                      s1, buf_offset, max_range_pages, sendbuf, stream=None):
-    _check(lib().mc_kv_pack_batch(C.byref(pool), layer_begin, layer_end, batch, _ptr(page_table),
-                                  _ptr(cu_pages), _ptr(s0), _ptr(s1), _ptr(buf_offset),
-                                  max_range_pages, _ptr(sendbuf), _stream(stream)),
-           "mc_kv_pack_batch")
+    _check(_calls.pack_batch(pool, layer_begin, layer_end, batch, page_table, cu_pages, s0, s1,
+                             buf_offset, max_range_pages, sendbuf, stream), "mc_kv_pack_batch")
 
 
 def mc_kv_unpack_batch(pool: mc_pool_desc, layer_begin, layer_end, batch, page_table, cu_pages,
                        s0, s1, buf_offset, max_range_pages, sendbuf, stream=None):
-    _check(lib().mc_kv_unpack_batch(C.byref(pool), layer_begin, layer_end, batch,
-                                    _ptr(page_table), _ptr(cu_pages), _ptr(s0), _ptr(s1),
-                                    _ptr(buf_offset), max_range_pages, _ptr(sendbuf),
-                                    _stream(stream)), "mc_kv_unpack_batch")
+    _check(_calls.unpack_batch(pool, layer_begin, layer_end, batch, page_table, cu_pages, s0, s1,
+                               buf_offset, max_range_pages, sendbuf, stream), "mc_kv_unpack_batch")
 
 
 def mc_plan_remote_send(sender_match, receiver_match, begin, end) -> dict:
     """Token ranges (begin, end) under "copy", "prefill", "send"."""
-    p = mc_send_plan()
-    _check(lib().mc_plan_remote_send(sender_match, receiver_match, begin, end, C.byref(p)),
-           "mc_plan_remote_send")
-    return {"copy": (p.copy_begin, p.copy_end), "prefill": (p.prefill_begin, p.prefill_end),
-            "send": (p.send_begin, p.send_end)}
+    st, copy, prefill, send = _calls.plan_remote_send(sender_match, receiver_match, begin, end)
+    _check(st, "mc_plan_remote_send")
+    return {"copy": copy, "prefill": prefill, "send": send}
 
 
 def mc_addr_compress(pages):
     """Page list -> list of (first page, count) runs."""
-    n = len(pages)
-    arr, runs, nr = _i32_array(pages), (C.c_int32 * (2 * max(n, 1)))(), C.c_int32(0)
-    _check(lib().mc_addr_compress(arr, n, runs, C.byref(nr)), "mc_addr_compress")
-    return [(runs[2 * i], runs[2 * i + 1]) for i in range(nr.value)]
+    st, runs = _calls.addr_compress(pages)
+    _check(st, "mc_addr_compress")
+    return runs
 
 
 def mc_addr_expand(runs, capacity=None):
     """List of (first page, count) runs -> page list."""
-    flat = [int(x) for r in runs for x in r]
-    if capacity is None:
-        capacity = max(0, sum(max(0, int(c)) for _, c in runs))
-    out, n = (C.c_int32 * max(capacity, 1))(), C.c_int32(0)
-    _check(lib().mc_addr_expand(_i32_array(flat), len(runs), out, capacity, C.byref(n)),
-           "mc_addr_expand")
-    return [out[i] for i in range(n.value)]
+    st, pages = _calls.addr_expand(runs, capacity)
+    _check(st, "mc_addr_expand")
+    return pages
 
 
 def mc_prefix_index_create():
@@ -313,24 +308,21 @@ def mc_prefix_index_destroy(index):
 
 
 def mc_prefix_index_insert(index, tokens, pages):
-    _check(lib().mc_prefix_index_insert(index, _i32_array(tokens), len(tokens), _i32_array(pages)),
-           "mc_prefix_index_insert")
+    _check(_calls.index_insert(index, tokens, pages), "mc_prefix_index_insert")
 
 
 def mc_prefix_index_match(index, tokens):
     """Returns (match_len, pages of the matched whole pages)."""
-    out, m = (C.c_int32 * max(len(tokens) // 16, 1))(), C.c_int32(0)
-    _check(lib().mc_prefix_index_match(index, _i32_array(tokens), len(tokens), out, C.byref(m)),
-           "mc_prefix_index_match")
-    return m.value, [out[i] for i in range(m.value // 16)]
+    st, match_len, pages = _calls.index_match(index, tokens)
+    _check(st, "mc_prefix_index_match")
+    return match_len, pages
 
 
 def mc_prep_recv(index, alloc, prompt, end):
     """Returns (page list for prompt[0, end): matched pages then fresh ones, match_len)."""
-    out, m = (C.c_int32 * max(-(-end // 16), 1))(), C.c_int32(0)
-    _check(lib().mc_prep_recv(index, alloc, _i32_array(prompt), end, out, C.byref(m)),
-           "mc_prep_recv")
-    return [out[i] for i in range(-(-end // 16))], m.value
+    st, match_len, pages = _calls.prep_recv(index, alloc, prompt, end)
+    _check(st, "mc_prep_recv")
+    return pages, match_len
 
 
 def mc_kv_fork_sequence(alloc, parent_pages, n_tokens):
@@ -345,5 +337,5 @@ def mc_kv_fork_sequence(alloc, parent_pages, n_tokens):
 
 def mc_kv_copy_page(pool: mc_pool_desc, layer_begin, layer_end, src_page, dst_page, slots,
                     stream=None):
-    _check(lib().mc_kv_copy_page(C.byref(pool), layer_begin, layer_end, src_page, dst_page, slots,
-                                 _stream(stream)), "mc_kv_copy_page")
+    _check(_calls.copy_page(pool, layer_begin, layer_end, src_page, dst_page, slots, stream),
+           "mc_kv_copy_page")

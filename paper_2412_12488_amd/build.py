@@ -1,6 +1,8 @@
-"""Compile the HIP library for gfx950 into paper_2412_12488_amd/libmc_kv.so (in-tree)."""
+"""Compile the HIP library for gfx950 into paper_2412_12488_amd/libmc_kv.so and the binding's
+native half into paper_2412_12488_amd/_calls.so (both in-tree)."""
 import os
 import subprocess
+import sysconfig
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
@@ -18,6 +20,20 @@ def sources():
     return [os.path.join(CSRC, s) for s in SOURCES]
 
 
+def build_calls() -> str:
+    """_calls.so: host code only; finds libmc_kv.so beside itself."""
+    out = os.path.join(HERE, "_calls.so")
+    cmd = [os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall",
+           "-I", sysconfig.get_paths()["include"], "-I", os.path.join(ROOT, "include"),
+           "-o", out + ".tmp", os.path.join(CSRC, "py_calls.cc"),
+           "-L", HERE, "-lmc_kv", "-Wl,-rpath,$ORIGIN"]
+    res = subprocess.run(cmd, capture_output=True, text=True)
+    if res.returncode != 0:
+        raise RuntimeError("g++ failed:\n" + res.stderr)
+    os.replace(out + ".tmp", out)
+    return out
+
+
 def build(verbose: bool = False) -> str:
     cmd = [HIPCC] + FLAGS + ["-o", LIB + ".tmp"] + sources()
     res = subprocess.run(cmd, capture_output=True, text=True)
@@ -28,6 +44,7 @@ def build(verbose: bool = False) -> str:
     if verbose and err.strip():
         print(err)
     os.replace(LIB + ".tmp", LIB)
+    build_calls()
     return LIB
 
 

@@ -3,8 +3,8 @@
 // does not hold), and a host check of destination page tables.
 #include <algorithm>
 #include <array>
-#include <map>
 #include <new>
+#include <unordered_map>
 #include <utility>
 #include <vector>
 
@@ -20,8 +20,21 @@ struct Allocator {
 
 // Trie over 16-token blocks: (parent node, the block's tokens) -> node; a node knows its page.
 struct PrefixIndex {
+  // Hashed: a block costs one look-up whatever the number of blocks recorded (an ordered map
+  // compared 68-byte keys log2(blocks) times, each a cache miss).
   typedef std::pair<int32_t, std::array<int32_t, mc::kPage>> Key;
-  std::map<Key, int32_t> child;
+  struct Hash {
+    size_t operator()(const Key& k) const {
+      uint64_t h = (uint32_t)k.first;
+      for (int i = 0; i < mc::kPage; i += 2) {
+        const uint64_t two = (uint32_t)k.second[i] | ((uint64_t)(uint32_t)k.second[i + 1] << 32);
+        h = (h ^ two) * 0x9e3779b97f4a7c15ull;
+        h ^= h >> 32;
+      }
+      return (size_t)h;
+    }
+  };
+  std::unordered_map<Key, int32_t, Hash> child;
   std::vector<int32_t> page_of;   // by node id
 
   static Key key(int32_t parent, const int32_t* block) {
@@ -237,7 +250,7 @@ mc_status mc_prep_recv(void* index, void* alloc, const int32_t* prompt, int32_t 
   if (end < 0) return MC_ERR_RANGE;
   if (end > 0 && (!prompt || !pages_out)) return MC_ERR_INVALID;
   const int32_t total = (end + mc::kPage - 1) / mc::kPage;
-  std::vector<int32_t> matched(static_cast<size_t>(end / mc::kPage));
+  std::vector<int32_t> matched(static_cast<size_t>(end / mc::kPage) + 1);
   const int32_t m = x->match(prompt, end, matched.data());
   mc_status st = mc_kv_alloc_pages(alloc, total - m, pages_out + m);   // all or nothing
   if (st != MC_OK) return st;

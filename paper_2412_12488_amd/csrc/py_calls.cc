@@ -1,0 +1,493 @@
+// CPython side of the binding: the calls an engine makes per layer or per request, from Python
+// objects to the C ABI in native code.  binding.py keeps the public functions (names, arguments,
+// defaults, errors) and hands their arguments here positionally; every function returns the
+// mc_status, or a tuple that starts with it.
+//
+// Why not ctypes for these: a launch takes about 2 us, and marshalling its 10 to 16 arguments
+// through ctypes took another 5 to 7, so that a decode step over eight layers (17 calls) was
+// bound by the host; a request's token list went through three Python-level loops.
+//
+// Accepted as before: tensors (anything with data_ptr()), integer addresses or None for buffers;
+// ctypes handles for host objects; integers wrap to 32 bits as C's do; sequences of numbers for
+// token and page lists.  The interpreter lock is released around every library call.
+#define PY_SSIZE_T_CLEAN
+#include <Python.h>
+
+#include <stdint.h>
+#include <string.h>
+
+#include <vector>
+
+#include "mc_kv.h"
+
+namespace {
+
+PyObject* s_data_ptr;      // interned attribute names
+PyObject* s_cuda_stream;
+PyObject* g_get_device;    // torch's current-device and current-stream look-ups
+PyObject* g_get_stream;
+
+// ---- one argument each; false with a Python error set ----
+bool to_i32(PyObject* o, int32_t* out) {
+  const unsigned long long v = PyLong_AsUnsignedLongLongMask(o);
+  if (v == (unsigned long long)-1 && PyErr_Occurred()) return false;
+  *out = (int32_t)(uint32_t)v;
+  return true;
+}
+
+bool to_size(PyObject* o, size_t* out) {
+  const unsigned long long v = PyLong_AsUnsignedLongLongMask(o);
+  if (v == (unsigned long long)-1 && PyErr_Occurred()) return false;
+  *out = (size_t)v;
+  return true;
+}
+
+// device buffer: None, an integer address, or an object with data_ptr()
+bool to_ptr(PyObject* o, void** out) {
+  if (o == Py_None) { *out = nullptr; return true; }
+  PyObject* v = nullptr;
+  if (!PyLong_Check(o)) {
+    v = PyObject_CallMethodNoArgs(o, s_data_ptr);
+    if (!v) return false;
+    o = v;
+  }
+  *out = (void*)(uintptr_t)PyLong_AsUnsignedLongLongMask(o);
+  const bool ok = !PyErr_Occurred();
+  Py_XDECREF(v);
+  return ok;
+}
+
+// host handle: None, an integer, or a ctypes c_void_p
+bool to_handle(PyObject* o, void** out) {
+  if (o == Py_None) { *out = nullptr; return true; }
+  if (PyLong_Check(o)) {
+    *out = (void*)(uintptr_t)PyLong_AsUnsignedLongLongMask(o);
+    return !PyErr_Occurred();
+  }
+  Py_buffer b;
+  if (PyObject_GetBuffer(o, &b, PyBUF_SIMPLE) != 0) return false;
+  const bool ok = b.len == (Py_ssize_t)sizeof(void*);
+  if (ok) memcpy(out, b.buf, sizeof(void*));
+  else PyErr_SetString(PyExc_TypeError, "a handle of this library is expected");
+  PyBuffer_Release(&b);
+  return ok;
+}
+
+// pool descriptor: the ctypes structure's own bytes
+bool to_pool(PyObject* o, mc_pool_desc* out) {
+  Py_buffer b;
+  if (PyObject_GetBuffer(o, &b, PyBUF_SIMPLE) != 0) return false;
+  const bool ok = b.len == (Py_ssize_t)sizeof(mc_pool_desc);
+  if (ok) memcpy(out, b.buf, sizeof(mc_pool_desc));
+  else PyErr_SetString(PyExc_TypeError, "an mc_pool_desc is expected");
+  PyBuffer_Release(&b);
+  return ok;
+}
+
+// stream: None = torch's current stream, an integer handle, or an object with cuda_stream
+bool to_stream(PyObject* o, void** out) {
+  PyObject* v = nullptr;
+  if (o == Py_None) {
+    if (!g_get_stream) {
+      PyObject* c = PyImport_ImportModule("torch._C");
+      if (!c) return false;
+      g_get_device = PyObject_GetAttrString(c, "_cuda_getDevice");
+      PyObject* s = g_get_device ? PyObject_GetAttrString(c, "_cuda_getCurrentRawStream") : nullptr;
+      Py_DECREF(c);
+      if (!s) return false;
+      g_get_stream = s;
+    }
+    PyObject* dev = PyObject_CallNoArgs(g_get_device);
+    if (!dev) return false;
+    v = PyObject_CallOneArg(g_get_stream, dev);
+    Py_DECREF(dev);
+  } else if (!PyLong_Check(o)) {
+    v = PyObject_GetAttr(o, s_cuda_stream);
+  } else {
+    Py_INCREF(o);
+    v = o;
+  }
+  if (!v) return false;
+  *out = (void*)(uintptr_t)PyLong_AsUnsignedLongLongMask(v);
+  const bool ok = !PyErr_Occurred();
+  Py_DECREF(v);
+  return ok;
+}
+
+// page or token list: any sequence of numbers; int32 buffers (numpy) in one copy
+bool to_list(PyObject* o, std::vector<int32_t>* out) {
+  if (!PyList_Check(o) && !PyTuple_Check(o) && PyObject_CheckBuffer(o)) {
+    Py_buffer b;
+    if (PyObject_GetBuffer(o, &b, PyBUF_FORMAT | PyBUF_C_CONTIGUOUS) == 0) {
+      const bool plain = b.ndim == 1 && b.itemsize == 4 && b.format && !strcmp(b.format, "i");
+      if (plain) {
+        out->resize((size_t)b.shape[0]);
+        if (b.len) memcpy(out->data(), b.buf, (size_t)b.len);
+      }
+      PyBuffer_Release(&b);
+      if (plain) return true;
+    } else {
+      PyErr_Clear();
+    }
+  }
+  PyObject* f = PySequence_Fast(o, "a sequence of integers is expected");
+  if (!f) return false;
+  const Py_ssize_t n = PySequence_Fast_GET_SIZE(f);
+  out->resize((size_t)n);
+  bool ok = true;
+  for (Py_ssize_t i = 0; i < n && ok; ++i) {
+    PyObject* x = PySequence_Fast_GET_ITEM(f, i);
+    if (PyLong_Check(x)) {
+      ok = to_i32(x, &(*out)[(size_t)i]);
+    } else {                                   // numpy scalars, floats: as int(x)
+      PyObject* v = PyNumber_Long(x);
+      ok = v && to_i32(v, &(*out)[(size_t)i]);
+      Py_XDECREF(v);
+    }
+  }
+  Py_DECREF(f);
+  return ok;
+}
+
+PyObject* from_list(const int32_t* v, int64_t n) {
+  PyObject* l = PyList_New((Py_ssize_t)n);
+  if (!l) return nullptr;
+  for (int64_t i = 0; i < n; ++i) {
+    PyObject* x = PyLong_FromLong(v[i]);
+    if (!x) { Py_DECREF(l); return nullptr; }
+    PyList_SET_ITEM(l, (Py_ssize_t)i, x);
+  }
+  return l;
+}
+
+PyObject* status(mc_status st) { return PyLong_FromLong((long)st); }
+
+// (status, value): takes the reference
+PyObject* with_status(mc_status st, PyObject* value) {
+  return value ? Py_BuildValue("(iN)", (int)st, value) : nullptr;
+}
+
+// Positional arguments, read in order.
+struct Args {
+  PyObject* const* a;
+  Py_ssize_t n, at = 0;
+  bool ok = true;
+  Args(PyObject* const* a_, Py_ssize_t n_, Py_ssize_t want) : a(a_), n(n_) {
+    if (n != want) {
+      PyErr_Format(PyExc_TypeError, "%zd arguments given, %zd expected", n, want);
+      ok = false;
+    }
+  }
+  template <typename T, typename F>
+  T get(F f) {
+    T v{};
+    if (ok) ok = f(a[at++], &v);
+    return v;
+  }
+  int32_t i32() { return get<int32_t>(to_i32); }
+  size_t size() { return get<size_t>(to_size); }
+  void* ptr() { return get<void*>(to_ptr); }
+  void* handle() { return get<void*>(to_handle); }
+  void* stream() { return get<void*>(to_stream); }
+  mc_pool_desc pool() { return get<mc_pool_desc>(to_pool); }
+  std::vector<int32_t> list() { return get<std::vector<int32_t>>(to_list); }
+  const int32_t* pi32() { return static_cast<const int32_t*>(ptr()); }
+  float f32() {
+    if (!ok) return 0.f;
+    const double v = PyFloat_AsDouble(a[at++]);
+    if (v == -1.0 && PyErr_Occurred()) ok = false;
+    return (float)v;
+  }
+};
+
+#define CALL(expr)            \
+  mc_status st;               \
+  Py_BEGIN_ALLOW_THREADS      \
+  st = (expr);                \
+  Py_END_ALLOW_THREADS        \
+  return status(st)
+
+// ---- device calls ----
+PyObject* append(PyObject*, PyObject* const* a, Py_ssize_t n) {
+  Args g(a, n, 11);
+  const mc_pool_desc pool = g.pool();
+  const int32_t layer = g.i32();
+  const void *k = g.ptr(), *v = g.ptr();
+  const int32_t batch = g.i32(), tq = g.i32();
+  const int32_t *cu_q = g.pi32(), *begin = g.pi32(), *table = g.pi32(), *cu_pages = g.pi32();
+  void* stream = g.stream();
+  if (!g.ok) return nullptr;
+  CALL(mc_kv_append(&pool, layer, k, v, batch, tq, cu_q, begin, table, cu_pages, stream));
+}
+
+PyObject* append_send(PyObject*, PyObject* const* a, Py_ssize_t n) {
+  Args g(a, n, 16);
+  const mc_pool_desc pool = g.pool();
+  const int32_t layer = g.i32();
+  const void *k = g.ptr(), *v = g.ptr();
+  const int32_t batch = g.i32(), tq = g.i32();
+  const int32_t *cu_q = g.pi32(), *begin = g.pi32(), *table = g.pi32(), *cu_pages = g.pi32();
+  const int32_t first = g.i32();
+  const int32_t *s0 = g.pi32(), *s1 = g.pi32();
+  const int64_t* off = static_cast<const int64_t*>(g.ptr());
+  void *buf = g.ptr(), *stream = g.stream();
+  if (!g.ok) return nullptr;
+  CALL(mc_kv_append_send(&pool, layer, k, v, batch, tq, cu_q, begin, table, cu_pages, first, s0,
+                         s1, off, buf, stream));
+}
+
+// plan(pool, hq, batch, total_q, cu_q, begin, table, cu_pages, ahead, ws, ws_bytes, stream)
+PyObject* plan(PyObject*, PyObject* const* a, Py_ssize_t n) {
+  Args g(a, n, 12);
+  const mc_pool_desc pool = g.pool();
+  const int32_t hq = g.i32(), batch = g.i32(), tq = g.i32();
+  const int32_t *cu_q = g.pi32(), *begin = g.pi32(), *table = g.pi32(), *cu_pages = g.pi32();
+  const int32_t ahead = g.i32();
+  void* ws = g.ptr();
+  const size_t bytes = g.size();
+  void* stream = g.stream();
+  if (!g.ok) return nullptr;
+  CALL(mc_attn_plan_ahead(&pool, hq, batch, tq, cu_q, begin, table, cu_pages, ahead, ws, bytes,
+                          stream));
+}
+
+PyObject* attn(PyObject*, PyObject* const* a, Py_ssize_t n) {
+  Args g(a, n, 16);
+  const mc_pool_desc pool = g.pool();
+  const int32_t layer = g.i32();
+  const void* q = g.ptr();
+  const int32_t hq = g.i32(), batch = g.i32(), tq = g.i32();
+  const int32_t *cu_q = g.pi32(), *begin = g.pi32(), *table = g.pi32(), *cu_pages = g.pi32();
+  const float scale = g.f32();
+  void* out = g.ptr();
+  float* lse = static_cast<float*>(g.ptr());
+  void* ws = g.ptr();
+  const size_t bytes = g.size();
+  void* stream = g.stream();
+  if (!g.ok) return nullptr;
+  CALL(mc_prefix_prefill_attn(&pool, layer, q, hq, batch, tq, cu_q, begin, table, cu_pages, scale,
+                              out, lse, ws, bytes, stream));
+}
+
+PyObject* attn_noalloc(PyObject*, PyObject* const* a, Py_ssize_t n) {
+  Args g(a, n, 14);
+  const mc_pool_desc pool = g.pool();
+  const int32_t layer = g.i32();
+  const void* q = g.ptr();
+  const int32_t hq = g.i32(), batch = g.i32(), tq = g.i32();
+  const int32_t *cu_q = g.pi32(), *begin = g.pi32(), *table = g.pi32(), *cu_pages = g.pi32();
+  const float scale = g.f32();
+  void* out = g.ptr();
+  float* lse = static_cast<float*>(g.ptr());
+  void* stream = g.stream();
+  if (!g.ok) return nullptr;
+  CALL(mc_prefix_prefill_attn_noalloc(&pool, layer, q, hq, batch, tq, cu_q, begin, table, cu_pages,
+                                      scale, out, lse, stream));
+}
+
+template <bool kPack>
+PyObject* copy_range(PyObject*, PyObject* const* a, Py_ssize_t n) {
+  Args g(a, n, 9);
+  const mc_pool_desc pool = g.pool();
+  const int32_t l0 = g.i32(), l1 = g.i32();
+  const int32_t* pages = g.pi32();
+  const int32_t n_pages = g.i32(), s0 = g.i32(), s1 = g.i32();
+  void *buf = g.ptr(), *stream = g.stream();
+  if (!g.ok) return nullptr;
+  CALL(kPack ? mc_kv_pack_range(&pool, l0, l1, pages, n_pages, s0, s1, buf, stream)
+             : mc_kv_unpack_range(&pool, l0, l1, pages, n_pages, s0, s1, buf, stream));
+}
+
+template <bool kPack>
+PyObject* copy_batch(PyObject*, PyObject* const* a, Py_ssize_t n) {
+  Args g(a, n, 12);
+  const mc_pool_desc pool = g.pool();
+  const int32_t l0 = g.i32(), l1 = g.i32(), batch = g.i32();
+  const int32_t *table = g.pi32(), *cu_pages = g.pi32(), *s0 = g.pi32(), *s1 = g.pi32();
+  const int64_t* off = static_cast<const int64_t*>(g.ptr());
+  const int32_t most = g.i32();
+  void *buf = g.ptr(), *stream = g.stream();
+  if (!g.ok) return nullptr;
+  CALL(kPack ? mc_kv_pack_batch(&pool, l0, l1, batch, table, cu_pages, s0, s1, off, most, buf, stream)
+             : mc_kv_unpack_batch(&pool, l0, l1, batch, table, cu_pages, s0, s1, off, most, buf,
+                                  stream));
+}
+
+PyObject* copy_page(PyObject*, PyObject* const* a, Py_ssize_t n) {
+  Args g(a, n, 7);
+  const mc_pool_desc pool = g.pool();
+  const int32_t l0 = g.i32(), l1 = g.i32(), src = g.i32(), dst = g.i32(), slots = g.i32();
+  void* stream = g.stream();
+  if (!g.ok) return nullptr;
+  CALL(mc_kv_copy_page(&pool, l0, l1, src, dst, slots, stream));
+}
+
+// ---- host calls ----
+PyObject* alloc_pages(PyObject*, PyObject* const* a, Py_ssize_t n) {
+  Args g(a, n, 2);
+  void* alloc = g.handle();
+  const int32_t want = g.i32();
+  if (!g.ok) return nullptr;
+  std::vector<int32_t> out((size_t)(want > 0 ? want : 0) + 1);
+  const mc_status st = mc_kv_alloc_pages(alloc, want, out.data());
+  return with_status(st, from_list(out.data(), st == MC_OK ? want : 0));
+}
+
+PyObject* free_pages(PyObject*, PyObject* const* a, Py_ssize_t n) {
+  Args g(a, n, 2);
+  void* alloc = g.handle();
+  const std::vector<int32_t> pages = g.list();
+  if (!g.ok) return nullptr;
+  return status(mc_kv_free_pages(alloc, (int32_t)pages.size(), pages.data()));
+}
+
+PyObject* check_page_table(PyObject*, PyObject* const* a, Py_ssize_t n) {
+  Args g(a, n, 2);
+  const std::vector<int32_t> pages = g.list();
+  const int32_t num_pages = g.i32();
+  if (!g.ok) return nullptr;
+  return status(mc_kv_check_page_table(pages.data(), (int64_t)pages.size(), num_pages));
+}
+
+PyObject* plan_remote_send(PyObject*, PyObject* const* a, Py_ssize_t n) {
+  Args g(a, n, 4);
+  const int32_t sm = g.i32(), rm = g.i32(), begin = g.i32(), end = g.i32();
+  if (!g.ok) return nullptr;
+  mc_send_plan p = {};
+  const mc_status st = mc_plan_remote_send(sm, rm, begin, end, &p);
+  return Py_BuildValue("(i(ii)(ii)(ii))", (int)st, p.copy_begin, p.copy_end, p.prefill_begin,
+                       p.prefill_end, p.send_begin, p.send_end);
+}
+
+PyObject* addr_compress(PyObject*, PyObject* const* a, Py_ssize_t n) {
+  Args g(a, n, 1);
+  const std::vector<int32_t> pages = g.list();
+  if (!g.ok) return nullptr;
+  std::vector<int32_t> runs(2 * pages.size() + 2);
+  int32_t nr = 0;
+  const mc_status st = mc_addr_compress(pages.data(), (int32_t)pages.size(), runs.data(), &nr);
+  if (st != MC_OK) nr = 0;
+  PyObject* l = PyList_New(nr);
+  for (int32_t i = 0; l && i < nr; ++i) {
+    PyObject* t = PyTuple_New(2);
+    PyObject *first = PyLong_FromLong(runs[2 * i]), *count = PyLong_FromLong(runs[2 * i + 1]);
+    if (!t || !first || !count) {
+      Py_XDECREF(t); Py_XDECREF(first); Py_XDECREF(count);
+      Py_CLEAR(l);
+      break;
+    }
+    PyTuple_SET_ITEM(t, 0, first);
+    PyTuple_SET_ITEM(t, 1, count);
+    PyList_SET_ITEM(l, i, t);
+  }
+  return with_status(st, l);
+}
+
+// addr_expand(runs, capacity or None)
+PyObject* addr_expand(PyObject*, PyObject* const* a, Py_ssize_t n) {
+  Args g(a, n, 2);
+  if (!g.ok) return nullptr;
+  PyObject* f = PySequence_Fast(a[0], "a sequence of (first page, count) runs is expected");
+  if (!f) return nullptr;
+  const Py_ssize_t n_runs = PySequence_Fast_GET_SIZE(f);
+  std::vector<int32_t> flat;
+  flat.reserve(2 * (size_t)n_runs);
+  std::vector<int32_t> pair;
+  int64_t sum = 0;
+  for (Py_ssize_t i = 0; i < n_runs; ++i) {
+    PyObject* r = PySequence_Fast_GET_ITEM(f, i);
+    if (PyTuple_Check(r) && PyTuple_GET_SIZE(r) == 2 && PyLong_Check(PyTuple_GET_ITEM(r, 0)) &&
+        PyLong_Check(PyTuple_GET_ITEM(r, 1))) {
+      pair.resize(2);
+      if (!to_i32(PyTuple_GET_ITEM(r, 0), &pair[0]) || !to_i32(PyTuple_GET_ITEM(r, 1), &pair[1])) {
+        Py_DECREF(f);
+        return nullptr;
+      }
+    } else if (!to_list(r, &pair)) {
+      Py_DECREF(f);
+      return nullptr;
+    }
+    if (pair.size() == 2 && pair[1] > 0) sum += pair[1];
+    flat.insert(flat.end(), pair.begin(), pair.end());
+  }
+  Py_DECREF(f);
+  flat.resize(2 * (size_t)n_runs + 1);      // runs are pairs: two numbers each
+  int32_t capacity = 0;
+  if (a[1] != Py_None) {
+    if (!to_i32(a[1], &capacity)) return nullptr;
+  } else {
+    capacity = (int32_t)(sum < 0x7fffffff ? sum : 0x7fffffff);
+  }
+  std::vector<int32_t> out((size_t)(capacity > 0 ? capacity : 0) + 1);
+  int32_t got = 0;
+  const mc_status st = mc_addr_expand(flat.data(), (int32_t)n_runs, out.data(), capacity, &got);
+  return with_status(st, from_list(out.data(), st == MC_OK ? got : 0));
+}
+
+PyObject* index_insert(PyObject*, PyObject* const* a, Py_ssize_t n) {
+  Args g(a, n, 3);
+  void* index = g.handle();
+  const std::vector<int32_t> tokens = g.list(), pages = g.list();
+  if (!g.ok) return nullptr;
+  if (pages.size() < tokens.size() / 16) {
+    PyErr_SetString(PyExc_IndexError, "fewer pages than whole blocks of tokens");
+    return nullptr;
+  }
+  return status(mc_prefix_index_insert(index, tokens.data(), (int32_t)tokens.size(), pages.data()));
+}
+
+PyObject* index_match(PyObject*, PyObject* const* a, Py_ssize_t n) {
+  Args g(a, n, 2);
+  void* index = g.handle();
+  const std::vector<int32_t> tokens = g.list();
+  if (!g.ok) return nullptr;
+  std::vector<int32_t> out(tokens.size() / 16 + 1);
+  int32_t m = 0;
+  const mc_status st =
+      mc_prefix_index_match(index, tokens.data(), (int32_t)tokens.size(), out.data(), &m);
+  PyObject* l = from_list(out.data(), st == MC_OK ? m / 16 : 0);
+  return l ? Py_BuildValue("(iiN)", (int)st, (int)m, l) : nullptr;
+}
+
+// prep_recv(index, alloc, prompt, end) -> (status, match_len, pages)
+PyObject* prep_recv(PyObject*, PyObject* const* a, Py_ssize_t n) {
+  Args g(a, n, 4);
+  void *index = g.handle(), *alloc = g.handle();
+  const std::vector<int32_t> prompt = g.list();
+  const int32_t end = g.i32();
+  if (!g.ok) return nullptr;
+  if (end > 0 && (size_t)end > prompt.size()) {
+    PyErr_SetString(PyExc_IndexError, "end lies beyond the prompt");
+    return nullptr;
+  }
+  const int64_t pages = end > 0 ? ((int64_t)end + 15) / 16 : 0;
+  std::vector<int32_t> out((size_t)pages + 1);
+  int32_t m = 0;
+  const mc_status st = mc_prep_recv(index, alloc, prompt.data(), end, out.data(), &m);
+  PyObject* l = from_list(out.data(), st == MC_OK ? pages : 0);
+  return l ? Py_BuildValue("(iiN)", (int)st, (int)m, l) : nullptr;
+}
+
+#define FN(name) {#name, (PyCFunction)(void (*)(void))name, METH_FASTCALL, nullptr}
+PyMethodDef kMethods[] = {
+    FN(append), FN(append_send), FN(plan), FN(attn), FN(attn_noalloc), FN(copy_page),
+    {"pack_range", (PyCFunction)(void (*)(void))copy_range<true>, METH_FASTCALL, nullptr},
+    {"unpack_range", (PyCFunction)(void (*)(void))copy_range<false>, METH_FASTCALL, nullptr},
+    {"pack_batch", (PyCFunction)(void (*)(void))copy_batch<true>, METH_FASTCALL, nullptr},
+    {"unpack_batch", (PyCFunction)(void (*)(void))copy_batch<false>, METH_FASTCALL, nullptr},
+    FN(alloc_pages), FN(free_pages), FN(check_page_table), FN(plan_remote_send),
+    FN(addr_compress), FN(addr_expand), FN(index_insert), FN(index_match), FN(prep_recv),
+    {nullptr, nullptr, 0, nullptr}};
+
+PyModuleDef kModule = {PyModuleDef_HEAD_INIT, "_calls",
+                       "Native argument marshalling for the calls of libmc_kv.so.", -1, kMethods,
+                       nullptr, nullptr, nullptr, nullptr};
+
+}  // namespace
+
+PyMODINIT_FUNC PyInit__calls(void) {
+  s_data_ptr = PyUnicode_InternFromString("data_ptr");
+  s_cuda_stream = PyUnicode_InternFromString("cuda_stream");
+  if (!s_data_ptr || !s_cuda_stream) return nullptr;
+  return PyModule_Create(&kModule);
+}

@@ -1,0 +1,51 @@
+"""The native marshalling of the binding (CPU): every form of argument the calls take."""
+import ctypes
+
+import numpy as np
+import pytest
+
+import paper_2412_12488_amd as mc
+
+
+@pytest.mark.parametrize("form", [list, tuple, lambda v: np.array(v, dtype=np.int32),
+                                  lambda v: np.array(v, dtype=np.int64),
+                                  lambda v: [np.int32(x) for x in v], lambda v: [float(x) for x in v],
+                                  lambda v: np.repeat(np.array(v, dtype=np.int32), 2)[::2]])
+def test_lists_of_numbers_in_every_form(form):
+    pages = [7, 8, 9, 3, 0, 1]
+    assert mc.mc_addr_compress(form(pages)) == [(7, 3), (3, 1), (0, 2)]
+    assert mc.mc_kv_check_page_table(form(pages), 10) == mc.MC_OK
+    ix = mc.mc_prefix_index_create()
+    tokens = list(range(40))
+    mc.mc_prefix_index_insert(ix, form(tokens), form([5, 6]))
+    assert mc.mc_prefix_index_match(ix, form(tokens[:33])) == (32, [5, 6])
+    mc.mc_prefix_index_destroy(ix)
+
+
+def test_runs_in_every_form_and_capacity():
+    assert mc.mc_addr_expand([[2, 2], (9, 1)]) == [2, 3, 9]
+    assert mc.mc_addr_expand(np.array([[2, 2], [9, 1]], dtype=np.int32)) == [2, 3, 9]
+    assert mc.mc_addr_expand([(2, 2)], 5) == [2, 3]
+    with pytest.raises(mc.McError) as e:
+        mc.mc_addr_expand([(2, 2), (9, 1)], capacity=2)
+    assert e.value.status == mc.MC_ERR_RANGE
+
+
+def test_wrong_arguments_raise_and_do_not_crash():
+    with pytest.raises(TypeError):
+        mc.mc_addr_compress(5)
+    with pytest.raises((TypeError, ValueError)):
+        mc.mc_addr_compress(["x"])
+    with pytest.raises(TypeError):
+        mc.mc_kv_alloc_pages(b"four", 1)                    # not a handle
+    with pytest.raises(TypeError):
+        mc.mc_kv_pack_range(ctypes.c_int32(1), 0, 1, 16, 1, 0, 1, 16, stream=0)
+    with pytest.raises(mc.McError) as e:
+        mc.mc_kv_alloc_pages(None, 1)
+    assert e.value.status == mc.MC_ERR_INVALID
+    ix, al = mc.mc_prefix_index_create(), mc.mc_kv_allocator_create(8)
+    with pytest.raises(IndexError):
+        mc.mc_prep_recv(ix, al, [1, 2, 3], 17)              # reaches past the prompt
+    assert mc.mc_kv_allocator_num_free(al) == 8
+    mc.mc_prefix_index_destroy(ix)
+    mc.mc_kv_allocator_destroy(al)
