@@ -127,59 +127,80 @@ struct AppendArgs {
 };
 
 // grid.x: 2 * (chunk of 16 consecutive tokens of the ragged new-token stream) + (0 = K, 1 = V)
-template <bool kSend>
+// Small batches are bound by the chain of dependent reads, not by bytes: the sequence is found by
+// the token's 16 lanes together (16 offsets a round: one round for 16 sequences, two for 256,
+// where a binary search took four and eight), everything indexed by the sequence is requested at
+// once, and the K/V rows right behind it, ahead of the table entry.  (Not ahead of the search:
+// vector loads return in order, so the look-ups would wait for the rows.)
+// kFull: the heads are a multiple of kMaxHeadsInFlight, so no load stands under a condition and the
+// compiler can count the row loads in flight instead of waiting for them with the look-ups.
+// A layer of eight decode rows (64 / 8 heads; append + attention + merge) 34.2 -> 32.9 us, of 500
+// new tokens with their send 72.4 -> 70.4 us.
+template <bool kSend, bool kFull>
 __global__ __launch_bounds__(kThreads) void append_kernel(AppendArgs a) {
   const int g = (blockIdx.x >> 1) * kPage + (threadIdx.x >> 4);
   const int lane16 = threadIdx.x & 15;
   const int kv = blockIdx.x & 1;
   if (g >= a.total_q) return;
+  const char* src = (kv ? a.v_new : a.k_new) + (int64_t)g * a.hkv * kRowBytes + lane16 * 16;
+  u32x4 r[kMaxHeadsInFlight];
+  auto load = [&](int h0) __attribute__((always_inline)) {
+#pragma unroll
+    for (int i = 0; i < kMaxHeadsInFlight; ++i)
+      if (kFull || h0 + i < a.hkv)
+        r[i] = __builtin_nontemporal_load(
+            reinterpret_cast<const u32x4*>(src + (h0 + i) * kRowBytes));
+  };
   // sequence of token g: last s with cu_q[s] <= g
-  int lo = 0, hi = a.batch;
-  while (hi - lo > 1) {
-    const int mid = (lo + hi) >> 1;
-    if (a.cu_q[mid] <= g) lo = mid; else hi = mid;
+  int s = 0, cnt = a.batch;
+  while (cnt > 1) {
+    const int step = (cnt + 15) / 16, end = s + cnt, i = s + lane16 * step;
+    const bool le = i < end && a.cu_q[i] <= g;
+    const unsigned m = (unsigned)(__ballot(le) >> (threadIdx.x & 48)) & 0xffffu;
+    s += max(__popc(m) - 1, 0) * step;   // cu_q rises with s; the first one holds by definition
+    cnt = min(step, end - s);
   }
-  const int s = lo;
-  const int q0 = a.cu_q[s];
-  const bool reporter = kv == 0 && lane16 == 0;      // one lane per token
-  if (g < q0 || g >= a.cu_q[s + 1]) { report_skip(a.skipped, reporter); return; }   // malformed offsets
-  const int pos = a.begin[s] + (g - q0);
-  if (pos < 0) { report_skip(a.skipped, reporter); return; }
+  const int q0 = a.cu_q[s], q1 = a.cu_q[s + 1], b = a.begin[s];
   const int p0 = a.cu_pages[s], p1 = a.cu_pages[s + 1];
+  int s0 = 0, s1 = 0;
+  int64_t off = 0;
+  if (kSend) {
+    s0 = a.s0_of[s];
+    s1 = a.s1_of[s];
+    off = a.buf_offset[s];
+  }
+  asm volatile("" ::: "memory");   // keeps the order of the requests
+  load(0);
+  asm volatile("" ::: "memory");
+  const bool reporter = kv == 0 && lane16 == 0;      // one lane per token
+  const int pos = b + (g - q0);
   const int tp = pos / kPage;
-  if (p0 < 0 || tp >= p1 - p0) { report_skip(a.skipped, reporter); return; }       // table too short
+  // malformed offsets, or a table that is too short
+  if (g < q0 || g >= q1 || pos < 0 || p0 < 0 || tp >= p1 - p0) { report_skip(a.skipped, reporter); return; }
   const int32_t page = a.page_table[p0 + tp];
   if (page < 0 || page >= a.num_pages) { report_skip(a.skipped, reporter); return; }
-  const char* src = (kv ? a.v_new : a.k_new) + (int64_t)g * a.hkv * kRowBytes + lane16 * 16;
   char* dst = a.pool_layer + page * a.page_stride + (int64_t)kv * a.hkv * kHeadPageBytes +
               (pos % kPage) * kRowBytes + lane16 * 16;
   // the token's row in the transfer buffer, if it is marked: [layer][K|V][token - s0][head][D]
   char* sent = nullptr;
-  if (kSend) {
-    const int s0 = a.s0_of[s], s1 = a.s1_of[s];
-    const int64_t off = a.buf_offset[s];
-    if (s0 >= 0 && pos >= s0 && pos < s1 && off >= 0 && (off & 15) == 0)
-      sent = a.buf + off +
-             ((int64_t)(a.layer_rel * 2 + kv) * (s1 - s0) + (pos - s0)) * a.hkv * kRowBytes + lane16 * 16;
-  }
-  for (int h0 = 0; h0 < a.hkv; h0 += kMaxHeadsInFlight) {
-    u32x4 r[kMaxHeadsInFlight];
+  if (kSend && s0 >= 0 && pos >= s0 && pos < s1 && off >= 0 && (off & 15) == 0)
+    sent = a.buf + off +
+           ((int64_t)(a.layer_rel * 2 + kv) * (s1 - s0) + (pos - s0)) * a.hkv * kRowBytes + lane16 * 16;
+  for (int h0 = 0;;) {
 #pragma unroll
     for (int i = 0; i < kMaxHeadsInFlight; ++i)
-      if (h0 + i < a.hkv)
-        r[i] = __builtin_nontemporal_load(
-            reinterpret_cast<const u32x4*>(src + (h0 + i) * kRowBytes));
-#pragma unroll
-    for (int i = 0; i < kMaxHeadsInFlight; ++i)
-      if (h0 + i < a.hkv)
+      if (kFull || h0 + i < a.hkv)
         __builtin_nontemporal_store(
             r[i], reinterpret_cast<u32x4*>(dst + (int64_t)(h0 + i) * kHeadPageBytes));
     if (kSend && sent) {
 #pragma unroll
       for (int i = 0; i < kMaxHeadsInFlight; ++i)
-        if (h0 + i < a.hkv)
+        if (kFull || h0 + i < a.hkv)
           __builtin_nontemporal_store(r[i], reinterpret_cast<u32x4*>(sent + (h0 + i) * kRowBytes));
     }
+    h0 += kMaxHeadsInFlight;
+    if (h0 >= a.hkv) break;
+    load(h0);
   }
 }
 
@@ -357,10 +378,10 @@ static mc_status append_impl(const mc_pool_desc* pool, int32_t layer, const void
   a.skipped = pool->skipped;
   dim3 grid(2u * ((total_q + kPage - 1) / kPage));
   hipStream_t hs = static_cast<hipStream_t>(stream);
-  if (send)
-    hipLaunchKernelGGL(append_kernel<true>, grid, dim3(kThreads), 0, hs, a);
-  else
-    hipLaunchKernelGGL(append_kernel<false>, grid, dim3(kThreads), 0, hs, a);
+  const bool full = pool->num_kv_heads % kMaxHeadsInFlight == 0;
+  auto* kernel = send ? (full ? append_kernel<true, true> : append_kernel<true, false>)
+                      : (full ? append_kernel<false, true> : append_kernel<false, false>);
+  hipLaunchKernelGGL(kernel, grid, dim3(kThreads), 0, hs, a);
   return mc::launch_status();
 }
 

@@ -1,0 +1,35 @@
+"""Appends at the batch sizes where the rounds of the sequence search (16 offsets each) change."""
+import numpy as np
+import pytest
+
+import mc_inputs as mi
+from test_gpu_parity import canary, small_workload
+from gpu_harness import DevBatch, DevPool, bits, dev, gpu_append
+
+import oracle
+import torch
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("batch", [1, 2, 16, 17, 31, 256, 257, 300])
+@pytest.mark.parametrize("Hkv", [1, 8, 16])
+def test_append_finds_every_sequence(batch, Hkv):
+    # one to three new tokens a sequence, every fifth sequence (the last included) with none
+    rng = mi.rng_for(900 + batch)
+    begins = [int(x) for x in rng.integers(0, 40, size=batch)]
+    new = [0 if batch > 1 and (batch - 1 - i) % 5 == 0 else 1 + i % 3 for i in range(batch)]
+    lens = [max(b + n, 1) for b, n in zip(begins, new)]
+    w = small_workload(900 + batch, mi.BF16, Hkv, Hkv, lens, begins)
+    init = canary(3, DevPool(w).elems)
+    pool, opool, db = DevPool(w, fill=init), init.copy(), DevBatch(w)
+    ks, vs = [], []
+    for s in range(w.batch):
+        k, v = w.kv(s, 0)
+        k, v = k[w.b[s]:], v[w.b[s]:]
+        ks.append(k), vs.append(v)
+        if len(k):
+            oracle.append(opool, pool.shape, 0, k, v, int(w.b[s]), w.page_tables[s])
+    gpu_append(pool, 0, dev(np.concatenate(ks)), dev(np.concatenate(vs)), db)
+    torch.cuda.synchronize()
+    assert np.array_equal(bits(pool.t), opool)
