@@ -112,7 +112,14 @@ constexpr int kCuTilesInLds = 1024;
 constexpr int kValidateInPlan = 256;  // batches up to this have their page ids checked by plan_kernel
 constexpr int kTailTilesMax = 2048;   // q tiles up to which the remainder round is looked at
 constexpr int kMinSharedTiles = 8;    // a shared prefix shorter than 512 tokens is not worth a group
-constexpr int kMinChunkTiles = 8;     // never cut a KV range into pieces shorter than 512 keys
+// Shortest piece a KV range is cut into.  A piece walks its tiles one after the other, a memory
+// latency each, and every piece costs a partial row (fp32) for each of its rows, written and read.
+// Decode steps (at most one new token a sequence) have few rows: short pieces, 2 tiles as long as
+// a row then has no more than the kMergeAhead pieces that merge_kernel requests early, else 4.  Ranges
+// of more tokens keep 8.  Append + attention + merge of a layer, 32 / 8 heads, pieces of 8 / 4 / 2 tiles:
+// decode of 2 x 1024 tokens 17.7 / 15.0 / 13.7 us, 4 x 2048 20.5 / 18.0 / 18.2, 1 x 4096 18.2 / 16.3 /
+// 16.5; prefill of 512 tokens 20.0 / 23.1 / 25.7, of 4 x 512 27.0 / 40.8 / 40.8.
+constexpr int kMinChunkTiles = 8, kMinChunkTilesDecode = 4, kMinChunkTilesShort = 2;
 constexpr int kMergeAhead = 8;        // partial rows merge_kernel requests beside their LSEs
 constexpr int kRoundsWanted = 4;      // cut only while the launch has fewer items than 4 per slot
 // ... and then aim for about one item per slot: measured best on decode batches and on 500-token
@@ -611,7 +618,10 @@ __global__ __launch_bounds__(NT) void plan_kernel(PlanArgs a) {
     cost = block_sum<NT>(cost, scan);
     const long long want =
         (cost * a.hkv + (long long)kItemsPerSlot * a.slots - 1) / ((long long)kItemsPerSlot * a.slots);
-    L = want < kMinChunkTiles ? kMinChunkTiles : want > (1 << 28) ? (1 << 28) : (int)want;
+    const int shortest = a.total_q > a.batch ? kMinChunkTiles
+                         : s_maxcost <= kMinChunkTilesShort * kMergeAhead ? kMinChunkTilesShort
+                                                                          : kMinChunkTilesDecode;
+    L = want < shortest ? shortest : want > (1 << 28) ? (1 << 28) : (int)want;
     L = (L + 1) & ~1;
     for (;;) {
       if (L >= s_maxcost) { L = 0; break; }   // nothing is long enough to be cut

@@ -1,9 +1,11 @@
-"""Appends at the batch sizes where the rounds of the sequence search (16 offsets each) change."""
+"""Decode batches and appends at the sizes where the short-batch paths change: the rounds of the
+append's sequence search (16 offsets each), the pieces KV ranges are cut into, the merge's early
+rows and its records beyond the first 64."""
 import numpy as np
 import pytest
 
 import mc_inputs as mi
-from test_gpu_parity import canary, small_workload
+from test_gpu_parity import (canary, check_attention, plan_header, small_workload)
 from gpu_harness import DevBatch, DevPool, bits, dev, gpu_append
 
 import oracle
@@ -33,3 +35,18 @@ def test_append_finds_every_sequence(batch, Hkv):
     gpu_append(pool, 0, dev(np.concatenate(ks)), dev(np.concatenate(vs)), db)
     torch.cuda.synchronize()
     assert np.array_equal(bits(pool.t), opool)
+
+
+@pytest.mark.parametrize("dtype", [mi.BF16, mi.F16])
+@pytest.mark.parametrize("lens,chunk", [
+    ([128], 0),                       # two tiles: nothing to cut
+    ([129], 2), ([1024], 2),          # up to 16 tiles: pieces of two tiles, at most eight
+    ([1025], 4), ([2048, 700, 1], 4), # longer: pieces of four
+    ([4097], 4),                      # more pieces than rows requested early
+    ([200] * 65, 2),                  # more merge records than lanes
+])
+def test_decode_pieces(dtype, lens, chunk):
+    Hq, Hkv = (8, 1) if len(lens) > 3 else (32, 8)
+    w = small_workload(950 + len(lens) + lens[0], dtype, Hq, Hkv, lens, [n - 1 for n in lens])
+    assert plan_header(w)["chunk_tiles"] == chunk
+    check_attention(w)
