@@ -407,11 +407,16 @@ PyObject* addr_expand(PyObject*, PyObject* const* a, Py_ssize_t n) {
       Py_DECREF(f);
       return nullptr;
     }
-    if (pair.size() == 2 && pair[1] > 0) sum += pair[1];
+    // joined without this check, numbers of a malformed run would be read as the next run's
+    if (pair.size() != 2) {
+      Py_DECREF(f);
+      return PyErr_Format(PyExc_ValueError, "run %zd holds %zu numbers, not (first page, count)", i,
+                          pair.size());
+    }
+    if (pair[1] > 0) sum += pair[1];
     flat.insert(flat.end(), pair.begin(), pair.end());
   }
   Py_DECREF(f);
-  flat.resize(2 * (size_t)n_runs + 1);      // runs are pairs: two numbers each
   int32_t capacity = 0;
   if (a[1] != Py_None) {
     if (!to_i32(a[1], &capacity)) return nullptr;

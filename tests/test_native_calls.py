@@ -49,3 +49,12 @@ def test_wrong_arguments_raise_and_do_not_crash():
     assert mc.mc_kv_allocator_num_free(al) == 8
     mc.mc_prefix_index_destroy(ix)
     mc.mc_kv_allocator_destroy(al)
+
+
+@pytest.mark.parametrize("runs", [[(3,), (9,)], [(1, 1, 5), (1, 2)], [(3, 1, 9, 1), (50, 4)],
+                                  [(1, 1, 5), (1,)], [()], np.zeros((2, 3), dtype=np.int32)])
+@pytest.mark.parametrize("capacity", [None, 64])
+def test_runs_that_are_not_pairs_are_refused(runs, capacity):
+    # never re-cut into other pairs: their pages would be another sequence's
+    with pytest.raises(ValueError):
+        mc.mc_addr_expand(runs, capacity)
