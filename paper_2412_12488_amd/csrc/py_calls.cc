@@ -130,22 +130,29 @@ bool to_list(PyObject* o, std::vector<int32_t>* out) {
       PyErr_Clear();
     }
   }
-  PyObject* f = PySequence_Fast(o, "a sequence of integers is expected");
-  if (!f) return false;
-  const Py_ssize_t n = PySequence_Fast_GET_SIZE(f);
+  // Exact ints are read in place: no Python code runs between two of them.  Any other number goes
+  // through its __int__, which may change the caller's own list or let another thread do so: the
+  // items are then read from a copy that holds them.
+  if (PyList_CheckExact(o) || PyTuple_CheckExact(o)) {
+    const Py_ssize_t n = PySequence_Fast_GET_SIZE(o);
+    PyObject** items = PySequence_Fast_ITEMS(o);
+    Py_ssize_t i = 0;
+    out->resize((size_t)n);
+    while (i < n && PyLong_CheckExact(items[i]) && to_i32(items[i], &(*out)[(size_t)i])) ++i;
+    if (i == n) return true;
+    if (PyErr_Occurred()) return false;
+  }
+  PyObject* t = PySequence_Tuple(o);
+  if (!t) return false;
+  const Py_ssize_t n = PyTuple_GET_SIZE(t);
   out->resize((size_t)n);
   bool ok = true;
-  for (Py_ssize_t i = 0; i < n && ok; ++i) {
-    PyObject* x = PySequence_Fast_GET_ITEM(f, i);
-    if (PyLong_Check(x)) {
-      ok = to_i32(x, &(*out)[(size_t)i]);
-    } else {                                   // numpy scalars, floats: as int(x)
-      PyObject* v = PyNumber_Long(x);
-      ok = v && to_i32(v, &(*out)[(size_t)i]);
-      Py_XDECREF(v);
-    }
+  for (Py_ssize_t i = 0; i < n && ok; ++i) {   // numpy scalars, floats: as int(x)
+    PyObject* v = PyNumber_Long(PyTuple_GET_ITEM(t, i));
+    ok = v && to_i32(v, &(*out)[(size_t)i]);
+    Py_XDECREF(v);
   }
-  Py_DECREF(f);
+  Py_DECREF(t);
   return ok;
 }
 
@@ -387,17 +394,17 @@ PyObject* addr_compress(PyObject*, PyObject* const* a, Py_ssize_t n) {
 PyObject* addr_expand(PyObject*, PyObject* const* a, Py_ssize_t n) {
   Args g(a, n, 2);
   if (!g.ok) return nullptr;
-  PyObject* f = PySequence_Fast(a[0], "a sequence of (first page, count) runs is expected");
+  PyObject* f = PySequence_Tuple(a[0]);     // a run's own numbers may run Python code: see to_list
   if (!f) return nullptr;
-  const Py_ssize_t n_runs = PySequence_Fast_GET_SIZE(f);
+  const Py_ssize_t n_runs = PyTuple_GET_SIZE(f);
   std::vector<int32_t> flat;
   flat.reserve(2 * (size_t)n_runs);
   std::vector<int32_t> pair;
   int64_t sum = 0;
   for (Py_ssize_t i = 0; i < n_runs; ++i) {
-    PyObject* r = PySequence_Fast_GET_ITEM(f, i);
-    if (PyTuple_Check(r) && PyTuple_GET_SIZE(r) == 2 && PyLong_Check(PyTuple_GET_ITEM(r, 0)) &&
-        PyLong_Check(PyTuple_GET_ITEM(r, 1))) {
+    PyObject* r = PyTuple_GET_ITEM(f, i);
+    if (PyTuple_CheckExact(r) && PyTuple_GET_SIZE(r) == 2 && PyLong_CheckExact(PyTuple_GET_ITEM(r, 0)) &&
+        PyLong_CheckExact(PyTuple_GET_ITEM(r, 1))) {
       pair.resize(2);
       if (!to_i32(PyTuple_GET_ITEM(r, 0), &pair[0]) || !to_i32(PyTuple_GET_ITEM(r, 1), &pair[1])) {
         Py_DECREF(f);

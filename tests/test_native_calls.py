@@ -1,10 +1,23 @@
 """The native marshalling of the binding (CPU): every form of argument the calls take."""
 import ctypes
+import os
+import subprocess
+import sys
 
 import numpy as np
 import pytest
 
 import paper_2412_12488_amd as mc
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+
+
+def in_child(code, timeout=120):
+    """Runs code in a process of its own (what it tests used to end the process); its output."""
+    res = subprocess.run([sys.executable, "-c", "import paper_2412_12488_amd as mc\n" + code], cwd=ROOT,
+                         capture_output=True, text=True, timeout=timeout)
+    assert res.returncode == 0, (res.returncode, res.stderr[-2000:])
+    return res.stdout
 
 
 @pytest.mark.parametrize("form", [list, tuple, lambda v: np.array(v, dtype=np.int32),
@@ -58,3 +71,31 @@ def test_runs_that_are_not_pairs_are_refused(runs, capacity):
     # never re-cut into other pairs: their pages would be another sequence's
     with pytest.raises(ValueError):
         mc.mc_addr_expand(runs, capacity)
+
+
+def test_lists_that_change_while_they_are_read():
+    # __int__ is the caller's code: it may empty the very list that is being converted
+    out = in_child("""
+class Clears:
+    def __int__(self):
+        pages.clear()
+        return 1
+pages = [Clears() for _ in range(1000)]
+print(mc.mc_addr_compress(pages) == [(1, 1)] * 1000, pages)
+pages = [Clears() for _ in range(1000)]
+print(mc.mc_addr_expand([(7, 1), pages[:2], (9, 1)]) == [7, 1, 9], pages)
+runs = pages = [[Clears(), 1] for _ in range(1000)]
+print(mc.mc_addr_expand(runs) == [1] * 1000, runs)
+pages = [1, 2, Clears(), 4, 5]
+print(mc.mc_addr_compress(pages) == [(1, 2), (1, 1), (4, 2)], pages)
+""")
+    assert out.split() == ["True", "[]"] * 4
+
+
+def test_numbers_are_read_as_int_reads_them():
+    class Nine(int):
+        def __int__(self):
+            return 9
+    assert mc.mc_addr_compress([4, Nine(5), True, np.int64(2)]) == [(4, 1), (9, 1), (1, 2)]
+    assert mc.mc_addr_expand([(Nine(5), 1)]) == [9]
+    assert mc.mc_addr_compress([2**32 + 3, -2**32 + 4]) == [(3, 2)]       # wraps as a C int does
