@@ -16,6 +16,10 @@
 #include <stdint.h>
 #include <string.h>
 
+#include <exception>
+#include <memory>
+#include <new>
+#include <stdexcept>
 #include <vector>
 
 #include "mc_kv.h"
@@ -26,6 +30,37 @@ PyObject* s_data_ptr;      // interned attribute names
 PyObject* s_cuda_stream;
 PyObject* g_get_device;    // torch's current-device and current-stream look-ups
 PyObject* g_get_stream;
+
+// A reference, a buffer and the released interpreter lock: given back on every way out, a C++
+// exception's included.
+struct Ref {
+  PyObject* p;
+  explicit Ref(PyObject* p_) : p(p_) {}
+  ~Ref() { Py_XDECREF(p); }
+  Ref(const Ref&) = delete;
+  Ref& operator=(const Ref&) = delete;
+};
+
+struct Buffer {
+  Py_buffer b;
+  bool held;
+  Buffer(PyObject* o, int flags) : held(PyObject_GetBuffer(o, &b, flags) == 0) {}
+  ~Buffer() {
+    if (held) PyBuffer_Release(&b);
+  }
+  Buffer(const Buffer&) = delete;
+  Buffer& operator=(const Buffer&) = delete;
+};
+
+struct Unlocked {
+  PyThreadState* state = PyEval_SaveThread();
+  ~Unlocked() { PyEval_RestoreThread(state); }
+};
+
+// Room for n >= 0 results, not cleared: the library writes what is read of it.
+std::unique_ptr<int32_t[]> room(int64_t n) {
+  return std::unique_ptr<int32_t[]>(new int32_t[(size_t)n + 1]);
+}
 
 // ---- one argument each; false with a Python error set ----
 bool to_i32(PyObject* o, int32_t* out) {
@@ -64,23 +99,21 @@ bool to_handle(PyObject* o, void** out) {
     *out = (void*)(uintptr_t)PyLong_AsUnsignedLongLongMask(o);
     return !PyErr_Occurred();
   }
-  Py_buffer b;
-  if (PyObject_GetBuffer(o, &b, PyBUF_SIMPLE) != 0) return false;
-  const bool ok = b.len == (Py_ssize_t)sizeof(void*);
-  if (ok) memcpy(out, b.buf, sizeof(void*));
+  const Buffer v(o, PyBUF_SIMPLE);
+  if (!v.held) return false;
+  const bool ok = v.b.len == (Py_ssize_t)sizeof(void*);
+  if (ok) memcpy(out, v.b.buf, sizeof(void*));
   else PyErr_SetString(PyExc_TypeError, "a handle of this library is expected");
-  PyBuffer_Release(&b);
   return ok;
 }
 
 // pool descriptor: the ctypes structure's own bytes
 bool to_pool(PyObject* o, mc_pool_desc* out) {
-  Py_buffer b;
-  if (PyObject_GetBuffer(o, &b, PyBUF_SIMPLE) != 0) return false;
-  const bool ok = b.len == (Py_ssize_t)sizeof(mc_pool_desc);
-  if (ok) memcpy(out, b.buf, sizeof(mc_pool_desc));
+  const Buffer v(o, PyBUF_SIMPLE);
+  if (!v.held) return false;
+  const bool ok = v.b.len == (Py_ssize_t)sizeof(mc_pool_desc);
+  if (ok) memcpy(out, v.b.buf, sizeof(mc_pool_desc));
   else PyErr_SetString(PyExc_TypeError, "an mc_pool_desc is expected");
-  PyBuffer_Release(&b);
   return ok;
 }
 
@@ -117,17 +150,13 @@ bool to_stream(PyObject* o, void** out) {
 // page or token list: any sequence of numbers; int32 buffers (numpy) in one copy
 bool to_list(PyObject* o, std::vector<int32_t>* out) {
   if (!PyList_Check(o) && !PyTuple_Check(o) && PyObject_CheckBuffer(o)) {
-    Py_buffer b;
-    if (PyObject_GetBuffer(o, &b, PyBUF_FORMAT | PyBUF_C_CONTIGUOUS) == 0) {
-      const bool plain = b.ndim == 1 && b.itemsize == 4 && b.format && !strcmp(b.format, "i");
-      if (plain) {
-        out->resize((size_t)b.shape[0]);
-        if (b.len) memcpy(out->data(), b.buf, (size_t)b.len);
-      }
-      PyBuffer_Release(&b);
-      if (plain) return true;
-    } else {
+    const Buffer v(o, PyBUF_FORMAT | PyBUF_C_CONTIGUOUS);
+    if (!v.held) {
       PyErr_Clear();
+    } else if (v.b.ndim == 1 && v.b.itemsize == 4 && v.b.format && !strcmp(v.b.format, "i")) {
+      out->resize((size_t)v.b.shape[0]);
+      if (v.b.len) memcpy(out->data(), v.b.buf, (size_t)v.b.len);
+      return true;
     }
   }
   // Exact ints are read in place: no Python code runs between two of them.  Any other number goes
@@ -142,18 +171,15 @@ bool to_list(PyObject* o, std::vector<int32_t>* out) {
     if (i == n) return true;
     if (PyErr_Occurred()) return false;
   }
-  PyObject* t = PySequence_Tuple(o);
-  if (!t) return false;
-  const Py_ssize_t n = PyTuple_GET_SIZE(t);
+  const Ref t(PySequence_Tuple(o));
+  if (!t.p) return false;
+  const Py_ssize_t n = PyTuple_GET_SIZE(t.p);
   out->resize((size_t)n);
-  bool ok = true;
-  for (Py_ssize_t i = 0; i < n && ok; ++i) {   // numpy scalars, floats: as int(x)
-    PyObject* v = PyNumber_Long(PyTuple_GET_ITEM(t, i));
-    ok = v && to_i32(v, &(*out)[(size_t)i]);
-    Py_XDECREF(v);
+  for (Py_ssize_t i = 0; i < n; ++i) {         // numpy scalars, floats: as int(x)
+    const Ref v(PyNumber_Long(PyTuple_GET_ITEM(t.p, i)));
+    if (!v.p || !to_i32(v.p, &(*out)[(size_t)i])) return false;
   }
-  Py_DECREF(t);
-  return ok;
+  return true;
 }
 
 PyObject* from_list(const int32_t* v, int64_t n) {
@@ -207,11 +233,12 @@ struct Args {
   }
 };
 
-#define CALL(expr)            \
-  mc_status st;               \
-  Py_BEGIN_ALLOW_THREADS      \
-  st = (expr);                \
-  Py_END_ALLOW_THREADS        \
+#define CALL(expr)        \
+  mc_status st;           \
+  {                       \
+    const Unlocked u;     \
+    st = (expr);          \
+  }                       \
   return status(st)
 
 // ---- device calls ----
@@ -335,9 +362,12 @@ PyObject* alloc_pages(PyObject*, PyObject* const* a, Py_ssize_t n) {
   void* alloc = g.handle();
   const int32_t want = g.i32();
   if (!g.ok) return nullptr;
-  std::vector<int32_t> out((size_t)(want > 0 ? want : 0) + 1);
-  const mc_status st = mc_kv_alloc_pages(alloc, want, out.data());
-  return with_status(st, from_list(out.data(), st == MC_OK ? want : 0));
+  // room for what the pool can give: the library refuses more before it writes any
+  int32_t free_now = 0;
+  mc_kv_allocator_num_free(alloc, &free_now);
+  const auto out = room(want > free_now ? free_now : want > 0 ? want : 0);
+  const mc_status st = mc_kv_alloc_pages(alloc, want, out.get());
+  return with_status(st, from_list(out.get(), st == MC_OK ? want : 0));
 }
 
 PyObject* free_pages(PyObject*, PyObject* const* a, Py_ssize_t n) {
@@ -370,9 +400,9 @@ PyObject* addr_compress(PyObject*, PyObject* const* a, Py_ssize_t n) {
   Args g(a, n, 1);
   const std::vector<int32_t> pages = g.list();
   if (!g.ok) return nullptr;
-  std::vector<int32_t> runs(2 * pages.size() + 2);
+  const auto runs = room(2 * (int64_t)pages.size());
   int32_t nr = 0;
-  const mc_status st = mc_addr_compress(pages.data(), (int32_t)pages.size(), runs.data(), &nr);
+  const mc_status st = mc_addr_compress(pages.data(), (int32_t)pages.size(), runs.get(), &nr);
   if (st != MC_OK) nr = 0;
   PyObject* l = PyList_New(nr);
   for (int32_t i = 0; l && i < nr; ++i) {
@@ -394,46 +424,42 @@ PyObject* addr_compress(PyObject*, PyObject* const* a, Py_ssize_t n) {
 PyObject* addr_expand(PyObject*, PyObject* const* a, Py_ssize_t n) {
   Args g(a, n, 2);
   if (!g.ok) return nullptr;
-  PyObject* f = PySequence_Tuple(a[0]);     // a run's own numbers may run Python code: see to_list
-  if (!f) return nullptr;
-  const Py_ssize_t n_runs = PyTuple_GET_SIZE(f);
+  const Ref f(PySequence_Tuple(a[0]));      // a run's own numbers may run Python code: see to_list
+  if (!f.p) return nullptr;
+  const Py_ssize_t n_runs = PyTuple_GET_SIZE(f.p);
   std::vector<int32_t> flat;
   flat.reserve(2 * (size_t)n_runs);
   std::vector<int32_t> pair;
   int64_t sum = 0;
   for (Py_ssize_t i = 0; i < n_runs; ++i) {
-    PyObject* r = PyTuple_GET_ITEM(f, i);
+    PyObject* r = PyTuple_GET_ITEM(f.p, i);
     if (PyTuple_CheckExact(r) && PyTuple_GET_SIZE(r) == 2 && PyLong_CheckExact(PyTuple_GET_ITEM(r, 0)) &&
         PyLong_CheckExact(PyTuple_GET_ITEM(r, 1))) {
       pair.resize(2);
-      if (!to_i32(PyTuple_GET_ITEM(r, 0), &pair[0]) || !to_i32(PyTuple_GET_ITEM(r, 1), &pair[1])) {
-        Py_DECREF(f);
+      if (!to_i32(PyTuple_GET_ITEM(r, 0), &pair[0]) || !to_i32(PyTuple_GET_ITEM(r, 1), &pair[1]))
         return nullptr;
-      }
     } else if (!to_list(r, &pair)) {
-      Py_DECREF(f);
       return nullptr;
     }
     // joined without this check, numbers of a malformed run would be read as the next run's
-    if (pair.size() != 2) {
-      Py_DECREF(f);
+    if (pair.size() != 2)
       return PyErr_Format(PyExc_ValueError, "run %zd holds %zu numbers, not (first page, count)", i,
                           pair.size());
-    }
     if (pair[1] > 0) sum += pair[1];
     flat.insert(flat.end(), pair.begin(), pair.end());
   }
-  Py_DECREF(f);
   int32_t capacity = 0;
   if (a[1] != Py_None) {
     if (!to_i32(a[1], &capacity)) return nullptr;
   } else {
     capacity = (int32_t)(sum < 0x7fffffff ? sum : 0x7fffffff);
   }
-  std::vector<int32_t> out((size_t)(capacity > 0 ? capacity : 0) + 1);
+  // The runs come from another engine: no room is taken for counts that the capacity refuses.
+  if (capacity > 0 && sum > capacity) capacity = 0;
+  const auto out = room(sum <= capacity ? sum : 0);
   int32_t got = 0;
-  const mc_status st = mc_addr_expand(flat.data(), (int32_t)n_runs, out.data(), capacity, &got);
-  return with_status(st, from_list(out.data(), st == MC_OK ? got : 0));
+  const mc_status st = mc_addr_expand(flat.data(), (int32_t)n_runs, out.get(), capacity, &got);
+  return with_status(st, from_list(out.get(), st == MC_OK ? got : 0));
 }
 
 PyObject* index_insert(PyObject*, PyObject* const* a, Py_ssize_t n) {
@@ -453,11 +479,11 @@ PyObject* index_match(PyObject*, PyObject* const* a, Py_ssize_t n) {
   void* index = g.handle();
   const std::vector<int32_t> tokens = g.list();
   if (!g.ok) return nullptr;
-  std::vector<int32_t> out(tokens.size() / 16 + 1);
+  const auto out = room((int64_t)tokens.size() / 16);
   int32_t m = 0;
   const mc_status st =
-      mc_prefix_index_match(index, tokens.data(), (int32_t)tokens.size(), out.data(), &m);
-  PyObject* l = from_list(out.data(), st == MC_OK ? m / 16 : 0);
+      mc_prefix_index_match(index, tokens.data(), (int32_t)tokens.size(), out.get(), &m);
+  PyObject* l = from_list(out.get(), st == MC_OK ? m / 16 : 0);
   return l ? Py_BuildValue("(iiN)", (int)st, (int)m, l) : nullptr;
 }
 
@@ -473,20 +499,34 @@ PyObject* prep_recv(PyObject*, PyObject* const* a, Py_ssize_t n) {
     return nullptr;
   }
   const int64_t pages = end > 0 ? ((int64_t)end + 15) / 16 : 0;
-  std::vector<int32_t> out((size_t)pages + 1);
+  const auto out = room(pages);
   int32_t m = 0;
-  const mc_status st = mc_prep_recv(index, alloc, prompt.data(), end, out.data(), &m);
-  PyObject* l = from_list(out.data(), st == MC_OK ? pages : 0);
+  const mc_status st = mc_prep_recv(index, alloc, prompt.data(), end, out.get(), &m);
+  PyObject* l = from_list(out.get(), st == MC_OK ? pages : 0);
   return l ? Py_BuildValue("(iiN)", (int)st, (int)m, l) : nullptr;
 }
 
-#define FN(name) {#name, (PyCFunction)(void (*)(void))name, METH_FASTCALL, nullptr}
+// C++ exceptions end here: one that reached the interpreter would end the process.
+template <PyObject* (*F)(PyObject*, PyObject* const*, Py_ssize_t)>
+PyObject* guarded(PyObject* self, PyObject* const* a, Py_ssize_t n) {
+  try {
+    return F(self, a, n);
+  } catch (const std::bad_alloc&) {
+    return PyErr_NoMemory();
+  } catch (const std::length_error&) {
+    return PyErr_NoMemory();
+  } catch (const std::exception& e) {
+    PyErr_SetString(PyExc_RuntimeError, e.what());
+    return nullptr;
+  }
+}
+
+#define ENTRY(name, fn) {name, (PyCFunction)(void (*)(void))guarded<fn>, METH_FASTCALL, nullptr}
+#define FN(fn) ENTRY(#fn, fn)
 PyMethodDef kMethods[] = {
     FN(append), FN(append_send), FN(plan), FN(attn), FN(attn_noalloc), FN(copy_page),
-    {"pack_range", (PyCFunction)(void (*)(void))copy_range<true>, METH_FASTCALL, nullptr},
-    {"unpack_range", (PyCFunction)(void (*)(void))copy_range<false>, METH_FASTCALL, nullptr},
-    {"pack_batch", (PyCFunction)(void (*)(void))copy_batch<true>, METH_FASTCALL, nullptr},
-    {"unpack_batch", (PyCFunction)(void (*)(void))copy_batch<false>, METH_FASTCALL, nullptr},
+    ENTRY("pack_range", copy_range<true>), ENTRY("unpack_range", copy_range<false>),
+    ENTRY("pack_batch", copy_batch<true>), ENTRY("unpack_batch", copy_batch<false>),
     FN(alloc_pages), FN(free_pages), FN(check_page_table), FN(plan_remote_send),
     FN(addr_compress), FN(addr_expand), FN(index_insert), FN(index_match), FN(prep_recv),
     {nullptr, nullptr, 0, nullptr}};

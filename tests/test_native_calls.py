@@ -99,3 +99,30 @@ def test_numbers_are_read_as_int_reads_them():
     assert mc.mc_addr_compress([4, Nine(5), True, np.int64(2)]) == [(4, 1), (9, 1), (1, 2)]
     assert mc.mc_addr_expand([(Nine(5), 1)]) == [9]
     assert mc.mc_addr_compress([2**32 + 3, -2**32 + 4]) == [(3, 2)]       # wraps as a C int does
+
+
+def test_no_memory_is_an_exception_not_the_end_of_the_process():
+    # 1 GiB is left; the sizes asked for take 2 GiB and more
+    out = in_child("""
+import resource
+alloc = mc.mc_kv_allocator_create(8)
+now = int(open("/proc/self/statm").read().split()[0]) * resource.getpagesize()
+resource.setrlimit(resource.RLIMIT_AS, (now + (1 << 30), -1))
+def tried(f):
+    try:
+        return f()
+    except MemoryError:
+        return "MemoryError"
+    except mc.McError as e:
+        return mc.status_string(e.status)
+most = 2**31 - 1
+print(tried(lambda: mc.mc_addr_expand([(0, most)])))
+print(tried(lambda: mc.mc_addr_expand([(0, most)], capacity=8)))
+print(tried(lambda: mc.mc_addr_expand([(0, 2)] * 3, capacity=most)))
+print(tried(lambda: mc.mc_addr_expand([(0, most)] * 3)))
+print(tried(lambda: mc.mc_kv_alloc_pages(alloc, most)))
+print(tried(lambda: mc.mc_kv_check_page_table([0], most)))
+print(tried(lambda: mc.mc_kv_alloc_pages(alloc, 8)))
+""")
+    assert out.splitlines() == ["MemoryError", "MC_ERR_RANGE", "[0, 1, 0, 1, 0, 1]", "MC_ERR_RANGE",
+                                "MC_ERR_NO_PAGES", "MemoryError", "[0, 1, 2, 3, 4, 5, 6, 7]"]
