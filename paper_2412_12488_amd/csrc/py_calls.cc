@@ -147,8 +147,8 @@ bool to_stream(PyObject* o, void** out) {
   return ok;
 }
 
-// page or token list: any sequence of numbers; int32 buffers (numpy) in one copy
-bool to_list(PyObject* o, std::vector<int32_t>* out) {
+// the numbers of any iterable; int32 buffers (numpy) in one copy
+bool to_numbers(PyObject* o, std::vector<int32_t>* out) {
   if (!PyList_Check(o) && !PyTuple_Check(o) && PyObject_CheckBuffer(o)) {
     const Buffer v(o, PyBUF_FORMAT | PyBUF_C_CONTIGUOUS);
     if (!v.held) {
@@ -180,6 +180,11 @@ bool to_list(PyObject* o, std::vector<int32_t>* out) {
     if (!v.p || !to_i32(v.p, &(*out)[(size_t)i])) return false;
   }
   return true;
+}
+
+// page or token list: anything with a length (an iterator may be empty by the second look at it)
+bool to_list(PyObject* o, std::vector<int32_t>* out) {
+  return PyObject_Size(o) >= 0 && to_numbers(o, out);
 }
 
 PyObject* from_list(const int32_t* v, int64_t n) {
@@ -424,7 +429,8 @@ PyObject* addr_compress(PyObject*, PyObject* const* a, Py_ssize_t n) {
 PyObject* addr_expand(PyObject*, PyObject* const* a, Py_ssize_t n) {
   Args g(a, n, 2);
   if (!g.ok) return nullptr;
-  const Ref f(PySequence_Tuple(a[0]));      // a run's own numbers may run Python code: see to_list
+  if (PyObject_Size(a[0]) < 0) return nullptr;
+  const Ref f(PySequence_Tuple(a[0]));   // a run's own numbers may run Python code: see to_numbers
   if (!f.p) return nullptr;
   const Py_ssize_t n_runs = PyTuple_GET_SIZE(f.p);
   std::vector<int32_t> flat;
@@ -438,7 +444,7 @@ PyObject* addr_expand(PyObject*, PyObject* const* a, Py_ssize_t n) {
       pair.resize(2);
       if (!to_i32(PyTuple_GET_ITEM(r, 0), &pair[0]) || !to_i32(PyTuple_GET_ITEM(r, 1), &pair[1]))
         return nullptr;
-    } else if (!to_list(r, &pair)) {
+    } else if (!to_numbers(r, &pair)) {
       return nullptr;
     }
     // joined without this check, numbers of a malformed run would be read as the next run's

@@ -126,3 +126,14 @@ print(tried(lambda: mc.mc_kv_alloc_pages(alloc, 8)))
 """)
     assert out.splitlines() == ["MemoryError", "MC_ERR_RANGE", "[0, 1, 0, 1, 0, 1]", "MC_ERR_RANGE",
                                 "MC_ERR_NO_PAGES", "MemoryError", "[0, 1, 2, 3, 4, 5, 6, 7]"]
+
+
+def test_iterators_are_refused():
+    for numbers in (iter([1, 2]), (x for x in [1, 2]), map(int, "12")):
+        with pytest.raises(TypeError):
+            mc.mc_addr_compress(numbers)
+    with pytest.raises(TypeError):
+        mc.mc_addr_expand(iter([(1, 2)]))
+    assert mc.mc_addr_compress({4: 0, 5: 0}) == [(4, 2)]        # what has a length is a list of numbers
+    assert mc.mc_addr_compress("12") == [(1, 2)]
+    assert mc.mc_addr_compress(range(3)) == [(0, 3)]
