@@ -232,9 +232,9 @@ struct Args {
   const int32_t* pi32() { return static_cast<const int32_t*>(ptr()); }
   float f32() {
     if (!ok) return 0.f;
-    const double v = PyFloat_AsDouble(a[at++]);
-    if (v == -1.0 && PyErr_Occurred()) ok = false;
-    return (float)v;
+    const Ref v(PyNumber_Float(a[at++]));      // as float(x), text included
+    if (!v.p) ok = false;
+    return v.p ? (float)PyFloat_AS_DOUBLE(v.p) : 0.f;
   }
 };
 

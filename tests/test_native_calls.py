@@ -137,3 +137,14 @@ def test_iterators_are_refused():
     assert mc.mc_addr_compress({4: 0, 5: 0}) == [(4, 2)]        # what has a length is a list of numbers
     assert mc.mc_addr_compress("12") == [(1, 2)]
     assert mc.mc_addr_compress(range(3)) == [(0, 3)]
+
+
+@pytest.mark.parametrize("scale", [0.5, 1, "0.5", np.float32(0.5), np.float64(0.5), True])
+def test_scales_are_read_as_float_reads_them(scale):
+    pool = mc.pool_desc(4096, 1, 1, 1, mc.MC_BF16)
+    with pytest.raises(mc.McError) as e:        # read; then refused for the workspace of no bytes
+        mc.mc_prefix_prefill_attn(pool, 0, 16, 1, 1, 1, 16, 16, 16, 16, scale, 16, 16, 16, 0, stream=0)
+    assert e.value.status == mc.MC_ERR_INVALID
+    for bad, error in ((None, TypeError), ("half", ValueError)):
+        with pytest.raises(error):
+            mc.mc_prefix_prefill_attn(pool, 0, 16, 1, 1, 1, 16, 16, 16, 16, bad, 16, 16, 16, 0, stream=0)
