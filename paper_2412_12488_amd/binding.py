@@ -37,6 +37,10 @@ class McError(RuntimeError):
         super().__init__(f"{where}: {status_string(status)}")
 
 
+class McArgumentError(C.ArgumentError, TypeError):
+    """An argument of a type the call does not take."""
+
+
 class mc_send_plan(C.Structure):
     _fields_ = [(n, C.c_int32) for n in ("copy_begin", "copy_end", "prefill_begin", "prefill_end",
                                          "send_begin", "send_end")]
@@ -54,8 +58,10 @@ class _LazyCalls:
     def __getattr__(self, name):
         global _calls
         lib()                        # builds what is missing; loads libmc_kv.so
-        _calls = importlib.import_module("._calls", __package__)
-        return getattr(_calls, name)
+        native = importlib.import_module("._calls", __package__)
+        native.setup(mc_pool_desc, C.c_void_p, C.c_int32, C.c_size_t, McArgumentError)
+        _calls = native
+        return getattr(native, name)
 
 
 _calls = _LazyCalls()

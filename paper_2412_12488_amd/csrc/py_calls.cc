@@ -7,9 +7,10 @@
 // through ctypes took another 5 to 7, so that a decode step over eight layers (17 calls) was
 // bound by the host; a request's token list went through three Python-level loops.
 //
-// Accepted as before: tensors (anything with data_ptr()), integer addresses or None for buffers;
-// ctypes handles for host objects; integers wrap to 32 bits as C's do; sequences of numbers for
-// token and page lists.  The interpreter lock is released around every library call.
+// Accepted: tensors (anything with data_ptr()), integer addresses or None for buffers; c_void_p,
+// integers or None for handles of host objects; the library's own mc_pool_desc; for counts what
+// ctypes takes as c_int32 (integers wrap to 32 bits as C's do); sequences of numbers for token and
+// page lists.  Anything else is an ArgumentError before the library is called.  The interpreter lock is released around every library call.
 #define PY_SSIZE_T_CLEAN
 #include <Python.h>
 
@@ -28,6 +29,10 @@ namespace {
 
 PyObject* s_data_ptr;      // interned attribute names
 PyObject* s_cuda_stream;
+PyObject* s_value;
+PyObject* s_as_parameter;
+// from binding.py (setup): the types whose content is taken over, and the error for other objects
+PyObject *t_pool, *t_pointer, *t_i32, *t_size, *t_error;
 PyObject* g_get_device;    // torch's current-device and current-stream look-ups
 PyObject* g_get_stream;
 
@@ -63,88 +68,103 @@ std::unique_ptr<int32_t[]> room(int64_t n) {
 }
 
 // ---- one argument each; false with a Python error set ----
+bool is_a(PyObject* o, PyObject* type) {
+  return type && PyObject_TypeCheck(o, reinterpret_cast<PyTypeObject*>(type));
+}
+
+bool wrong_type(PyObject* o, const char* wanted) {
+  PyErr_Format(t_error ? t_error : PyExc_TypeError, "%s is expected, not %.200s", wanted,
+               Py_TYPE(o)->tp_name);
+  return false;
+}
+
+// What stands for o in a C call: the value of a ctypes number, or its _as_parameter_.  Null (and
+// no error) if nothing does.
+PyObject* stand_in(PyObject* o, PyObject* type) {
+  if (is_a(o, type)) return PyObject_GetAttr(o, s_value);
+  PyObject* v = PyObject_GetAttr(o, s_as_parameter);
+  if (!v && PyErr_ExceptionMatches(PyExc_AttributeError)) PyErr_Clear();
+  return v;
+}
+
+// An integer of any size, wrapped; type is the ctypes number that stands for it too.
+bool to_u64(PyObject* o, PyObject* type, unsigned long long* out) {
+  if (PyIndex_Check(o)) {
+    *out = PyLong_AsUnsignedLongLongMask(o);
+    return *out != (unsigned long long)-1 || !PyErr_Occurred();
+  }
+  const Ref v(stand_in(o, type));
+  if (!v.p) return !PyErr_Occurred() && wrong_type(o, "an integer");
+  if (Py_EnterRecursiveCall(" in an integer argument")) return false;
+  const bool ok = to_u64(v.p, type, out);
+  Py_LeaveRecursiveCall();
+  return ok;
+}
+
 bool to_i32(PyObject* o, int32_t* out) {
-  const unsigned long long v = PyLong_AsUnsignedLongLongMask(o);
-  if (v == (unsigned long long)-1 && PyErr_Occurred()) return false;
+  unsigned long long v = 0;
+  if (!to_u64(o, t_i32, &v)) return false;
   *out = (int32_t)(uint32_t)v;
   return true;
 }
 
 bool to_size(PyObject* o, size_t* out) {
-  const unsigned long long v = PyLong_AsUnsignedLongLongMask(o);
-  if (v == (unsigned long long)-1 && PyErr_Occurred()) return false;
+  unsigned long long v = 0;
+  if (!to_u64(o, t_size, &v)) return false;
   *out = (size_t)v;
   return true;
 }
 
-// device buffer: None, an integer address, or an object with data_ptr()
-bool to_ptr(PyObject* o, void** out) {
-  if (o == Py_None) { *out = nullptr; return true; }
-  PyObject* v = nullptr;
-  if (!PyLong_Check(o)) {
-    v = PyObject_CallMethodNoArgs(o, s_data_ptr);
-    if (!v) return false;
-    o = v;
-  }
-  *out = (void*)(uintptr_t)PyLong_AsUnsignedLongLongMask(o);
-  const bool ok = !PyErr_Occurred();
-  Py_XDECREF(v);
-  return ok;
-}
-
-// host handle: None, an integer, or a ctypes c_void_p
+// address or host handle: None, an integer, or a c_void_p
 bool to_handle(PyObject* o, void** out) {
   if (o == Py_None) { *out = nullptr; return true; }
   if (PyLong_Check(o)) {
     *out = (void*)(uintptr_t)PyLong_AsUnsignedLongLongMask(o);
     return !PyErr_Occurred();
   }
-  const Buffer v(o, PyBUF_SIMPLE);
-  if (!v.held) return false;
-  const bool ok = v.b.len == (Py_ssize_t)sizeof(void*);
-  if (ok) memcpy(out, v.b.buf, sizeof(void*));
-  else PyErr_SetString(PyExc_TypeError, "a handle of this library is expected");
+  const Ref v(stand_in(o, t_pointer));
+  if (!v.p) return !PyErr_Occurred() && wrong_type(o, "an address or a handle of this library");
+  if (Py_EnterRecursiveCall(" in a pointer argument")) return false;
+  const bool ok = to_handle(v.p, out);
+  Py_LeaveRecursiveCall();
   return ok;
+}
+
+// device buffer: None, an integer address, or an object with data_ptr()
+bool to_ptr(PyObject* o, void** out) {
+  if (o == Py_None || PyLong_Check(o)) return to_handle(o, out);
+  const Ref v(PyObject_CallMethodNoArgs(o, s_data_ptr));
+  return v.p && to_handle(v.p, out);
 }
 
 // pool descriptor: the ctypes structure's own bytes
 bool to_pool(PyObject* o, mc_pool_desc* out) {
+  if (!is_a(o, t_pool)) return wrong_type(o, "an mc_pool_desc");
   const Buffer v(o, PyBUF_SIMPLE);
-  if (!v.held) return false;
-  const bool ok = v.b.len == (Py_ssize_t)sizeof(mc_pool_desc);
-  if (ok) memcpy(out, v.b.buf, sizeof(mc_pool_desc));
-  else PyErr_SetString(PyExc_TypeError, "an mc_pool_desc is expected");
-  return ok;
+  if (!v.held || v.b.len < (Py_ssize_t)sizeof(mc_pool_desc)) return false;
+  memcpy(out, v.b.buf, sizeof(mc_pool_desc));
+  return true;
 }
 
 // stream: None = torch's current stream, an integer handle, or an object with cuda_stream
 bool to_stream(PyObject* o, void** out) {
-  PyObject* v = nullptr;
   if (o == Py_None) {
     if (!g_get_stream) {
-      PyObject* c = PyImport_ImportModule("torch._C");
-      if (!c) return false;
-      g_get_device = PyObject_GetAttrString(c, "_cuda_getDevice");
-      PyObject* s = g_get_device ? PyObject_GetAttrString(c, "_cuda_getCurrentRawStream") : nullptr;
-      Py_DECREF(c);
-      if (!s) return false;
-      g_get_stream = s;
+      const Ref c(PyImport_ImportModule("torch._C"));
+      if (!c.p) return false;
+      if (!g_get_device) g_get_device = PyObject_GetAttrString(c.p, "_cuda_getDevice");
+      if (!g_get_device) return false;
+      g_get_stream = PyObject_GetAttrString(c.p, "_cuda_getCurrentRawStream");
+      if (!g_get_stream) return false;
     }
-    PyObject* dev = PyObject_CallNoArgs(g_get_device);
-    if (!dev) return false;
-    v = PyObject_CallOneArg(g_get_stream, dev);
-    Py_DECREF(dev);
-  } else if (!PyLong_Check(o)) {
-    v = PyObject_GetAttr(o, s_cuda_stream);
-  } else {
-    Py_INCREF(o);
-    v = o;
+    const Ref dev(PyObject_CallNoArgs(g_get_device));
+    if (!dev.p) return false;
+    const Ref v(PyObject_CallOneArg(g_get_stream, dev.p));
+    return v.p && to_handle(v.p, out);
   }
-  if (!v) return false;
-  *out = (void*)(uintptr_t)PyLong_AsUnsignedLongLongMask(v);
-  const bool ok = !PyErr_Occurred();
-  Py_DECREF(v);
-  return ok;
+  if (PyLong_Check(o)) return to_handle(o, out);
+  const Ref v(PyObject_GetAttr(o, s_cuda_stream));
+  return v.p && to_handle(v.p, out);
 }
 
 // the numbers of any iterable; int32 buffers (numpy) in one copy
@@ -223,6 +243,11 @@ struct Args {
     return v;
   }
   int32_t i32() { return get<int32_t>(to_i32); }
+  // a count that sizes a result: Python integers only
+  int32_t count() {
+    if (ok && !PyIndex_Check(a[at])) ok = wrong_type(a[at], "an integer");
+    return i32();
+  }
   size_t size() { return get<size_t>(to_size); }
   void* ptr() { return get<void*>(to_ptr); }
   void* handle() { return get<void*>(to_handle); }
@@ -365,7 +390,7 @@ PyObject* copy_page(PyObject*, PyObject* const* a, Py_ssize_t n) {
 PyObject* alloc_pages(PyObject*, PyObject* const* a, Py_ssize_t n) {
   Args g(a, n, 2);
   void* alloc = g.handle();
-  const int32_t want = g.i32();
+  const int32_t want = g.count();
   if (!g.ok) return nullptr;
   // room for what the pool can give: the library refuses more before it writes any
   int32_t free_now = 0;
@@ -456,6 +481,7 @@ PyObject* addr_expand(PyObject*, PyObject* const* a, Py_ssize_t n) {
   }
   int32_t capacity = 0;
   if (a[1] != Py_None) {
+    if (!PyIndex_Check(a[1])) { wrong_type(a[1], "an integer"); return nullptr; }
     if (!to_i32(a[1], &capacity)) return nullptr;
   } else {
     capacity = (int32_t)(sum < 0x7fffffff ? sum : 0x7fffffff);
@@ -498,7 +524,7 @@ PyObject* prep_recv(PyObject*, PyObject* const* a, Py_ssize_t n) {
   Args g(a, n, 4);
   void *index = g.handle(), *alloc = g.handle();
   const std::vector<int32_t> prompt = g.list();
-  const int32_t end = g.i32();
+  const int32_t end = g.count();
   if (!g.ok) return nullptr;
   if (end > 0 && (size_t)end > prompt.size()) {
     PyErr_SetString(PyExc_IndexError, "end lies beyond the prompt");
@@ -527,10 +553,23 @@ PyObject* guarded(PyObject* self, PyObject* const* a, Py_ssize_t n) {
   }
 }
 
+// setup(mc_pool_desc, c_void_p, c_int32, c_size_t, error): once, by binding.py
+PyObject* setup(PyObject*, PyObject* const* a, Py_ssize_t n) {
+  if (n != 5) return PyErr_Format(PyExc_TypeError, "%zd arguments given, 5 expected", n);
+  PyObject** to[5] = {&t_pool, &t_pointer, &t_i32, &t_size, &t_error};
+  for (int i = 0; i < 5; ++i)
+    if (!PyType_Check(a[i])) return PyErr_Format(PyExc_TypeError, "types are expected");
+  for (int i = 0; i < 5; ++i) {
+    Py_INCREF(a[i]);
+    Py_XSETREF(*to[i], a[i]);
+  }
+  Py_RETURN_NONE;
+}
+
 #define ENTRY(name, fn) {name, (PyCFunction)(void (*)(void))guarded<fn>, METH_FASTCALL, nullptr}
 #define FN(fn) ENTRY(#fn, fn)
 PyMethodDef kMethods[] = {
-    FN(append), FN(append_send), FN(plan), FN(attn), FN(attn_noalloc), FN(copy_page),
+    FN(setup), FN(append), FN(append_send), FN(plan), FN(attn), FN(attn_noalloc), FN(copy_page),
     ENTRY("pack_range", copy_range<true>), ENTRY("unpack_range", copy_range<false>),
     ENTRY("pack_batch", copy_batch<true>), ENTRY("unpack_batch", copy_batch<false>),
     FN(alloc_pages), FN(free_pages), FN(check_page_table), FN(plan_remote_send),
@@ -546,6 +585,8 @@ PyModuleDef kModule = {PyModuleDef_HEAD_INIT, "_calls",
 PyMODINIT_FUNC PyInit__calls(void) {
   s_data_ptr = PyUnicode_InternFromString("data_ptr");
   s_cuda_stream = PyUnicode_InternFromString("cuda_stream");
-  if (!s_data_ptr || !s_cuda_stream) return nullptr;
+  s_value = PyUnicode_InternFromString("value");
+  s_as_parameter = PyUnicode_InternFromString("_as_parameter_");
+  if (!s_data_ptr || !s_cuda_stream || !s_value || !s_as_parameter) return nullptr;
   return PyModule_Create(&kModule);
 }

@@ -148,3 +148,75 @@ def test_scales_are_read_as_float_reads_them(scale):
     for bad, error in ((None, TypeError), ("half", ValueError)):
         with pytest.raises(error):
             mc.mc_prefix_prefill_attn(pool, 0, 16, 1, 1, 1, 16, 16, 16, 16, bad, 16, 16, 16, 0, stream=0)
+
+
+class Stands:
+    def __init__(self, for_what):
+        self._as_parameter_ = for_what
+
+
+class Holds:
+    def __init__(self, address):
+        self.address = self.cuda_stream = address
+
+    def data_ptr(self):
+        return self.address
+
+
+@pytest.mark.parametrize("one", [1, True, np.int64(1), ctypes.c_int32(1), Stands(1),
+                                 Stands(Stands(ctypes.c_int32(1)))])
+def test_counts_that_c_int32_takes(one):
+    assert mc.mc_plan_remote_send(one, 0, 0, 5) == {"copy": (0, 1), "prefill": (1, 5), "send": (1, 5)}
+    pool = mc.pool_desc(4096, 1, 1, 1, mc.MC_BF16)
+    with pytest.raises(mc.McError) as e:        # the range reaches past the one layer
+        mc.mc_kv_pack_range(pool, one, 2, 16, 1, 0, 1, 16, stream=0)
+    assert e.value.status == mc.MC_ERR_RANGE
+
+
+def test_arguments_of_other_types_never_reach_the_library():
+    pool = mc.pool_desc(4096, 1, 1, 1, mc.MC_BF16)
+    other = (ctypes.c_int32 * (ctypes.sizeof(pool) // 4))()
+    for bad in (bytes(ctypes.sizeof(pool)), bytearray(ctypes.sizeof(pool)), other,
+                np.zeros(ctypes.sizeof(pool), dtype=np.uint8), ctypes.pointer(pool), None, 4096):
+        with pytest.raises(TypeError):
+            mc.mc_kv_pack_range(bad, 0, 1, 16, 1, 0, 1, 16, stream=0)
+    alloc = mc.mc_kv_allocator_create(8)
+    for bad in (np.array([0, 0], dtype=np.int32), np.int64(16), b"8 bytes.", (ctypes.c_int32 * 2)(),
+                ctypes.c_int64(16), 1.0, "x"):
+        with pytest.raises((TypeError, ctypes.ArgumentError)):
+            mc.mc_kv_alloc_pages(bad, 1)
+    for bad in (1.0, "1", None, ctypes.c_int64(1), ctypes.c_float(1), Stands("1")):
+        with pytest.raises(ctypes.ArgumentError):
+            mc.mc_plan_remote_send(bad, 0, 0, 5)
+    own = Stands(None)
+    own._as_parameter_ = own
+    with pytest.raises(RecursionError):
+        mc.mc_plan_remote_send(own, 0, 0, 5)
+    for bad in (1.0, np.int64(16), b"x"):       # of data_ptr() and cuda_stream
+        with pytest.raises(ctypes.ArgumentError):
+            mc.mc_kv_pack_range(pool, 0, 1, Holds(bad), 1, 0, 1, 16, stream=0)
+        with pytest.raises(ctypes.ArgumentError):
+            mc.mc_kv_pack_range(pool, 0, 1, 16, 1, 0, 1, 16, stream=Holds(bad))
+    for bad in (ctypes.c_int32(1), 1.0):        # counts that size a result: integers
+        with pytest.raises(TypeError):
+            mc.mc_kv_alloc_pages(alloc, bad)
+        with pytest.raises(TypeError):
+            mc.mc_addr_expand([(1, 1)], capacity=bad)
+    mc.mc_kv_allocator_destroy(alloc)
+
+
+def test_handles_and_addresses_in_every_form():
+    alloc = mc.mc_kv_allocator_create(4)
+    assert mc.mc_kv_alloc_pages(alloc.value, 1) == [0]
+    assert mc.mc_kv_alloc_pages(Stands(alloc), np.int64(1)) == [1]
+    assert mc.mc_kv_alloc_pages(ctypes.c_void_p(alloc.value), 2) == [2, 3]
+    for null in (None, ctypes.c_void_p(None), 0):
+        with pytest.raises(mc.McError) as e:
+            mc.mc_kv_alloc_pages(null, 1)
+        assert e.value.status == mc.MC_ERR_INVALID
+    mc.mc_kv_allocator_destroy(alloc)
+    pool = mc.pool_desc(4096, 1, 1, 1, mc.MC_BF16)
+    for null in (None, 0, Holds(None), Holds(ctypes.c_void_p(None))):
+        with pytest.raises(mc.McError) as e:
+            mc.mc_kv_pack_range(pool, 0, 1, null, 1, 0, 1, 16, stream=Holds(None))
+        assert e.value.status == mc.MC_ERR_INVALID
