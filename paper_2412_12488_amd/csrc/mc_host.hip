@@ -1,6 +1,8 @@
 // Host-only parts of the library: status names, the page allocator behind
 // prep_recv (paper Sec. 3.1: the receiver reserves entries for the part of the prompt it
 // does not hold), and a host check of destination page tables.
+#include <unistd.h>
+
 #include <algorithm>
 #include <array>
 #include <new>
@@ -18,29 +20,34 @@ struct Allocator {
   std::vector<uint8_t> state;       // 0 free, 1 handed out, 2 = seen earlier in this free call
 };
 
-// Trie over 16-token blocks: (parent node, the block's tokens) -> node; a node knows its page.
+// Trie over 16-token blocks: (the block's tokens, parent node) -> node; a node knows its page.
 struct PrefixIndex {
-  // Hashed: a block costs one look-up whatever the number of blocks recorded (an ordered map
-  // compared 68-byte keys log2(blocks) times, each a cache miss).
-  typedef std::pair<int32_t, std::array<int32_t, mc::kPage>> Key;
+  // Hashed: a block is expected to cost one look-up whatever the number of blocks recorded (an
+  // ordered map compared 68-byte keys log2(blocks) times, each a cache miss).  Tokens come from the
+  // clients of an engine, so the hash is drawn from a strongly universal family by random numbers of
+  // the index's own (pair-multiply-shift, M. Thorup, "High Speed Hashing for Integers and Strings"):
+  // any two keys chosen without those numbers agree in its 32 bits with probability 2^-32, where
+  // blocks made to fit a fixed hash would all fall into one bucket.  (It is not noexcept, so the
+  // table keeps it beside each block and compares blocks on equal ones only.)
+  typedef std::pair<std::array<int32_t, mc::kPage>, int32_t> Key;
   struct Hash {
+    std::array<uint64_t, mc::kPage + 3> a;
     size_t operator()(const Key& k) const {
-      uint64_t h = (uint32_t)k.first;
-      for (int i = 0; i < mc::kPage; i += 2) {
-        const uint64_t two = (uint32_t)k.second[i] | ((uint64_t)(uint32_t)k.second[i + 1] << 32);
-        h = (h ^ two) * 0x9e3779b97f4a7c15ull;
-        h ^= h >> 32;
-      }
-      return (size_t)h;
+      uint64_t h = a[mc::kPage + 2] + a[mc::kPage] * (a[mc::kPage + 1] + (uint32_t)k.second);
+      for (int i = 0; i < mc::kPage; i += 2)     // sums with no chain between the products
+        h += (a[i] + (uint32_t)k.first[i + 1]) * (a[i + 1] + (uint32_t)k.first[i]);
+      return (size_t)(h >> 32);
     }
   };
   std::unordered_map<Key, int32_t, Hash> child;
   std::vector<int32_t> page_of;   // by node id
 
+  explicit PrefixIndex(const Hash& h) : child(0, h) {}
+
   static Key key(int32_t parent, const int32_t* block) {
     Key k;
-    k.first = parent;
-    std::copy(block, block + mc::kPage, k.second.begin());
+    std::copy(block, block + mc::kPage, k.first.begin());
+    k.second = parent;
     return k;
   }
   // whole pages of tokens[0, n) found: their pages go to pages_out (if given)
@@ -199,7 +206,9 @@ mc_status mc_addr_expand(const int32_t* runs, int32_t n_runs, int32_t* pages_out
 
 mc_status mc_prefix_index_create(void** index_out) {
   if (!index_out) return MC_ERR_INVALID;
-  PrefixIndex* x = new (std::nothrow) PrefixIndex();
+  PrefixIndex::Hash hash;
+  if (getentropy(hash.a.data(), sizeof(hash.a)) != 0) return MC_ERR_INVALID;
+  PrefixIndex* x = new (std::nothrow) PrefixIndex(hash);
   if (!x) return MC_ERR_INVALID;
   *index_out = x;
   return MC_OK;

@@ -3,6 +3,7 @@ declares, its host allocator agrees with the oracle's, and argument validation
 rejects bad calls before anything would be launched (no compute call is made here)."""
 import os
 import re
+import time
 
 import numpy as np
 import pytest
@@ -272,6 +273,39 @@ def test_prefix_index_and_prep_recv_match_oracle():
     finally:
         mc.mc_prefix_index_destroy(ix)
         mc.mc_kv_allocator_destroy(al)
+
+
+def colliding_blocks(n, rng):
+    """Blocks that an unkeyed multiply-and-shift chain over pairs of tokens maps to one value: the
+    last two tokens cancel what the first fourteen came to."""
+    mask, blocks = (1 << 64) - 1, []
+    for _ in range(n):
+        tokens = [int(x) for x in rng.integers(0, 1 << 31, size=14)]
+        h = 0xffffffff
+        for i in range(0, 14, 2):
+            h = ((h ^ (tokens[i] | tokens[i + 1] << 32)) * 0x9e3779b97f4a7c15) & mask
+            h ^= h >> 32
+        h ^= 0x123456789abcdef
+        blocks.append(tokens + [x - (x >> 31 << 32) for x in (h & 0xffffffff, h >> 32)])
+    return blocks
+
+
+def test_blocks_chosen_to_collide_cost_what_others_cost():
+    rng, n = np.random.default_rng(12), 10000
+    def seconds(blocks):
+        best = 1e9
+        for _ in range(3):
+            ix = mc.mc_prefix_index_create()
+            t0 = time.perf_counter()
+            for i, b in enumerate(blocks):
+                mc.mc_prefix_index_insert(ix, b, [i])
+            best = min(best, time.perf_counter() - t0)
+            assert mc.mc_prefix_index_match(ix, blocks[n // 2]) == (16, [n // 2])
+            mc.mc_prefix_index_destroy(ix)
+        return best
+    others = [[int(x) for x in b] for b in rng.integers(0, 1 << 31, size=(n, 16))]
+    # one bucket of 10000 blocks: 35 times the others' time here
+    assert seconds(colliding_blocks(n, rng)) < 10 * seconds(others)
 
 
 def test_prefix_index_errors():
