@@ -167,6 +167,9 @@ bool to_stream(PyObject* o, void** out) {
   return v.p && to_handle(v.p, out);
 }
 
+// an exact int's low 32 bits: nothing of it can fail
+int32_t wrapped(PyObject* o) { return (int32_t)(uint32_t)PyLong_AsUnsignedLongLongMask(o); }
+
 // the numbers of any iterable; int32 buffers (numpy) in one copy
 bool to_numbers(PyObject* o, std::vector<int32_t>* out) {
   if (!PyList_Check(o) && !PyTuple_Check(o) && PyObject_CheckBuffer(o)) {
@@ -187,9 +190,9 @@ bool to_numbers(PyObject* o, std::vector<int32_t>* out) {
     PyObject** items = PySequence_Fast_ITEMS(o);
     Py_ssize_t i = 0;
     out->resize((size_t)n);
-    while (i < n && PyLong_CheckExact(items[i]) && to_i32(items[i], &(*out)[(size_t)i])) ++i;
+    int32_t* to = out->data();
+    for (; i < n && PyLong_CheckExact(items[i]); ++i) to[i] = wrapped(items[i]);
     if (i == n) return true;
-    if (PyErr_Occurred()) return false;
   }
   const Ref t(PySequence_Tuple(o));
   if (!t.p) return false;
@@ -466,9 +469,7 @@ PyObject* addr_expand(PyObject*, PyObject* const* a, Py_ssize_t n) {
     PyObject* r = PyTuple_GET_ITEM(f.p, i);
     if (PyTuple_CheckExact(r) && PyTuple_GET_SIZE(r) == 2 && PyLong_CheckExact(PyTuple_GET_ITEM(r, 0)) &&
         PyLong_CheckExact(PyTuple_GET_ITEM(r, 1))) {
-      pair.resize(2);
-      if (!to_i32(PyTuple_GET_ITEM(r, 0), &pair[0]) || !to_i32(PyTuple_GET_ITEM(r, 1), &pair[1]))
-        return nullptr;
+      pair.assign({wrapped(PyTuple_GET_ITEM(r, 0)), wrapped(PyTuple_GET_ITEM(r, 1))});
     } else if (!to_numbers(r, &pair)) {
       return nullptr;
     }
