@@ -50,3 +50,15 @@ def test_decode_pieces(dtype, lens, chunk):
     w = small_workload(950 + len(lens) + lens[0], dtype, Hq, Hkv, lens, [n - 1 for n in lens])
     assert plan_header(w)["chunk_tiles"] == chunk
     check_attention(w)
+
+
+@pytest.mark.parametrize("lens,begins,chunk", [
+    ([1280] + [16] * 255, [1024] + [16] * 255, 8),    # one range among idle sequences: no decode step
+    ([16] * 255 + [700], [16] * 255 + [699], 2),      # one decode row among idle sequences
+    ([16] * 40 + [1300] * 2, [16] * 40 + [1299] * 2, 4),
+    ([900] * 63 + [902], [899] * 63 + [900], 8),      # one row of two new tokens: a range
+])
+def test_decode_pieces_are_for_single_new_tokens(lens, begins, chunk):
+    w = small_workload(970 + chunk, mi.BF16, 8, 1, lens, begins)
+    assert plan_header(w)["chunk_tiles"] == chunk
+    check_attention(w)
