@@ -342,7 +342,7 @@ template <int NT>
 __global__ __launch_bounds__(NT) void plan_kernel(PlanArgs a) {
   __shared__ int scan[5 * NT / 64];   // wavefront totals of the block scans and sums
   __shared__ int hist[kBuckets];
-  __shared__ int s_err, s_maxcost, s_ranges;   // s_ranges: a sequence has more than one new token
+  __shared__ int s_err, s_maxcost;
   // per-sequence arrays of batches that fit: the searches and tile look-ups below stay in LDS
   __shared__ int s_cu[kCuTilesInLds + 1], s_cuq[kCuTilesInLds + 1], s_beg[kCuTilesInLds],
       s_cup[kCuTilesInLds + 1];
@@ -357,7 +357,7 @@ __global__ __launch_bounds__(NT) void plan_kernel(PlanArgs a) {
   __shared__ uint8_t s_tailflag[kTailTilesMax];
   __shared__ int s_tail_bucket, s_tail_take, s_tail_taken;
   const int t = threadIdx.x;
-  if (t == 0) { s_err = 0; s_maxcost = 1; s_ranges = 0; }
+  if (t == 0) { s_err = 0; s_maxcost = 1; }
   for (int i = t; i < kBuckets; i += NT) hist[i] = 0;
   const bool cu_in_lds = a.batch <= kCuTilesInLds;
   if (cu_in_lds) {
@@ -391,7 +391,6 @@ __global__ __launch_bounds__(NT) void plan_kernel(PlanArgs a) {
   }
   // 1. validate, count tiles per sequence (contiguous chunk of sequences per thread)
   int my_tiles = 0, err = 0, maxcost = 1;
-  bool ranges = false;
   if (t == 0 && (cuq(0) != 0 || cuq(a.batch) != a.total_q || cup(0) < 0)) err = 1;
   for (int s = s_lo; s < s_hi; ++s) {
     const int q = cuq(s + 1) - cuq(s), b = beg(s);
@@ -401,12 +400,10 @@ __global__ __launch_bounds__(NT) void plan_kernel(PlanArgs a) {
     const int64_t end = (int64_t)b + q + a.ahead;
     if ((end + kPage - 1) / kPage > np) { err = 1; continue; }
     my_tiles += (q + a.tile_tokens - 1) / a.tile_tokens;
-    ranges |= q > 1;
     maxcost = max(maxcost, (int)((end + kBN - 1) / kBN));
   }
   // (one LDS atomic per wavefront, not per thread: 1024 atomics on one address take microseconds)
   if (__ballot(err != 0) != 0 && (t & 63) == 0) atomicOr(&s_err, 1);
-  if (__ballot(ranges) != 0 && (t & 63) == 0) atomicOr(&s_ranges, 1);
 #pragma unroll
   for (int off = 32; off > 0; off >>= 1) maxcost = max(maxcost, __shfl_xor(maxcost, off));
   if ((t & 63) == 0) atomicMax(&s_maxcost, maxcost);
@@ -622,7 +619,8 @@ __global__ __launch_bounds__(NT) void plan_kernel(PlanArgs a) {
     cost = block_sum<NT>(cost, scan);
     const long long want =
         (cost * a.hkv + (long long)kItemsPerSlot * a.slots - 1) / ((long long)kItemsPerSlot * a.slots);
-    const int shortest = s_ranges ? kMinChunkTiles
+    // (as many q tiles as new tokens: no sequence has two)
+    const int shortest = a.total_q > total_tiles ? kMinChunkTiles
                          : s_maxcost <= kMinChunkTilesShort * kMergeAhead ? kMinChunkTilesShort
                                                                           : kMinChunkTilesDecode;
     L = want < shortest ? shortest : want > (1 << 28) ? (1 << 28) : (int)want;
