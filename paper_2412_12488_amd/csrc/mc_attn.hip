@@ -1594,9 +1594,12 @@ __global__ __launch_bounds__(256) void merge_kernel(MergeArgs a) {
     f32x2 acc = {0.f, 0.f};
     for (int c0 = 0; c0 < nchunks; c0 += 64) {
       const int c = c0 + lane;
-      // exp(-inf) = 0 for a chunk with no key, and for the lanes beyond the last chunk
-      const float w_lane =
-          c < nchunks ? __expf((c0 == 0 ? lse0 : a.part_lse[row_of(c)]) - mx) : 0.f;
+      const float lse = c >= nchunks ? -INFINITY : c0 == 0 ? lse0 : a.part_lse[row_of(c)];
+      // exp(-inf) = 0 for a chunk with no key, and for the lanes beyond the last chunk.  Their rows
+      // are left out, not weighed: a chunk that was not computed left in them what the memory held
+      // before, which may be NaN.
+      const float w_lane = __expf(lse - mx);
+      const unsigned long long computed = __ballot(lse != -INFINITY);
       float sum = w_lane;
 #pragma unroll
       for (int off = 32; off > 0; off >>= 1) sum += __shfl_xor(sum, off);
@@ -1606,7 +1609,7 @@ __global__ __launch_bounds__(256) void merge_kernel(MergeArgs a) {
       if (c0 == 0) {
 #pragma unroll
         for (; k < kMergeAhead; ++k)
-          if (k < n) acc += o_first[k] * __shfl(w_lane, k);
+          if (computed >> k & 1) acc += o_first[k] * __shfl(w_lane, k);
       }
       for (; k < n; k += kMergeAhead) {   // rows in groups whose loads are in flight together
         f32x2 v[kMergeAhead];
@@ -1614,7 +1617,7 @@ __global__ __launch_bounds__(256) void merge_kernel(MergeArgs a) {
         for (int u = 0; u < kMergeAhead; ++u) v[u] = o_of(c0 + min(k + u, n - 1));
 #pragma unroll
         for (int u = 0; u < kMergeAhead; ++u)
-          if (k + u < n) acc += v[u] * __shfl(w_lane, k + u);
+          if (computed >> (k + u) & 1) acc += v[u] * __shfl(w_lane, k + u);
       }
     }
     const float inv = 1.f / den;

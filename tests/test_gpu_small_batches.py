@@ -5,8 +5,10 @@ import numpy as np
 import pytest
 
 import mc_inputs as mi
-from test_gpu_parity import (canary, check_attention, plan_header, small_workload)
-from gpu_harness import DevBatch, DevPool, bits, dev, gpu_append
+import paper_2412_12488_amd as mc
+from test_gpu_parity import (LSE_TOL, O_TOL, canary, check_attention, fill_both, forked_decode_workload,
+                             plan_header, small_workload)
+from gpu_harness import DEV, DevBatch, DevPool, bits, dev, gpu_append
 
 import oracle
 import torch
@@ -62,3 +64,32 @@ def test_decode_pieces_are_for_single_new_tokens(lens, begins, chunk):
     w = small_workload(970 + chunk, mi.BF16, 8, 1, lens, begins)
     assert plan_header(w)["chunk_tiles"] == chunk
     check_attention(w)
+
+
+@pytest.mark.parametrize("dtype", [mi.BF16, mi.F16])
+@pytest.mark.parametrize("start", [[1500, 2100, 900], [1000, 640, 129]])
+def test_pieces_that_are_not_computed_leave_nothing_behind(dtype, start):
+    """A begin below the planned one leaves the last pieces of a row without a key.  The merge gives
+    them no weight whatever their partial rows held: here, and in any recycled memory, NaN."""
+    Hq, Hkv, B = 32, 8, 3
+    w = small_workload(980, dtype, Hq, Hkv, [n + 1 for n in start], start)
+    pool = DevPool(w)
+    opool = oracle.new_pool(pool.shape)
+    fill_both(w, pool, opool)
+    db = DevBatch(w)
+    ws_bytes = mc.mc_attn_workspace_size(B, B, Hq, Hkv)
+    ws = torch.full((ws_bytes,), 0xff, dtype=torch.uint8, device=DEV)
+    mc.mc_attn_plan(pool.desc, Hq, B, B, db.cu_q, db.begin, db.page_table, db.cu_pages, ws, ws_bytes)
+    mc.mc_attn_plan_check(ws)
+    assert int(ws[:64].view(torch.int32)[6]) == B           # every row is cut
+    q = np.concatenate([w.q(s) for s in range(B)])
+    out = torch.full((B, Hq, 128), 0x7fc1, dtype=torch.int16, device=DEV)
+    lse = torch.full((B, Hq), float("nan"), dtype=torch.float32, device=DEV)
+    at = [3, start[1] - 300, start[2]]          # far below the plan, some pieces below it, as planned
+    mc.mc_prefix_prefill_attn(pool.desc, 0, dev(q), Hq, B, B, db.cu_q, dev(np.array(at, dtype=np.int32)),
+                              db.page_table, db.cu_pages, 0.0, out, lse, ws, ws_bytes)
+    torch.cuda.synchronize()
+    for s in range(B):
+        ro, rl = oracle.attention(opool, pool.shape, 0, w.page_tables[s], w.q(s), Hq, at[s], at[s] + 1)
+        assert np.max(np.abs(oracle.decode(bits(out[s:s + 1]), dtype) - ro)) <= O_TOL, s
+        assert np.max(np.abs(lse[s:s + 1].cpu().numpy() - rl)) <= LSE_TOL, s
