@@ -39,6 +39,46 @@ def test_append_finds_every_sequence(batch, Hkv):
     assert np.array_equal(bits(pool.t), opool)
 
 
+@pytest.mark.parametrize("batch", [1, 17, 257])
+@pytest.mark.parametrize("Hkv", [1, 3, 8, 16])
+def test_append_send_finds_every_sequence(batch, Hkv):
+    # heads below, at and above what a lane loads at once, every round of the sequence search; each
+    # sequence marks another range: its new tokens, from or up to one inside them, beyond them, none
+    rng = mi.rng_for(930 + batch)
+    begins = [int(x) for x in rng.integers(0, 40, size=batch)]
+    new = [0 if batch > 1 and (batch - 1 - i) % 5 == 0 else 1 + i % 3 for i in range(batch)]
+    lens = [max(b + n, 1) for b, n in zip(begins, new)]
+    new = [n - b for n, b in zip(lens, begins)]
+    marks = [[(b, b + n), (b + 1, b + n + 2), (max(b - 2, 0), b + 1), (b + n, b + n + 3), (b, b)][i % 5]
+             for i, (b, n) in enumerate(zip(begins, new))]
+    w = small_workload(930 + batch, mi.BF16, Hkv, Hkv, lens, begins)
+    init = canary(4, DevPool(w).elems)
+    pool, opool, db = DevPool(w, fill=init), init.copy(), DevBatch(w)
+    row = Hkv * 128
+    offs = np.concatenate([[0], np.cumsum([2 * (e - s) * row + 64 for s, e in marks])]) + 64
+    raw = canary(5, int(offs[-1]))
+    send, expect = dev(raw), raw.copy()
+    ks, vs = [], []
+    for i in range(batch):
+        k, v = (x[begins[i]:] if new[i] else x[:0] for x in w.kv(i, 0))
+        ks.append(k), vs.append(v)
+        if new[i]:
+            oracle.append(opool, pool.shape, 0, k, v, begins[i], w.page_tables[i])
+        s0, s1 = marks[i]
+        for h, x in enumerate((k, v)):                    # [K|V][token - s0][head][D]
+            for t in range(max(s0, begins[i]), min(s1, begins[i] + new[i])):
+                at = int(offs[i]) + (h * (s1 - s0) + t - s0) * row
+                expect[at:at + row] = np.ascontiguousarray(x[t - begins[i]]).reshape(-1).view(np.uint16)
+    mc.mc_kv_append_send(pool.desc, 0, dev(np.concatenate(ks)), dev(np.concatenate(vs)), db.batch, db.total_q,
+                         db.cu_q, db.begin, db.page_table, db.cu_pages, 0,
+                         dev(np.array([m[0] for m in marks], np.int32)),
+                         dev(np.array([m[1] for m in marks], np.int32)),
+                         torch.tensor([2 * int(o) for o in offs[:-1]], dtype=torch.int64, device=DEV), send)
+    torch.cuda.synchronize()
+    assert np.array_equal(bits(pool.t), opool)
+    assert np.array_equal(bits(send), expect)             # marked rows, holes and guards
+
+
 @pytest.mark.parametrize("dtype", [mi.BF16, mi.F16])
 @pytest.mark.parametrize("lens,chunk", [
     ([128], 0),                       # two tiles: nothing to cut
@@ -93,3 +133,15 @@ def test_pieces_that_are_not_computed_leave_nothing_behind(dtype, start):
         ro, rl = oracle.attention(opool, pool.shape, 0, w.page_tables[s], w.q(s), Hq, at[s], at[s] + 1)
         assert np.max(np.abs(oracle.decode(bits(out[s:s + 1]), dtype) - ro)) <= O_TOL, s
         assert np.max(np.abs(lse[s:s + 1].cpu().numpy() - rl)) <= LSE_TOL, s
+
+
+@pytest.mark.parametrize("dtype", [mi.BF16, mi.F16])
+@pytest.mark.parametrize("Hq,Hkv", [(8, 8), (32, 8), (8, 1)])
+def test_short_pieces_inside_a_shared_prefix(dtype, Hq, Hkv):
+    # forks of at most 16 tiles: the prefix they share and their own parts in pieces of two tiles
+    w = forked_decode_workload(985, Hq, Hkv, dtype, [
+        [(600, 0), (1024, 528), (640, 528), (577, 528)],      # prefix of 8 tiles: 4 pieces
+        [(1000, 0), (1010, 992), (1024, 992)]])               # prefix of 14 tiles: 7 pieces
+    h = plan_header(w)
+    assert h["chunk_tiles"] == 2 and h["num_groups_rows"] == 4 * 4 + 7 * 3, h
+    check_attention(w)
