@@ -57,7 +57,10 @@ class _LazyCalls:
 
     def __getattr__(self, name):
         global _calls
-        lib()                        # builds what is missing; loads libmc_kv.so
+        lib()
+        if not os.path.exists(CALLS_PATH):
+            from . import build as _build
+            _build.build_calls()
         native = importlib.import_module("._calls", __package__)
         native.setup(mc_pool_desc, C.c_void_p, C.c_int32, C.c_size_t, McArgumentError)
         _calls = native
@@ -69,11 +72,12 @@ _lib = None
 
 
 def lib():
-    """Load the built library; build it only if nothing is built."""
+    """The library, for the calls made through ctypes (the prototypes below are of the whole ABI, for
+    callers who take it from here); built only if it is not there."""
     global _lib
     if _lib is not None:
         return _lib
-    if not (os.path.exists(LIB_PATH) and os.path.exists(CALLS_PATH)):
+    if not os.path.exists(LIB_PATH):
         from . import build as _build
         _build.build()
     L = C.CDLL(LIB_PATH)

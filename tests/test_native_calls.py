@@ -1,6 +1,7 @@
 """The native marshalling of the binding (CPU): every form of argument the calls take."""
 import ctypes
 import os
+import shutil
 import subprocess
 import sys
 
@@ -12,10 +13,10 @@ import paper_2412_12488_amd as mc
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 
 
-def in_child(code, timeout=120):
+def in_child(code, cwd=ROOT, env=None):
     """Runs code in a process of its own (what it tests used to end the process); its output."""
-    res = subprocess.run([sys.executable, "-c", "import paper_2412_12488_amd as mc\n" + code], cwd=ROOT,
-                         capture_output=True, text=True, timeout=timeout)
+    res = subprocess.run([sys.executable, "-c", "import paper_2412_12488_amd as mc\n" + code], cwd=cwd,
+                         capture_output=True, text=True, timeout=120, env=env)
     assert res.returncode == 0, (res.returncode, res.stderr[-2000:])
     return res.stdout
 
@@ -220,3 +221,20 @@ def test_handles_and_addresses_in_every_form():
         with pytest.raises(mc.McError) as e:
             mc.mc_kv_pack_range(pool, 0, 1, null, 1, 0, 1, 16, stream=Holds(None))
         assert e.value.status == mc.MC_ERR_INVALID
+
+
+def test_the_library_alone_serves_the_calls_of_pools_and_plans(tmp_path):
+    # a copy without the native module and without compilers: what goes through ctypes works, the rest
+    # says what is missing
+    src = os.path.join(ROOT, "paper_2412_12488_amd")
+    shutil.copytree(src, tmp_path / "paper_2412_12488_amd",
+                    ignore=shutil.ignore_patterns("_calls.so", "__pycache__"))
+    out = in_child("""
+alloc = mc.mc_kv_allocator_create(8)
+print(mc.mc_abi_version(), mc.mc_kv_allocator_num_free(alloc), mc.mc_attn_workspace_size(1, 1, 32, 8) > 0)
+try:
+    mc.mc_kv_alloc_pages(alloc, 1)
+except (RuntimeError, OSError):
+    print("not built")
+""", cwd=tmp_path, env=dict(os.environ, HIPCC="/nonexistent/hipcc", CXX="/nonexistent/g++"))
+    assert out.split() == ["2", "8", "True", "not", "built"]
