@@ -115,10 +115,12 @@ constexpr int kMinSharedTiles = 8;    // a shared prefix shorter than 512 tokens
 // Shortest piece a KV range is cut into.  A piece walks its tiles one after the other, a memory
 // latency each, and every piece costs a partial row (fp32) for each of its rows, written and read.
 // Decode steps (at most one new token a sequence) have few rows: short pieces, 2 tiles as long as
-// a row then has no more than the kMergeAhead pieces that merge_kernel requests early, else 4.  Ranges
-// of more tokens keep 8.  Append + attention + merge of a layer, 32 / 8 heads, pieces of 8 / 4 / 2 tiles:
-// decode of 2 x 1024 tokens 17.7 / 15.0 / 13.7 us, 4 x 2048 20.5 / 18.0 / 18.2, 1 x 4096 18.2 / 16.3 /
-// 16.5; prefill of 512 tokens 20.0 / 23.1 / 25.7, of 4 x 512 27.0 / 40.8 / 40.8.
+// a row then has no more than the kMergeAhead pieces that merge_kernel requests early, else 4, if
+// they pay (short_pieces_pay).  Ranges of more tokens keep 8.  Append + attention + merge of a layer,
+// 32 / 8 heads, pieces of 8 / 4 / 2 tiles: decode of 1 x 1024 tokens 16.5 / 13.8 / 12.5 us, 1 x 1100
+// 16.5 / 13.8 / 13.1, 1 x 2048 16.7 / 14.1 / 13.6, 1 x 4096 17.4 / 15.6 / 15.8, 4 x 1024 17.6 / 15.1 /
+// 13.8, 4 x 2048 20.7 / 17.7 / 18.0 (between 17 and 32 tiles 2 would still be the better one, by 3 to
+// 5 %); prefill of 512 tokens 20.0 / 23.1 / 25.7, of 4 x 512 27.0 / 40.8 / 40.8.
 constexpr int kMinChunkTiles = 8, kMinChunkTilesDecode = 4, kMinChunkTilesShort = 2;
 constexpr int kMergeAhead = 8;        // partial rows merge_kernel requests beside their LSEs
 constexpr int kRoundsWanted = 4;      // cut only while the launch has fewer items than 4 per slot
@@ -299,6 +301,38 @@ __device__ int block_inclusive_max_scan(int v, int* lds) {
   for (int w = 0; w < NT / 64; ++w)
     if (w < wave) before = max(before, lds[w]);
   return max(before, incl);
+}
+
+// Whether pieces of L < kMinChunkTiles tiles gain more than they cost over pieces of kMinChunkTiles
+// (over whole ranges, if the longest has no more).  us of append + attention + merge of a layer with
+// pieces of 8 (whole) / of L tiles; heads q / kv:
+//   - All items have to run at once: the ones left over take a turn of their own.  334 items for 512
+//     slots, 64 x 64..500 tokens, 8 / 2: 16.8 / 15.5; 610 items, 128 x 64..900, 8 / 2: 21.9 / 24.6; 680
+//     items, 48 x 560..1400 of forks, 32 / 8: 28.7 / 31.7.  (The count is an estimate, up to a tenth
+//     above the true one.)
+//   - Rows of more than 24 pieces: half the slots.  8 / 2 heads, 8192 tokens: 1 row 17.3 / 16.7, 4
+//     rows (256 items) 19.5 / 19.4, 8 rows (512) 23.4 / 24.7; 6000 tokens (24 pieces), 8 rows 21.0 / 20.5.
+//   - The merge reads every partial row: 8 heads, one of them kv, forks of a 4096-token prompt: 64 rows
+//     (9200 partial rows x heads) 22.0 / 21.2, 128 (18400) 23.5 / 24.7.
+//   - Pieces of 6 differ from those of 8 in how well they fill the slots only, and add rows to a group's
+//     merges: 32 / 8 heads, 8 x 1024..4096 tokens (472 items) 29.2 / 28.3, 6 (368) 23.5 / 24.0; 8 / 2,
+//     128 forks of 2048 tokens 24.9 / 28.2.
+//   - Whole ranges have no merge: what is saved, longest - L tiles of latency, has to outweigh one, and
+//     the items that then read at once.  32 / 8 heads: 24 x 64..500 tokens 17.7 / 15.7, 16 x 320
+//     14.7 / 14.5, 20 x 320 15.2 / 15.8, 16 x 200 13.9 / 14.2; 8 / 1: 128 x 100..512 16.5 / 15.8,
+//     160 x 100..300 14.8 / 15.8.
+// cost: tiles of all the ranges, at most 8 x slots / hkv.  No division: this is part of every step's
+// plan.  A q tile has kBM rows, so q heads are kv heads x kBM / tile_tokens.
+__device__ __forceinline__ bool short_pieces_pay(const PlanArgs& a, int L, int longest, bool groups, int tiles,
+                                                 int cost) {
+  // items x 2 L; a range's last piece has half of L on average
+  const int items = (2 * cost + tiles * L) * a.hkv, full = 2 * L * a.slots;
+  if (16 * items > 17 * (longest > 24 * L ? full / 2 : full)) return false;
+  const int whole = tiles * a.hkv;                               // of q heads: whole x kBM / tile_tokens
+  if ((float)whole * (float)longest > 96.f * (float)(L * a.tile_tokens)) return false;     // 12288 / kBM
+  if (L > kMinChunkTilesDecode && (groups || 8 * items < 7 * full)) return false;
+  const int saved = longest - L;
+  return longest > kMinChunkTiles || whole <= min(8 + 64 * (saved - 1), (1 + 2 * saved) * a.tile_tokens);
 }
 
 // Page ids of every needed table entry, for batches too large for the planner's one workgroup
@@ -619,10 +653,15 @@ __global__ __launch_bounds__(NT) void plan_kernel(PlanArgs a) {
     cost = block_sum<NT>(cost, scan);
     const long long want =
         (cost * a.hkv + (long long)kItemsPerSlot * a.slots - 1) / ((long long)kItemsPerSlot * a.slots);
-    // (as many q tiles as new tokens: no sequence has two)
-    const int shortest = a.total_q > total_tiles ? kMinChunkTiles
-                         : s_maxcost <= kMinChunkTilesShort * kMergeAhead ? kMinChunkTilesShort
-                                                                          : kMinChunkTilesDecode;
+    // short pieces: only if no sequence has two new tokens (as many q tiles as new tokens)
+    int shortest = kMinChunkTiles;
+    if (a.total_q <= total_tiles && want < kMinChunkTiles) {
+      shortest = s_maxcost <= kMinChunkTilesShort * kMergeAhead ? kMinChunkTilesShort : kMinChunkTilesDecode;
+      shortest = max(shortest, ((int)want + 1) & ~1);
+      while (shortest < kMinChunkTiles &&
+             !short_pieces_pay(a, shortest, s_maxcost, groups, total_tiles, (int)cost))
+        shortest = min(2 * shortest, kMinChunkTiles);
+    }
     L = want < shortest ? shortest : want > (1 << 28) ? (1 << 28) : (int)want;
     L = (L + 1) & ~1;
     for (;;) {

@@ -106,6 +106,29 @@ def test_decode_pieces_are_for_single_new_tokens(lens, begins, chunk):
     check_attention(w)
 
 
+# per line: both sides of one bound, as it lies with 512 workgroup slots
+@pytest.mark.parametrize("Hq,Hkv,lens,chunk", [
+    (8, 2, [800] * 38, 2), (8, 2, [800] * 39, 4),           # pieces of two in one turn, or of four
+    (8, 2, [900] * 80, 6), (8, 2, [900] * 100, 8),          # pieces of six, or of eight
+    (8, 2, [6000] * 8, 4), (8, 2, [7000] * 8, 8),           # 24 pieces a row, or more
+    (32, 8, [2600] * 8, 6), (32, 8, [2300] * 8, 8),         # six fill the slots, or not
+    (32, 8, [500] * 24, 4), (32, 8, [500] * 32, 0),         # whole ranges: few to read at once, or many
+    (8, 1, [500] * 144, 4), (8, 1, [500] * 145, 0),
+    (8, 1, [300] * 64, 2), (8, 1, [300] * 65, 2), (8, 1, [300] * 130, 0),
+])
+def test_short_pieces_only_where_they_pay(Hq, Hkv, lens, chunk):
+    w = small_workload(960 + len(lens), mi.BF16, Hq, Hkv, lens, [n - 1 for n in lens])
+    assert plan_header(w)["chunk_tiles"] == chunk
+    check_attention(w)
+
+
+@pytest.mark.parametrize("forks,chunk", [(64, 4), (128, 8)])
+def test_short_pieces_of_groups_whose_merges_are_small(forks, chunk):
+    w = forked_decode_workload(990, 8, 1, mi.BF16, [[(4400, 0)] + [(4390, 4096)] * (forks - 1)])
+    h = plan_header(w)
+    assert h["chunk_tiles"] == chunk and h["num_groups_rows"] == forks * 64 // chunk, h
+
+
 @pytest.mark.parametrize("dtype", [mi.BF16, mi.F16])
 @pytest.mark.parametrize("start", [[1500, 2100, 900], [1000, 640, 129]])
 def test_pieces_that_are_not_computed_leave_nothing_behind(dtype, start):
