@@ -309,7 +309,9 @@ __device__ int block_inclusive_max_scan(int v, int* lds) {
 //   - All items have to run at once: the ones left over take a turn of their own.  334 items for 512
 //     slots, 64 x 64..500 tokens, 8 / 2: 16.8 / 15.5; 610 items, 128 x 64..900, 8 / 2: 21.9 / 24.6; 680
 //     items, 48 x 560..1400 of forks, 32 / 8: 28.7 / 31.7.  (The count is an estimate, up to a tenth
-//     above the true one.)
+//     above the true one.)  An eighth more than the slots is made up for if the pieces are not the
+//     shortest nor many a row, and no group's merges grow: 536 items, 24 x 300..1000, 32 / 8: 22.7 / 21.8; 584, 32 x
+//     64..900: 22.4 / 22.8; 534, 100 forks of a 2048-token prompt, 8 / 2: 23.1 / 25.0.
 //   - Rows of more than 24 pieces: half the slots.  8 / 2 heads, 8192 tokens: 1 row 17.3 / 16.7, 4
 //     rows (256 items) 19.5 / 19.4, 8 rows (512) 23.4 / 24.7; 6000 tokens (24 pieces), 8 rows 21.0 / 20.5.
 //   - The merge reads every partial row: 8 heads, one of them kv, forks of a 4096-token prompt: 64 rows
@@ -327,7 +329,9 @@ __device__ __forceinline__ bool short_pieces_pay(const PlanArgs& a, int L, int l
                                                  int cost) {
   // items x 2 L; a range's last piece has half of L on average
   const int items = (2 * cost + tiles * L) * a.hkv, full = 2 * L * a.slots;
-  if (16 * items > 17 * (longest > 24 * L ? full / 2 : full)) return false;
+  const bool many = longest > 24 * L;
+  const int share = groups || many || L < kMinChunkTilesDecode ? 17 : 18;      // of 16
+  if (16 * items > share * (many ? full / 2 : full)) return false;
   const int whole = tiles * a.hkv;                               // of q heads: whole x kBM / tile_tokens
   if ((float)whole * (float)longest > 96.f * (float)(L * a.tile_tokens)) return false;     // 12288 / kBM
   if (L > kMinChunkTilesDecode && (groups || 8 * items < 7 * full)) return false;

@@ -110,6 +110,7 @@ def test_decode_pieces_are_for_single_new_tokens(lens, begins, chunk):
 @pytest.mark.parametrize("Hq,Hkv,lens,chunk", [
     (8, 2, [800] * 38, 2), (8, 2, [800] * 39, 4),           # pieces of two in one turn, or of four
     (8, 2, [900] * 80, 6), (8, 2, [900] * 100, 8),          # pieces of six, or of eight
+    (32, 8, [1150] * 14, 4), (32, 8, [960] * 17, 8),        # pieces of four, or of eight
     (8, 2, [6000] * 8, 4), (8, 2, [7000] * 8, 8),           # 24 pieces a row, or more
     (32, 8, [2600] * 8, 6), (32, 8, [2300] * 8, 8),         # six fill the slots, or not
     (32, 8, [500] * 24, 4), (32, 8, [500] * 32, 0),         # whole ranges: few to read at once, or many
