@@ -997,14 +997,19 @@ __global__ __launch_bounds__(kThreads, kCB == 1 ? 2 : 1) void attn_kernel(AttnAr
   const int hk = blockIdx.x % a.hkv;
   const int wi = blockIdx.x / a.hkv;
   // The item record is requested together with the plan's header (the grid never exceeds the
-  // room for records, whatever the header says): one memory round trip instead of two.
+  // room for records, whatever the header says): one memory round trip, with every argument the
+  // look-ups behind it need already in registers.  (Left alone the compiler reads the header field
+  // by field, a wait and a branch each, then the record, then the arguments.)
   typedef int32_t i32x8 __attribute__((ext_vector_type(8)));
   const auto* rec = (const __attribute__((address_space(4))) i32x8*)(a.items + wi);
-  const i32x8 item = rec[0], item_b = rec[1];
+  i32x8 item = rec[0], item_b = rec[1];
+  i32x8 hdr = *(const __attribute__((address_space(4))) i32x8*)a.hdr;
+  asm volatile("" ::"s"(a.pool_layer), "s"(a.begin), "s"(a.q), "s"(a.num_pages), "s"(a.total_q));
+  asm volatile("" : "+s"(item), "+s"(item_b), "+s"(hdr));
   // the work list must come from a plan made for this very batch
-  if (a.hdr->magic != kPlanMagic || wi >= a.hdr->num_items || a.hdr->tile_tokens != TOK ||
-      a.hdr->batch != a.batch || a.hdr->total_q != a.total_q)
-    return;
+  const bool ours = (hdr[0] == kPlanMagic) & (wi < hdr[2]) & (hdr[3] == TOK) & (hdr[4] == a.batch) &
+                    (hdr[5] == a.total_q);
+  if (!ours) return;
 
   const int tid = threadIdx.x, lane = tid & 63;
   if (tid == 0) s_redo = 0;   // published by the prologue's barrier
@@ -1019,58 +1024,13 @@ __global__ __launch_bounds__(kThreads, kCB == 1 ? 2 : 1) void attn_kernel(AttnAr
   const int ntok = item[7];                          // valid tokens in this tile (>= 1)
   const int table_off = item_b[0], pidx_cap = item_b[1];
   // a record that cannot come from the planner (a workspace written over by something else)
-  if ((unsigned)seq >= (unsigned)a.batch || row0 < 0 || t0 < 0 || item[3] <= t0 || gsize < 0 ||
-      gsize > TOK || ntok < 1 || ntok > TOK || (gsize > 0 && ntok != gsize) || q_first < 0 ||
-      (int64_t)q_first + ntok > a.total_q || table_off < 0 || pidx_cap < 0)
-    return;
-  // begin is read here, not taken from the plan (one plan may serve many decode steps); it is
-  // the only look-up between the record and the first copies
-  const int b = a.begin[seq];
-  // The position of the tile's first token.  The rows of a shared-prefix item are new tokens of
-  // consecutive sequences; all of them lie beyond the prefix, so any position at or past the
-  // item's last key serves.
-  const int first_pos = gsize > 0 ? item[3] * kBN : b + row0;
-  // keys [64 t0, kv_len) are this item's: up to the end of its chunk, or of the tile's range
-  const int kv_len = min(first_pos + ntok, item[3] * kBN);
-  const int n_kv_tiles = (kv_len + kBN - 1) / kBN;   // (absolute) index after the last KV tile
-  const int n_halves = (kv_len + kHalf - 1) / kHalf;
-  // half h is fully visible to every row of the q tile iff 32 (h+1) <= first_pos + 1
-  const int n_full = (first_pos + 1) / kHalf;
-  // A begin that no longer fits the item - negative, or so small that the item's first tile
-  // lies past the range - ends the workgroup before any page is read; table indices never
-  // pass the last entry the plan validated for the sequence.
-  if (b < 0 || kv_len <= kBN * t0) {
-    // a chunk that is not computed says so in its partial rows (no key seen: LSE = -inf), so
-    // that the merge gives it no weight, and writes nothing if no chunk of the row was computed
-    if (part >= 0)
-      for (int i = tid; i < ntok * G; i += kThreads)
-        a.part_lse[(int64_t)(part + i / G) * a.hq + hk * G + i % G] = -INFINITY;
-    return;
-  }
-  const int last_pidx = min((kv_len - 1) / kPage, pidx_cap);   // last entry that holds a needed key
-
-  // this lane's query rows, one per row block
-  int g[kCB], tt[kCB], my_pos[kCB];
-  bool row_ok[kCB];
-  // Q as the B operand: lane holds d = 16 kk + 8 half + [0,8) of its row, kk = 0..7
-  vec8 qreg[kCB][8];
-#pragma unroll
-  for (int cb = 0; cb < kCB; ++cb) {
-    const int r = wave * kWaveRows + cb * 32 + l32;    // row in tile
-    g[cb] = r % G;                                     // token-major: the rows of a short tile
-    tt[cb] = r / G;                                    // (a decode step's G rows) fill whole waves
-    row_ok[cb] = tt[cb] < ntok;
-    my_pos[cb] = first_pos + (row_ok[cb] ? tt[cb] : ntok - 1);   // causal limit of the row
-    const int64_t q_row = ((int64_t)(q_first + tt[cb]) * a.hq + hk * G + g[cb]) * kRowBytes;
-#pragma unroll
-    for (int kk = 0; kk < 8; ++kk) {
-      u32x4 v = {0, 0, 0, 0};
-      if (row_ok[cb]) v = *reinterpret_cast<const u32x4*>(a.q + q_row + kk * 32 + half * 16);
-      qreg[cb][kk] = __builtin_bit_cast(vec8, v);
-    }
-  }
-  // a wavefront none of whose rows exists only helps with the copies and the barriers
-  const bool wave_active = !kGate || wave * kWaveRows < ntok * G;
+  const bool odd = ((unsigned)seq >= (unsigned)a.batch) | (row0 < 0) | (t0 < 0) | (item[3] <= t0) |
+                   (gsize < 0) | (gsize > TOK) | (ntok < 1) | (ntok > TOK) |
+                   ((gsize > 0) & (ntok != gsize)) | (q_first < 0) |
+                   ((int64_t)q_first + ntok > a.total_q) | (table_off < 0) | (pidx_cap < 0);
+  if (odd) return;
+  // begin is read here, not taken from the plan (one plan may serve many decode steps)
+  const int b = ((const_i32_ptr)a.begin)[seq];
 
   // ---- global -> LDS copies (no VGPR staging) -------------------------------------
   // A wavefront's copy instruction fills 1 KiB of LDS linearly (lane L -> bytes 16 L..),
@@ -1095,6 +1055,69 @@ __global__ __launch_bounds__(kThreads, kCB == 1 ? 2 : 1) void attn_kernel(AttnAr
   auto copy_page = [&](const char* base, bool is_v, uint32_t lds_page) __attribute__((always_inline)) {   // 16 rows = 4 KiB
     copy16_to_lds(base, is_v ? v_lane_off : k_lane_off, lds_page + wave * 1024);
   };
+  // The first tiles' copies - K halves 0, 1, 2 and V(0) of the item - need the record alone (it holds
+  // the ids of table entries 4 t0 .. 4 t0 + 5): they leave before anything that depends on `begin`.
+  // With the look-ups at the kernel's start in one request, one decode row over 1000 keys (32 / 8
+  // heads): append, attention and merge of a layer 12.0 -> 11.4 us from first to last instruction;
+  // eight rows (64 / 8 heads, 1024..4096 keys) 29.6 -> 29.0 us a layer.
+  auto first_copies = [&]() __attribute__((always_inline)) {
+    const char* pb[6];
+#pragma unroll
+    for (int i = 0; i < 6; ++i) pb[i] = page_base(item_b[2 + i]);
+#pragma unroll
+    for (int i = 0; i < 6; ++i) copy_page(pb[i], false, lds_k + i * 4096);
+#pragma unroll
+    for (int i = 0; i < 4; ++i) copy_page(pb[i], true, lds_v + i * 4096);
+  };
+  first_copies();
+  // The position of the tile's first token.  The rows of a shared-prefix item are new tokens of
+  // consecutive sequences; all of them lie beyond the prefix, so any position at or past the
+  // item's last key serves.
+  const int first_pos = gsize > 0 ? item[3] * kBN : b + row0;
+  // keys [64 t0, kv_len) are this item's: up to the end of its chunk, or of the tile's range
+  const int kv_len = min(first_pos + ntok, item[3] * kBN);
+  const int n_kv_tiles = (kv_len + kBN - 1) / kBN;   // (absolute) index after the last KV tile
+  const int n_halves = (kv_len + kHalf - 1) / kHalf;
+  // half h is fully visible to every row of the q tile iff 32 (h+1) <= first_pos + 1
+  const int n_full = (first_pos + 1) / kHalf;
+  // A begin that no longer fits the item - negative, or so small that the item's first tile
+  // lies past the range - ends the workgroup before the page table is read; table indices never
+  // pass the last entry the plan validated for the sequence.
+  if (b < 0 || kv_len <= kBN * t0) {
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // the copies write this workgroup's LDS
+    // a chunk that is not computed says so in its partial rows (no key seen: LSE = -inf), so
+    // that the merge gives it no weight, and writes nothing if no chunk of the row was computed
+    if (part >= 0)
+      for (int i = tid; i < ntok * G; i += kThreads)
+        a.part_lse[(int64_t)(part + i / G) * a.hq + hk * G + i % G] = -INFINITY;
+    return;
+  }
+  const int last_pidx = min((kv_len - 1) / kPage, pidx_cap);   // last entry that holds a needed key
+
+  // this lane's query rows, one per row block
+  int g[kCB], tt[kCB], my_pos[kCB];
+  bool row_ok[kCB];
+  // Q as the B operand: lane holds d = 16 kk + 8 half + [0,8) of its row, kk = 0..7
+  vec8 qreg[kCB][8];
+#pragma unroll
+  for (int cb = 0; cb < kCB; ++cb) {
+    const int r = wave * kWaveRows + cb * 32 + l32;    // row in tile
+    g[cb] = r % G;                                     // token-major: the rows of a short tile
+    tt[cb] = r / G;                                    // (a decode step's G rows) fill whole waves
+    row_ok[cb] = tt[cb] < ntok;
+    my_pos[cb] = first_pos + (row_ok[cb] ? tt[cb] : ntok - 1);   // causal limit of the row
+    // (a row that does not exist reads the last one's q: no load under a condition; its results are
+    // never stored)
+    const int64_t q_row =
+        ((int64_t)(q_first + min(tt[cb], ntok - 1)) * a.hq + hk * G + g[cb]) * kRowBytes;
+#pragma unroll
+    for (int kk = 0; kk < 8; ++kk)
+      qreg[cb][kk] = __builtin_bit_cast(
+          vec8, *reinterpret_cast<const u32x4*>(a.q + q_row + kk * 32 + half * 16));
+  }
+  // a wavefront none of whose rows exists only helps with the copies and the barriers
+  const bool wave_active = !kGate || wave * kWaveRows < ntok * G;
+
   // ---- the page ids of the next copies -----------------------------------------------
   // The page ids of a tile's copies are fetched one tile early by a vector load (lane i & 7
   // holds table entry first + i).  It is an ordinary load, which the compiler tracks: wherever
@@ -1369,17 +1392,7 @@ __global__ __launch_bounds__(kThreads, kCB == 1 ? 2 : 1) void attn_kernel(AttnAr
       m_run[cb] = -INFINITY;
       l_run[cb] = 0.f;
     }
-    // ---- prologue: K halves 0, 1, 2 and V(0) in flight together; S(half 0) -------------
-    {
-      // table entries 0..5 of the item (K halves 0..2), 0..3 (V tile 0): their ids are in the record
-      const char* pb[6];
-#pragma unroll
-      for (int i = 0; i < 6; ++i) pb[i] = page_base(item_b[2 + i]);
-#pragma unroll
-      for (int i = 0; i < 6; ++i) copy_page(pb[i], false, lds_k + i * 4096);
-#pragma unroll
-      for (int i = 0; i < 4; ++i) copy_page(pb[i], true, lds_v + i * 4096);
-    }
+    // ---- prologue: K halves 0, 1, 2 and V(0) are in flight (first_copies); S(half 0) ---------
     ids.issue(4 * t0 + 4);
     wait_copies_and_sync();
     if (wave_active) {
@@ -1478,7 +1491,10 @@ __global__ __launch_bounds__(kThreads, kCB == 1 ? 2 : 1) void attn_kernel(AttnAr
     const bool bad = wave_active && !(sums_ok && o_chk == 0.f);
     if (__builtin_amdgcn_ballot_w64(bad) != 0 && lane == 0) s_redo = 1;
     __syncthreads();
-    if (s_redo != 0) run_pass(std::false_type{});
+    if (s_redo != 0) {
+      first_copies();
+      run_pass(std::false_type{});
+    }
   } else {
     run_pass(std::false_type{});
   }
