@@ -15,8 +15,8 @@
 //     start its first copies.
 //   * attn_kernel: one workgroup (4 wavefronts of 64) per (item, kv head), so every
 //     K/V byte staged in LDS serves the whole GQA group.  Items that cover a whole
-//     range write out/lse; the others write partial rows that merge_kernel weighs
-//     together by their log-sum-exp.
+//     range write out/lse; the others write partial rows, which the last of a q
+//     tile's items to finish weighs together by their log-sum-exp.
 // Kernel shape
 //   * the KV loop walks 64-key tiles (4 pages) through the page table; each page
 //     contributes one contiguous 4 KiB run of K and one of V for this kv head.
@@ -72,41 +72,63 @@ struct PlanHeader {
   int32_t chunk_tiles;  // chunk length the planner settled on (KV tiles); 0 = nothing was cut
   int32_t num_groups_rows;  // partial rows written by shared-prefix items (0 = no groups)
   int32_t tail_chunks;  // chunks per q tile of the remainder round (0 = not applied)
-  int32_t merge_tokens; // new tokens of all q tiles with partial results (what merge_kernel walks)
+  int32_t arrive_words; // arrival words per merge record and kv head (see MergeRec)
   int32_t pad[5];
 };
 static_assert(sizeof(PlanHeader) == 64, "header is 64 bytes");
 
 // One work item: q tile (seq, row0) over the KV tiles [t0, t1) of its sequence.  t0 is even.
-// part < 0: the item covers the tile's whole KV range and writes out/lse itself.  Otherwise it
-// writes a partial result (O normalised within the chunk, fp32, and the chunk's LSE) for token
-// tt of the tile at row part + tt of the partial arrays, and merge_kernel combines the chunks.
-// gsize > 0: a shared-prefix item.  Its rows are the gsize new tokens of consecutive sequences
-// starting at seq (neighbours in the q array: tokens cu_q[seq] .. cu_q[seq] + gsize - 1), whose
+// chunk < 0: the item covers the tile's whole KV range and writes out/lse itself.  Otherwise it is
+// that chunk of the tile `merge` describes: its result (O normalised within the chunk, fp32, and the
+// chunk's LSE) is combined with the other chunks' by whichever item comes last (see MergeRec).
+// kItemGroup: a shared-prefix item.  Its rows are the ntok new tokens of consecutive sequences
+// starting at seq (neighbours in the q array: tokens cu_q[seq] .. cu_q[seq] + ntok - 1), whose
 // page tables begin with the same pages; it covers tiles of that common prefix (all of it
-// visible to every row) and always writes partial rows.
+// visible to every row) and is always a chunk.  Its members' merge records follow one another from
+// `merge` on.
 // The record also carries what the kernel needs to start its first copies without further
 // look-ups (each would be one more dependent memory round trip before the first tile): the
 // tile's first token in the q array and its token count, where the sequence's page table starts,
-// the last table entry the plan has validated for the sequence, and the page ids of table
-// entries 4 t0 .. 4 t0 + 5 (clamped to that last entry).
+// the last table entry the plan has validated for the sequence (as far as the item can reach it:
+// which entry of tile t1 - 1 that is), and the page ids of table entries 4 t0 .. 4 t0 + 7
+// (clamped to that last entry).
 struct ItemRec {
-  int32_t seq, row0, t0, t1, part, gsize;
-  int32_t q_first, ntok, table_off, pidx_cap;
-  int32_t ids[6];
+  int32_t seq, row0;
+  uint32_t t0_ntok;   // t0 / 2 (24 bits), ntok - 1
+  uint32_t t1_flags;  // t1 (26 bits), last validated entry of tile t1 - 1 (2 bits), kItemGroup
+  int32_t chunk, q_first, table_off;
+  int32_t merge;      // the tile's (of a group: the first member's) merge record
+  int32_t ids[8];
 };
 static_assert(sizeof(ItemRec) == 64, "item record is 64 bytes");
+constexpr uint32_t kItemGroup = 1u << 28;
 
-// One q tile with partial results: chunk c of its own KV range has its partial rows at
-// part + c * ntok; if the tile's sequence belongs to a shared-prefix group, chunk c of the
-// prefix has this sequence's rows from g_part + c * g_stride on (g_stride = the group's tokens).
+// One q tile of several chunks: nsplit of its own KV range and, if its sequence belongs to a
+// shared-prefix group, g_nsplit of the prefix, which the g_stride new tokens of the group's members
+// share (g_off: the tile's first among them).  Partial rows are kept per chunk and kv head: the
+// R = ntok x G (of the prefix: g_stride x G) rows of chunk c and kv head h start at row
+// (part + c ntok) hq + h R (of the prefix: (g_part + c g_stride) hq + h R) of the partial arrays.
+//   * Chunks of up to kFlatRows rows (decode steps): every item writes its rows and counts itself; the
+//     last one reads all the others'.
+//   * Chunks of more rows: a binary tree over the chunks.  Of two neighbours the first to be done
+//     writes its rows and ends, the second reads them, combines, and goes on one level up; half of the
+//     rows are never written.  The last one up has the tile's result in registers.  These rows are
+//     kept as the registers lie, 16 bytes of every row together (by_reg below).
+//   * With a group, the prefix (as one chunk, if a tree has combined it) and the tile's own chunks
+//     (likewise) are then counted, and the last of them combines.
+// Which chunk comes last differs from run to run; the sums and their order do not.
 struct MergeRec {
   int32_t q_row;   // index of the tile's first token among all new tokens of the batch
   int32_t ntok, nsplit, part;
-  int32_t g_nsplit, g_part, g_stride;
-  int32_t tok_off; // tokens of the merge records before this one
+  int32_t g_nsplit, g_part, g_stride, g_off;
 };
 static_assert(sizeof(MergeRec) == 32, "merge record is 32 bytes");
+constexpr int kFlatRows = 16;
+// Arrivals: per merge record and kv head arrive_words words that the plan clears.  Word 0 counts
+// (and wraps to 0 with the last arrival); of the others, one bit a node, half are the tile's tree and
+// half, at a group's first member, the prefix's (set by the first of two, cleared by the second).
+// They fill the end of the partial LSE array from its last word downwards, for which the planner
+// leaves rows of that array (hq >= hkv words each) unused.
 
 constexpr int kCuTilesInLds = 1024;
 constexpr int kValidateInPlan = 256;  // batches up to this have their page ids checked by plan_kernel
@@ -115,14 +137,14 @@ constexpr int kMinSharedTiles = 8;    // a shared prefix shorter than 512 tokens
 // Shortest piece a KV range is cut into.  A piece walks its tiles one after the other, a memory
 // latency each, and every piece costs a partial row (fp32) for each of its rows, written and read.
 // Decode steps (at most one new token a sequence) have few rows: short pieces, 2 tiles as long as
-// a row then has no more than the kMergeAhead pieces that merge_kernel requests early, else 4, if
+// a row then has no more than the kMergeAhead pieces that a merge requests early, else 4, if
 // they pay (short_pieces_pay).  Ranges of more tokens keep 8.  Append + attention + merge of a layer,
 // 32 / 8 heads, pieces of 8 / 4 / 2 tiles: decode of 1 x 1024 tokens 16.5 / 13.8 / 12.5 us, 1 x 1100
 // 16.5 / 13.8 / 13.1, 1 x 2048 16.7 / 14.1 / 13.6, 1 x 4096 17.4 / 15.6 / 15.8, 4 x 1024 17.6 / 15.1 /
 // 13.8, 4 x 2048 20.7 / 17.7 / 18.0 (between 17 and 32 tiles 2 would still be the better one, by 3 to
 // 5 %); prefill of 512 tokens 20.0 / 23.1 / 25.7, of 4 x 512 27.0 / 40.8 / 40.8.
 constexpr int kMinChunkTiles = 8, kMinChunkTilesDecode = 4, kMinChunkTilesShort = 2;
-constexpr int kMergeAhead = 8;        // partial rows merge_kernel requests beside their LSEs
+constexpr int kMergeAhead = 8;        // partial rows a merge of few rows requests beside their LSEs
 constexpr int kRoundsWanted = 4;      // cut only while the launch has fewer items than 4 per slot
 // ... and then aim for about one item per slot: measured best on decode batches and on 500-token
 // ranges over long contexts (more chunks mean more partial rows to write and merge)
@@ -199,7 +221,8 @@ struct PlanArgs {
   ItemRec* items;
   MergeRec* merges;
   int32_t batch, total_q, tile_tokens, num_pages, max_tiles, max_items, part_cap;
-  int32_t hkv, slots;   // kv heads; workgroups the GPU runs at a time
+  uint32_t* arrivals_end;  // one past the last arrival word (see MergeRec)
+  int32_t hq, hkv, slots;   // q and kv heads; workgroups the GPU runs at a time
   int32_t allow_groups; // look for decode rows of neighbouring sequences that share a prefix
   int32_t ahead;        // tokens every sequence's begin may still grow by while the plan is in use
   int32_t wide_tile_tokens, slots_wide;   // the wide q tiles, if the host allows them (else 0)
@@ -364,7 +387,7 @@ __global__ __launch_bounds__(256) void validate_pages_kernel(PlanArgs a) {
   if (__ballot(err) != 0 && lane == 0) {
     a.hdr->num_items = 0;
     a.hdr->num_merges = 0;
-    a.hdr->merge_tokens = 0;
+   
     a.hdr->err = MC_ERR_RANGE;
   }
 }
@@ -447,7 +470,7 @@ __global__ __launch_bounds__(NT) void plan_kernel(PlanArgs a) {
   if ((t & 63) == 0) atomicMax(&s_maxcost, maxcost);
   __syncthreads();
   if (s_err) {
-    if (t == 0) { a.hdr->err = MC_ERR_RANGE; a.hdr->num_items = 0; a.hdr->num_merges = 0; a.hdr->merge_tokens = 0; a.hdr->magic = kPlanMagic; }
+    if (t == 0) { a.hdr->err = MC_ERR_RANGE; a.hdr->num_items = 0; a.hdr->num_merges = 0; a.hdr->magic = kPlanMagic; }
     return;
   }
   // 2. page ids of every needed table entry.  Small batches (their offsets sit in LDS): a
@@ -500,7 +523,7 @@ __global__ __launch_bounds__(NT) void plan_kernel(PlanArgs a) {
   __threadfence_block();
   __syncthreads();
   if (s_err || total_tiles > a.max_tiles) {
-    if (t == 0) { a.hdr->err = MC_ERR_RANGE; a.hdr->num_items = 0; a.hdr->num_merges = 0; a.hdr->merge_tokens = 0; a.hdr->magic = kPlanMagic; }
+    if (t == 0) { a.hdr->err = MC_ERR_RANGE; a.hdr->num_items = 0; a.hdr->num_merges = 0; a.hdr->magic = kPlanMagic; }
     return;
   }
 
@@ -633,13 +656,18 @@ __global__ __launch_bounds__(NT) void plan_kernel(PlanArgs a) {
   // [pt+kL, T) with pt + kL <= dmax; the group's prefix itself in chunks of L
   auto own_splits = [&](const Tile& x, int L) { return L > 0 ? (x.dmax - x.pt) / L + 1 : 1; };
   auto grp_splits = [&](const Tile& x, int L) { return x.pt > 0 ? (L > 0 ? (x.pt + L - 1) / L : 1) : 0; };
-  auto part_rows = [&](const Tile& x, int L) {
+  // arrival words per merge record and kv head: a tree over n chunks has up to n + log2(n) nodes; the
+  // rows of the partial arrays they take
+  auto arrive_words = [&](int L) { return 1 + 2 * ((L > 0 ? s_maxcost / L + 16 : 16) / 32 + 1); };
+  auto arrive_rows = [&](int L) { return (arrive_words(L) * a.hkv + a.hq - 1) / a.hq; };
+  auto part_rows = [&](const Tile& x, int L, int arrive) {
     const int ns = own_splits(x, L);
-    return (ns > 1 || x.pt > 0 ? ns * x.ntok : 0) + (x.gm ? grp_splits(x, L) * x.gm : 0);
+    return (ns > 1 || x.pt > 0 ? ns * x.ntok + arrive : 0) + (x.gm ? grp_splits(x, L) * x.gm : 0);
   };
   auto total_part_rows = [&](int L) {   // block-wide
     long long rows = 0;
-    for (int i = t; i < total_tiles; i += NT) rows += part_rows(locate(i), L);
+    const int arrive = arrive_rows(L);
+    for (int i = t; i < total_tiles; i += NT) rows += part_rows(locate(i), L, arrive);
     return block_sum<NT>(rows, scan);
   };
 
@@ -693,7 +721,7 @@ __global__ __launch_bounds__(NT) void plan_kernel(PlanArgs a) {
     const int c = rem > 0 ? min(8, (a.slots + rem - 1) / rem) : 0;
     if (L == 0 && !groups && total_tiles <= kTailTilesMax && n >= a.slots &&
         n < (int64_t)kRoundsWanted * a.slots && rem_tiles >= 1 && 10 * rem <= 7 * a.slots && c >= 2 &&
-        (int64_t)rem_tiles * a.tile_tokens * c <= a.part_cap) {
+        (int64_t)rem_tiles * (a.tile_tokens * c + arrive_rows(0)) <= a.part_cap) {
       if (t == 0) { s_tail_bucket = kBuckets; s_tail_take = 0; s_tail_taken = 0; }
       for (int i = t; i < total_tiles; i += NT) atomicAdd(&hist[bucket(locate(i).T)], 1);
       __syncthreads();
@@ -730,24 +758,25 @@ __global__ __launch_bounds__(NT) void plan_kernel(PlanArgs a) {
   // 5. items and merge records: count per contiguous range of tiles, scan, histogram of costs
   const int tper = (total_tiles + NT - 1) / NT;
   const int i_lo = min(t * tper, total_tiles), i_hi = min(i_lo + tper, total_tiles);
-  int n_items = 0, n_own = 0, n_grp = 0, n_merge = 0, n_mtok = 0;
+  int n_items = 0, n_own = 0, n_grp = 0, n_merge = 0;
   for (int i = i_lo; i < i_hi; ++i) {
     const Tile x = locate(i);
     const int Li = chunk_len(i, x);
     const int ns = own_splits(x, Li), ng = x.gm ? grp_splits(x, Li) : 0;
     n_items += ns + ng;
-    if (ns > 1 || x.pt > 0) { n_own += ns * x.ntok; ++n_merge; n_mtok += x.ntok; }
+    if (ns > 1 || x.pt > 0) { n_own += ns * x.ntok; ++n_merge; }
     n_grp += ng * x.gm;
     for (int c = 0; c < ns; ++c)
       atomicAdd(&hist[bucket(c + 1 < ns ? Li : x.T - x.pt - c * Li)], 1);
-    for (int c = 0; c < ng; ++c)
-      atomicAdd(&hist[bucket(Li > 0 ? min(Li, x.pt - c * Li) : x.pt)], 1);
+    // (a group's items first: their rows fill a q tile, so a tile takes them longest, and what their
+    // members' own items find finished they need not wait for - the last of the group's items would
+    // have to combine the rows of every member)
+    if (ng > 0) atomicAdd(&hist[bucket(s_maxcost)], ng);
   }
-  int offs[5] = {n_items, n_own, n_grp, n_merge, n_mtok}, tots[5];
+  int offs[4] = {n_items, n_own, n_grp, n_merge}, tots[4];
   block_exclusive_scan_n<NT>(offs, scan, tots);
-  const int tot_items = tots[0], tot_own = tots[1], tot_grp = tots[2], tot_merge = tots[3],
-            tot_mtok = tots[4];
-  int own_off = offs[1], grp_off = offs[2], merge_off = offs[3], mtok_off = offs[4];
+  const int tot_items = tots[0], tot_own = tots[1], tot_grp = tots[2], tot_merge = tots[3];
+  int own_off = offs[1], grp_off = offs[2], merge_off = offs[3];
   {
     constexpr int kPer = kBuckets / NT;
     int local[kPer], sum = 0;
@@ -756,8 +785,9 @@ __global__ __launch_bounds__(NT) void plan_kernel(PlanArgs a) {
     for (int i = 0; i < kPer; ++i) { hist[t * kPer + i] = off; off += local[i]; }
   }
   __syncthreads();
-  if (tot_items > a.max_items || tot_own + tot_grp > a.part_cap || tot_merge > a.max_tiles) {   // cannot happen
-    if (t == 0) { a.hdr->err = MC_ERR_RANGE; a.hdr->num_items = 0; a.hdr->num_merges = 0; a.hdr->merge_tokens = 0; a.hdr->magic = kPlanMagic; }
+  if (tot_items > a.max_items || tot_own + tot_grp + (int64_t)tot_merge * arrive_rows(L) > a.part_cap ||
+      tot_merge > a.max_tiles) {   // cannot happen
+    if (t == 0) { a.hdr->err = MC_ERR_RANGE; a.hdr->num_items = 0; a.hdr->num_merges = 0; a.hdr->magic = kPlanMagic; }
     return;
   }
   // where each group's partial rows start (after all the tiles' own): its members need it
@@ -769,6 +799,8 @@ __global__ __launch_bounds__(NT) void plan_kernel(PlanArgs a) {
     }
     __syncthreads();
   }
+  for (int64_t i = t; i < (int64_t)tot_merge * a.hkv * arrive_words(L); i += NT)
+    a.arrivals_end[-1 - i] = 0;   // nobody has arrived
   // 6. emit: counting sort of the items by cost (number of KV tiles), heaviest first
   for (int i = i_lo; i < i_hi; ++i) {
     const Tile x = locate(i);
@@ -782,10 +814,9 @@ __global__ __launch_bounds__(NT) void plan_kernel(PlanArgs a) {
       m.nsplit = ns;
       m.part = own_off;
       m.g_nsplit = ng;
-      m.g_part = x.pt > 0 ? s_gbase[s_glead[x.s]] + (s_cuq[x.s] - s_cuq[s_glead[x.s]]) : 0;
+      m.g_part = x.pt > 0 ? s_gbase[s_glead[x.s]] : 0;
       m.g_stride = x.pt > 0 ? s_gsize[s_glead[x.s]] : 0;
-      m.tok_off = mtok_off;
-      mtok_off += x.ntok;
+      m.g_off = x.pt > 0 ? s_cuq[x.s] - s_cuq[s_glead[x.s]] : 0;
       a.merges[merge_off++] = m;
     }
     // what every item of this tile's sequence shares
@@ -794,34 +825,29 @@ __global__ __launch_bounds__(NT) void plan_kernel(PlanArgs a) {
     const int sb = cu_in_lds ? s_beg[x.s] : a.begin[x.s];
     const int tab = cu_in_lds ? s_cup[x.s] : a.cu_pages[x.s];
     const int cap = (int)(((int64_t)sb + sq_len + a.ahead + kPage - 1) / kPage) - 1;   // validated above
-    auto finish = [&](ItemRec& it, int q_first, int ntok) {
+    auto finish = [&](ItemRec& it, int t0, int t1, int q_first, int ntok, uint32_t flags) {
+      it.seq = x.s;
       it.q_first = q_first;
-      it.ntok = ntok;
+      it.t0_ntok = (uint32_t)(t0 >> 1) | (uint32_t)(ntok - 1) << 24;
+      // every tile of the item holds a validated entry, so the last one lies in tile t1 - 1 or beyond
+      it.t1_flags = (uint32_t)t1 | (uint32_t)min(cap - 4 * (t1 - 1), 3) << 26 | flags;
       it.table_off = tab;
-      it.pidx_cap = cap;
+      it.merge = merged ? merge_off - 1 : -1;
 #pragma unroll
-      for (int k = 0; k < 6; ++k) it.ids[k] = a.page_table[tab + min(4 * it.t0 + k, cap)];
-      a.items[atomicAdd(&hist[bucket(it.t1 - it.t0)], 1)] = it;
+      for (int k = 0; k < 8; ++k) it.ids[k] = a.page_table[tab + min(4 * t0 + k, cap)];
+      a.items[atomicAdd(&hist[bucket(flags & kItemGroup ? s_maxcost : t1 - t0)], 1)] = it;
     };
     for (int c = 0; c < ns; ++c) {
       ItemRec it;
-      it.seq = x.s;
       it.row0 = x.row0;
-      it.t0 = x.pt + c * Li;
-      it.t1 = (c + 1 < ns ? x.pt + (c + 1) * Li : x.T);
-      it.part = merged ? own_off + c * x.ntok : -1;
-      it.gsize = 0;
-      finish(it, sq0 + x.row0, x.ntok);
+      it.chunk = merged ? c : -1;
+      finish(it, x.pt + c * Li, c + 1 < ns ? x.pt + (c + 1) * Li : x.T, sq0 + x.row0, x.ntok, 0);
     }
     for (int c = 0; x.gm && c < ng; ++c) {
       ItemRec it;
-      it.seq = x.s;
       it.row0 = 0;
-      it.t0 = c * Li;
-      it.t1 = Li > 0 ? min((c + 1) * Li, x.pt) : x.pt;
-      it.part = s_gbase[x.s] + c * x.gm;
-      it.gsize = x.gm;
-      finish(it, sq0, x.gm);
+      it.chunk = c;
+      finish(it, c * Li, Li > 0 ? min((c + 1) * Li, x.pt) : x.pt, sq0, x.gm, kItemGroup);
     }
     if (merged) own_off += ns * x.ntok;
   }
@@ -829,13 +855,13 @@ __global__ __launch_bounds__(NT) void plan_kernel(PlanArgs a) {
     a.hdr->err = MC_OK;
     a.hdr->num_items = tot_items;
     a.hdr->num_merges = tot_merge;
-    a.hdr->merge_tokens = tot_mtok;
     a.hdr->chunk_tiles = L;
     a.hdr->tile_tokens = a.tile_tokens;
     a.hdr->batch = a.batch;
     a.hdr->total_q = a.total_q;
     a.hdr->num_groups_rows = tot_grp;
     a.hdr->tail_chunks = tail_c;
+    a.hdr->arrive_words = arrive_words(L);
     a.hdr->magic = kPlanMagic;
   }
 }
@@ -895,10 +921,12 @@ struct AttnArgs {
   const int32_t* cu_pages;
   const PlanHeader* hdr;
   const ItemRec* items;
-  float* part_lse;         // [partial row][hq]
+  const MergeRec* merges;
+  float* part_lse;         // [partial row][hq], the arrival counts at its end
   float* part_o;           // [partial row][hq][128]
   int64_t page_stride;     // bytes
   int32_t num_pages, hkv, hq, batch, total_q;
+  int32_t part_cap;        // rows of the partial arrays
   float scale, scale_log2;  // softmax scale, and scale * log2(e)
 };
 
@@ -949,6 +977,141 @@ __device__ __forceinline__ void copy16_to_lds(const char* base, uint32_t lane_of
                :: "v"(lane_off), "s"(base), "s"(lds_base) : "memory", "m0");
 }
 
+// ---- partial rows ------------------------------------------------------------------------
+// They are written by one workgroup and read by another of the same launch, on any XCD: through
+// buffer instructions of device scope (sc1), which write to and read from the level all XCDs
+// share, so that no L2 has to be written back or invalidated as a whole.
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+typedef __amdgpu_buffer_rsrc_t buffer_rsrc;
+constexpr int kDeviceScope = 16;          // sc1
+__device__ __forceinline__ buffer_rsrc make_rsrc(void* p, uint32_t bytes) {
+  return __builtin_amdgcn_make_buffer_rsrc(p, 0, bytes, 0x00020000);   // raw, 32-bit; bounds checked
+}
+__device__ __forceinline__ void store_device(buffer_rsrc r, uint32_t off, f32x4 v) {
+  __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, v), r, off, 0, kDeviceScope);
+}
+__device__ __forceinline__ void store_device(buffer_rsrc r, uint32_t off, float v) {
+  __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(uint32_t, v), r, off, 0, kDeviceScope);
+}
+__device__ __forceinline__ f32x4 load_device4(buffer_rsrc r, uint32_t off) {
+  return __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(r, off, 0, kDeviceScope));
+}
+__device__ __forceinline__ float load_device(buffer_rsrc r, uint32_t off) {
+  return __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(r, off, 0, kDeviceScope));
+}
+
+// Chunks a merge record's last step combines: the prefix's and the tile's own, a tree's counting as one.
+template <int G>
+__device__ __forceinline__ int flat_chunks(int nsplit, int ntok) { return ntok * G <= kFlatRows ? nsplit : 1; }
+template <int G, typename Rec>
+__device__ __forceinline__ int flat_chunks_of(const Rec& m) {
+  return flat_chunks<G>(m[2], m[1]) + (m[4] > 0 ? flat_chunks<G>(m[4], m[6]) : 0);
+}
+
+// The members of a shared-prefix group, for the item that counts itself at all of them: their merge
+// records, whether this item was the last to arrive there, and the member a token belongs to.  In LDS
+// (the tiles are consumed), behind the part in which a workgroup stages its output rows.
+struct MemberList {
+  int32_t rec[kBM][8];             // MergeRec
+  int32_t last[kBM], of[kBM];
+};
+constexpr int kStageBytes = kBM * kRowBytes;
+static_assert(kStageBytes + sizeof(MemberList) <= 4 * kTileBytes, "the list takes the tiles' LDS");
+
+// One more chunk of a row (LSE lse) beside those summed so far (their maximum mx, their weights' sum
+// den): the factors of both.  Every place that sums chunks does it by this step, chunk after chunk in
+// their order, so that the result does not depend on the place.
+__device__ __forceinline__ void chunk_step(float lse, float& mx, float& den, float& f_old, float& f_new) {
+  const float m = fmaxf(mx, lse);
+  const bool any = m > -INFINITY;          // (a chunk without a key has no weight, and no maximum)
+  f_old = any ? __expf(mx - m) : 1.f;
+  f_new = any && lse != -INFINITY ? __expf(lse - m) : 0.f;
+  mx = m;
+  den = __builtin_fmaf(den, f_old, f_new);
+}
+
+// One kv head's rows of `tokens` tokens of tiles of few rows from their chunks: with L_c the chunk
+// LSEs, LSE = log sum_c exp(L_c) and O = sum_c exp(L_c - LSE) O_c, chunks in order: those of the
+// group's prefix, then the tile's own.  record(i, first) gives the merge record of token i and the
+// first token of that record.
+// A chain of memory round trips and little else, run once by code that is not in the instruction
+// cache: half a wavefront takes a row, 16 bytes a lane; every lane forms the row's weights by itself
+// from LSEs it reads beside the rows (no exchange, no barrier); kRows rows x kChunks chunks are in
+// flight, and nothing but the loop stands under a condition.
+template <typename T, int G, int kRows, int kChunks, typename Record>
+__device__ __forceinline__ void merge_rows(const AttnArgs& a, buffer_rsrc rs_o, buffer_rsrc rs_lse,
+                                           int hk, int tokens, Record&& record) {
+  const int rows = tokens * G, piece = threadIdx.x & 31;
+  for (int r0 = threadIdx.x >> 5; r0 < rows; r0 += kRows * (kThreads / 32)) {
+    // per row: chunks, the prefix's among them, partial row and byte of this lane's piece in the first
+    // chunk, the same from one chunk to the next
+    int nch[kRows], g_nsplit[kRows], out_row[kRows];
+    uint32_t g_row[kRows], g_byte[kRows], g_step[kRows], own_row[kRows], own_step[kRows];
+    float mx[kRows], den[kRows];
+    f32x4 acc[kRows];
+    int nmax = 0;
+#pragma unroll
+    for (int u = 0; u < kRows; ++u) {
+      const int r = min(r0 + u * (kThreads / 32), rows - 1), i = r / G;
+      int first;
+      const auto m = record(i, first);
+      const int tt = i - first, g_rows = m[6] * G;
+      g_nsplit[u] = m[4] > 0 ? flat_chunks<G>(m[4], m[6]) : 0;
+      nch[u] = m[2] + g_nsplit[u];
+      const uint32_t g0 = m[5] * a.hq + hk * g_rows, gr = (m[7] + tt) * G + r % G;
+      g_row[u] = g0 + gr;
+      g_byte[u] = g_rows <= kFlatRows ? g_row[u] * 512u + piece * 16u
+                                      : g0 * 512u + (piece >> 1) * g_rows * 32u + gr * 32u + (piece & 1) * 16u;
+      g_step[u] = m[6] * a.hq;
+      own_row[u] = m[3] * a.hq + (hk * m[1] + tt) * G + r % G;
+      own_step[u] = m[1] * a.hq;
+      out_row[u] = (m[0] + tt) * a.hq + hk * G + r % G;
+      mx[u] = -INFINITY;
+      den[u] = 0.f;
+      acc[u] = f32x4{0.f, 0.f, 0.f, 0.f};
+      nmax = max(nmax, nch[u]);
+    }
+    for (int c0 = 0; c0 < nmax; c0 += kChunks) {
+      f32x4 o[kRows][kChunks];
+      float lse[kRows][kChunks];
+#pragma unroll
+      for (int u = 0; u < kRows; ++u)
+#pragma unroll
+        for (int k = 0; k < kChunks; ++k) {
+          const int c = min(c0 + k, nch[u] - 1);
+          const bool in_group = c < g_nsplit[u];
+          const uint32_t on = (in_group ? c : c - g_nsplit[u]) * (in_group ? g_step[u] : own_step[u]);
+          lse[u][k] = load_device(rs_lse, ((in_group ? g_row[u] : own_row[u]) + on) * 4u);
+          o[u][k] = load_device4(rs_o, (in_group ? g_byte[u] : own_row[u] * 512u + piece * 16u) + on * 512u);
+        }
+#pragma unroll
+      for (int u = 0; u < kRows; ++u)
+#pragma unroll
+        for (int k = 0; k < kChunks; ++k) {
+          const float l = c0 + k < nch[u] ? lse[u][k] : -INFINITY;
+          float f_old, f_new;
+          chunk_step(l, mx[u], den[u], f_old, f_new);
+          // A chunk without a key is left out, not weighed by 0: one that was not computed left in its
+          // rows what the memory held before, which may be NaN.
+#pragma unroll
+          for (int j = 0; j < 4; ++j)
+            acc[u][j] = __builtin_fmaf(l != -INFINITY ? o[u][k][j] : 0.f, f_new, acc[u][j] * f_old);
+        }
+    }
+#pragma unroll
+    for (int u = 0; u < kRows; ++u) {
+      // (no chunk of the row was computed: nothing is written)
+      if (r0 + u * (kThreads / 32) >= rows || !(mx[u] > -INFINITY)) continue;
+      const float inv = 1.f / den[u];
+      u32x2 v;
+      v[0] = Mfma<T>::pack2(acc[u][0] * inv, acc[u][1] * inv);
+      v[1] = Mfma<T>::pack2(acc[u][2] * inv, acc[u][3] * inv);
+      *reinterpret_cast<u32x2*>(a.out + (int64_t)out_row[u] * kRowBytes + piece * 8) = v;
+      if (piece == 0) a.lse[out_row[u]] = mx[u] + __logf(den[u]);
+    }
+  }
+}
+
 // LDS tile: 64 rows (keys) x 256 B.  16-byte chunk c of row r sits at chunk position
 //   K: c ^ (r & 15)        -> 16 lanes reading one chunk of 16 consecutive rows hit 16 positions
 //   V: c ^ ((r & 3) << 2)  -> a transposing read of 4 consecutive rows x 64 B hits 16 positions
@@ -993,9 +1156,16 @@ __global__ __launch_bounds__(kThreads, kCB == 1 ? 2 : 1) void attn_kernel(AttnAr
   // 4 K half tiles then 2 V tiles; reused as the output staging area at the end
   __shared__ __attribute__((aligned(1024))) char lds[4 * kTileBytes];
   __shared__ int s_redo;   // a row of the fixed-reference pass overflowed: run the pass again
+  __shared__ int s_last;   // chunks' arrivals this workgroup was the last of
+  __shared__ int s_second; // the neighbouring chunk's rows are there
 
-  const int hk = blockIdx.x % a.hkv;
-  const int wi = blockIdx.x / a.hkv;
+  // (the division goes through the vector unit, and the compiler may leave its result there, and with
+  // it the addresses that the copies below take from scalar registers; the builtin for this is dropped
+  // on a value that is the same in all lanes; the s_nop is the wait state that reading a lane of a
+  // register needs after a vector instruction wrote it, which the compiler does not add for assembly)
+  int wi;
+  asm("s_nop 1\n\tv_readfirstlane_b32 %0, %1" : "=s"(wi) : "v"(blockIdx.x / a.hkv));
+  const int hk = blockIdx.x - wi * a.hkv;
   // The item record is requested together with the plan's header (the grid never exceeds the
   // room for records, whatever the header says): one memory round trip, with every argument the
   // look-ups behind it need already in registers.  (Left alone the compiler reads the header field
@@ -1012,22 +1182,25 @@ __global__ __launch_bounds__(kThreads, kCB == 1 ? 2 : 1) void attn_kernel(AttnAr
   if (!ours) return;
 
   const int tid = threadIdx.x, lane = tid & 63;
-  if (tid == 0) s_redo = 0;   // published by the prologue's barrier
+  if (tid == 0) s_redo = s_last = 0;   // published by the barriers below
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int l32 = lane & 31, half = lane >> 5;
 
   const int seq = item[0], row0 = item[1];
-  const int t0 = item[2];                            // first KV tile of the item (even)
-  const int part = item[4];                          // >= 0: partial result, merged afterwards
-  const int gsize = item[5];                         // > 0: shared-prefix item over gsize tokens
-  const int q_first = item[6];                       // the tile's first token in the q array
-  const int ntok = item[7];                          // valid tokens in this tile (>= 1)
-  const int table_off = item_b[0], pidx_cap = item_b[1];
+  const int t0 = (item[2] & 0xffffff) << 1;          // first KV tile of the item (even)
+  const int t1 = item[3] & 0x3ffffff;                // the one after its last
+  const int chunk = item[4];                         // >= 0: one of several chunks
+  const bool group = (item[3] & kItemGroup) != 0;    // shared-prefix item
+  const int q_first = item[5];                       // the tile's first token in the q array
+  const int ntok = (int)((uint32_t)item[2] >> 24) + 1;   // valid tokens in this tile (>= 1)
+  const int table_off = item[6];
+  const int pidx_cap = 4 * (t1 - 1) + (int)((uint32_t)item[3] >> 26 & 3);
+  const int merge = item[7];                         // merge record, if chunk >= 0
   // a record that cannot come from the planner (a workspace written over by something else)
-  const bool odd = ((unsigned)seq >= (unsigned)a.batch) | (row0 < 0) | (t0 < 0) | (item[3] <= t0) |
-                   (gsize < 0) | (gsize > TOK) | (ntok < 1) | (ntok > TOK) |
-                   ((gsize > 0) & (ntok != gsize)) | (q_first < 0) |
-                   ((int64_t)q_first + ntok > a.total_q) | (table_off < 0) | (pidx_cap < 0);
+  const bool odd = ((unsigned)seq >= (unsigned)a.batch) | (row0 < 0) | (t1 <= t0) | (ntok > TOK) |
+                   (q_first < 0) | ((int64_t)q_first + ntok > a.total_q) | (table_off < 0) |
+                   ((chunk >= 0) & ((unsigned)merge >= (unsigned)hdr[6])) |
+                   (group & (kCB != 1 || chunk < 0));   // (wide q tiles and groups exclude each other)
   if (odd) return;
   // begin is read here, not taken from the plan (one plan may serve many decode steps)
   const int b = ((const_i32_ptr)a.begin)[seq];
@@ -1056,14 +1229,14 @@ __global__ __launch_bounds__(kThreads, kCB == 1 ? 2 : 1) void attn_kernel(AttnAr
     copy16_to_lds(base, is_v ? v_lane_off : k_lane_off, lds_page + wave * 1024);
   };
   // The first tiles' copies - K halves 0, 1, 2 and V(0) of the item - need the record alone (it holds
-  // the ids of table entries 4 t0 .. 4 t0 + 5): they leave before anything that depends on `begin`.
+  // the ids of table entries 4 t0 .. 4 t0 + 7): they leave before anything that depends on `begin`.
   // With the look-ups at the kernel's start in one request, one decode row over 1000 keys (32 / 8
   // heads): append, attention and merge of a layer 12.0 -> 11.4 us from first to last instruction;
   // eight rows (64 / 8 heads, 1024..4096 keys) 29.6 -> 29.0 us a layer.
   auto first_copies = [&]() __attribute__((always_inline)) {
     const char* pb[6];
 #pragma unroll
-    for (int i = 0; i < 6; ++i) pb[i] = page_base(item_b[2 + i]);
+    for (int i = 0; i < 6; ++i) pb[i] = page_base(item_b[i]);
 #pragma unroll
     for (int i = 0; i < 6; ++i) copy_page(pb[i], false, lds_k + i * 4096);
 #pragma unroll
@@ -1073,24 +1246,20 @@ __global__ __launch_bounds__(kThreads, kCB == 1 ? 2 : 1) void attn_kernel(AttnAr
   // The position of the tile's first token.  The rows of a shared-prefix item are new tokens of
   // consecutive sequences; all of them lie beyond the prefix, so any position at or past the
   // item's last key serves.
-  const int first_pos = gsize > 0 ? item[3] * kBN : b + row0;
+  const int first_pos = group ? t1 * kBN : b + row0;
   // keys [64 t0, kv_len) are this item's: up to the end of its chunk, or of the tile's range
-  const int kv_len = min(first_pos + ntok, item[3] * kBN);
+  const int kv_len = min(first_pos + ntok, t1 * kBN);
   const int n_kv_tiles = (kv_len + kBN - 1) / kBN;   // (absolute) index after the last KV tile
   const int n_halves = (kv_len + kHalf - 1) / kHalf;
   // half h is fully visible to every row of the q tile iff 32 (h+1) <= first_pos + 1
   const int n_full = (first_pos + 1) / kHalf;
   // A begin that no longer fits the item - negative, or so small that the item's first tile
-  // lies past the range - ends the workgroup before the page table is read; table indices never
-  // pass the last entry the plan validated for the sequence.
-  if (b < 0 || kv_len <= kBN * t0) {
+  // lies past the range - skips the item before the page table is read (a chunk still arrives, with no
+  // key in its rows); table indices never pass the last entry the plan validated for the sequence.
+  const bool fits = b >= 0 && kv_len > kBN * t0;
+  if (!fits) {
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // the copies write this workgroup's LDS
-    // a chunk that is not computed says so in its partial rows (no key seen: LSE = -inf), so
-    // that the merge gives it no weight, and writes nothing if no chunk of the row was computed
-    if (part >= 0)
-      for (int i = tid; i < ntok * G; i += kThreads)
-        a.part_lse[(int64_t)(part + i / G) * a.hq + hk * G + i % G] = -INFINITY;
-    return;
+    if (chunk < 0) return;
   }
   const int last_pidx = min((kv_len - 1) / kPage, pidx_cap);   // last entry that holds a needed key
 
@@ -1473,62 +1642,256 @@ __global__ __launch_bounds__(kThreads, kCB == 1 ? 2 : 1) void attn_kernel(AttnAr
       tile(jt, jt & 1, 2 * jt + 1 >= n_full, 2 * jt + 2 >= n_full, false);
   };
 
-  if constexpr (kTryFixedRef<T>) {
-    // First with the fixed reference.  A row whose sum left the range in which nothing can have
-    // overflowed (or is not a number) sends the whole workgroup through the pass again with the
-    // moving reference; on scores like the workloads' (a few units wide) that never happens.
-    run_pass(std::true_type{});
-    bool sums_ok = true;
-    float o_chk = 0.f;                     // NaN if any accumulator is infinite or not a number
+  if (fits) {
+    if constexpr (kTryFixedRef<T>) {
+      // First with the fixed reference.  A row whose sum left the range in which nothing can have
+      // overflowed (or is not a number) sends the whole workgroup through the pass again with the
+      // moving reference; on scores like the workloads' (a few units wide) that never happens.
+      run_pass(std::true_type{});
+      bool sums_ok = true;
+      float o_chk = 0.f;                     // NaN if any accumulator is infinite or not a number
 #pragma unroll
-    for (int cb = 0; cb < kCB; ++cb) {
-      sums_ok = sums_ok && l_run[cb] + __shfl_xor(l_run[cb], 32) < kFixedRefSumLimit;
+      for (int cb = 0; cb < kCB; ++cb) {
+        sums_ok = sums_ok && l_run[cb] + __shfl_xor(l_run[cb], 32) < kFixedRefSumLimit;
 #pragma unroll
-      for (int dc = 0; dc < 4; ++dc)
+        for (int dc = 0; dc < 4; ++dc)
 #pragma unroll
-        for (int i = 0; i < 16; ++i) o_chk = __builtin_fmaf(o_acc[cb][dc][i], 0.f, o_chk);
-    }
-    const bool bad = wave_active && !(sums_ok && o_chk == 0.f);
-    if (__builtin_amdgcn_ballot_w64(bad) != 0 && lane == 0) s_redo = 1;
-    __syncthreads();
-    if (s_redo != 0) {
-      first_copies();
+          for (int i = 0; i < 16; ++i) o_chk = __builtin_fmaf(o_acc[cb][dc][i], 0.f, o_chk);
+      }
+      const bool bad = wave_active && !(sums_ok && o_chk == 0.f);
+      if (__builtin_amdgcn_ballot_w64(bad) != 0 && lane == 0) s_redo = 1;
+      __syncthreads();
+      if (s_redo != 0) {
+        first_copies();
+        run_pass(std::false_type{});
+      }
+    } else {
       run_pass(std::false_type{});
     }
-  } else {
-    run_pass(std::false_type{});
   }
-  if (kGate && !wave_active) return;
 
-  // ---- epilogue: normalise, stage O through LDS for full-row stores, write LSE ----
-  float l_tot[kCB], inv[kCB];
+  // ---- epilogue: normalise ----
+  bool row_live[kCB];                     // the row exists and this wavefront has it
+  float lse_row[kCB];
 #pragma unroll
   for (int cb = 0; cb < kCB; ++cb) {
-    l_tot[cb] = l_run[cb] + __shfl_xor(l_run[cb], 32);
-    inv[cb] = 1.f / l_tot[cb];
-  }
-  if (part >= 0) {
-    // One chunk of a cut KV range: O normalised within the chunk (fp32) and the chunk's LSE go
-    // to the partial arrays; merge_kernel weighs the chunks together.  A lane holds, for its
-    // row, d = 32 dc + 8 j + 4 half + {0..3}: 16 bytes per (dc, j).
-#pragma unroll
-    for (int cb = 0; cb < kCB; ++cb) {
-      if (!row_ok[cb]) continue;
-      const int64_t prow = (int64_t)(part + tt[cb]) * a.hq + hk * G + g[cb];
-      float* po = a.part_o + prow * mc::kHeadDim;
+    row_live[cb] = row_ok[cb] && wave_active;
+    if (fits) {
+      const float l_tot = l_run[cb] + __shfl_xor(l_run[cb], 32), inv = 1.f / l_tot;
+      lse_row[cb] = m_run[cb] * a.scale + __logf(l_tot);
 #pragma unroll
       for (int dc = 0; dc < 4; ++dc)
 #pragma unroll
-        for (int j = 0; j < 4; ++j) {
-          typedef float f32x4 __attribute__((ext_vector_type(4)));
-          f32x4 v = {o_acc[cb][dc][4 * j] * inv[cb], o_acc[cb][dc][4 * j + 1] * inv[cb],
-                     o_acc[cb][dc][4 * j + 2] * inv[cb], o_acc[cb][dc][4 * j + 3] * inv[cb]};
-          *reinterpret_cast<f32x4*>(po + 32 * dc + 8 * j + 4 * half) = v;
-        }
-      if (half == 0) a.part_lse[prow] = m_run[cb] * a.scale + __logf(l_tot[cb]);
+        for (int i = 0; i < 16; ++i) o_acc[cb][dc][i] *= inv;
+    } else {
+      lse_row[cb] = -INFINITY;
+#pragma unroll
+      for (int dc = 0; dc < 4; ++dc) o_acc[cb][dc] = zero16;
     }
-    return;
   }
+
+  if (chunk >= 0) {
+    // ---- one of several chunks (see MergeRec).  Partial rows reach the memory all XCDs see before
+    //      the workgroup says so, and are read after the word that says so.  Nobody waits for anybody.
+    //      As a launch of its own behind this one, reading every partial row, the merge took 3.6 us of the
+    //      12 us a layer of one decode row over 1000 keys needs, 10 of the 63 us of 500 new tokens over
+    //      4500 (four chunks of 128 rows), and 4.7 us where nothing was cut; now 2.5, 4.4 and none
+    //      (32 / 8 heads; per layer 13.9 -> 12.9 and 70 -> 60 us).
+    const buffer_rsrc rs_o = make_rsrc(a.part_o, (uint32_t)a.part_cap * a.hq * 512u);
+    const buffer_rsrc rs_lse = make_rsrc(a.part_lse, (uint32_t)a.part_cap * a.hq * 4u);
+    i32x8 m = *(const __attribute__((address_space(4))) i32x8*)(a.merges + merge);
+    const int words = ((const_i32_ptr)a.hdr)[10];
+    const int rows = ntok * G;
+    const int chunks = group ? m[4] : m[2];
+    const uint32_t step = ntok * a.hq;                        // partial rows of a chunk
+    const uint32_t chunk0 = (group ? m[5] : m[3]) * a.hq + hk * rows;
+    uint32_t* arrivals = reinterpret_cast<uint32_t*>(a.part_lse) + (int64_t)a.part_cap * a.hq - 1;
+    // A row's 32 pieces of 16 bytes lie row by row, for readers that take rows, or as the registers lie
+    // (a store fills 1 KiB).  Registers 4 j .. 4 j + 3 of o_acc[dc] hold d = 32 dc + 8 j + 4 half +
+    // {0..3}: piece 2 i + half with i = 4 dc + j.  Where piece `half` of row r is, if a chunk's rows
+    // start at row0, and from one i to the next:
+    struct Place { uint32_t byte, step; };
+    auto by_row = [&](uint32_t row0, int r, int) __attribute__((always_inline)) {
+      return Place{(row0 + r) * 512u + half * 16, 32u};
+    };
+    auto by_reg = [&](uint32_t row0, int r, int of_rows) __attribute__((always_inline)) {
+      return Place{row0 * 512u + r * 32u + half * 16, of_rows * 32u};
+    };
+    auto tile_row = [&](int cb) __attribute__((always_inline)) { return wave * kWaveRows + cb * 32 + l32; };
+    auto write_rows = [&](uint32_t row0, auto&& place) __attribute__((always_inline)) {
+#pragma unroll
+      for (int cb = 0; cb < kCB; ++cb) {
+        if (!row_live[cb]) continue;
+        const Place at = place(row0, tile_row(cb), rows);
+#pragma unroll
+        for (int i = 0; i < 16; ++i) {
+          const f32x16& o = o_acc[cb][i >> 2];
+          const int j = 4 * (i & 3);
+          store_device(rs_o, at.byte + i * at.step, f32x4{o[j], o[j + 1], o[j + 2], o[j + 3]});
+        }
+        if (half == 0) store_device(rs_lse, (row0 + tile_row(cb)) * 4u, lse_row[cb]);
+      }
+      asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+      __syncthreads();
+    };
+    auto read_row = [&](Place at, f32x4 (&o)[16]) __attribute__((always_inline)) {
+#pragma unroll
+      for (int i = 0; i < 16; ++i) o[i] = load_device4(rs_o, at.byte + i * at.step);
+    };
+
+    if (rows > kFlatRows) {
+      uint32_t* word0 = arrivals - ((int64_t)merge * a.hkv + hk) * words - 1 - (group ? words / 2 : 0);
+      int idx = chunk, count = chunks, node0 = 0;
+      for (int level = 0; count > 1; ++level) {
+        if ((idx ^ 1) < count) {
+          const int node = node0 + (idx >> 1);
+          uint32_t* word = word0 - (node >> 5);
+          const uint32_t bit = 1u << (node & 31);
+          if (tid == 0) {
+            const bool there = __hip_atomic_load(word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) & bit;
+            if (there) atomicXor(word, bit);
+            s_second = there;
+          }
+          __syncthreads();
+          bool second = s_second != 0;
+          __syncthreads();
+          if (!second) {
+            write_rows(chunk0 + (idx << level) * step, by_reg);
+            if (tid == 0) s_second = (atomicXor(word, bit) & bit) != 0;
+            __syncthreads();
+            second = s_second != 0;
+            __syncthreads();
+            if (!second) return;
+          }
+          const uint32_t other = chunk0 + ((idx ^ 1) << level) * step;
+#pragma unroll
+          for (int cb = 0; cb < kCB; ++cb) {
+            if (!row_live[cb]) continue;
+            const float lse = load_device(rs_lse, (other + tile_row(cb)) * 4u);
+            f32x4 o[16];
+            read_row(by_reg(other, tile_row(cb), rows), o);
+            const float mx = fmaxf(lse, lse_row[cb]);
+            if (!(mx > -INFINITY)) continue;        // neither chunk holds a key of this row
+            const float w0 = __expf(lse_row[cb] - mx), w1 = __expf(lse - mx), den = w0 + w1;
+            const float f0 = w0 / den, f1 = w1 / den;
+            lse_row[cb] = mx + __logf(den);
+            // the same sum whichever of the two is the second: products, then their sum
+#pragma unroll
+            for (int i = 0; i < 16; ++i)
+#pragma unroll
+              for (int j = 0; j < 4; ++j) {
+#pragma clang fp contract(off)
+                const float x = o_acc[cb][i >> 2][4 * (i & 3) + j] * f0, y = o[i][j] * f1;
+                o_acc[cb][i >> 2][4 * (i & 3) + j] = x + y;
+              }
+          }
+        }
+        node0 += (count + 1) >> 1;
+        count = (count + 1) >> 1;
+        idx >>= 1;
+      }
+    }
+    const bool few = rows <= kFlatRows;
+    if (few || group || m[4] > 0) {
+      // ---- the prefix's chunks and the tile's own, or the chunks of few rows: counted
+      MemberList& list = *reinterpret_cast<MemberList*>(lds + kStageBytes);
+      i32x8 mr = m;
+      if (group) mr = *reinterpret_cast<const i32x8*>(a.merges + min(merge + tid, hdr[6] - 1));
+      if (few) write_rows(chunk0 + chunk * step, by_row);
+      else write_rows(chunk0, by_reg);
+      // records of this item: one, or the group's members' (their tokens follow one another)
+      if (tid < (group ? ntok : 1) && merge + tid < hdr[6] && mr[0] < q_first + ntok) {
+        const int n = flat_chunks_of<G>(mr);
+        const bool last =
+            atomicInc(arrivals - ((int64_t)(merge + tid) * a.hkv + hk) * words, n - 1) == (unsigned)n - 1;
+        if (last) s_last = 1;
+        if (group) {
+          *reinterpret_cast<i32x8*>(list.rec[tid]) = mr;
+          list.last[tid] = last;
+          for (int i = 0; i < mr[1]; ++i) list.of[mr[7] + i] = tid;
+        }
+      }
+      __syncthreads();
+      if (s_last == 0) return;
+      if (few) {
+        if (group) {
+          // (few rows: member after member)
+          for (int k = 0; k < ntok && merge + k < hdr[6]; ++k) {
+            const i32x8 r = *reinterpret_cast<const i32x8*>(list.rec[k]);
+            const int first = __builtin_amdgcn_readfirstlane(r[7]), n = __builtin_amdgcn_readfirstlane(r[1]);
+            if (__builtin_amdgcn_readfirstlane(list.last[k]))
+              merge_rows<T, G, 1, kMergeAhead>(a, rs_o, rs_lse, hk, n, [&](int, int& f) __attribute__((always_inline)) { f = 0; return r; });
+            if (first + n >= ntok) break;
+          }
+        } else {
+          merge_rows<T, G, 1, kMergeAhead>(a, rs_o, rs_lse, hk, ntok,
+                                           [&](int, int& f) __attribute__((always_inline)) { f = 0; return m; });
+        }
+        return;
+      }
+      // ---- the last of prefix and own range has one of them in registers, chunk by chunk the rest is
+      //      added: a group's item the own chunks of the members it completed, a tile of more rows the
+      //      prefix, which comes before it
+#pragma unroll
+      for (int cb = 0; cb < kCB; ++cb) {
+        const int r = tile_row(cb);
+        i32x8 of = m;
+        if (group) {
+          const int k = list.of[min(r / G, ntok - 1)];
+          row_live[cb] = row_live[cb] && list.last[k] != 0;
+          of = *reinterpret_cast<const i32x8*>(list.rec[k]);
+        }
+        if (!row_live[cb]) continue;
+        float mx = lse_row[cb], den = mx != -INFINITY ? 1.f : 0.f, f_old, f_new;
+        f32x4 o[16];
+        if (!group) {
+          const int g_rows = of[6] * G, gr = of[7] * G + r;
+          const uint32_t row0 = of[5] * a.hq + hk * g_rows;
+          const float mine = lse_row[cb];
+          mx = load_device(rs_lse, (row0 + gr) * 4u);
+          den = mx != -INFINITY ? 1.f : 0.f;
+          read_row(by_reg(row0, gr, g_rows), o);
+          chunk_step(mine, mx, den, f_old, f_new);
+#pragma unroll
+          for (int i = 0; i < 16; ++i)
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+              const float x = o_acc[cb][i >> 2][4 * (i & 3) + j];
+              o_acc[cb][i >> 2][4 * (i & 3) + j] = __builtin_fmaf(x, f_new, o[i][j] * f_old);
+            }
+        } else {
+          const int own_rows = of[1] * G, own = r - of[7] * G, n = flat_chunks<G>(of[2], of[1]);
+          for (int c = 0; c < n; ++c) {
+            const uint32_t row0 = (of[3] + c * of[1]) * a.hq + hk * own_rows;
+            const float lse = load_device(rs_lse, (row0 + own) * 4u);
+            read_row(own_rows <= kFlatRows ? by_row(row0, own, 0) : by_reg(row0, own, own_rows), o);
+            chunk_step(lse, mx, den, f_old, f_new);
+#pragma unroll
+            for (int i = 0; i < 16; ++i)
+#pragma unroll
+              for (int j = 0; j < 4; ++j) {
+                const float x = o_acc[cb][i >> 2][4 * (i & 3) + j];
+                o_acc[cb][i >> 2][4 * (i & 3) + j] =
+                    __builtin_fmaf(lse != -INFINITY ? o[i][j] : 0.f, f_new, x * f_old);
+              }
+          }
+        }
+        lse_row[cb] = mx + __logf(den);
+        const float inv = mx > -INFINITY ? 1.f / den : 0.f;
+#pragma unroll
+        for (int dc = 0; dc < 4; ++dc) o_acc[cb][dc] *= inv;
+      }
+    }
+  }
+  if (kGate && !wave_active) return;
+  if (chunk >= 0) {      // no chunk of these rows was computed: nothing is written
+    bool some = false;
+#pragma unroll
+    for (int cb = 0; cb < kCB; ++cb) some |= row_live[cb] && lse_row[cb] != -INFINITY;
+    if (__builtin_amdgcn_ballot_w64(some) == 0) return;
+  }
+
+  // ---- the tile's result: stage O through LDS for full-row stores, write LSE ----
   // 8 KiB per wave and row block; all tiles are consumed
 #pragma unroll
   for (int cb = 0; cb < kCB; ++cb) {
@@ -1539,13 +1902,12 @@ __global__ __launch_bounds__(kThreads, kCB == 1 ? 2 : 1) void attn_kernel(AttnAr
       for (int j = 0; j < 4; ++j) {
         // registers 4j..4j+3 hold d = 32 dc + 8 j + 4 half + {0..3}: 8 bytes of chunk 4 dc + j
         u32x2 w;
-        w[0] = Mfma<T>::pack2(o_acc[cb][dc][4 * j] * inv[cb], o_acc[cb][dc][4 * j + 1] * inv[cb]);
-        w[1] = Mfma<T>::pack2(o_acc[cb][dc][4 * j + 2] * inv[cb], o_acc[cb][dc][4 * j + 3] * inv[cb]);
+        w[0] = Mfma<T>::pack2(o_acc[cb][dc][4 * j], o_acc[cb][dc][4 * j + 1]);
+        w[1] = Mfma<T>::pack2(o_acc[cb][dc][4 * j + 2], o_acc[cb][dc][4 * j + 3]);
         *reinterpret_cast<u32x2*>(stage + k_swz(l32, 4 * dc + j) + half * 8) = w;
       }
-    if (row_ok[cb] && half == 0)
-      a.lse[(int64_t)(q_first + tt[cb]) * a.hq + hk * G + g[cb]] =
-          m_run[cb] * a.scale + __logf(l_tot[cb]);
+    if (row_live[cb] && half == 0)
+      a.lse[(int64_t)(q_first + tt[cb]) * a.hq + hk * G + g[cb]] = lse_row[cb];
   }
   __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
   __builtin_amdgcn_wave_barrier();
@@ -1557,133 +1919,16 @@ __global__ __launch_bounds__(kThreads, kCB == 1 ? 2 : 1) void attn_kernel(AttnAr
       const int lr = 4 * i + (lane >> 4);               // row of this block's 32
       const int rr = wave * kWaveRows + cb * 32 + lr, gg = rr % G, t2 = rr / G;
       const u32x4 v = *reinterpret_cast<const u32x4*>(stage + k_swz(lr, lane & 15));
-      if (t2 < ntok)
+      // (of a group, the members' rows that were completed here)
+      bool live = t2 < ntok;
+      if (kCB == 1 && group && live) {
+        const MemberList& list = *reinterpret_cast<const MemberList*>(lds + kStageBytes);
+        live = list.last[list.of[t2]] != 0;
+      }
+      if (live)
         *reinterpret_cast<u32x4*>(a.out + ((int64_t)(q_first + t2) * a.hq + hk * G + gg) * kRowBytes +
                                   (lane & 15) * 16) = v;
     }
-  }
-}
-
-// Combines the chunks of every q tile whose KV range was cut: with L_c the chunk LSEs,
-// LSE = log sum_c exp(L_c) and O = sum_c exp(L_c - LSE) O_c.  The grid walks the (token, four q
-// heads) pairs of those tiles - the host does not know how many tiles were cut, usually none, so
-// it sizes the grid for the batch's new tokens - one wavefront per q head, two d per lane; a
-// chunk's loads do not depend on another chunk's, so they are all in flight together.
-struct MergeArgs {
-  const PlanHeader* hdr;
-  const MergeRec* merges;
-  const float* part_lse;
-  const float* part_o;
-  char* out;
-  float* lse;
-  int32_t hq, max_merges;   // q heads; records the list has room for
-};
-
-// The merge is a chain of dependent reads and little else, so whatever can be requested early is:
-// the first 64 records with the header, the first kMergeAhead chunks' rows with the chunk LSEs.
-// Append + attention + merge of eight decode rows (64 / 8 heads, 1024..4096 keys): 32.9 -> 30.3 us a
-// layer.
-template <typename T>
-__global__ __launch_bounds__(256) void merge_kernel(MergeArgs a) {
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  // records 0..63, one a lane (as many as the list has room for), requested beside the header
-  typedef int32_t i32x4 __attribute__((ext_vector_type(4)));
-  const i32x4* rec = reinterpret_cast<const i32x4*>(a.merges + min(lane, a.max_merges - 1));
-  const i32x4 rec_lo = rec[0], rec_hi = rec[1];
-  if (a.hdr->magic != kPlanMagic) return;
-  const int head_groups = (a.hq + 3) / 4;
-  const int n_rec = min(a.hdr->num_merges, a.max_merges);
-  const int64_t total = (int64_t)a.hdr->merge_tokens * head_groups;   // usually 0: nothing was cut
-  typedef float f32x2 __attribute__((ext_vector_type(2)));
-  for (int64_t wk = blockIdx.x; wk < total; wk += gridDim.x) {
-    const int tok = (int)(wk / head_groups), h = (int)(wk % head_groups) * 4 + wave;
-    // the record whose token range [tok_off, tok_off + ntok) holds tok: among the first 64 it
-    // is in a lane's registers already; else a search that looks at 64 records per round
-    MergeRec m;
-    if (n_rec <= 64) {
-      const bool le = lane < n_rec && rec_hi[3] <= tok;
-      const int k = max(__popcll(__ballot(le)) - 1, 0);   // tok_off rises with the record index
-      m.q_row = __builtin_amdgcn_readlane(rec_lo[0], k);
-      m.ntok = __builtin_amdgcn_readlane(rec_lo[1], k);
-      m.nsplit = __builtin_amdgcn_readlane(rec_lo[2], k);
-      m.part = __builtin_amdgcn_readlane(rec_lo[3], k);
-      m.g_nsplit = __builtin_amdgcn_readlane(rec_hi[0], k);
-      m.g_part = __builtin_amdgcn_readlane(rec_hi[1], k);
-      m.g_stride = __builtin_amdgcn_readlane(rec_hi[2], k);
-      m.tok_off = __builtin_amdgcn_readlane(rec_hi[3], k);
-    } else {
-      int lo = 0, cnt = n_rec;
-      while (cnt > 1) {
-        const int step = (cnt + 63) / 64, end = lo + cnt;
-        const int i = lo + lane * step;
-        const bool le = i < end && a.merges[i].tok_off <= tok;
-        const int k = max(__popcll(__ballot(le)) - 1, 0);
-        lo += k * step;
-        cnt = min(step, end - lo);
-      }
-      m = a.merges[lo];
-    }
-    const int tt = tok - m.tok_off;
-    if (tt < 0 || tt >= m.ntok || h >= a.hq) continue;
-    // partial row of chunk c: the shared prefix's chunks first, then the tile's own
-    auto row_of = [&](int c) {
-      return (int64_t)(c < m.g_nsplit ? m.g_part + c * m.g_stride + tt
-                                      : m.part + (c - m.g_nsplit) * m.ntok + tt) * a.hq + h;
-    };
-    auto o_of = [&](int c) {
-      return *reinterpret_cast<const f32x2*>(a.part_o + row_of(c) * mc::kHeadDim + 2 * lane);
-    };
-    const int nchunks = m.g_nsplit + m.nsplit;
-    // the chunks' LSEs: one per lane (in rounds of 64), so that their loads are in flight
-    // together instead of one after the other; the maximum by a butterfly over the wavefront.
-    // The first chunks' rows follow at once: their place does not depend on the LSEs.
-    const float lse0 = lane < nchunks ? a.part_lse[row_of(lane)] : -INFINITY;
-    f32x2 o_first[kMergeAhead];
-#pragma unroll
-    for (int k = 0; k < kMergeAhead; ++k) o_first[k] = o_of(min(k, nchunks - 1));
-    float mx = lse0;
-    for (int c0 = 64; c0 < nchunks; c0 += 64) {
-      const int c = c0 + lane;
-      mx = fmaxf(mx, c < nchunks ? a.part_lse[row_of(c)] : -INFINITY);
-    }
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) mx = fmaxf(mx, __shfl_xor(mx, off));
-    if (!(mx > -INFINITY)) continue;   // no chunk of this row was computed: nothing to write
-    float den = 0.f;
-    f32x2 acc = {0.f, 0.f};
-    for (int c0 = 0; c0 < nchunks; c0 += 64) {
-      const int c = c0 + lane;
-      const float lse = c >= nchunks ? -INFINITY : c0 == 0 ? lse0 : a.part_lse[row_of(c)];
-      // exp(-inf) = 0 for a chunk with no key, and for the lanes beyond the last chunk.  Their rows
-      // are left out, not weighed: a chunk that was not computed left in them what the memory held
-      // before, which may be NaN.
-      const float w_lane = __expf(lse - mx);
-      const unsigned long long computed = __ballot(lse != -INFINITY);
-      float sum = w_lane;
-#pragma unroll
-      for (int off = 32; off > 0; off >>= 1) sum += __shfl_xor(sum, off);
-      den += sum;
-      const int n = min(64, nchunks - c0);
-      int k = 0;
-      if (c0 == 0) {
-#pragma unroll
-        for (; k < kMergeAhead; ++k)
-          if (computed >> k & 1) acc += o_first[k] * __shfl(w_lane, k);
-      }
-      for (; k < n; k += kMergeAhead) {   // rows in groups whose loads are in flight together
-        f32x2 v[kMergeAhead];
-#pragma unroll
-        for (int u = 0; u < kMergeAhead; ++u) v[u] = o_of(c0 + min(k + u, n - 1));
-#pragma unroll
-        for (int u = 0; u < kMergeAhead; ++u)
-          if (computed >> (k + u) & 1) acc += v[u] * __shfl(w_lane, k + u);
-      }
-    }
-    const float inv = 1.f / den;
-    const int64_t orow = (int64_t)(m.q_row + tt) * a.hq + h;
-    *reinterpret_cast<uint32_t*>(a.out + orow * kRowBytes + 4 * lane) =
-        Mfma<T>::pack2(acc[0] * inv, acc[1] * inv);
-    if (lane == 0) a.lse[orow] = mx + __logf(den);
   }
 }
 
@@ -1741,11 +1986,12 @@ bool may_group(const WorkspaceLayout& w, int32_t total_q, int tile_tokens) {
 }
 
 // Upper bound of the planner's item count: a q tile with T KV tiles becomes at most T / L + 1
-// items, and the planner's chunk length L is at least (sum of T) x hkv / (kRoundsWanted x slots).
-// A shared-prefix group adds at most one item per sequence beyond that.
+// items, and the planner's chunk length L is at least (sum of T) x hkv / (kItemsPerSlot x slots); the
+// remainder round adds fewer than slots / hkv.  A shared-prefix group adds at most one item per
+// sequence beyond that.
 int32_t item_bound(const WorkspaceLayout& w, int hkv, int slots, bool groups) {
   int64_t b = w.max_tiles;
-  if (may_cut(w, hkv, slots)) b += (int64_t)kRoundsWanted * slots / hkv + 1;
+  if (may_cut(w, hkv, slots)) b += (int64_t)kItemsPerSlot * slots / hkv + 1;
   if (groups) b += w.batch;
   return (int32_t)(b < w.max_items ? b : w.max_items);
 }
@@ -1789,11 +2035,13 @@ mc_status plan_impl(const mc_pool_desc* pool, int32_t num_q_heads, int32_t batch
   a.cu_tiles = reinterpret_cast<int32_t*>(ws + w.cu_tiles);
   a.items = reinterpret_cast<ItemRec*>(ws + w.items);
   a.merges = reinterpret_cast<MergeRec*>(ws + w.merges);
+  a.arrivals_end = reinterpret_cast<uint32_t*>(ws + w.part_lse) + (size_t)w.part_cap * num_q_heads;
   a.batch = batch;
   a.total_q = total_q;
   a.tile_tokens = tile_tokens;
   a.num_pages = pool->num_pages;
   a.max_tiles = w.max_tiles;
+  a.hq = num_q_heads;
   a.hkv = pool->num_kv_heads;
   a.slots = device_slots(1);
   if (a.slots <= 0) return MC_ERR_HIP;
@@ -1857,8 +2105,10 @@ mc_status attn_impl(const mc_pool_desc* pool, int32_t layer, const void* q, int3
   a.cu_pages = cu_pages;
   a.hdr = reinterpret_cast<const PlanHeader*>(ws);
   a.items = reinterpret_cast<const ItemRec*>(ws + w.items);
+  a.merges = reinterpret_cast<const MergeRec*>(ws + w.merges);
   a.part_lse = reinterpret_cast<float*>(ws + w.part_lse);
   a.part_o = reinterpret_cast<float*>(ws + w.part_o);
+  a.part_cap = w.part_cap;
   a.page_stride = mc::page_stride_bytes(pool);
   a.num_pages = pool->num_pages;
   a.hkv = pool->num_kv_heads;
@@ -1880,25 +2130,7 @@ mc_status attn_impl(const mc_pool_desc* pool, int32_t layer, const void* q, int3
     st = pool->dtype == MC_F16 ? launch_attn<_Float16>(G, false, 2, grid, hs, a)
                                : launch_attn<__bf16>(G, false, 2, grid, hs, a);
   }
-  if (st != MC_OK || !(may_cut(w, pool->num_kv_heads, slots) || groups)) return st;
-  // the planner may have cut KV ranges: weigh the chunks together (does nothing if it did not)
-  MergeArgs m;
-  m.hdr = a.hdr;
-  m.merges = reinterpret_cast<const MergeRec*>(ws + w.merges);
-  m.part_lse = a.part_lse;
-  m.part_o = a.part_o;
-  m.out = a.out;
-  m.lse = a.lse;
-  m.hq = num_q_heads;
-  m.max_merges = w.max_tiles;
-  // one workgroup per (token, four q heads) pair if they all run at once, else a grid-stride walk
-  const int64_t pairs = (int64_t)total_q * ((num_q_heads + 3) / 4);
-  const dim3 mgrid((unsigned)(pairs < 4ll * slots ? pairs : 4ll * slots));
-  if (pool->dtype == MC_F16)
-    hipLaunchKernelGGL(merge_kernel<_Float16>, mgrid, dim3(256), 0, hs, m);
-  else
-    hipLaunchKernelGGL(merge_kernel<__bf16>, mgrid, dim3(256), 0, hs, m);
-  return mc::launch_status();
+  return st;
 }
 
 

@@ -1,0 +1,100 @@
+"""Chunks of a cut KV range are combined inside the attention launch: rows that are counted (up to 16
+a q tile and kv head) and trees over two to many chunks, groups of both kinds, at the row counts where
+one becomes the other.  Launch after launch on one plan (the arrival words wrap), every launch the same
+bits whichever chunk comes last, and the oracle's result."""
+import numpy as np
+import pytest
+
+import mc_inputs as mi
+import oracle
+import paper_2412_12488_amd as mc
+import torch
+from gpu_harness import DEV, DevBatch, DevPool, bits, dev
+from test_gpu_parity import LSE_TOL, O_TOL, fill_both, forked_decode_workload, small_workload
+
+pytestmark = pytest.mark.gpu
+
+
+def launches(w, n=6):
+    """(out bits, lse) of n launches on one plan, the plan's header, and the oracle's pool."""
+    pool = DevPool(w)
+    pool.t.fill_(0x7fc1)
+    opool = np.full(pool.elems, 0x7fc1, dtype=np.uint16)
+    fill_both(w, pool, opool)
+    db, Hq, Hkv = DevBatch(w), w.num_q_heads, w.num_kv_heads
+    size = mc.mc_attn_workspace_size(db.batch, db.total_q, Hq, Hkv)
+    ws = torch.full((size,), 0xff, dtype=torch.uint8, device=DEV)     # NaN wherever nothing is written
+    mc.mc_attn_plan(pool.desc, Hq, db.batch, db.total_q, db.cu_q, db.begin, db.page_table, db.cu_pages, ws, size)
+    mc.mc_attn_plan_check(ws)
+    q = dev(np.concatenate([w.q(s) for s in range(w.batch)]))
+    got = []
+    for _ in range(n):
+        out = torch.full((db.total_q, Hq, 128), 0x7fc1, dtype=torch.int16, device=DEV)
+        lse = torch.full((db.total_q, Hq), float("nan"), dtype=torch.float32, device=DEV)
+        mc.mc_prefix_prefill_attn(pool.desc, 0, q, Hq, db.batch, db.total_q, db.cu_q, db.begin, db.page_table,
+                                  db.cu_pages, 0.0, out, lse, ws, size)
+        got.append((out, lse))
+    torch.cuda.synchronize()
+    return got, ws[:64].view(torch.int32).cpu().numpy(), pool, opool
+
+
+def check(w, n=6):
+    got, h, pool, opool = launches(w, n)
+    out, lse = bits(got[0][0]), got[0][1].cpu().numpy()
+    for o, l in got[1:]:
+        assert np.array_equal(bits(o), out) and np.array_equal(l.cpu().numpy(), lse)
+    for s in range(w.batch):
+        at, q_len = int(w.cu_q[s]), int(w.n[s] - w.b[s])
+        if q_len == 0:
+            continue
+        ro, rl = oracle.attention(opool, pool.shape, 0, w.page_tables[s], w.q(s), w.num_q_heads, int(w.b[s]),
+                                  int(w.n[s]))
+        assert np.max(np.abs(oracle.decode(out[at:at + q_len], w.dtype) - ro)) <= O_TOL, s
+        assert np.max(np.abs(lse[at:at + q_len] - rl)) <= LSE_TOL, s
+    return h
+
+
+@pytest.mark.parametrize("dtype", [mi.BF16, mi.F16])
+@pytest.mark.parametrize("Hq,Hkv,new,keys", [
+    (32, 8, 4, 2100), (32, 8, 5, 2100),       # 16 rows: counted; 20: a tree (G = 4)
+    (64, 8, 2, 1100), (64, 8, 3, 1600),       # 16 rows, 24 (G = 8): two chunks, three
+    (8, 8, 16, 2700), (8, 8, 17, 2700),       # 16 rows, 17 (G = 1): five chunks
+    (8, 8, 128, 3200), (8, 8, 129, 4300),     # a full tile; a tile and one row
+    (32, 8, 33, 1000), (16, 8, 40, 700),      # two tiles; one tile, two chunks (G = 2)
+    (8, 1, 20, 40000),                        # more chunks than one word of arrivals has nodes
+])
+def test_ranges_of_few_and_many_rows(dtype, Hq, Hkv, new, keys):
+    w = small_workload(1200 + new, dtype, Hq, Hkv, [keys], [keys - new])
+    h = check(w)
+    assert h[6] == -(-new // (128 * Hkv // Hq)) and h[7] > 0, h[:9]     # every tile is cut
+
+
+@pytest.mark.parametrize("Hq,Hkv", [(32, 8), (8, 8), (64, 8)])
+def test_many_rounds_of_chunks(Hq, Hkv):
+    # more items than run at once, decode rows beside ranges of several tiles
+    w = small_workload(1230, mi.BF16, Hq, Hkv, [5000, 3000, 4100, 1800, 2600, 900], [4900, 2999, 4000, 1790, 2580, 899])
+    assert check(w)[6] >= 5
+
+
+@pytest.mark.parametrize("dtype", [mi.BF16, mi.F16])
+@pytest.mark.parametrize("Hq,Hkv,members", [
+    (32, 8, 4), (32, 8, 5), (8, 8, 16), (8, 8, 17), (64, 8, 2), (64, 8, 3),    # 16 rows of a prefix, more
+    (32, 8, 40), (8, 1, 12),
+])
+def test_prefixes_of_few_and_many_rows(dtype, Hq, Hkv, members):
+    # own parts from one token to several chunks: the prefix or the member's own chunks come last
+    own = [1, 700, 40, 1500, 64, 3000, 300]
+    w = forked_decode_workload(1240 + members, Hq, Hkv, dtype,
+                               [[(1600 + own[i % 7], 1600 if i else 0) for i in range(members)]])
+    assert check(w)[8] > 0
+
+
+@pytest.mark.parametrize("dtype", [mi.BF16, mi.F16])
+def test_members_with_trees_of_their_own(dtype):
+    # forks that bring 5..8 new tokens (20..32 rows of a kv head) over own middle parts of up to five
+    # chunks: the members' own chunks are a tree, the prefix's are one
+    begins, new = [2048, 2300, 4700, 2048, 3300], [5, 6, 8, 4, 7]
+    w = small_workload(1260, dtype, 32, 8, [b + n for b, n in zip(begins, new)], begins)
+    for s in range(1, 5):
+        w.share_prefix(s, 0, 2048)
+    assert check(w)[8] > 0
