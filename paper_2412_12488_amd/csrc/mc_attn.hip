@@ -16,7 +16,9 @@
 //   * attn_kernel: one workgroup (4 wavefronts of 64) per (item, kv head), so every
 //     K/V byte staged in LDS serves the whole GQA group.  Items that cover a whole
 //     range write out/lse; the others write partial rows, which the last of a q
-//     tile's items to finish weighs together by their log-sum-exp.
+//     tile's items to finish weighs together by their log-sum-exp (the members of
+//     shared prefixes in larger batches: group_merge_kernel).  Items of at most 16
+//     rows (decode steps) go another way through the kernel, few_rows_item.
 // Kernel shape
 //   * the KV loop walks 64-key tiles (4 pages) through the page table; each page
 //     contributes one contiguous 4 KiB run of K and one of V for this kv head.
@@ -49,7 +51,9 @@ using mc::kRowBytes;
 typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef short s16x4 __attribute__((ext_vector_type(4)));
+typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef float f32x16 __attribute__((ext_vector_type(16)));
+typedef int32_t i32x8 __attribute__((ext_vector_type(8)));
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 
@@ -81,11 +85,10 @@ static_assert(sizeof(PlanHeader) == 64, "header is 64 bytes");
 // chunk < 0: the item covers the tile's whole KV range and writes out/lse itself.  Otherwise it is
 // that chunk of the tile `merge` describes: its result (O normalised within the chunk, fp32, and the
 // chunk's LSE) is combined with the other chunks' by whichever item comes last (see MergeRec).
-// kItemGroup: a shared-prefix item.  Its rows are the ntok new tokens of consecutive sequences
-// starting at seq (neighbours in the q array: tokens cu_q[seq] .. cu_q[seq] + ntok - 1), whose
-// page tables begin with the same pages; it covers tiles of that common prefix (all of it
-// visible to every row) and is always a chunk.  Its members' merge records follow one another from
-// `merge` on.
+// kItemGroup: a shared-prefix item.  Its rows are the ntok new tokens (neighbours in the q array) of
+// consecutive sequences whose page tables begin with the same pages as sequence seq's; it covers tiles
+// of that common prefix (all of it visible to every row) and is always a chunk.  Its members' merge
+// records follow one another from `merge` on.
 // The record also carries what the kernel needs to start its first copies without further
 // look-ups (each would be one more dependent memory round trip before the first tile): the
 // tile's first token in the q array and its token count, where the sequence's page table starts,
@@ -114,8 +117,15 @@ constexpr uint32_t kItemGroup = 1u << 28;
 //     writes its rows and ends, the second reads them, combines, and goes on one level up; half of the
 //     rows are never written.  The last one up has the tile's result in registers.  These rows are
 //     kept as the registers lie, 16 bytes of every row together (by_reg below).
-//   * With a group, the prefix (as one chunk, if a tree has combined it) and the tile's own chunks
-//     (likewise) are then counted, and the last of them combines.
+//   * With a group, the prefix's chunks are counted one by one beside the tile's own (a tree's counting
+//     as one), and the last of them combines.  Their rows lie row by row.  That is for batches of up
+//     to kGroupsInLaunch sequences, whose decode rows share a prefix in items of kFlatRows rows at
+//     most; of larger ones group_merge_kernel combines the members' chunks, in a launch of its own.
+//     A workgroup reads partial rows at 30 GB/s or so, and the last item of a prefix may find every
+//     member waiting: for 24 forks of a 2304-token prompt (32 / 8 heads) it would be alone for 20 us
+//     where the launch takes 5.  (Nor do a tree over the prefix's chunks, 2.4 to 3.7 us a level, or
+//     items of 16 rows, which read the prefix again, make up for it: 64 forks 50, 45 us a layer instead
+//     of 42; 12 forks of 1920 tokens with 53..445 of their own 29, 20 instead of 20.)
 // Which chunk comes last differs from run to run; the sums and their order do not.
 struct MergeRec {
   int32_t q_row;   // index of the tile's first token among all new tokens of the batch
@@ -124,10 +134,10 @@ struct MergeRec {
 };
 static_assert(sizeof(MergeRec) == 32, "merge record is 32 bytes");
 constexpr int kFlatRows = 16;
+constexpr int kGroupsInLaunch = 8;
 // Arrivals: per merge record and kv head arrive_words words that the plan clears.  Word 0 counts
-// (and wraps to 0 with the last arrival); of the others, one bit a node, half are the tile's tree and
-// half, at a group's first member, the prefix's (set by the first of two, cleared by the second).
-// They fill the end of the partial LSE array from its last word downwards, for which the planner
+// (and wraps to 0 with the last arrival), the others are the tree, one bit a node (set by the first of
+// two, cleared by the second).  They fill the end of the partial LSE array from its last word downwards, for which the planner
 // leaves rows of that array (hq >= hkv words each) unused.
 
 constexpr int kCuTilesInLds = 1024;
@@ -289,7 +299,7 @@ __device__ void block_exclusive_scan_n(int (&v)[N], int* lds, int (&total)[N]) {
 // Block-wide sum of one value per thread, to every thread: butterfly inside each wavefront, the
 // 16 wavefront sums through LDS (lds holds 2 x 16 ints).
 template <int NT>
-__device__ long long block_sum(long long v, int* lds) {
+__device__ __forceinline__ long long block_sum(long long v, int* lds) {
   const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
 #pragma unroll
   for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off);
@@ -655,10 +665,15 @@ __global__ __launch_bounds__(NT) void plan_kernel(PlanArgs a) {
   // own chunks of L tiles (L even) from the end of the group's prefix: [pt, pt+L), ...,
   // [pt+kL, T) with pt + kL <= dmax; the group's prefix itself in chunks of L
   auto own_splits = [&](const Tile& x, int L) { return L > 0 ? (x.dmax - x.pt) / L + 1 : 1; };
+  // Items of a group's prefix: in small batches decode rows share one in items of a few rows (see
+  // MergeRec), tokens `slice` of one.
+  const bool sliced = a.batch <= kGroupsInLaunch && a.total_q <= total_tiles;
+  const int slice = max(kFlatRows * a.tile_tokens / kBM, 1);
+  auto slices = [&](const Tile& x) { return (x.gm + slice - 1) / slice; };
   auto grp_splits = [&](const Tile& x, int L) { return x.pt > 0 ? (L > 0 ? (x.pt + L - 1) / L : 1) : 0; };
   // arrival words per merge record and kv head: a tree over n chunks has up to n + log2(n) nodes; the
   // rows of the partial arrays they take
-  auto arrive_words = [&](int L) { return 1 + 2 * ((L > 0 ? s_maxcost / L + 16 : 16) / 32 + 1); };
+  auto arrive_words = [&](int L) { return 2 + (L > 0 ? s_maxcost / L + 16 : 16) / 32; };
   auto arrive_rows = [&](int L) { return (arrive_words(L) * a.hkv + a.hq - 1) / a.hq; };
   auto part_rows = [&](const Tile& x, int L, int arrive) {
     const int ns = own_splits(x, L);
@@ -708,6 +723,8 @@ __global__ __launch_bounds__(NT) void plan_kernel(PlanArgs a) {
   int shift = 0;
   while ((s_maxcost >> shift) >= kBuckets) ++shift;
   auto bucket = [&](int len) { return kBuckets - 1 - (len >> shift); };
+  // (a prefix's item of a whole q tile takes longer a tile than decode rows' items: those go first)
+  auto group_bucket = [&](int len) { return bucket(sliced ? len : s_maxcost); };
 
   // 4b. remainder round.  Between one and kRoundsWanted rounds of uncut, similar items the last
   //     round is the problem: n items on S slots take ceil(n / S) rounds although the last one
@@ -763,15 +780,13 @@ __global__ __launch_bounds__(NT) void plan_kernel(PlanArgs a) {
     const Tile x = locate(i);
     const int Li = chunk_len(i, x);
     const int ns = own_splits(x, Li), ng = x.gm ? grp_splits(x, Li) : 0;
-    n_items += ns + ng;
+    n_items += ns + (sliced ? ng * slices(x) : ng);
     if (ns > 1 || x.pt > 0) { n_own += ns * x.ntok; ++n_merge; }
     n_grp += ng * x.gm;
     for (int c = 0; c < ns; ++c)
       atomicAdd(&hist[bucket(c + 1 < ns ? Li : x.T - x.pt - c * Li)], 1);
-    // (a group's items first: their rows fill a q tile, so a tile takes them longest, and what their
-    // members' own items find finished they need not wait for - the last of the group's items would
-    // have to combine the rows of every member)
-    if (ng > 0) atomicAdd(&hist[bucket(s_maxcost)], ng);
+    for (int c = 0; c < ng; ++c)
+      atomicAdd(&hist[group_bucket(Li > 0 ? min(Li, x.pt - c * Li) : x.pt)], sliced ? slices(x) : 1);
   }
   int offs[4] = {n_items, n_own, n_grp, n_merge}, tots[4];
   block_exclusive_scan_n<NT>(offs, scan, tots);
@@ -825,30 +840,35 @@ __global__ __launch_bounds__(NT) void plan_kernel(PlanArgs a) {
     const int sb = cu_in_lds ? s_beg[x.s] : a.begin[x.s];
     const int tab = cu_in_lds ? s_cup[x.s] : a.cu_pages[x.s];
     const int cap = (int)(((int64_t)sb + sq_len + a.ahead + kPage - 1) / kPage) - 1;   // validated above
-    auto finish = [&](ItemRec& it, int t0, int t1, int q_first, int ntok, uint32_t flags) {
+    auto finish = [&](ItemRec& it, int t0, int t1, int q_first, int ntok, int merge, uint32_t flags) {
       it.seq = x.s;
       it.q_first = q_first;
       it.t0_ntok = (uint32_t)(t0 >> 1) | (uint32_t)(ntok - 1) << 24;
       // every tile of the item holds a validated entry, so the last one lies in tile t1 - 1 or beyond
       it.t1_flags = (uint32_t)t1 | (uint32_t)min(cap - 4 * (t1 - 1), 3) << 26 | flags;
       it.table_off = tab;
-      it.merge = merged ? merge_off - 1 : -1;
+      it.merge = merge;
 #pragma unroll
       for (int k = 0; k < 8; ++k) it.ids[k] = a.page_table[tab + min(4 * t0 + k, cap)];
-      a.items[atomicAdd(&hist[bucket(flags & kItemGroup ? s_maxcost : t1 - t0)], 1)] = it;
+      a.items[atomicAdd(&hist[flags & kItemGroup ? group_bucket(t1 - t0) : bucket(t1 - t0)], 1)] = it;
     };
     for (int c = 0; c < ns; ++c) {
       ItemRec it;
       it.row0 = x.row0;
       it.chunk = merged ? c : -1;
-      finish(it, x.pt + c * Li, c + 1 < ns ? x.pt + (c + 1) * Li : x.T, sq0 + x.row0, x.ntok, 0);
+      finish(it, x.pt + c * Li, c + 1 < ns ? x.pt + (c + 1) * Li : x.T, sq0 + x.row0, x.ntok,
+             merged ? merge_off - 1 : -1, 0);
     }
-    for (int c = 0; x.gm && c < ng; ++c) {
-      ItemRec it;
-      it.row0 = 0;
-      it.chunk = c;
-      finish(it, c * Li, Li > 0 ? min((c + 1) * Li, x.pt) : x.pt, sq0, x.gm, kItemGroup);
-    }
+    // (sliced: a member is one token, and one merge record)
+    const int per_item = sliced ? slice : x.gm;
+    for (int c = 0; x.gm && c < ng; ++c)
+      for (int i = 0; i < x.gm; i += per_item) {
+        ItemRec it;
+        it.row0 = 0;
+        it.chunk = c;
+        finish(it, c * Li, Li > 0 ? min((c + 1) * Li, x.pt) : x.pt, sq0 + i, min(per_item, x.gm - i),
+               merge_off - 1 + i, kItemGroup);
+      }
     if (merged) own_off += ns * x.ntok;
   }
   if (t == 0) {
@@ -873,7 +893,10 @@ template <> struct Mfma<_Float16> {
   static __device__ __forceinline__ f32x16 run(vec8 a, vec8 b, f32x16 c) {
     return __builtin_amdgcn_mfma_f32_32x32x16_f16(a, b, c, 0, 0, 0);
   }
-  // the same instruction with its result pinned to vector registers (see attn_kernel: with
+  static __device__ __forceinline__ f32x4 run16(vec8 a, vec8 b, f32x4 c) {
+    return __builtin_amdgcn_mfma_f32_16x16x32_f16(a, b, c, 0, 0, 0);
+  }
+  // the 32x32x16 one with its result pinned to vector registers (see attn_kernel: with
   // two row blocks the allocator would otherwise park the scores in accumulation registers,
   // which the softmax's vector instructions cannot read)
   static __device__ __forceinline__ void run_v0(vec8 a, vec8 b, f32x16& c) {
@@ -894,6 +917,9 @@ template <> struct Mfma<__bf16> {
   typedef bf16x8 vec8;
   static __device__ __forceinline__ f32x16 run(vec8 a, vec8 b, f32x16 c) {
     return __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, c, 0, 0, 0);
+  }
+  static __device__ __forceinline__ f32x4 run16(vec8 a, vec8 b, f32x4 c) {
+    return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, 0, 0, 0);
   }
   static __device__ __forceinline__ void run_v0(vec8 a, vec8 b, f32x16& c) {
     asm("v_mfma_f32_32x32x16_bf16 %0, %1, %2, 0" : "=v"(c) : "v"(a), "v"(b));
@@ -981,7 +1007,6 @@ __device__ __forceinline__ void copy16_to_lds(const char* base, uint32_t lane_of
 // They are written by one workgroup and read by another of the same launch, on any XCD: through
 // buffer instructions of device scope (sc1), which write to and read from the level all XCDs
 // share, so that no L2 has to be written back or invalidated as a whole.
-typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef __amdgpu_buffer_rsrc_t buffer_rsrc;
 constexpr int kDeviceScope = 16;          // sc1
 __device__ __forceinline__ buffer_rsrc make_rsrc(void* p, uint32_t bytes) {
@@ -1002,21 +1027,15 @@ __device__ __forceinline__ float load_device(buffer_rsrc r, uint32_t off) {
 
 // Chunks a merge record's last step combines: the prefix's and the tile's own, a tree's counting as one.
 template <int G>
-__device__ __forceinline__ int flat_chunks(int nsplit, int ntok) { return ntok * G <= kFlatRows ? nsplit : 1; }
-template <int G, typename Rec>
-__device__ __forceinline__ int flat_chunks_of(const Rec& m) {
-  return flat_chunks<G>(m[2], m[1]) + (m[4] > 0 ? flat_chunks<G>(m[4], m[6]) : 0);
-}
+__device__ __forceinline__ int own_chunks(int nsplit, int ntok) { return ntok * G <= kFlatRows ? nsplit : 1; }
 
-// The members of a shared-prefix group, for the item that counts itself at all of them: their merge
-// records, whether this item was the last to arrive there, and the member a token belongs to.  In LDS
-// (the tiles are consumed), behind the part in which a workgroup stages its output rows.
-struct MemberList {
+// What a workgroup was the last to arrive at, in LDS (the tiles are consumed): the merge records, the
+// first token of each among all whose rows are to be combined, and the record a token belongs to.
+struct MergeList {
   int32_t rec[kBM][8];             // MergeRec
-  int32_t last[kBM], of[kBM];
+  int32_t first[kBM], rec_of[2 * kBM];
 };
-constexpr int kStageBytes = kBM * kRowBytes;
-static_assert(kStageBytes + sizeof(MemberList) <= 4 * kTileBytes, "the list takes the tiles' LDS");
+static_assert(sizeof(MergeList) <= 4 * kTileBytes, "the list takes the tiles' LDS");
 
 // One more chunk of a row (LSE lse) beside those summed so far (their maximum mx, their weights' sum
 // den): the factors of both.  Every place that sums chunks does it by this step, chunk after chunk in
@@ -1030,8 +1049,7 @@ __device__ __forceinline__ void chunk_step(float lse, float& mx, float& den, flo
   den = __builtin_fmaf(den, f_old, f_new);
 }
 
-// One kv head's rows of `tokens` tokens of tiles of few rows from their chunks: with L_c the chunk
-// LSEs, LSE = log sum_c exp(L_c) and O = sum_c exp(L_c - LSE) O_c, chunks in order: those of the
+// One kv head's rows of `tokens` tokens from their chunks: with L_c the chunk LSEs, LSE = log sum_c exp(L_c) and O = sum_c exp(L_c - LSE) O_c, chunks in order: those of the
 // group's prefix, then the tile's own.  record(i, first) gives the merge record of token i and the
 // first token of that record.
 // A chain of memory round trips and little else, run once by code that is not in the instruction
@@ -1046,7 +1064,7 @@ __device__ __forceinline__ void merge_rows(const AttnArgs& a, buffer_rsrc rs_o, 
     // per row: chunks, the prefix's among them, partial row and byte of this lane's piece in the first
     // chunk, the same from one chunk to the next
     int nch[kRows], g_nsplit[kRows], out_row[kRows];
-    uint32_t g_row[kRows], g_byte[kRows], g_step[kRows], own_row[kRows], own_step[kRows];
+    uint32_t g_row[kRows], g_byte[kRows], g_step[kRows], own_row[kRows], own_byte[kRows], own_step[kRows];
     float mx[kRows], den[kRows];
     f32x4 acc[kRows];
     int nmax = 0;
@@ -1055,15 +1073,22 @@ __device__ __forceinline__ void merge_rows(const AttnArgs& a, buffer_rsrc rs_o, 
       const int r = min(r0 + u * (kThreads / 32), rows - 1), i = r / G;
       int first;
       const auto m = record(i, first);
-      const int tt = i - first, g_rows = m[6] * G;
-      g_nsplit[u] = m[4] > 0 ? flat_chunks<G>(m[4], m[6]) : 0;
-      nch[u] = m[2] + g_nsplit[u];
-      const uint32_t g0 = m[5] * a.hq + hk * g_rows, gr = (m[7] + tt) * G + r % G;
-      g_row[u] = g0 + gr;
-      g_byte[u] = g_rows <= kFlatRows ? g_row[u] * 512u + piece * 16u
-                                      : g0 * 512u + (piece >> 1) * g_rows * 32u + gr * 32u + (piece & 1) * 16u;
+      const int tt = i - first;
+      // row r of the chunk whose rows, of_rows of them, start at row0
+      auto place = [&](uint32_t row0, int r, int of_rows) __attribute__((always_inline)) {
+        return row0 * 512u + (of_rows <= kFlatRows
+                                  ? r * 512u + piece * 16u
+                                  : (piece >> 1) * of_rows * 32u + r * 32u + (piece & 1) * 16u);
+      };
+      g_nsplit[u] = m[4];
+      nch[u] = own_chunks<G>(m[2], m[1]) + m[4];
+      const uint32_t g0 = m[5] * a.hq + hk * m[6] * G, own0 = m[3] * a.hq + hk * m[1] * G;
+      const int g_r = (m[7] + tt) * G + r % G, own_r = tt * G + r % G;
+      g_row[u] = g0 + g_r;
+      g_byte[u] = (g0 + g_r) * 512u + piece * 16u;
       g_step[u] = m[6] * a.hq;
-      own_row[u] = m[3] * a.hq + (hk * m[1] + tt) * G + r % G;
+      own_row[u] = own0 + own_r;
+      own_byte[u] = place(own0, own_r, m[1] * G);
       own_step[u] = m[1] * a.hq;
       out_row[u] = (m[0] + tt) * a.hq + hk * G + r % G;
       mx[u] = -INFINITY;
@@ -1082,7 +1107,7 @@ __device__ __forceinline__ void merge_rows(const AttnArgs& a, buffer_rsrc rs_o, 
           const bool in_group = c < g_nsplit[u];
           const uint32_t on = (in_group ? c : c - g_nsplit[u]) * (in_group ? g_step[u] : own_step[u]);
           lse[u][k] = load_device(rs_lse, ((in_group ? g_row[u] : own_row[u]) + on) * 4u);
-          o[u][k] = load_device4(rs_o, (in_group ? g_byte[u] : own_row[u] * 512u + piece * 16u) + on * 512u);
+          o[u][k] = load_device4(rs_o, (in_group ? g_byte[u] : own_byte[u]) + on * 512u);
         }
 #pragma unroll
       for (int u = 0; u < kRows; ++u)
@@ -1129,6 +1154,255 @@ __device__ __forceinline__ float max3(float a, float b, float c) {
   return r;
 }
 
+// ---- items of few rows (decode steps) ----------------------------------------------------
+// What an item needs of its record.
+struct Item {
+  int t0, t1, chunk, q_first, ntok, table_off, pidx_cap, merge, n_rec;   // n_rec: merge records there are
+  bool group;
+};
+
+// The first of the partial rows of a chunk and kv head that an item writes (m: its merge record, of a
+// group its first member's).
+template <int G>
+__device__ __forceinline__ uint32_t first_part_row(const AttnArgs& a, const Item& it, int hk, const i32x8& m) {
+  return it.group ? (m[5] + it.chunk * m[6]) * a.hq + (hk * m[6] + m[7]) * G
+                  : (m[3] + it.chunk * m[1]) * a.hq + hk * m[1] * G;
+}
+
+// Counts written rows - a chunk of few rows, a chunk of a prefix (at every member's record), or a tree's
+// result - and, if they were the last there, combines the record's chunks.  s_last: 0, and published;
+// list: free LDS.
+template <typename T, int G>
+__device__ __forceinline__ void arrive(const AttnArgs& a, const Item& it, int hk, buffer_rsrc rs_o,
+                                       buffer_rsrc rs_lse, const i32x8& m, int words, int& s_last,
+                                       MergeList& list) {
+  const int tid = threadIdx.x;
+  if ((it.group || m[4] > 0) && a.batch > kGroupsInLaunch) return;      // group_merge_kernel's
+  const bool listed = it.group || it.ntok * G > kFlatRows;
+  uint32_t* arrivals = reinterpret_cast<uint32_t*>(a.part_lse) + (int64_t)a.part_cap * a.hq - 1;
+  i32x8 mr = m;
+  if (it.group) mr = *reinterpret_cast<const i32x8*>(a.merges + min(it.merge + tid, it.n_rec - 1));
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // this wavefront's rows have been written
+  __syncthreads();
+  // records of this item: one, or the group's members' (their tokens follow one another)
+  if (tid < (it.group ? it.ntok : 1) && it.merge + tid < it.n_rec && mr[0] < it.q_first + it.ntok) {
+    const int n = own_chunks<G>(mr[2], mr[1]) + mr[4];
+    if (atomicInc(arrivals - ((int64_t)(it.merge + tid) * a.hkv + hk) * words, n - 1) == (unsigned)n - 1) {
+      const int at = atomicAdd(&s_last, mr[1]);
+      if (listed) {
+        *reinterpret_cast<i32x8*>(list.rec[tid]) = mr;
+        list.first[tid] = at;
+        if (it.group)
+          for (int i = 0; i < mr[1]; ++i) list.rec_of[at + i] = tid;
+      }
+    }
+  }
+  if (listed && !it.group && tid < it.ntok) list.rec_of[tid] = 0;
+  __syncthreads();
+  const int tokens = __builtin_amdgcn_readfirstlane(s_last);
+  if (tokens == 0) return;
+  if (listed)
+    merge_rows<T, G, 2, 12>(a, rs_o, rs_lse, hk, tokens, [&](int i, int& first) __attribute__((always_inline)) {
+      const int k = list.rec_of[i];
+      first = list.first[k];
+      return *reinterpret_cast<const i32x8*>(list.rec[k]);
+    });
+  else
+    merge_rows<T, G, 1, kMergeAhead>(a, rs_o, rs_lse, hk, tokens,
+                                     [&](int, int& first) __attribute__((always_inline)) { first = 0; return m; });
+}
+
+// max or sum over the four lanes l, l ^ 16, l ^ 32, l ^ 48: a swap of the wavefront's halves, then one
+// of its odd with its even rows of 16 lanes, each given the value in both operands (see
+// max_across_halves below for the assembly)
+template <typename Op>
+__device__ __forceinline__ float across_rows(float x, Op&& op) {
+  uint32_t lo = __builtin_bit_cast(uint32_t, x), hi = lo;
+  asm volatile("s_nop 1\n\tv_permlane32_swap_b32 %0, %1" : "+v"(lo), "+v"(hi));
+  lo = hi = __builtin_bit_cast(uint32_t, op(__builtin_bit_cast(float, lo), __builtin_bit_cast(float, hi)));
+  asm volatile("s_nop 1\n\tv_permlane16_swap_b32 %0, %1" : "+v"(lo), "+v"(hi));
+  return op(__builtin_bit_cast(float, lo), __builtin_bit_cast(float, hi));
+}
+
+// An item of at most kFlatRows rows.  All four wavefronts hold those rows and take half tiles (32
+// keys, 2 pages) in turn, each by itself: K straight into registers, V through its own 16 KiB of LDS,
+// no barrier until their sums are put together at the end.  v_mfma_f32_16x16x32: S^T = K Q^T (A = 16
+// keys, lane l: key l % 16, d 8 (l / 16) ..), a lane then has one row (l % 16) and 8 of the 32 keys;
+// O^T += V^T P^T with P^T straight from S^T: operand slot 8 g + j is key 4 g + j of the first 16 keys
+// (j < 4) or of the second, for both operands (g = l / 16).
+// Decode steps are bound by memory: on few rows by the latency of the requests that follow one
+// another, else by the reads themselves.  Walked by one wavefront of four, as items of more rows are
+// (the other three without a row), a piece of two tiles took 5.0 us from the first instruction to the
+// vote at its end, three requests behind the record; here one, the first half tile of every wavefront.
+// What a wavefront has in flight, 16 KiB, is waited for as a whole: the next half tile is requested
+// as soon as S has been formed, and eight wavefronts a compute unit keep 128 KiB under way.
+// A layer (append and attention) of one row over 1000 keys, 32 / 8 heads, 12.9 -> 10.5 us; of eight rows
+// over 1024..4096, 64 / 8 heads, 27.7 -> 25.5; 256 rows, bound by the reads, the same.
+template <typename T, int G>
+__device__ __forceinline__ void few_rows_item(const AttnArgs& a, const Item& it, int hk, int b, int row0,
+                                              const i32x8& ids, char* lds, float* stat, int& s_last) {
+  typedef typename Mfma<T>::vec8 vec8;
+  constexpr int kHalf = kBN / 2, kHalfBytes = kHalf * kRowBytes;
+  const int tid = threadIdx.x, lane = tid & 63, l16 = lane & 15, g4 = lane >> 4;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int rows = it.ntok * G;
+  const uint32_t lds_own = lds_addr(lds) + wave * (2 * kHalfBytes);
+  const char* pool_k = a.pool_layer + (int64_t)hk * kHeadPageBytes;
+  const uint32_t page_blocks = 2u * a.hkv;                     // 4 KiB blocks per page
+  auto page_base = [&](int32_t pg) __attribute__((always_inline)) {
+    pg = min(max(pg, 0), a.num_pages - 1);         // checked by the plan; stay in bounds anyway
+    return pool_k + ((uint64_t)((uint32_t)pg * page_blocks) << 12);
+  };
+  // K: key l16 of each page, chunks 4 kk + g4; V: 4 rows an instruction, swizzled as tiles are
+  const uint32_t k_off = l16 * kRowBytes + g4 * 16;
+  const uint32_t v_off = g4 * kRowBytes + ((l16 ^ (g4 << 2)) << 4) + (uint32_t)a.hkv * kHeadPageBytes;
+  vec8 kf[2][4], q[4];
+  auto request = [&](int32_t id0, int32_t id1, int buf) __attribute__((always_inline)) {
+    const char* page[2] = {page_base(id0), page_base(id1)};
+#pragma unroll
+    for (int i = 0; i < 8; ++i)
+      copy16_to_lds(page[i >> 2] + (i & 3) * 1024, v_off, lds_own + buf * kHalfBytes + i * 1024);
+#pragma unroll
+    for (int p = 0; p < 2; ++p)
+#pragma unroll
+      for (int kk = 0; kk < 4; ++kk)
+        kf[p][kk] = __builtin_bit_cast(vec8, *reinterpret_cast<const u32x4*>(page[p] + k_off + kk * 64));
+  };
+  // page ids of the wavefront's half tile h (the first: in the record); clamped to validated entries
+  const const_i32_ptr table = (const_i32_ptr)(a.page_table + it.table_off);
+  auto id_of = [&](int h, int p) __attribute__((always_inline)) { return table[min(2 * h + p, it.pidx_cap)]; };
+  int h = 2 * it.t0 + wave;
+  int32_t next0 = id_of(h + 4, 0), next1 = id_of(h + 4, 1);
+  if (h < 2 * it.t1) {
+    const int32_t id0 = wave == 0 ? ids[0] : wave == 1 ? ids[2] : wave == 2 ? ids[4] : ids[6];
+    const int32_t id1 = wave == 0 ? ids[1] : wave == 1 ? ids[3] : wave == 2 ? ids[5] : ids[7];
+    request(id0, id1, 0);
+  }
+  // the row of this lane (one that does not exist reads the last one's q)
+  const int my_row = min(l16, rows - 1), tt = my_row / G;
+  const char* q_row = a.q + ((int64_t)(it.q_first + tt) * a.hq + hk * G + my_row % G) * kRowBytes;
+#pragma unroll
+  for (int kk = 0; kk < 4; ++kk)
+    q[kk] = __builtin_bit_cast(vec8, *reinterpret_cast<const u32x4*>(q_row + kk * 64 + g4 * 16));
+
+  // positions: as in attn_kernel
+  const int first_pos = it.group ? it.t1 * kBN : b + row0;
+  const int kv_len = min(first_pos + it.ntok, it.t1 * kBN);
+  const bool fits = b >= 0 && kv_len > kBN * it.t0;
+  const int n_halves = fits ? (kv_len + kHalf - 1) / kHalf : 0;
+  const int n_full = (first_pos + 1) / kHalf;
+  const int my_pos = first_pos + tt;
+  const float c2 = a.scale_log2;
+
+  f32x4 o[8];
+#pragma unroll
+  for (int i = 0; i < 8; ++i) o[i] = f32x4{0.f, 0.f, 0.f, 0.f};
+  float m_run = -INFINITY, l_run = 0.f;     // the row's running maximum (raw); this lane's part of its sum
+  int buf = 0;
+  for (; h < n_halves; h += 4, buf ^= 1) {
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    f32x4 s[2] = {{0.f, 0.f, 0.f, 0.f}, {0.f, 0.f, 0.f, 0.f}};
+#pragma unroll
+    for (int kk = 0; kk < 4; ++kk)
+#pragma unroll
+      for (int p = 0; p < 2; ++p) s[p] = Mfma<T>::run16(kf[p][kk], q[kk], s[p]);
+    if (h + 4 < n_halves) {
+      request(next0, next1, buf ^ 1);
+      next0 = id_of(h + 8, 0);
+      next1 = id_of(h + 8, 1);
+    }
+    if (h >= n_full) {
+#pragma unroll
+      for (int i = 0; i < 8; ++i)
+        if (h * kHalf + 16 * (i >> 2) + 4 * g4 + (i & 3) > my_pos) s[i >> 2][i & 3] = -INFINITY;
+    }
+    const uint32_t v_buf = lds_own + buf * kHalfBytes;
+    if (kv_len < (h + 1) * kHalf) {      // V rows of keys past the range: 0 x NaN would poison O
+      const int valid = kv_len - h * kHalf;
+      const u32x4 zero = {0, 0, 0, 0};
+#pragma unroll
+      for (int i = 0; i < 8; ++i)
+        if (4 * i + g4 >= valid)
+          *reinterpret_cast<u32x4 __attribute__((address_space(3)))*>((size_t)(v_buf + i * 1024 + lane * 16)) = zero;
+    }
+    float mx = fmaxf(fmaxf(fmaxf(s[0][0], s[0][1]), fmaxf(s[0][2], s[0][3])),
+                     fmaxf(fmaxf(s[1][0], s[1][1]), fmaxf(s[1][2], s[1][3])));
+    mx = fmaxf(m_run, across_rows(mx, [](float x, float y) { return fmaxf(x, y); }));
+    const float ref = mx > -INFINITY ? mx : 0.f, mc2 = ref * c2;      // (no key seen yet: no maximum)
+    const float alpha = __builtin_amdgcn_exp2f((m_run - ref) * c2);
+    m_run = mx;
+    float p[8];
+#pragma unroll
+    for (int i = 0; i < 8; ++i) p[i] = __builtin_amdgcn_exp2f(__builtin_fmaf(s[i >> 2][i & 3], c2, -mc2));
+    l_run = __builtin_fmaf(l_run, alpha, ((p[0] + p[1]) + (p[2] + p[3])) + ((p[4] + p[5]) + (p[6] + p[7])));
+    const u32x4 pw = {Mfma<T>::pack2(p[0], p[1]), Mfma<T>::pack2(p[2], p[3]), Mfma<T>::pack2(p[4], p[5]),
+                      Mfma<T>::pack2(p[6], p[7])};
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+      const int key = 4 * g4 + (l16 >> 2), at = 2 * i + ((l16 & 3) >> 1), sub = (l16 & 1) * 8;
+      const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4_ptr)(size_t)(v_buf + v_swz(key, at) + sub));
+      const s16x4 hi =
+          __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4_ptr)(size_t)(v_buf + v_swz(key + 16, at) + sub));
+      const vec8 vf = __builtin_bit_cast(vec8, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
+      o[i] *= alpha;
+      o[i] = Mfma<T>::run16(vf, __builtin_bit_cast(vec8, pw), o[i]);
+    }
+  }
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // (a half tile past the range may be under way)
+  if (!fits && it.chunk < 0) return;
+
+  // ---- the four wavefronts' sums: O by rows of 32 pieces of 16 bytes (piece 4 i + g4: d = 16 i + 4 g4
+  //      + {0..3}; the swizzle spreads the rows over the banks), each in its own LDS
+  l_run = across_rows(l_run, [](float x, float y) { return x + y; });
+  if (l16 < rows) {
+#pragma unroll
+    for (int i = 0; i < 8; ++i)
+      *reinterpret_cast<f32x4*>(lds + wave * (2 * kHalfBytes) + l16 * 512 + (((4 * i + g4) ^ l16) << 4)) = o[i];
+  }
+  if (lane < 16) {
+    stat[wave * 16 + lane] = m_run;
+    stat[64 + wave * 16 + lane] = l_run;
+  }
+  __syncthreads();
+  const buffer_rsrc rs_o = make_rsrc(a.part_o, (uint32_t)a.part_cap * a.hq * 512u);
+  const buffer_rsrc rs_lse = make_rsrc(a.part_lse, (uint32_t)a.part_cap * a.hq * 4u);
+  i32x8 m = {0, 0, 0, 0, 0, 0, 0, 0};
+  int words = 0;
+  if (it.chunk >= 0) {
+    m = *(const __attribute__((address_space(4))) i32x8*)(a.merges + it.merge);
+    words = ((const_i32_ptr)a.hdr)[10];
+  }
+  const uint32_t part0 = first_part_row<G>(a, it, hk, m);
+  for (int r = tid >> 5; r < rows; r += kThreads / 32) {
+    const int piece = tid & 31;
+    float mx = -INFINITY;
+#pragma unroll
+    for (int w = 0; w < 4; ++w) mx = fmaxf(mx, stat[w * 16 + r]);
+    const float ref = mx > -INFINITY ? mx : 0.f;
+    float sum = 0.f;
+    f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int w = 0; w < 4; ++w) {
+      const float f = __builtin_amdgcn_exp2f((stat[w * 16 + r] - ref) * c2);
+      sum = __builtin_fmaf(stat[64 + w * 16 + r], f, sum);
+      acc += f * *reinterpret_cast<const f32x4*>(lds + w * (2 * kHalfBytes) + r * 512 + ((piece ^ r) << 4));
+    }
+    const float inv = fits ? 1.f / sum : 0.f, lse = fits ? mx * a.scale + __logf(sum) : -INFINITY;
+    acc *= inv;
+    if (it.chunk >= 0) {
+      store_device(rs_o, (part0 + r) * 512u + piece * 16u, acc);
+      if (piece == 0) store_device(rs_lse, (part0 + r) * 4u, lse);
+    } else {
+      const int64_t out_row = (int64_t)(it.q_first + r / G) * a.hq + hk * G + r % G;
+      const u32x2 v = {Mfma<T>::pack2(acc[0], acc[1]), Mfma<T>::pack2(acc[2], acc[3])};
+      *reinterpret_cast<u32x2*>(a.out + out_row * kRowBytes + piece * 8) = v;
+      if (piece == 0) a.lse[out_row] = lse;
+    }
+  }
+  if (it.chunk >= 0)
+    arrive<T, G>(a, it, hk, rs_o, rs_lse, m, words, s_last, *reinterpret_cast<MergeList*>(lds));
+}
+
 // Pipeline of one workgroup.  A KV tile (64 keys, 4 pages) is the unit of the V staging
 // and of the workgroup barrier; a half tile (32 keys, 2 pages) is the unit of the K staging and
 // of the softmax pipeline.  Half tile h lives in slot h % 4 of a ring of four K buffers, V
@@ -1170,7 +1444,6 @@ __global__ __launch_bounds__(kThreads, kCB == 1 ? 2 : 1) void attn_kernel(AttnAr
   // room for records, whatever the header says): one memory round trip, with every argument the
   // look-ups behind it need already in registers.  (Left alone the compiler reads the header field
   // by field, a wait and a branch each, then the record, then the arguments.)
-  typedef int32_t i32x8 __attribute__((ext_vector_type(8)));
   const auto* rec = (const __attribute__((address_space(4))) i32x8*)(a.items + wi);
   i32x8 item = rec[0], item_b = rec[1];
   i32x8 hdr = *(const __attribute__((address_space(4))) i32x8*)a.hdr;
@@ -1204,6 +1477,12 @@ __global__ __launch_bounds__(kThreads, kCB == 1 ? 2 : 1) void attn_kernel(AttnAr
   if (odd) return;
   // begin is read here, not taken from the plan (one plan may serve many decode steps)
   const int b = ((const_i32_ptr)a.begin)[seq];
+  const Item it = {t0, t1, chunk, q_first, ntok, table_off, pidx_cap, merge, hdr[6], group};
+  if (kGate && ntok * G <= kFlatRows) {
+    __shared__ float s_stat[2 * 4 * kFlatRows];   // maximum and sum per wavefront and row
+    few_rows_item<T, G>(a, it, hk, b, row0, item_b, lds, s_stat, s_last);
+    return;
+  }
 
   // ---- global -> LDS copies (no VGPR staging) -------------------------------------
   // A wavefront's copy instruction fills 1 KiB of LDS linearly (lane L -> bytes 16 L..),
@@ -1702,10 +1981,8 @@ __global__ __launch_bounds__(kThreads, kCB == 1 ? 2 : 1) void attn_kernel(AttnAr
     i32x8 m = *(const __attribute__((address_space(4))) i32x8*)(a.merges + merge);
     const int words = ((const_i32_ptr)a.hdr)[10];
     const int rows = ntok * G;
-    const int chunks = group ? m[4] : m[2];
     const uint32_t step = ntok * a.hq;                        // partial rows of a chunk
-    const uint32_t chunk0 = (group ? m[5] : m[3]) * a.hq + hk * rows;
-    uint32_t* arrivals = reinterpret_cast<uint32_t*>(a.part_lse) + (int64_t)a.part_cap * a.hq - 1;
+    const uint32_t chunk0 = m[3] * a.hq + hk * rows;          // of chunk 0 (of a tile, not of a group)
     // A row's 32 pieces of 16 bytes lie row by row, for readers that take rows, or as the registers lie
     // (a store fills 1 KiB).  Registers 4 j .. 4 j + 3 of o_acc[dc] hold d = 32 dc + 8 j + 4 half +
     // {0..3}: piece 2 i + half with i = 4 dc + j.  Where piece `half` of row r is, if a chunk's rows
@@ -1731,17 +2008,16 @@ __global__ __launch_bounds__(kThreads, kCB == 1 ? 2 : 1) void attn_kernel(AttnAr
         }
         if (half == 0) store_device(rs_lse, (row0 + tile_row(cb)) * 4u, lse_row[cb]);
       }
-      asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-      __syncthreads();
     };
     auto read_row = [&](Place at, f32x4 (&o)[16]) __attribute__((always_inline)) {
 #pragma unroll
       for (int i = 0; i < 16; ++i) o[i] = load_device4(rs_o, at.byte + i * at.step);
     };
 
-    if (rows > kFlatRows) {
-      uint32_t* word0 = arrivals - ((int64_t)merge * a.hkv + hk) * words - 1 - (group ? words / 2 : 0);
-      int idx = chunk, count = chunks, node0 = 0;
+    if (rows > kFlatRows && !group) {
+      uint32_t* word0 = reinterpret_cast<uint32_t*>(a.part_lse) + (int64_t)a.part_cap * a.hq - 1 -
+                        ((int64_t)merge * a.hkv + hk) * words - 1;
+      int idx = chunk, count = m[2], node0 = 0;
       for (int level = 0; count > 1; ++level) {
         if ((idx ^ 1) < count) {
           const int node = node0 + (idx >> 1);
@@ -1757,6 +2033,8 @@ __global__ __launch_bounds__(kThreads, kCB == 1 ? 2 : 1) void attn_kernel(AttnAr
           __syncthreads();
           if (!second) {
             write_rows(chunk0 + (idx << level) * step, by_reg);
+            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+            __syncthreads();
             if (tid == 0) s_second = (atomicXor(word, bit) & bit) != 0;
             __syncthreads();
             second = s_second != 0;
@@ -1791,96 +2069,11 @@ __global__ __launch_bounds__(kThreads, kCB == 1 ? 2 : 1) void attn_kernel(AttnAr
         idx >>= 1;
       }
     }
-    const bool few = rows <= kFlatRows;
-    if (few || group || m[4] > 0) {
-      // ---- the prefix's chunks and the tile's own, or the chunks of few rows: counted
-      MemberList& list = *reinterpret_cast<MemberList*>(lds + kStageBytes);
-      i32x8 mr = m;
-      if (group) mr = *reinterpret_cast<const i32x8*>(a.merges + min(merge + tid, hdr[6] - 1));
-      if (few) write_rows(chunk0 + chunk * step, by_row);
+    if (rows <= kFlatRows || group || m[4] > 0) {
+      if (rows <= kFlatRows || group) write_rows(first_part_row<G>(a, it, hk, m), by_row);
       else write_rows(chunk0, by_reg);
-      // records of this item: one, or the group's members' (their tokens follow one another)
-      if (tid < (group ? ntok : 1) && merge + tid < hdr[6] && mr[0] < q_first + ntok) {
-        const int n = flat_chunks_of<G>(mr);
-        const bool last =
-            atomicInc(arrivals - ((int64_t)(merge + tid) * a.hkv + hk) * words, n - 1) == (unsigned)n - 1;
-        if (last) s_last = 1;
-        if (group) {
-          *reinterpret_cast<i32x8*>(list.rec[tid]) = mr;
-          list.last[tid] = last;
-          for (int i = 0; i < mr[1]; ++i) list.of[mr[7] + i] = tid;
-        }
-      }
-      __syncthreads();
-      if (s_last == 0) return;
-      if (few) {
-        if (group) {
-          // (few rows: member after member)
-          for (int k = 0; k < ntok && merge + k < hdr[6]; ++k) {
-            const i32x8 r = *reinterpret_cast<const i32x8*>(list.rec[k]);
-            const int first = __builtin_amdgcn_readfirstlane(r[7]), n = __builtin_amdgcn_readfirstlane(r[1]);
-            if (__builtin_amdgcn_readfirstlane(list.last[k]))
-              merge_rows<T, G, 1, kMergeAhead>(a, rs_o, rs_lse, hk, n, [&](int, int& f) __attribute__((always_inline)) { f = 0; return r; });
-            if (first + n >= ntok) break;
-          }
-        } else {
-          merge_rows<T, G, 1, kMergeAhead>(a, rs_o, rs_lse, hk, ntok,
-                                           [&](int, int& f) __attribute__((always_inline)) { f = 0; return m; });
-        }
-        return;
-      }
-      // ---- the last of prefix and own range has one of them in registers, chunk by chunk the rest is
-      //      added: a group's item the own chunks of the members it completed, a tile of more rows the
-      //      prefix, which comes before it
-#pragma unroll
-      for (int cb = 0; cb < kCB; ++cb) {
-        const int r = tile_row(cb);
-        i32x8 of = m;
-        if (group) {
-          const int k = list.of[min(r / G, ntok - 1)];
-          row_live[cb] = row_live[cb] && list.last[k] != 0;
-          of = *reinterpret_cast<const i32x8*>(list.rec[k]);
-        }
-        if (!row_live[cb]) continue;
-        float mx = lse_row[cb], den = mx != -INFINITY ? 1.f : 0.f, f_old, f_new;
-        f32x4 o[16];
-        if (!group) {
-          const int g_rows = of[6] * G, gr = of[7] * G + r;
-          const uint32_t row0 = of[5] * a.hq + hk * g_rows;
-          const float mine = lse_row[cb];
-          mx = load_device(rs_lse, (row0 + gr) * 4u);
-          den = mx != -INFINITY ? 1.f : 0.f;
-          read_row(by_reg(row0, gr, g_rows), o);
-          chunk_step(mine, mx, den, f_old, f_new);
-#pragma unroll
-          for (int i = 0; i < 16; ++i)
-#pragma unroll
-            for (int j = 0; j < 4; ++j) {
-              const float x = o_acc[cb][i >> 2][4 * (i & 3) + j];
-              o_acc[cb][i >> 2][4 * (i & 3) + j] = __builtin_fmaf(x, f_new, o[i][j] * f_old);
-            }
-        } else {
-          const int own_rows = of[1] * G, own = r - of[7] * G, n = flat_chunks<G>(of[2], of[1]);
-          for (int c = 0; c < n; ++c) {
-            const uint32_t row0 = (of[3] + c * of[1]) * a.hq + hk * own_rows;
-            const float lse = load_device(rs_lse, (row0 + own) * 4u);
-            read_row(own_rows <= kFlatRows ? by_row(row0, own, 0) : by_reg(row0, own, own_rows), o);
-            chunk_step(lse, mx, den, f_old, f_new);
-#pragma unroll
-            for (int i = 0; i < 16; ++i)
-#pragma unroll
-              for (int j = 0; j < 4; ++j) {
-                const float x = o_acc[cb][i >> 2][4 * (i & 3) + j];
-                o_acc[cb][i >> 2][4 * (i & 3) + j] =
-                    __builtin_fmaf(lse != -INFINITY ? o[i][j] : 0.f, f_new, x * f_old);
-              }
-          }
-        }
-        lse_row[cb] = mx + __logf(den);
-        const float inv = mx > -INFINITY ? 1.f / den : 0.f;
-#pragma unroll
-        for (int dc = 0; dc < 4; ++dc) o_acc[cb][dc] *= inv;
-      }
+      arrive<T, G>(a, it, hk, rs_o, rs_lse, m, words, s_last, *reinterpret_cast<MergeList*>(lds));
+      return;
     }
   }
   if (kGate && !wave_active) return;
@@ -1919,16 +2112,39 @@ __global__ __launch_bounds__(kThreads, kCB == 1 ? 2 : 1) void attn_kernel(AttnAr
       const int lr = 4 * i + (lane >> 4);               // row of this block's 32
       const int rr = wave * kWaveRows + cb * 32 + lr, gg = rr % G, t2 = rr / G;
       const u32x4 v = *reinterpret_cast<const u32x4*>(stage + k_swz(lr, lane & 15));
-      // (of a group, the members' rows that were completed here)
-      bool live = t2 < ntok;
-      if (kCB == 1 && group && live) {
-        const MemberList& list = *reinterpret_cast<const MemberList*>(lds + kStageBytes);
-        live = list.last[list.of[t2]] != 0;
-      }
-      if (live)
+      if (t2 < ntok)
         *reinterpret_cast<u32x4*>(a.out + ((int64_t)(q_first + t2) * a.hq + hk * G + gg) * kRowBytes +
                                   (lane & 15) * 16) = v;
     }
+  }
+}
+
+// The members of shared-prefix groups in batches of more than kGroupsInLaunch sequences: a workgroup
+// per merge record and kv head.  (It does nothing where the plan found no group.)
+template <typename T, int G>
+__global__ __launch_bounds__(kThreads) void group_merge_kernel(AttnArgs a) {
+  const i32x8 hdr = *(const __attribute__((address_space(4))) i32x8*)a.hdr;
+  const int group_rows = ((const_i32_ptr)a.hdr)[8];
+  if (hdr[0] != kPlanMagic || group_rows == 0 || hdr[4] != a.batch || hdr[5] != a.total_q) return;
+  const buffer_rsrc rs_o = make_rsrc(a.part_o, (uint32_t)a.part_cap * a.hq * 512u);
+  const buffer_rsrc rs_lse = make_rsrc(a.part_lse, (uint32_t)a.part_cap * a.hq * 4u);
+  for (int64_t w = blockIdx.x; w < (int64_t)hdr[6] * a.hkv; w += gridDim.x) {
+    const int rec = __builtin_amdgcn_readfirstlane((int)(w / a.hkv)), hk = (int)(w - (int64_t)rec * a.hkv);
+    const i32x8 m = *(const __attribute__((address_space(4))) i32x8*)(a.merges + rec);
+    if (m[4] == 0) continue;
+    auto one = [&](int, int& first) __attribute__((always_inline)) { first = 0; return m; };
+    if (m[1] * G <= kThreads / 32) merge_rows<T, G, 1, kMergeAhead>(a, rs_o, rs_lse, hk, m[1], one);
+    else merge_rows<T, G, 4, 4>(a, rs_o, rs_lse, hk, m[1], one);
+  }
+}
+
+template <typename T>
+void launch_group_merge(int G, dim3 grid, hipStream_t hs, const AttnArgs& a) {
+  switch (G) {
+    case 1: hipLaunchKernelGGL((group_merge_kernel<T, 1>), grid, dim3(kThreads), 0, hs, a); break;
+    case 2: hipLaunchKernelGGL((group_merge_kernel<T, 2>), grid, dim3(kThreads), 0, hs, a); break;
+    case 4: hipLaunchKernelGGL((group_merge_kernel<T, 4>), grid, dim3(kThreads), 0, hs, a); break;
+    default: hipLaunchKernelGGL((group_merge_kernel<T, 8>), grid, dim3(kThreads), 0, hs, a); break;
   }
 }
 
@@ -1988,11 +2204,13 @@ bool may_group(const WorkspaceLayout& w, int32_t total_q, int tile_tokens) {
 // Upper bound of the planner's item count: a q tile with T KV tiles becomes at most T / L + 1
 // items, and the planner's chunk length L is at least (sum of T) x hkv / (kItemsPerSlot x slots); the
 // remainder round adds fewer than slots / hkv.  A shared-prefix group adds at most one item per
-// sequence beyond that.
-int32_t item_bound(const WorkspaceLayout& w, int hkv, int slots, bool groups) {
+// sequence beyond that, and where its decode rows go in items of few rows, as many more for each.
+int32_t item_bound(const WorkspaceLayout& w, int G, int hkv, int slots, bool groups) {
   int64_t b = w.max_tiles;
   if (may_cut(w, hkv, slots)) b += (int64_t)kItemsPerSlot * slots / hkv + 1;
   if (groups) b += w.batch;
+  if (groups && w.batch <= kGroupsInLaunch)
+    b += ((w.batch * G + kFlatRows - 1) / kFlatRows - 1) * ((int64_t)kItemsPerSlot * slots / hkv + w.batch);
   return (int32_t)(b < w.max_items ? b : w.max_items);
 }
 
@@ -2049,7 +2267,7 @@ mc_status plan_impl(const mc_pool_desc* pool, int32_t num_q_heads, int32_t batch
   a.wide_tile_tokens = wide ? 2 * tile_tokens : 0;
   a.slots_wide = device_slots(2);
   a.allow_groups = may_group(w, total_q, tile_tokens);
-  a.max_items = item_bound(w, a.hkv, a.slots, a.allow_groups);
+  a.max_items = item_bound(w, G, a.hkv, a.slots, a.allow_groups);
   a.part_cap = w.part_cap;
   a.ahead = ahead_tokens;
   // (few sequences only: the page-id checks and the table comparisons of shared prefixes go
@@ -2091,7 +2309,7 @@ mc_status attn_impl(const mc_pool_desc* pool, int32_t layer, const void* q, int3
   if (slots <= 0) return MC_ERR_HIP;
   const bool groups = may_group(w, total_q, tile_tokens);
   const int64_t blocks =
-      (int64_t)item_bound(w, pool->num_kv_heads, slots, groups) * pool->num_kv_heads;
+      (int64_t)item_bound(w, G, pool->num_kv_heads, slots, groups) * pool->num_kv_heads;
   if (blocks > 0x7fffffffll) return MC_ERR_UNSUPPORTED;
   char* ws = static_cast<char*>(workspace);
   AttnArgs a;
@@ -2130,7 +2348,14 @@ mc_status attn_impl(const mc_pool_desc* pool, int32_t layer, const void* q, int3
     st = pool->dtype == MC_F16 ? launch_attn<_Float16>(G, false, 2, grid, hs, a)
                                : launch_attn<__bf16>(G, false, 2, grid, hs, a);
   }
-  return st;
+  if (st != MC_OK || !groups || batch <= kGroupsInLaunch) return st;
+  // the planner may have found shared prefixes: their members' chunks are combined (one workgroup a
+  // sequence and kv head if they all run at once, else a grid-stride walk)
+  const int64_t pairs = (int64_t)batch * pool->num_kv_heads;
+  const dim3 mgrid((unsigned)(pairs < 4ll * slots ? pairs : 4ll * slots));
+  if (pool->dtype == MC_F16) launch_group_merge<_Float16>(G, mgrid, hs, a);
+  else launch_group_merge<__bf16>(G, mgrid, hs, a);
+  return mc::launch_status();
 }
 
 
