@@ -62,7 +62,7 @@ constexpr int kBN = 64;        // keys per KV tile
 constexpr int kThreads = 256;  // 4 wavefronts, 32 rows each
 constexpr int kPlanThreads = 1024;      // threads of the planner's one workgroup ...
 constexpr int kPlanThreadsSmall = 256;  // ... and for batches of few sequences and q tiles
-constexpr int kBuckets = 4096;
+constexpr int kBuckets = 1024;   // of item lengths, for their order (beyond 1023 tiles, 2, 4 ... share one)
 constexpr int32_t kPlanMagic = 0x6d63706c;
 
 struct PlanHeader {
@@ -238,45 +238,34 @@ struct PlanArgs {
   int32_t wide_tile_tokens, slots_wide;   // the wide q tiles, if the host allows them (else 0)
 };
 
-// Block-wide exclusive scan of one value per thread (NT threads): a shuffle scan
-// inside each wavefront, the 16 wavefront totals through LDS, two barriers in all.
-template <int NT>
-__device__ int block_exclusive_scan(int v, int* lds, int* total) {
-  const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
-  int incl = v;
-#pragma unroll
-  for (int off = 1; off < 64; off <<= 1) {
-    const int up = __shfl_up(incl, off);
-    if (lane >= off) incl += up;
-  }
-  __syncthreads();               // earlier readers of lds are done
-  if (lane == 63) lds[wave] = incl;
-  __syncthreads();
-  int before = 0, all = 0;
-#pragma unroll
-  for (int w = 0; w < NT / 64; ++w) {
-    const int x = lds[w];
-    if (w < wave) before += x;
-    all += x;
-  }
-  *total = all;
-  return before + incl - v;
+// Scans over a wavefront by data-parallel moves (rows of 16 lanes, then the rows' last lanes): no LDS
+// permutes, of which a scan of shuffles is six in a row.  The planner is one workgroup whose steps
+// follow one another, so their latency is its time: five scans of one decode row's plan.
+template <typename Op>
+__device__ __forceinline__ int wave_inclusive(int x, int identity, Op&& op) {
+  x = op(x, __builtin_amdgcn_update_dpp(identity, x, 0x111, 0xf, 0xf, false));   // row_shr:1
+  x = op(x, __builtin_amdgcn_update_dpp(identity, x, 0x112, 0xf, 0xf, false));
+  x = op(x, __builtin_amdgcn_update_dpp(identity, x, 0x114, 0xf, 0xf, false));
+  x = op(x, __builtin_amdgcn_update_dpp(identity, x, 0x118, 0xf, 0xf, false));
+  x = op(x, __builtin_amdgcn_update_dpp(identity, x, 0x142, 0xa, 0xf, false));   // row_bcast:15
+  x = op(x, __builtin_amdgcn_update_dpp(identity, x, 0x143, 0xc, 0xf, false));   // row_bcast:31
+  return x;
+}
+__device__ __forceinline__ int wave_inclusive_sum(int x) {
+  return wave_inclusive(x, 0, [](int p, int q) { return p + q; });
+}
+__device__ __forceinline__ int wave_inclusive_max(int x) {
+  return wave_inclusive(x, INT32_MIN, [](int p, int q) { return max(p, q); });
 }
 
-// The same for N values per thread at once (two barriers for all of them); lds holds N x 16 ints.
+// Block-wide exclusive scan of N values per thread at once (NT threads): the wavefront totals through
+// LDS (N x NT / 64 ints), two barriers in all.
 template <int NT, int N>
-__device__ void block_exclusive_scan_n(int (&v)[N], int* lds, int (&total)[N]) {
+__device__ __forceinline__ void block_exclusive_scan_n(int (&v)[N], int* lds, int (&total)[N]) {
   const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
   int incl[N];
 #pragma unroll
-  for (int k = 0; k < N; ++k) incl[k] = v[k];
-#pragma unroll
-  for (int off = 1; off < 64; off <<= 1)
-#pragma unroll
-    for (int k = 0; k < N; ++k) {
-      const int up = __shfl_up(incl[k], off);
-      if (lane >= off) incl[k] += up;
-    }
+  for (int k = 0; k < N; ++k) incl[k] = wave_inclusive_sum(v[k]);
   __syncthreads();               // earlier readers of lds are done
   if (lane == 63)
 #pragma unroll
@@ -295,37 +284,39 @@ __device__ void block_exclusive_scan_n(int (&v)[N], int* lds, int (&total)[N]) {
     v[k] = before + incl[k] - v[k];
   }
 }
+template <int NT>
+__device__ __forceinline__ int block_exclusive_scan(int v, int* lds, int* total) {
+  int one[1] = {v}, sum[1];
+  block_exclusive_scan_n<NT>(one, lds, sum);
+  *total = sum[0];
+  return one[0];
+}
 
-// Block-wide sum of one value per thread, to every thread: butterfly inside each wavefront, the
-// 16 wavefront sums through LDS (lds holds 2 x 16 ints).
+// Block-wide sum of one value (0 .. 2^63 - 1) per thread, to every thread: in three pieces of 21 bits
+// (lds holds 3 x NT / 64 ints).
 template <int NT>
 __device__ __forceinline__ long long block_sum(long long v, int* lds) {
   const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
+  int piece[3];
 #pragma unroll
-  for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off);
+  for (int k = 0; k < 3; ++k) piece[k] = wave_inclusive_sum((int)(v >> (21 * k)) & 0x1fffff);
   __syncthreads();               // earlier readers of lds are done
-  if (lane == 0) {
-    lds[2 * wave] = (int)(v & 0xffffffffll);
-    lds[2 * wave + 1] = (int)(v >> 32);
-  }
+  if (lane == 63)
+#pragma unroll
+    for (int k = 0; k < 3; ++k) lds[3 * wave + k] = piece[k];
   __syncthreads();
   long long all = 0;
 #pragma unroll
   for (int w = 0; w < NT / 64; ++w)
-    all += ((long long)lds[2 * w + 1] << 32) | (unsigned int)lds[2 * w];
+    all += lds[3 * w] + ((long long)lds[3 * w + 1] << 21) + ((long long)lds[3 * w + 2] << 42);
   return all;
 }
 
 // Block-wide inclusive running maximum of one value per thread.
 template <int NT>
-__device__ int block_inclusive_max_scan(int v, int* lds) {
+__device__ __forceinline__ int block_inclusive_max_scan(int v, int* lds) {
   const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
-  int incl = v;
-#pragma unroll
-  for (int off = 1; off < 64; off <<= 1) {
-    const int up = __shfl_up(incl, off);
-    if (lane >= off) incl = max(incl, up);
-  }
+  const int incl = wave_inclusive_max(v);
   __syncthreads();
   if (lane == 63) lds[wave] = incl;
   __syncthreads();
@@ -475,43 +466,48 @@ __global__ __launch_bounds__(NT) void plan_kernel(PlanArgs a) {
   }
   // (one LDS atomic per wavefront, not per thread: 1024 atomics on one address take microseconds)
   if (__ballot(err != 0) != 0 && (t & 63) == 0) atomicOr(&s_err, 1);
-#pragma unroll
-  for (int off = 32; off > 0; off >>= 1) maxcost = max(maxcost, __shfl_xor(maxcost, off));
-  if ((t & 63) == 0) atomicMax(&s_maxcost, maxcost);
+  maxcost = wave_inclusive_max(maxcost);
+  if ((t & 63) == 63) atomicMax(&s_maxcost, maxcost);
   __syncthreads();
   if (s_err) {
     if (t == 0) { a.hdr->err = MC_ERR_RANGE; a.hdr->num_items = 0; a.hdr->num_merges = 0; a.hdr->magic = kPlanMagic; }
     return;
   }
-  // 2. page ids of every needed table entry.  Small batches (their offsets sit in LDS): a
-  //    wavefront takes four sequences per trip and has up to 32 loads per lane in flight (the loop is
-  //    bound by memory latency); entries beyond the first 512 of a sequence follow one
-  //    sequence at a time.
+  // 2. page ids of every needed table entry.  Small batches (their offsets sit in LDS): a wavefront
+  //    takes eight sequences per trip, four entries a lane, all of their loads in flight (the loop is
+  //    bound by memory latency); entries beyond the first 256 of a sequence follow one sequence at a
+  //    time.  256 sequences of 64..256 pages 7.3 -> 2.7 us (eight loads of one entry a lane for each of
+  //    four sequences before).
   if (a.batch <= kValidateInPlan) {
-    for (int s4 = (t >> 6) * 4; s4 < a.batch; s4 += (NT >> 6) * 4) {
-      int32_t pg[4][8];
-      int need[4], p0[4];
+    typedef int32_t i32x4u __attribute__((ext_vector_type(4), aligned(4)));
+    auto bad = [&](i32x4u x) {
+      const int lo = min(min(x[0], x[1]), min(x[2], x[3])), hi = max(max(x[0], x[1]), max(x[2], x[3]));
+      return lo < 0 || hi >= a.num_pages;
+    };
+    const int lane4 = 4 * (t & 63);
+    for (int s8 = (t >> 6) * 8; s8 < a.batch; s8 += (NT >> 6) * 8) {
+      i32x4u pg[8];
+      int need[8], p0[8];
 #pragma unroll
-      for (int k = 0; k < 4; ++k) {
-        const int s = s4 + k;
+      for (int k = 0; k < 8; ++k) {
+        const int s = s8 + k;
         const int q = s < a.batch ? s_cuq[s + 1] - s_cuq[s] : 0;
         need[k] = q > 0 ? (s_beg[s] + q + a.ahead + kPage - 1) / kPage : 0;
         p0[k] = s < a.batch ? s_cup[s] : 0;
-#pragma unroll
-        for (int u = 0; u < 8; ++u) {
-          const int i = (t & 63) + 64 * u;
-          pg[k][u] = i < need[k] ? a.page_table[p0[k] + i] : 0;
+        pg[k] = i32x4u{0, 0, 0, 0};
+        // (the last lane's four entries end with the last needed one: nothing beyond it is read)
+        if (need[k] >= 4) {
+          if (lane4 < need[k])
+            pg[k] = *reinterpret_cast<const i32x4u*>(a.page_table + p0[k] + min(lane4, need[k] - 4));
+        } else if ((t & 63) < need[k]) {
+          pg[k][0] = a.page_table[p0[k] + (t & 63)];
         }
       }
 #pragma unroll
-      for (int k = 0; k < 4; ++k) {
-#pragma unroll
-        for (int u = 0; u < 8; ++u)
-          if (pg[k][u] < 0 || pg[k][u] >= a.num_pages) err = 1;
-        for (int i = 512 + (t & 63); i < need[k]; i += 64) {
-          const int32_t x = a.page_table[p0[k] + i];
-          if (x < 0 || x >= a.num_pages) err = 1;
-        }
+      for (int k = 0; k < 8; ++k) {
+        if (bad(pg[k])) err = 1;
+        for (int i = 256 + lane4; i < need[k]; i += 256)
+          if (bad(*reinterpret_cast<const i32x4u*>(a.page_table + p0[k] + min(i, need[k] - 4)))) err = 1;
       }
     }
   }
@@ -550,7 +546,7 @@ __global__ __launch_bounds__(NT) void plan_kernel(PlanArgs a) {
     __syncthreads();
     // pages in common between s and s+1, among the whole pages cached by both.  First every
     // pair at once, one thread each: unrelated sequences differ in their first page and are
-    // done (s_common = 1 marks a pair that is not).  Then one wavefront a remaining pair.
+    // done (s_common = 1 marks a pair that is not).  Then 16 lanes a remaining pair.
     constexpr int kMinPages = kMinSharedTiles * kBN / kPage;
     // a sequence can be a member if its new range leaves room for another token in a q tile
     auto is_short = [&](int sq) {
@@ -562,19 +558,28 @@ __global__ __launch_bounds__(NT) void plan_kernel(PlanArgs a) {
         a.page_table[s_cup[t]] == a.page_table[s_cup[t + 1]])
       s_common[t] = 1;
     __syncthreads();
-    for (int sq = t >> 6; sq + 1 < a.batch; sq += NT >> 6) {
+    // (16 lanes a pair, eight entries a lane and table in flight)
+    for (int sq = t >> 4; sq + 1 < a.batch; sq += NT >> 4) {
       if (s_common[sq] == 0) continue;
       const int lim = min(s_beg[sq], s_beg[sq + 1]) / kPage;
       const int pa = s_cup[sq], pb = s_cup[sq + 1];
-      int common = 0;
-      for (int i0 = 0; i0 < lim; i0 += 64) {
-        const int i = i0 + (t & 63);
-        const bool differ = i < lim && a.page_table[pa + i] != a.page_table[pb + i];
-        const unsigned long long m = __ballot(differ);
-        if (m) { common = i0 + __ffsll((long long)m) - 1; break; }
-        common = min(lim, i0 + 64);
+      int common = lim;
+      for (int i0 = t & 15; i0 - (t & 15) < common; i0 += 128) {
+        int x[8], y[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) {
+          x[u] = i0 + 16 * u < lim ? a.page_table[pa + i0 + 16 * u] : 0;
+          y[u] = i0 + 16 * u < lim ? a.page_table[pb + i0 + 16 * u] : 0;
+        }
+        int first = lim;               // the first entry that differs
+#pragma unroll
+        for (int u = 7; u >= 0; --u)
+          if (x[u] != y[u]) first = i0 + 16 * u;
+#pragma unroll
+        for (int off = 8; off > 0; off >>= 1) first = min(first, __shfl_xor(first, off));
+        common = min(common, first);
       }
-      if ((t & 63) == 0) s_common[sq] = common;
+      if ((t & 15) == 0) s_common[sq] = common;
     }
     __syncthreads();
     // Runs of such sequences linked by enough common pages, cut greedily into groups of at most
@@ -662,6 +667,11 @@ __global__ __launch_bounds__(NT) void plan_kernel(PlanArgs a) {
     x.gm = groups && s_glead[lo] == lo ? s_gsize[lo] : 0;
     return x;
   };
+  // (a batch of no more tiles than threads: a thread's tile is the same in every step)
+  const bool one_each = total_tiles <= NT;
+  Tile mine = {0, 0, 0, 0, 0, 0, 0};
+  if (one_each && t < total_tiles) mine = locate(t);
+  auto tile = [&](int i) { return one_each ? mine : locate(i); };
   // own chunks of L tiles (L even) from the end of the group's prefix: [pt, pt+L), ...,
   // [pt+kL, T) with pt + kL <= dmax; the group's prefix itself in chunks of L
   auto own_splits = [&](const Tile& x, int L) { return L > 0 ? (x.dmax - x.pt) / L + 1 : 1; };
@@ -682,7 +692,7 @@ __global__ __launch_bounds__(NT) void plan_kernel(PlanArgs a) {
   auto total_part_rows = [&](int L) {   // block-wide
     long long rows = 0;
     const int arrive = arrive_rows(L);
-    for (int i = t; i < total_tiles; i += NT) rows += part_rows(locate(i), L, arrive);
+    for (int i = t; i < total_tiles; i += NT) rows += part_rows(tile(i), L, arrive);
     return block_sum<NT>(rows, scan);
   };
 
@@ -694,12 +704,12 @@ __global__ __launch_bounds__(NT) void plan_kernel(PlanArgs a) {
   if ((int64_t)total_tiles * a.hkv < (int64_t)kRoundsWanted * a.slots) {
     long long cost = 0;
     for (int i = t; i < total_tiles; i += NT) {
-      const Tile x = locate(i);
+      const Tile x = tile(i);
       cost += x.T - x.pt + (x.gm ? x.pt : 0);
     }
     cost = block_sum<NT>(cost, scan);
-    const long long want =
-        (cost * a.hkv + (long long)kItemsPerSlot * a.slots - 1) / ((long long)kItemsPerSlot * a.slots);
+    const long long room = (long long)kItemsPerSlot * a.slots, heads = cost * a.hkv + room - 1;
+    const long long want = heads <= INT32_MAX ? (int)heads / (int)room : heads / room;
     // short pieces: only if no sequence has two new tokens (as many q tiles as new tokens)
     int shortest = kMinChunkTiles;
     if (a.total_q <= total_tiles && want < kMinChunkTiles) {
@@ -718,7 +728,10 @@ __global__ __launch_bounds__(NT) void plan_kernel(PlanArgs a) {
     }
   }
   // without cuts the groups still need partial rows: no room, no groups
-  if (L == 0 && groups && total_part_rows(0) > a.part_cap) groups = false;
+  if (L == 0 && groups && total_part_rows(0) > a.part_cap) {
+    groups = false;
+    mine.pt = mine.gm = 0;
+  }
 
   int shift = 0;
   while ((s_maxcost >> shift) >= kBuckets) ++shift;
@@ -777,7 +790,7 @@ __global__ __launch_bounds__(NT) void plan_kernel(PlanArgs a) {
   const int i_lo = min(t * tper, total_tiles), i_hi = min(i_lo + tper, total_tiles);
   int n_items = 0, n_own = 0, n_grp = 0, n_merge = 0;
   for (int i = i_lo; i < i_hi; ++i) {
-    const Tile x = locate(i);
+    const Tile x = tile(i);
     const int Li = chunk_len(i, x);
     const int ns = own_splits(x, Li), ng = x.gm ? grp_splits(x, Li) : 0;
     n_items += ns + (sliced ? ng * slices(x) : ng);
@@ -809,7 +822,7 @@ __global__ __launch_bounds__(NT) void plan_kernel(PlanArgs a) {
   if (groups) {
     int off = tot_own + grp_off;
     for (int i = i_lo; i < i_hi; ++i) {
-      const Tile x = locate(i);
+      const Tile x = tile(i);
       if (x.gm) { s_gbase[x.s] = off; off += grp_splits(x, chunk_len(i, x)) * x.gm; }
     }
     __syncthreads();
@@ -818,7 +831,7 @@ __global__ __launch_bounds__(NT) void plan_kernel(PlanArgs a) {
     a.arrivals_end[-1 - i] = 0;   // nobody has arrived
   // 6. emit: counting sort of the items by cost (number of KV tiles), heaviest first
   for (int i = i_lo; i < i_hi; ++i) {
-    const Tile x = locate(i);
+    const Tile x = tile(i);
     const int Li = chunk_len(i, x);
     const int ns = own_splits(x, Li), ng = grp_splits(x, Li);
     const bool merged = ns > 1 || x.pt > 0;
