@@ -1247,8 +1247,8 @@ __device__ __forceinline__ float across_rows(float x, Op&& op) {
 // another, else by the reads themselves.  Walked by one wavefront of four, as items of more rows are
 // (the other three without a row), a piece of two tiles took 5.0 us from the first instruction to the
 // vote at its end, three requests behind the record; here one, the first half tile of every wavefront.
-// What a wavefront has in flight, 16 KiB, is waited for as a whole: the next half tile is requested
-// as soon as S has been formed, and eight wavefronts a compute unit keep 128 KiB under way.
+// What a wavefront has in flight, 16 KiB, is waited for as a whole; then the next half tile's V is
+// requested at once, its K as soon as S has been formed, and eight wavefronts a compute unit keep 128 KiB under way.
 // A layer (append and attention) of one row over 1000 keys, 32 / 8 heads, 12.9 -> 10.5 us; of eight rows
 // over 1024..4096, 64 / 8 heads, 27.7 -> 25.5; 256 rows, bound by the reads, the same.
 template <typename T, int G>
@@ -1270,11 +1270,14 @@ __device__ __forceinline__ void few_rows_item(const AttnArgs& a, const Item& it,
   const uint32_t k_off = l16 * kRowBytes + g4 * 16;
   const uint32_t v_off = g4 * kRowBytes + ((l16 ^ (g4 << 2)) << 4) + (uint32_t)a.hkv * kHeadPageBytes;
   vec8 kf[2][4], q[4];
-  auto request = [&](int32_t id0, int32_t id1, int buf) __attribute__((always_inline)) {
+  auto request_v = [&](int32_t id0, int32_t id1, int buf) __attribute__((always_inline)) {
     const char* page[2] = {page_base(id0), page_base(id1)};
 #pragma unroll
     for (int i = 0; i < 8; ++i)
       copy16_to_lds(page[i >> 2] + (i & 3) * 1024, v_off, lds_own + buf * kHalfBytes + i * 1024);
+  };
+  auto request_k = [&](int32_t id0, int32_t id1) __attribute__((always_inline)) {
+    const char* page[2] = {page_base(id0), page_base(id1)};
 #pragma unroll
     for (int p = 0; p < 2; ++p)
 #pragma unroll
@@ -1289,7 +1292,8 @@ __device__ __forceinline__ void few_rows_item(const AttnArgs& a, const Item& it,
   if (h < 2 * it.t1) {
     const int32_t id0 = wave == 0 ? ids[0] : wave == 1 ? ids[2] : wave == 2 ? ids[4] : ids[6];
     const int32_t id1 = wave == 0 ? ids[1] : wave == 1 ? ids[3] : wave == 2 ? ids[5] : ids[7];
-    request(id0, id1, 0);
+    request_v(id0, id1, 0);
+    request_k(id0, id1);
   }
   // the row of this lane (one that does not exist reads the last one's q)
   const int my_row = min(l16, rows - 1), tt = my_row / G;
@@ -1314,13 +1318,15 @@ __device__ __forceinline__ void few_rows_item(const AttnArgs& a, const Item& it,
   int buf = 0;
   for (; h < n_halves; h += 4, buf ^= 1) {
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    const bool more = h + 4 < n_halves;
+    if (more) request_v(next0, next1, buf ^ 1);
     f32x4 s[2] = {{0.f, 0.f, 0.f, 0.f}, {0.f, 0.f, 0.f, 0.f}};
 #pragma unroll
     for (int kk = 0; kk < 4; ++kk)
 #pragma unroll
       for (int p = 0; p < 2; ++p) s[p] = Mfma<T>::run16(kf[p][kk], q[kk], s[p]);
-    if (h + 4 < n_halves) {
-      request(next0, next1, buf ^ 1);
+    if (more) {
+      request_k(next0, next1);
       next0 = id_of(h + 8, 0);
       next1 = id_of(h + 8, 1);
     }
