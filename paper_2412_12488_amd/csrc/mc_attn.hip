@@ -124,8 +124,8 @@ constexpr uint32_t kItemGroup = 1u << 28;
 //     A workgroup reads partial rows at 30 GB/s or so, and the last item of a prefix may find every
 //     member waiting: for 24 forks of a 2304-token prompt (32 / 8 heads) it would be alone for 20 us
 //     where the launch takes 5.  (Nor do a tree over the prefix's chunks, 2.4 to 3.7 us a level, or
-//     items of 16 rows, which read the prefix again, make up for it: 64 forks 50, 45 us a layer instead
-//     of 42; 12 forks of 1920 tokens with 53..445 of their own 29, 20 instead of 20.)
+//     items of 16 rows, which read the prefix again, make up for it: 64 forks 48, 50 us a layer instead
+//     of 45; 12 forks of 1920 tokens with 53..445 of their own 30, 20 instead of 20.)
 // Which chunk comes last differs from run to run; the sums and their order do not.
 struct MergeRec {
   int32_t q_row;   // index of the tile's first token among all new tokens of the batch
