@@ -1053,12 +1053,13 @@ static_assert(sizeof(MergeList) <= 4 * kTileBytes, "the list takes the tiles' LD
 
 // One more chunk of a row (LSE lse) beside those summed so far (their maximum mx, their weights' sum
 // den): the factors of both.  Every place that sums chunks does it by this step, chunk after chunk in
-// their order, so that the result does not depend on the place.
+// their order, so that the result does not depend on the place.  A chunk without a key (LSE -inf) has
+// no weight, and no maximum; one whose LSE is not a number has a weight that is none either, which den
+// and the row then are.  den is 0 until a chunk with a key has come.
 __device__ __forceinline__ void chunk_step(float lse, float& mx, float& den, float& f_old, float& f_new) {
   const float m = fmaxf(mx, lse);
-  const bool any = m > -INFINITY;          // (a chunk without a key has no weight, and no maximum)
-  f_old = any ? __expf(mx - m) : 1.f;
-  f_new = any && lse != -INFINITY ? __expf(lse - m) : 0.f;
+  f_old = m > -INFINITY ? __expf(mx - m) : 1.f;
+  f_new = lse != -INFINITY ? __expf(lse - m) : 0.f;
   mx = m;
   den = __builtin_fmaf(den, f_old, f_new);
 }
@@ -1140,7 +1141,7 @@ __device__ __forceinline__ void merge_rows(const AttnArgs& a, buffer_rsrc rs_o, 
 #pragma unroll
     for (int u = 0; u < kRows; ++u) {
       // (no chunk of the row was computed: nothing is written)
-      if (r0 + u * (kThreads / 32) >= rows || !(mx[u] > -INFINITY)) continue;
+      if (r0 + u * (kThreads / 32) >= rows || den[u] == 0.f) continue;
       const float inv = 1.f / den[u];
       u32x2 v;
       v[0] = Mfma<T>::pack2(acc[u][0] * inv, acc[u][1] * inv);
@@ -2068,8 +2069,8 @@ __global__ __launch_bounds__(kThreads, kCB == 1 ? 2 : 1) void attn_kernel(AttnAr
             const float lse = load_device(rs_lse, (other + tile_row(cb)) * 4u);
             f32x4 o[16];
             read_row(by_reg(other, tile_row(cb), rows), o);
+            if (lse == -INFINITY && lse_row[cb] == -INFINITY) continue;   // neither holds a key of this row
             const float mx = fmaxf(lse, lse_row[cb]);
-            if (!(mx > -INFINITY)) continue;        // neither chunk holds a key of this row
             const float w0 = __expf(lse_row[cb] - mx), w1 = __expf(lse - mx), den = w0 + w1;
             const float f0 = w0 / den, f1 = w1 / den;
             lse_row[cb] = mx + __logf(den);

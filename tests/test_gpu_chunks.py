@@ -15,8 +15,9 @@ from test_gpu_parity import LSE_TOL, O_TOL, fill_both, forked_decode_workload, s
 pytestmark = pytest.mark.gpu
 
 
-def launches(w, n=6):
-    """(out bits, lse) of n launches on one plan, the plan's header, and the oracle's pool."""
+def launches(w, n=6, q=None, begin=None, blank=(0x7fc1, float("nan"))):
+    """(out bits, lse) of n launches on one plan, the plan's header, and the oracle's pool.  The launches
+    take other q and begin if given, and find blank in out and lse."""
     pool = DevPool(w)
     pool.t.fill_(0x7fc1)
     opool = np.full(pool.elems, 0x7fc1, dtype=np.uint16)
@@ -26,12 +27,13 @@ def launches(w, n=6):
     ws = torch.full((size,), 0xff, dtype=torch.uint8, device=DEV)     # NaN wherever nothing is written
     mc.mc_attn_plan(pool.desc, Hq, db.batch, db.total_q, db.cu_q, db.begin, db.page_table, db.cu_pages, ws, size)
     mc.mc_attn_plan_check(ws)
-    q = dev(np.concatenate([w.q(s) for s in range(w.batch)]))
+    q = dev(np.concatenate([w.q(s) for s in range(w.batch)]) if q is None else q)
+    begin = db.begin if begin is None else dev(np.array(begin, np.int32))
     got = []
     for _ in range(n):
-        out = torch.full((db.total_q, Hq, 128), 0x7fc1, dtype=torch.int16, device=DEV)
-        lse = torch.full((db.total_q, Hq), float("nan"), dtype=torch.float32, device=DEV)
-        mc.mc_prefix_prefill_attn(pool.desc, 0, q, Hq, db.batch, db.total_q, db.cu_q, db.begin, db.page_table,
+        out = torch.full((db.total_q, Hq, 128), blank[0], dtype=torch.int16, device=DEV)
+        lse = torch.full((db.total_q, Hq), blank[1], dtype=torch.float32, device=DEV)
+        mc.mc_prefix_prefill_attn(pool.desc, 0, q, Hq, db.batch, db.total_q, db.cu_q, begin, db.page_table,
                                   db.cu_pages, 0.0, out, lse, ws, size)
         got.append((out, lse))
     torch.cuda.synchronize()
@@ -98,3 +100,47 @@ def test_members_with_trees_of_their_own(dtype):
     for s in range(1, 5):
         w.share_prefix(s, 0, 2048)
     assert check(w)[8] > 0
+
+
+# per line: where the chunks of the row of NaN come together
+@pytest.mark.parametrize("dtype", [mi.BF16, mi.F16])
+@pytest.mark.parametrize("Hq,Hkv,lens,new,shared", [
+    (32, 8, [1500, 900], [1, 1], 0),                                    # counted
+    (32, 8, [2100, 1600], [5, 7], 0),                                   # a tree
+    (32, 8, [2300, 2200, 2150], [1, 1, 1], 2048),                       # a prefix, combined in the launch
+    (32, 8, [2100 + 10 * i for i in range(12)], [1] * 12, 2048),        # and behind it
+    (32, 8, [2100, 2600, 3100], [5, 6, 8], 2048),                       # trees of members
+])
+def test_a_row_that_is_not_a_number_is_written_as_such(dtype, Hq, Hkv, lens, new, shared):
+    w = small_workload(1280, dtype, Hq, Hkv, lens, [n - k for n, k in zip(lens, new)])
+    for s in range(1, len(lens) if shared else 0):
+        w.share_prefix(s, 0, shared)
+    q = np.concatenate([w.q(s) for s in range(w.batch)])
+    token, head = int(w.cu_q[1]), 9
+    q[token, head] = 0x7fc1
+    got, h, pool, opool = launches(w, 3, q=q, blank=(0x1111, 7.0))
+    assert h[6] >= w.batch and (h[8] > 0) == (shared > 0), h[:9]
+    for out, lse in got:
+        o, l = oracle.decode(bits(out), dtype), lse.cpu().numpy()
+        assert np.isnan(o[token, head]).all() and np.isnan(l[token, head])
+        o[token, head], l[token, head] = 0, 0
+        for s in range(w.batch):
+            at, n = int(w.cu_q[s]), new[s]
+            ro, rl = oracle.attention(opool, pool.shape, 0, w.page_tables[s], w.q(s), Hq, lens[s] - n, lens[s])
+            if s == 1:
+                ro[0, head], rl[0, head] = 0, 0
+            assert np.max(np.abs(o[at:at + n] - ro)) <= O_TOL, s
+            assert np.max(np.abs(l[at:at + n] - rl)) <= LSE_TOL, s
+
+
+def test_a_row_that_is_not_a_number_beside_chunks_without_a_key():
+    # a tree whose last chunks hold no key (a begin below the planned one), whichever of two comes first
+    w = small_workload(1290, mi.BF16, 32, 8, [4100, 4100], [4092, 4092])
+    q = np.concatenate([w.q(s) for s in range(2)])
+    q[11, 9] = 0x7fc1
+    got, h, _, _ = launches(w, 6, q=q, begin=[700, 1900], blank=(0x1111, 7.0))
+    assert h[6] == 2, h[:9]
+    for out, lse in got:
+        o, l = oracle.decode(bits(out), mi.BF16), lse.cpu().numpy()
+        assert np.isnan(o[11, 9]).all() and np.isnan(l[11, 9])
+        assert np.isnan(o).sum() == 128 and np.isnan(l).sum() == 1
