@@ -1249,8 +1249,14 @@ __device__ __forceinline__ float across_rows(float x, Op&& op) {
 // another, else by the reads themselves.  Walked by one wavefront of four, as items of more rows are
 // (the other three without a row), a piece of two tiles took 5.0 us from the first instruction to the
 // vote at its end, three requests behind the record; here one, the first half tile of every wavefront.
-// What a wavefront has in flight, 16 KiB, is waited for as a whole; then the next half tile's V is
-// requested at once, its K as soon as S has been formed, and eight wavefronts a compute unit keep 128 KiB under way.
+// K and V take turns, 8 KiB in flight for each of a compute unit's eight wavefronts: the next half tile's V
+// is requested and waited for when K has come, then S is formed and the next K requested, which is under way
+// while the softmax and P V run.  More in flight is slower where the reads are the bound: with the next V
+// under way beside K (one wait a half tile, behind the next V's request), or beside S and the next K (no
+// second wait), us a pass of 43 rows over 166..1205 keys, 16 / 8 heads, four layers 143.9 -> 147.2, 148.4;
+// of 64 forks of a 2048-token prompt, 32 / 8, four layers 196.1 -> 200.3, 200.1; of 64 rows over 1024..4096
+// beside a prefill, two layers 328 -> 329, 336; of eight rows over 1024..4096, 64 / 8, eight layers 207.0 ->
+// 205.0, 205.4.
 // A layer (append and attention) of one row over 1000 keys, 32 / 8 heads, 12.9 -> 10.5 us; of eight rows
 // over 1024..4096, 64 / 8 heads, 27.7 -> 25.5; 256 rows, bound by the reads, the same.
 template <typename T, int G>
@@ -1322,6 +1328,13 @@ __device__ __forceinline__ void few_rows_item(const AttnArgs& a, const Item& it,
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     const bool more = h + 4 < n_halves;
     if (more) request_v(next0, next1, buf ^ 1);
+    // (K and q pass through the wait: the compiler, which counts its own loads but not the copies, would
+    // else wait for them once more ahead of S)
+    asm volatile("s_waitcnt vmcnt(0)"
+                 : "+v"(kf[0][0]), "+v"(kf[0][1]), "+v"(kf[0][2]), "+v"(kf[0][3]), "+v"(kf[1][0]), "+v"(kf[1][1]),
+                   "+v"(kf[1][2]), "+v"(kf[1][3]), "+v"(q[0]), "+v"(q[1]), "+v"(q[2]), "+v"(q[3])
+                 :
+                 : "memory");
     f32x4 s[2] = {{0.f, 0.f, 0.f, 0.f}, {0.f, 0.f, 0.f, 0.f}};
 #pragma unroll
     for (int kk = 0; kk < 4; ++kk)
