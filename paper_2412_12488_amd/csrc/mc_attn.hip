@@ -36,6 +36,7 @@
 //     reads (V) spread over all banks.
 #include <math.h>
 
+#include <algorithm>
 #include <atomic>
 #include <mutex>
 #include <type_traits>
@@ -118,14 +119,8 @@ constexpr uint32_t kItemGroup = 1u << 28;
 //     rows are never written.  The last one up has the tile's result in registers.  These rows are
 //     kept as the registers lie, 16 bytes of every row together (by_reg below).
 //   * With a group, the prefix's chunks are counted one by one beside the tile's own (a tree's counting
-//     as one), and the last of them combines.  Their rows lie row by row.  That is for batches of up
-//     to kGroupsInLaunch sequences, whose decode rows share a prefix in items of kFlatRows rows at
-//     most; of larger ones group_merge_kernel combines the members' chunks, in a launch of its own.
-//     A workgroup reads partial rows at 30 GB/s or so, and the last item of a prefix may find every
-//     member waiting: for 24 forks of a 2304-token prompt (32 / 8 heads) it would be alone for 20 us
-//     where the launch takes 5.  (Nor do a tree over the prefix's chunks, 2.4 to 3.7 us a level, or
-//     items of 16 rows, which read the prefix again, make up for it: 64 forks 48, 50 us a layer instead
-//     of 45; 12 forks of 1920 tokens with 53..445 of their own 30, 20 instead of 20.)
+//     as one), and the last of them combines.  Their rows lie row by row.  Where that would take too long
+//     (groups_in_launch) group_merge_kernel combines the members' chunks, in a launch of its own.
 // Which chunk comes last differs from run to run; the sums and their order do not.
 struct MergeRec {
   int32_t q_row;   // index of the tile's first token among all new tokens of the batch
@@ -134,7 +129,20 @@ struct MergeRec {
 };
 static_assert(sizeof(MergeRec) == 32, "merge record is 32 bytes");
 constexpr int kFlatRows = 16;
+// Whether chunks of shared prefixes are combined inside the attention launch: host, plan and kernel agree
+// by the batch's numbers alone.  Few sequences, and no more new tokens than those (some may be idle), which
+// share a prefix in items of about kFlatRows rows.  A workgroup reads partial rows at 30 GB/s or so, and the last item
+// of a prefix may find every member waiting: items of all rows leave it alone for longer than a launch
+// takes.  Append + attention of a layer, 32 / 8 heads, combined in the launch / behind it: 24 forks
+// of a 2304-token prompt, 20 us more for the last item / 5 for the launch; 4 forks of 1024 tokens with 4 new ones
+// each 30.1 / 18.6 us, with 8 48.8 / 20.1, 8 with 4 45.4 / 20.8; 8 / 1 heads, 8 with 4 49.2 / 19.0.  (Nor do a
+// tree over the prefix's chunks, 2.4 to 3.7 us a level, or items of 16 rows in larger batches, which read the
+// prefix again, make up for it: 64 forks 48, 50 us a layer instead of 45; 12 forks of 1920 tokens with 53..445
+// of their own 30, 20 instead of 20.)
 constexpr int kGroupsInLaunch = 8;
+__host__ __device__ constexpr bool groups_in_launch(int32_t batch, int32_t total_q) {
+  return batch <= kGroupsInLaunch && total_q <= batch;
+}
 // Arrivals: per merge record and kv head arrive_words words that the plan clears.  Word 0 counts
 // (and wraps to 0 with the last arrival), the others are the tree, one bit a node (set by the first of
 // two, cleared by the second).  They fill the end of the partial LSE array from its last word downwards, for which the planner
@@ -155,6 +163,12 @@ constexpr int kMinSharedTiles = 8;    // a shared prefix shorter than 512 tokens
 // 5 %); prefill of 512 tokens 20.0 / 23.1 / 25.7, of 4 x 512 27.0 / 40.8 / 40.8.
 constexpr int kMinChunkTiles = 8, kMinChunkTilesDecode = 4, kMinChunkTilesShort = 2;
 constexpr int kMergeAhead = 8;        // partial rows a merge of few rows requests beside their LSEs
+// ... and a merge of a shared prefix's rows, for which its pieces are so long that they and the member's own
+// one are no more, up to pieces of as many tiles.  Append + attention of a layer, 32 / 8 heads, pieces of 4 / 6 /
+// 8 / 12 / 16 tiles: 2 forks of 2048 tokens 12.8 / 13.6 / 14.7 / 16.8 / 19.0 us, of 4096 16.6 / 14.9 / 16.0 / 18.3 /
+// 20.7, of 8192 22.9 / 19.2 / 19.8 / 19.1 / 21.8, of 16384 26.7 / 29.2 / 25.6 / 23.1 / 24.9; 8 of 2048 14.5 / 15.2 /
+// 15.8 / 17.9 / 20.1, of 4096 19.8 / 17.0 / 17.7 / 19.6 / 21.6, of 8192 29.1 / 23.5 / 22.8 / 21.0 / 22.9.
+constexpr int kListedAhead = 12;
 constexpr int kRoundsWanted = 4;      // cut only while the launch has fewer items than 4 per slot
 // ... and then aim for about one item per slot: measured best on decode batches and on 500-token
 // ranges over long contexts (more chunks mean more partial rows to write and merge)
@@ -648,8 +662,20 @@ __global__ __launch_bounds__(NT) void plan_kernel(PlanArgs a) {
 
   // q tile i: its sequence, first row, token count, KV tiles, the last even tile index at which
   // a chunk may start (every row must see at least the first key of every chunk), the prefix
-  // tiles its shared-prefix group covers, and the group's new tokens if this tile leads one
-  struct Tile { int s, row0, ntok, T, dmax, pt, gm; };
+  // tiles its shared-prefix group covers, the group's new tokens if this tile leads one, and those of
+  // the prefix items that the tile leads
+  struct Tile { int s, row0, ntok, T, dmax, pt, gm, gi; };
+  // Prefix items hold the whole group's rows, or where they are combined in the launch (see MergeRec) those
+  // of the members whose first tokens lie in the same kFlatRows rows of it.
+  const bool sliced = groups_in_launch(a.batch, a.total_q);
+  const int slice = max(kFlatRows * a.tile_tokens / kBM, 1);
+  auto slice_tokens = [&](int lead, int sq) {     // of the slice that sequence sq leads, else 0
+    const int first = s_cuq[lead], id = (s_cuq[sq] - first) / slice;
+    if (sq > lead && (s_cuq[sq - 1] - first) / slice == id) return 0;
+    int end = sq + 1;
+    while (end <= s_glast[lead] && (s_cuq[end] - first) / slice == id) ++end;
+    return s_cuq[end] - s_cuq[sq];
+  };
   auto locate = [&](int i) {
     int lo = 0, hi = a.batch;
     while (hi - lo > 1) {
@@ -666,21 +692,17 @@ __global__ __launch_bounds__(NT) void plan_kernel(PlanArgs a) {
     x.dmax = ((b + x.row0) / kBN) & ~1;
     x.pt = groups ? s_gp[lo] : 0;
     x.gm = groups && s_glead[lo] == lo ? s_gsize[lo] : 0;
+    x.gi = !sliced ? x.gm : x.pt > 0 ? slice_tokens(s_glead[lo], lo) : 0;
     return x;
   };
   // (a batch of no more tiles than threads: a thread's tile is the same in every step)
   const bool one_each = total_tiles <= NT;
-  Tile mine = {0, 0, 0, 0, 0, 0, 0};
+  Tile mine = {0, 0, 0, 0, 0, 0, 0, 0};
   if (one_each && t < total_tiles) mine = locate(t);
   auto tile = [&](int i) { return one_each ? mine : locate(i); };
   // own chunks of L tiles (L even) from the end of the group's prefix: [pt, pt+L), ...,
   // [pt+kL, T) with pt + kL <= dmax; the group's prefix itself in chunks of L
   auto own_splits = [&](const Tile& x, int L) { return L > 0 ? (x.dmax - x.pt) / L + 1 : 1; };
-  // Items of a group's prefix: in small batches decode rows share one in items of a few rows (see
-  // MergeRec), tokens `slice` of one.
-  const bool sliced = a.batch <= kGroupsInLaunch && a.total_q <= total_tiles;
-  const int slice = max(kFlatRows * a.tile_tokens / kBM, 1);
-  auto slices = [&](const Tile& x) { return (x.gm + slice - 1) / slice; };
   auto grp_splits = [&](const Tile& x, int L) { return x.pt > 0 ? (L > 0 ? (x.pt + L - 1) / L : 1) : 0; };
   // arrival words per merge record and kv head: a tree over n chunks has up to n + log2(n) nodes; the
   // rows of the partial arrays they take
@@ -706,7 +728,7 @@ __global__ __launch_bounds__(NT) void plan_kernel(PlanArgs a) {
     long long cost = 0;
     for (int i = t; i < total_tiles; i += NT) {
       const Tile x = tile(i);
-      cost += x.T - x.pt + (x.gm ? x.pt : 0);
+      cost += x.T - x.pt + (x.gi ? x.pt : 0);
     }
     cost = block_sum<NT>(cost, scan);
     const long long room = (long long)kItemsPerSlot * a.slots, heads = cost * a.hkv + room - 1;
@@ -721,6 +743,11 @@ __global__ __launch_bounds__(NT) void plan_kernel(PlanArgs a) {
         shortest = min(2 * shortest, kMinChunkTiles);
     }
     L = want < shortest ? shortest : want > (1 << 28) ? (1 << 28) : (int)want;
+    if (groups && sliced) {
+      int longest = 0;
+      for (int sq = 0; sq < a.batch; ++sq) longest = max(longest, s_gp[sq]);
+      L = max(L, min((longest + kListedAhead - 2) / (kListedAhead - 1), kListedAhead));
+    }
     L = (L + 1) & ~1;
     for (;;) {
       if (L >= s_maxcost) { L = 0; break; }   // nothing is long enough to be cut
@@ -731,7 +758,7 @@ __global__ __launch_bounds__(NT) void plan_kernel(PlanArgs a) {
   // without cuts the groups still need partial rows: no room, no groups
   if (L == 0 && groups && total_part_rows(0) > a.part_cap) {
     groups = false;
-    mine.pt = mine.gm = 0;
+    mine.pt = mine.gm = mine.gi = 0;
   }
 
   int shift = 0;
@@ -793,14 +820,14 @@ __global__ __launch_bounds__(NT) void plan_kernel(PlanArgs a) {
   for (int i = i_lo; i < i_hi; ++i) {
     const Tile x = tile(i);
     const int Li = chunk_len(i, x);
-    const int ns = own_splits(x, Li), ng = x.gm ? grp_splits(x, Li) : 0;
-    n_items += ns + (sliced ? ng * slices(x) : ng);
+    const int ns = own_splits(x, Li), ng = x.gi ? grp_splits(x, Li) : 0;
+    n_items += ns + ng;
     if (ns > 1 || x.pt > 0) { n_own += ns * x.ntok; ++n_merge; }
     n_grp += ng * x.gm;
     for (int c = 0; c < ns; ++c)
       atomicAdd(&hist[bucket(c + 1 < ns ? Li : x.T - x.pt - c * Li)], 1);
     for (int c = 0; c < ng; ++c)
-      atomicAdd(&hist[group_bucket(Li > 0 ? min(Li, x.pt - c * Li) : x.pt)], sliced ? slices(x) : 1);
+      atomicAdd(&hist[group_bucket(Li > 0 ? min(Li, x.pt - c * Li) : x.pt)], 1);
   }
   int offs[4] = {n_items, n_own, n_grp, n_merge}, tots[4];
   block_exclusive_scan_n<NT>(offs, scan, tots);
@@ -873,16 +900,12 @@ __global__ __launch_bounds__(NT) void plan_kernel(PlanArgs a) {
       finish(it, x.pt + c * Li, c + 1 < ns ? x.pt + (c + 1) * Li : x.T, sq0 + x.row0, x.ntok,
              merged ? merge_off - 1 : -1, 0);
     }
-    // (sliced: a member is one token, and one merge record)
-    const int per_item = sliced ? slice : x.gm;
-    for (int c = 0; x.gm && c < ng; ++c)
-      for (int i = 0; i < x.gm; i += per_item) {
-        ItemRec it;
-        it.row0 = 0;
-        it.chunk = c;
-        finish(it, c * Li, Li > 0 ? min((c + 1) * Li, x.pt) : x.pt, sq0 + i, min(per_item, x.gm - i),
-               merge_off - 1 + i, kItemGroup);
-      }
+    for (int c = 0; x.gi && c < ng; ++c) {
+      ItemRec it;
+      it.row0 = 0;
+      it.chunk = c;
+      finish(it, c * Li, Li > 0 ? min((c + 1) * Li, x.pt) : x.pt, sq0, x.gi, merge_off - 1, kItemGroup);
+    }
     if (merged) own_off += ns * x.ntok;
   }
   if (t == 0) {
@@ -1020,23 +1043,29 @@ __device__ __forceinline__ void copy16_to_lds(const char* base, uint32_t lane_of
 // ---- partial rows ------------------------------------------------------------------------
 // They are written by one workgroup and read by another of the same launch, on any XCD: through
 // buffer instructions of device scope (sc1), which write to and read from the level all XCDs
-// share, so that no L2 has to be written back or invalidated as a whole.
+// share, so that no L2 has to be written back or invalidated as a whole.  Rows that group_merge_kernel
+// reads go by plain ones (kLaunchScope): the launch's end makes them visible, and an L2 gathers the 16
+// bytes a lane that a row by row store of 32 rows is made of.
 typedef __amdgpu_buffer_rsrc_t buffer_rsrc;
-constexpr int kDeviceScope = 16;          // sc1
+constexpr int kDeviceScope = 16, kLaunchScope = 0;          // sc1, none
 __device__ __forceinline__ buffer_rsrc make_rsrc(void* p, uint32_t bytes) {
   return __builtin_amdgcn_make_buffer_rsrc(p, 0, bytes, 0x00020000);   // raw, 32-bit; bounds checked
 }
-__device__ __forceinline__ void store_device(buffer_rsrc r, uint32_t off, f32x4 v) {
-  __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, v), r, off, 0, kDeviceScope);
+template <int kScope>
+__device__ __forceinline__ void store_part(buffer_rsrc r, uint32_t off, f32x4 v) {
+  __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, v), r, off, 0, kScope);
 }
-__device__ __forceinline__ void store_device(buffer_rsrc r, uint32_t off, float v) {
-  __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(uint32_t, v), r, off, 0, kDeviceScope);
+template <int kScope>
+__device__ __forceinline__ void store_part(buffer_rsrc r, uint32_t off, float v) {
+  __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(uint32_t, v), r, off, 0, kScope);
 }
-__device__ __forceinline__ f32x4 load_device4(buffer_rsrc r, uint32_t off) {
-  return __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(r, off, 0, kDeviceScope));
+template <int kScope>
+__device__ __forceinline__ f32x4 load_part4(buffer_rsrc r, uint32_t off) {
+  return __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(r, off, 0, kScope));
 }
-__device__ __forceinline__ float load_device(buffer_rsrc r, uint32_t off) {
-  return __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(r, off, 0, kDeviceScope));
+template <int kScope>
+__device__ __forceinline__ float load_part(buffer_rsrc r, uint32_t off) {
+  return __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(r, off, 0, kScope));
 }
 
 // Chunks a merge record's last step combines: the prefix's and the tile's own, a tree's counting as one.
@@ -1064,18 +1093,20 @@ __device__ __forceinline__ void chunk_step(float lse, float& mx, float& den, flo
   den = __builtin_fmaf(den, f_old, f_new);
 }
 
-// One kv head's rows of `tokens` tokens from their chunks: with L_c the chunk LSEs, LSE = log sum_c exp(L_c) and O = sum_c exp(L_c - LSE) O_c, chunks in order: those of the
-// group's prefix, then the tile's own.  record(i, first) gives the merge record of token i and the
-// first token of that record.
+// One kv head's rows of `tokens` tokens from their chunks: with L_c the chunk LSEs, LSE = log sum_c
+// exp(L_c) and O = sum_c exp(L_c - LSE) O_c, chunks in order: those of the group's prefix, then the tile's
+// own.  record(i, first) gives the merge record of token i and the first token of that record.  Of `blocks`
+// workgroups that share the rows this is number `block`.
 // A chain of memory round trips and little else, run once by code that is not in the instruction
 // cache: half a wavefront takes a row, 16 bytes a lane; every lane forms the row's weights by itself
 // from LSEs it reads beside the rows (no exchange, no barrier); kRows rows x kChunks chunks are in
 // flight, and nothing but the loop stands under a condition.
-template <typename T, int G, int kRows, int kChunks, typename Record>
+template <typename T, int G, int kScope, int kRows, int kChunks, typename Record>
 __device__ __forceinline__ void merge_rows(const AttnArgs& a, buffer_rsrc rs_o, buffer_rsrc rs_lse,
-                                           int hk, int tokens, Record&& record) {
+                                           int hk, int tokens, int block, int blocks, Record&& record) {
   const int rows = tokens * G, piece = threadIdx.x & 31;
-  for (int r0 = threadIdx.x >> 5; r0 < rows; r0 += kRows * (kThreads / 32)) {
+  for (int r0 = (threadIdx.x >> 5) + block * kRows * (kThreads / 32); r0 < rows;
+       r0 += blocks * kRows * (kThreads / 32)) {
     // per row: chunks, the prefix's among them, partial row and byte of this lane's piece in the first
     // chunk, the same from one chunk to the next
     int nch[kRows], g_nsplit[kRows], out_row[kRows];
@@ -1121,8 +1152,8 @@ __device__ __forceinline__ void merge_rows(const AttnArgs& a, buffer_rsrc rs_o, 
           const int c = min(c0 + k, nch[u] - 1);
           const bool in_group = c < g_nsplit[u];
           const uint32_t on = (in_group ? c : c - g_nsplit[u]) * (in_group ? g_step[u] : own_step[u]);
-          lse[u][k] = load_device(rs_lse, ((in_group ? g_row[u] : own_row[u]) + on) * 4u);
-          o[u][k] = load_device4(rs_o, (in_group ? g_byte[u] : own_byte[u]) + on * 512u);
+          lse[u][k] = load_part<kScope>(rs_lse, ((in_group ? g_row[u] : own_row[u]) + on) * 4u);
+          o[u][k] = load_part4<kScope>(rs_o, (in_group ? g_byte[u] : own_byte[u]) + on * 512u);
         }
 #pragma unroll
       for (int u = 0; u < kRows; ++u)
@@ -1184,6 +1215,11 @@ __device__ __forceinline__ uint32_t first_part_row(const AttnArgs& a, const Item
                   : (m[3] + it.chunk * m[1]) * a.hq + hk * m[1] * G;
 }
 
+// Whether an item's chunk is combined inside this launch; else group_merge_kernel does it behind it.
+__device__ __forceinline__ bool combined_here(const AttnArgs& a, const Item& it, const i32x8& m) {
+  return !(it.group || m[4] > 0) || groups_in_launch(a.batch, a.total_q);
+}
+
 // Counts written rows - a chunk of few rows, a chunk of a prefix (at every member's record), or a tree's
 // result - and, if they were the last there, combines the record's chunks.  s_last: 0, and published;
 // list: free LDS.
@@ -1192,7 +1228,6 @@ __device__ __forceinline__ void arrive(const AttnArgs& a, const Item& it, int hk
                                        buffer_rsrc rs_lse, const i32x8& m, int words, int& s_last,
                                        MergeList& list) {
   const int tid = threadIdx.x;
-  if ((it.group || m[4] > 0) && a.batch > kGroupsInLaunch) return;      // group_merge_kernel's
   const bool listed = it.group || it.ntok * G > kFlatRows;
   uint32_t* arrivals = reinterpret_cast<uint32_t*>(a.part_lse) + (int64_t)a.part_cap * a.hq - 1;
   i32x8 mr = m;
@@ -1217,14 +1252,14 @@ __device__ __forceinline__ void arrive(const AttnArgs& a, const Item& it, int hk
   const int tokens = __builtin_amdgcn_readfirstlane(s_last);
   if (tokens == 0) return;
   if (listed)
-    merge_rows<T, G, 2, 12>(a, rs_o, rs_lse, hk, tokens, [&](int i, int& first) __attribute__((always_inline)) {
+    merge_rows<T, G, kDeviceScope, 2, kListedAhead>(a, rs_o, rs_lse, hk, tokens, 0, 1, [&](int i, int& first) __attribute__((always_inline)) {
       const int k = list.rec_of[i];
       first = list.first[k];
       return *reinterpret_cast<const i32x8*>(list.rec[k]);
     });
   else
-    merge_rows<T, G, 1, kMergeAhead>(a, rs_o, rs_lse, hk, tokens,
-                                     [&](int, int& first) __attribute__((always_inline)) { first = 0; return m; });
+    merge_rows<T, G, kDeviceScope, 1, kMergeAhead>(
+        a, rs_o, rs_lse, hk, tokens, 0, 1, [&](int, int& first) __attribute__((always_inline)) { first = 0; return m; });
 }
 
 // max or sum over the four lanes l, l ^ 16, l ^ 32, l ^ 48: a swap of the wavefront's halves, then one
@@ -1423,9 +1458,12 @@ __device__ __forceinline__ void few_rows_item(const AttnArgs& a, const Item& it,
     }
     const float inv = fits ? 1.f / sum : 0.f, lse = fits ? mx * a.scale + __logf(sum) : -INFINITY;
     acc *= inv;
-    if (it.chunk >= 0) {
-      store_device(rs_o, (part0 + r) * 512u + piece * 16u, acc);
-      if (piece == 0) store_device(rs_lse, (part0 + r) * 4u, lse);
+    if (it.chunk >= 0 && !combined_here(a, it, m)) {
+      store_part<kLaunchScope>(rs_o, (part0 + r) * 512u + piece * 16u, acc);
+      if (piece == 0) store_part<kLaunchScope>(rs_lse, (part0 + r) * 4u, lse);
+    } else if (it.chunk >= 0) {
+      store_part<kDeviceScope>(rs_o, (part0 + r) * 512u + piece * 16u, acc);
+      if (piece == 0) store_part<kDeviceScope>(rs_lse, (part0 + r) * 4u, lse);
     } else {
       const int64_t out_row = (int64_t)(it.q_first + r / G) * a.hq + hk * G + r % G;
       const u32x2 v = {Mfma<T>::pack2(acc[0], acc[1]), Mfma<T>::pack2(acc[2], acc[3])};
@@ -1433,7 +1471,7 @@ __device__ __forceinline__ void few_rows_item(const AttnArgs& a, const Item& it,
       if (piece == 0) a.lse[out_row] = lse;
     }
   }
-  if (it.chunk >= 0)
+  if (it.chunk >= 0 && combined_here(a, it, m))
     arrive<T, G>(a, it, hk, rs_o, rs_lse, m, words, s_last, *reinterpret_cast<MergeList*>(lds));
 }
 
@@ -2029,23 +2067,25 @@ __global__ __launch_bounds__(kThreads, kCB == 1 ? 2 : 1) void attn_kernel(AttnAr
       return Place{row0 * 512u + r * 32u + half * 16, of_rows * 32u};
     };
     auto tile_row = [&](int cb) __attribute__((always_inline)) { return wave * kWaveRows + cb * 32 + l32; };
-    auto write_rows = [&](uint32_t row0, auto&& place) __attribute__((always_inline)) {
+    auto write_rows = [&](uint32_t row0, bool flat, auto scope) __attribute__((always_inline)) {
+      constexpr int kScope = decltype(scope)::value;
 #pragma unroll
       for (int cb = 0; cb < kCB; ++cb) {
         if (!row_live[cb]) continue;
-        const Place at = place(row0, tile_row(cb), rows);
+        const Place at = flat ? by_row(row0, tile_row(cb), rows) : by_reg(row0, tile_row(cb), rows);
 #pragma unroll
         for (int i = 0; i < 16; ++i) {
           const f32x16& o = o_acc[cb][i >> 2];
           const int j = 4 * (i & 3);
-          store_device(rs_o, at.byte + i * at.step, f32x4{o[j], o[j + 1], o[j + 2], o[j + 3]});
+          store_part<kScope>(rs_o, at.byte + i * at.step, f32x4{o[j], o[j + 1], o[j + 2], o[j + 3]});
         }
-        if (half == 0) store_device(rs_lse, (row0 + tile_row(cb)) * 4u, lse_row[cb]);
+        if (half == 0) store_part<kScope>(rs_lse, (row0 + tile_row(cb)) * 4u, lse_row[cb]);
       }
     };
+    constexpr std::integral_constant<int, kDeviceScope> in_launch{};
     auto read_row = [&](Place at, f32x4 (&o)[16]) __attribute__((always_inline)) {
 #pragma unroll
-      for (int i = 0; i < 16; ++i) o[i] = load_device4(rs_o, at.byte + i * at.step);
+      for (int i = 0; i < 16; ++i) o[i] = load_part4<kDeviceScope>(rs_o, at.byte + i * at.step);
     };
 
     if (rows > kFlatRows && !group) {
@@ -2066,7 +2106,7 @@ __global__ __launch_bounds__(kThreads, kCB == 1 ? 2 : 1) void attn_kernel(AttnAr
           bool second = s_second != 0;
           __syncthreads();
           if (!second) {
-            write_rows(chunk0 + (idx << level) * step, by_reg);
+            write_rows(chunk0 + (idx << level) * step, false, in_launch);
             asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
             __syncthreads();
             if (tid == 0) s_second = (atomicXor(word, bit) & bit) != 0;
@@ -2079,7 +2119,7 @@ __global__ __launch_bounds__(kThreads, kCB == 1 ? 2 : 1) void attn_kernel(AttnAr
 #pragma unroll
           for (int cb = 0; cb < kCB; ++cb) {
             if (!row_live[cb]) continue;
-            const float lse = load_device(rs_lse, (other + tile_row(cb)) * 4u);
+            const float lse = load_part<kDeviceScope>(rs_lse, (other + tile_row(cb)) * 4u);
             f32x4 o[16];
             read_row(by_reg(other, tile_row(cb), rows), o);
             if (lse == -INFINITY && lse_row[cb] == -INFINITY) continue;   // neither holds a key of this row
@@ -2104,8 +2144,13 @@ __global__ __launch_bounds__(kThreads, kCB == 1 ? 2 : 1) void attn_kernel(AttnAr
       }
     }
     if (rows <= kFlatRows || group || m[4] > 0) {
-      if (rows <= kFlatRows || group) write_rows(first_part_row<G>(a, it, hk, m), by_row);
-      else write_rows(chunk0, by_reg);
+      const bool flat = rows <= kFlatRows || group;
+      const uint32_t row0 = flat ? first_part_row<G>(a, it, hk, m) : chunk0;
+      if (!combined_here(a, it, m)) {
+        write_rows(row0, flat, std::integral_constant<int, kLaunchScope>{});
+        return;
+      }
+      write_rows(row0, flat, in_launch);
       arrive<T, G>(a, it, hk, rs_o, rs_lse, m, words, s_last, *reinterpret_cast<MergeList*>(lds));
       return;
     }
@@ -2153,8 +2198,8 @@ __global__ __launch_bounds__(kThreads, kCB == 1 ? 2 : 1) void attn_kernel(AttnAr
   }
 }
 
-// The members of shared-prefix groups in batches of more than kGroupsInLaunch sequences: a workgroup
-// per merge record and kv head.  (It does nothing where the plan found no group.)
+// The members of shared-prefix groups that attn_kernel's launch does not combine: a workgroup per merge
+// record, kv head and 8 rows.  (It does nothing where the plan found no group.)
 template <typename T, int G>
 __global__ __launch_bounds__(kThreads) void group_merge_kernel(AttnArgs a) {
   const i32x8 hdr = *(const __attribute__((address_space(4))) i32x8*)a.hdr;
@@ -2167,8 +2212,7 @@ __global__ __launch_bounds__(kThreads) void group_merge_kernel(AttnArgs a) {
     const i32x8 m = *(const __attribute__((address_space(4))) i32x8*)(a.merges + rec);
     if (m[4] == 0) continue;
     auto one = [&](int, int& first) __attribute__((always_inline)) { first = 0; return m; };
-    if (m[1] * G <= kThreads / 32) merge_rows<T, G, 1, kMergeAhead>(a, rs_o, rs_lse, hk, m[1], one);
-    else merge_rows<T, G, 4, 4>(a, rs_o, rs_lse, hk, m[1], one);
+    merge_rows<T, G, kLaunchScope, 1, kMergeAhead>(a, rs_o, rs_lse, hk, m[1], blockIdx.y, gridDim.y, one);
   }
 }
 
@@ -2237,14 +2281,12 @@ bool may_group(const WorkspaceLayout& w, int32_t total_q, int tile_tokens) {
 
 // Upper bound of the planner's item count: a q tile with T KV tiles becomes at most T / L + 1
 // items, and the planner's chunk length L is at least (sum of T) x hkv / (kItemsPerSlot x slots); the
-// remainder round adds fewer than slots / hkv.  A shared-prefix group adds at most one item per
-// sequence beyond that, and where its decode rows go in items of few rows, as many more for each.
-int32_t item_bound(const WorkspaceLayout& w, int G, int hkv, int slots, bool groups) {
+// remainder round adds fewer than slots / hkv.  The prefix of a group (or of a slice of one, whose tiles
+// are in that sum too) adds at most one item per sequence beyond that.
+int32_t item_bound(const WorkspaceLayout& w, int hkv, int slots, bool groups) {
   int64_t b = w.max_tiles;
   if (may_cut(w, hkv, slots)) b += (int64_t)kItemsPerSlot * slots / hkv + 1;
   if (groups) b += w.batch;
-  if (groups && w.batch <= kGroupsInLaunch)
-    b += ((w.batch * G + kFlatRows - 1) / kFlatRows - 1) * ((int64_t)kItemsPerSlot * slots / hkv + w.batch);
   return (int32_t)(b < w.max_items ? b : w.max_items);
 }
 
@@ -2301,7 +2343,7 @@ mc_status plan_impl(const mc_pool_desc* pool, int32_t num_q_heads, int32_t batch
   a.wide_tile_tokens = wide ? 2 * tile_tokens : 0;
   a.slots_wide = device_slots(2);
   a.allow_groups = may_group(w, total_q, tile_tokens);
-  a.max_items = item_bound(w, G, a.hkv, a.slots, a.allow_groups);
+  a.max_items = item_bound(w, a.hkv, a.slots, a.allow_groups);
   a.part_cap = w.part_cap;
   a.ahead = ahead_tokens;
   // (few sequences only: the page-id checks and the table comparisons of shared prefixes go
@@ -2343,7 +2385,7 @@ mc_status attn_impl(const mc_pool_desc* pool, int32_t layer, const void* q, int3
   if (slots <= 0) return MC_ERR_HIP;
   const bool groups = may_group(w, total_q, tile_tokens);
   const int64_t blocks =
-      (int64_t)item_bound(w, G, pool->num_kv_heads, slots, groups) * pool->num_kv_heads;
+      (int64_t)item_bound(w, pool->num_kv_heads, slots, groups) * pool->num_kv_heads;
   if (blocks > 0x7fffffffll) return MC_ERR_UNSUPPORTED;
   char* ws = static_cast<char*>(workspace);
   AttnArgs a;
@@ -2382,11 +2424,13 @@ mc_status attn_impl(const mc_pool_desc* pool, int32_t layer, const void* q, int3
     st = pool->dtype == MC_F16 ? launch_attn<_Float16>(G, false, 2, grid, hs, a)
                                : launch_attn<__bf16>(G, false, 2, grid, hs, a);
   }
-  if (st != MC_OK || !groups || batch <= kGroupsInLaunch) return st;
+  if (st != MC_OK || !groups || groups_in_launch(batch, total_q)) return st;
   // the planner may have found shared prefixes: their members' chunks are combined (one workgroup a
   // sequence and kv head if they all run at once, else a grid-stride walk)
   const int64_t pairs = (int64_t)batch * pool->num_kv_heads;
-  const dim3 mgrid((unsigned)(pairs < 4ll * slots ? pairs : 4ll * slots));
+  const int rows = (total_q + batch - 1) / batch * G, per_block = kThreads / 32;
+  const dim3 mgrid((unsigned)(pairs < 4ll * slots ? pairs : 4ll * slots),
+                   (unsigned)std::min((rows + per_block - 1) / per_block, kBM / per_block));
   if (pool->dtype == MC_F16) launch_group_merge<_Float16>(G, mgrid, hs, a);
   else launch_group_merge<__bf16>(G, mgrid, hs, a);
   return mc::launch_status();

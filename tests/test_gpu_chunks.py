@@ -144,3 +144,43 @@ def test_a_row_that_is_not_a_number_beside_chunks_without_a_key():
         o, l = oracle.decode(bits(out), mi.BF16), lse.cpu().numpy()
         assert np.isnan(o[11, 9]).all() and np.isnan(l[11, 9])
         assert np.isnan(o).sum() == 128 and np.isnan(l).sum() == 1
+
+
+def forks(seed, dtype, Hq, Hkv, shared, own, new):
+    """One workload of forks: own[i] tokens of sequence i lie between the prefix and its new[i]."""
+    begins = [shared + o for o in own]
+    w = small_workload(seed, dtype, Hq, Hkv, [b + n for b, n in zip(begins, new)], begins)
+    for s in range(1, len(own)):
+        w.share_prefix(s, 0, shared)
+    return w
+
+
+# up to 8 sequences with no more new tokens than those: combined in the launch, prefix items of members
+# whose first tokens lie in the same 16 rows; with more new tokens: behind it
+@pytest.mark.parametrize("dtype", [mi.BF16, mi.F16])
+@pytest.mark.parametrize("Hq,Hkv,new", [
+    (32, 8, [1] * 8), (64, 8, [1] * 8), (8, 8, [1] * 7),        # 4, 2, 16 tokens an item
+    (64, 8, [2, 1, 1, 1, 1, 1, 1, 0]),                          # an idle sequence, a member of two tokens
+    (64, 8, [3, 1, 1, 1, 1, 0, 1]), (64, 8, [1, 3, 1, 1, 0, 0]),    # of three: 24 rows an item, 32; two groups
+    (32, 8, [7, 1, 0, 0, 0, 0, 0, 0]),                          # 32 rows, members by a tree
+    (32, 8, [2, 1]), (32, 8, [2, 2, 2, 2]), (64, 8, [5, 8, 3]), (8, 8, [17, 30, 2, 1, 9]),
+])
+def test_small_batches_that_share_a_prefix(dtype, Hq, Hkv, new):
+    own = [5, 300, 64, 1200, 17, 40, 700, 2][:len(new)]
+    h = check(forks(1300 + len(new), dtype, Hq, Hkv, 1600, own, new))
+    assert h[8] > 0, h[:9]
+
+
+@pytest.mark.parametrize("tiles,chunk", [(44, 4), (46, 6), (64, 6), (68, 8), (130, 12), (140, 12)])
+def test_pieces_of_a_prefix_combined_in_the_launch(tiles, chunk):
+    # no more than eleven beside the member's own, up to pieces of twelve tiles
+    w = forks(1320, mi.BF16, 8, 1, 64 * tiles, [9, 70, 30], [1, 1, 1])
+    assert check(w, 2)[7] == chunk
+
+
+@pytest.mark.parametrize("new", [6, 15])
+def test_trees_of_members_in_larger_batches(new):
+    # own middle parts of up to five chunks: combined in a tree, read by the launch behind it, or all there
+    own = [0, 300, 2700, 40, 1300, 700, 90, 2000, 10, 550, 64]
+    w = forks(1330 + new, mi.BF16, 32, 8, 1600, own, [new + i % 2 for i in range(len(own))])
+    assert check(w)[8] > 0
