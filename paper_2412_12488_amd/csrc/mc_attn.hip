@@ -453,7 +453,9 @@ __global__ __launch_bounds__(NT) void plan_kernel(PlanArgs a) {
   auto beg = [&](int i) { return cu_in_lds ? s_beg[i] : a.begin[i]; };
   const int per = (a.batch + NT - 1) / NT;
   const int s_lo = min(t * per, a.batch), s_hi = min(s_lo + per, a.batch);
-  // 0. q tile width: wide tiles when a new token sees kWideMinKeys keys on average
+  // 0. q tile width: wide tiles when a new token sees kWideMinKeys keys on average.  Their ranges are not
+  //    cut: the host allows them where there are four a compute unit of a 256-unit GPU.
+  bool wide = false;
   if (a.wide_tile_tokens > 0) {
     long long keys = 0, rows = 0;
     for (int s = s_lo; s < s_hi; ++s) {
@@ -465,6 +467,7 @@ __global__ __launch_bounds__(NT) void plan_kernel(PlanArgs a) {
     if (rows > 0 && keys / rows >= kWideMinKeys) {
       a.tile_tokens = a.wide_tile_tokens;
       a.slots = a.slots_wide;
+      wide = true;
     }
   }
   // 1. validate, count tiles per sequence (contiguous chunk of sequences per thread)
@@ -724,7 +727,7 @@ __global__ __launch_bounds__(NT) void plan_kernel(PlanArgs a) {
   //    below the shortest piece of this kind of batch, doubled until the partial rows fit the
   //    workspace.
   int L = 0;
-  if ((int64_t)total_tiles * a.hkv < (int64_t)kRoundsWanted * a.slots) {
+  if (!wide && (int64_t)total_tiles * a.hkv < (int64_t)kRoundsWanted * a.slots) {
     long long cost = 0;
     for (int i = t; i < total_tiles; i += NT) {
       const Tile x = tile(i);
@@ -777,7 +780,7 @@ __global__ __launch_bounds__(NT) void plan_kernel(PlanArgs a) {
     const int rem = (int)(n % a.slots);
     const int rem_tiles = rem / a.hkv;
     const int c = rem > 0 ? min(8, (a.slots + rem - 1) / rem) : 0;
-    if (L == 0 && !groups && total_tiles <= kTailTilesMax && n >= a.slots &&
+    if (L == 0 && !groups && !wide && total_tiles <= kTailTilesMax && n >= a.slots &&
         n < (int64_t)kRoundsWanted * a.slots && rem_tiles >= 1 && 10 * rem <= 7 * a.slots && c >= 2 &&
         (int64_t)rem_tiles * (a.tile_tokens * c + arrive_rows(0)) <= a.part_cap) {
       if (t == 0) { s_tail_bucket = kBuckets; s_tail_take = 0; s_tail_taken = 0; }
@@ -1545,7 +1548,7 @@ __global__ __launch_bounds__(kThreads, kCB == 1 ? 2 : 1) void attn_kernel(AttnAr
   const bool odd = ((unsigned)seq >= (unsigned)a.batch) | (row0 < 0) | (t1 <= t0) | (ntok > TOK) |
                    (q_first < 0) | ((int64_t)q_first + ntok > a.total_q) | (table_off < 0) |
                    ((chunk >= 0) & ((unsigned)merge >= (unsigned)hdr[6])) |
-                   (group & (kCB != 1 || chunk < 0));   // (wide q tiles and groups exclude each other)
+                   (group & (chunk < 0)) | (kCB != 1 & chunk >= 0);   // (ranges of wide q tiles are never cut)
   if (odd) return;
   // begin is read here, not taken from the plan (one plan may serve many decode steps)
   const int b = ((const_i32_ptr)a.begin)[seq];
@@ -2041,7 +2044,7 @@ __global__ __launch_bounds__(kThreads, kCB == 1 ? 2 : 1) void attn_kernel(AttnAr
     }
   }
 
-  if (chunk >= 0) {
+  if (kCB == 1 && chunk >= 0) {
     // ---- one of several chunks (see MergeRec).  Partial rows reach the memory all XCDs see before
     //      the workgroup says so, and are read after the word that says so.  Nobody waits for anybody.
     //      As a launch of its own behind this one, reading every partial row, the merge took 3.6 us of the
@@ -2156,7 +2159,7 @@ __global__ __launch_bounds__(kThreads, kCB == 1 ? 2 : 1) void attn_kernel(AttnAr
     }
   }
   if (kGate && !wave_active) return;
-  if (chunk >= 0) {      // no chunk of these rows was computed: nothing is written
+  if (kCB == 1 && chunk >= 0) {      // no chunk of these rows was computed: nothing is written
     bool some = false;
 #pragma unroll
     for (int cb = 0; cb < kCB; ++cb) some |= row_live[cb] && lse_row[cb] != -INFINITY;
