@@ -16,9 +16,9 @@
 //   * attn_kernel: one workgroup (4 wavefronts of 64) per (item, kv head), so every
 //     K/V byte staged in LDS serves the whole GQA group.  Items that cover a whole
 //     range write out/lse; the others write partial rows, which the last of a q
-//     tile's items to finish weighs together by their log-sum-exp (the members of
-//     shared prefixes in larger batches: group_merge_kernel).  Items of at most 16
-//     rows (decode steps) go another way through the kernel, few_rows_item.
+//     tile's items to finish weighs together by their log-sum-exp (where that would
+//     take longer than a launch: merge_kernel).  Items of at most 16 rows (decode
+//     steps) go another way through the kernel, few_rows_item.
 // Kernel shape
 //   * the KV loop walks 64-key tiles (4 pages) through the page table; each page
 //     contributes one contiguous 4 KiB run of K and one of V for this kv head.
@@ -115,12 +115,15 @@ constexpr uint32_t kItemGroup = 1u << 28;
 //   * Chunks of up to kFlatRows rows (decode steps): every item writes its rows and counts itself; the
 //     last one reads all the others'.
 //   * Chunks of more rows: a binary tree over the chunks.  Of two neighbours the first to be done
-//     writes its rows and ends, the second reads them, combines, and goes on one level up; half of the
-//     rows are never written.  The last one up has the tile's result in registers.  These rows are
-//     kept as the registers lie, 16 bytes of every row together (by_reg below).
+//     writes its rows and ends, the second reads them, combines, and goes on one level up: of n chunks n - 1
+//     are written and read (up to twice as many written, where neighbours miss each other), but not by one
+//     workgroup after each other, and the last one up has the tile's result in registers.  These rows
+//     are kept as the registers lie, 16 bytes of every row together (by_reg below).
 //   * With a group, the prefix's chunks are counted one by one beside the tile's own (a tree's counting
-//     as one), and the last of them combines.  Their rows lie row by row.  Where that would take too long
-//     (groups_in_launch) group_merge_kernel combines the members' chunks, in a launch of its own.
+//     as one), and the last of them combines.  Their rows lie row by row.
+//   * What the launch would combine too slowly merge_kernel combines, in a launch of its own behind it: the
+//     chunks of members of groups and of trees, as the host's rules below say.  These rows lie row by row
+//     (a tree's result beside a group's excepted).
 // Which chunk comes last differs from run to run; the sums and their order do not.
 struct MergeRec {
   int32_t q_row;   // index of the tile's first token among all new tokens of the batch
@@ -129,6 +132,7 @@ struct MergeRec {
 };
 static_assert(sizeof(MergeRec) == 32, "merge record is 32 bytes");
 constexpr int kFlatRows = 16;
+constexpr int kGroupsBehind = 1, kTreesBehind = 2;   // what is left to merge_kernel
 // Whether chunks of shared prefixes are combined inside the attention launch: host, plan and kernel agree
 // by the batch's numbers alone.  Few sequences, and no more new tokens than those (some may be idle), which
 // share a prefix in items of about kFlatRows rows.  A workgroup reads partial rows at 30 GB/s or so, and the last item
@@ -143,10 +147,20 @@ constexpr int kGroupsInLaunch = 8;
 __host__ __device__ constexpr bool groups_in_launch(int32_t batch, int32_t total_q) {
   return batch <= kGroupsInLaunch && total_q <= batch;
 }
+// Whether trees are left to merge_kernel: where the q tiles x kv heads are so few that a tile has many chunks,
+// whose levels follow one another, 2 to 3 us each.  The host does not know how many, and the launch costs 1.3
+// to 2.2 us where nothing was cut (up to 512 keys): a launch of its own only up to a 64th of the slots (8 of
+// 512).  Append + attention of a layer, by trees / behind, over 600, 1100, 1500, 3000, 6000 keys: 8
+// (32 / 8 heads, 16 new tokens) 16.6 / 17.8, 19.1 / 17.8, 19.1 / 18.7, 22.8 / 19.6, 28.6 / 21.3 us; 16 (64) 17.1 /
+// 19.5, 20.7 / 20.3, 21.6 / 22.4, 24.9 / 22.3, 30.5 / 25.0; 32 (128) 17.2 / 20.7, 21.8 / 21.6, 23.5 / 23.1, 27.5 /
+// 24.5, 40.6 / 35.2; 64 (256) 19.0 / 22.4, 22.2 / 23.9, 24.2 / 24.7, 34.5 / 34.5, 46.3 / 46.3.  Where groups bring
+// the launch anyway, up to a 12th (42): over 700, 1500, 5000 keys, 40 (4 x 40 tokens) 22.3 / 23.4, 27.1 / 25.2,
+// 47.2 / 41.1; 48 (12 x 16) 23.5 / 24.8, 35.7 / 35.4, 65.4 / 64.0; 80 (8 x 40) 24.1 / 27.3, 33.6 / 35.5, 59.0 / 60.9.
+inline bool trees_behind(int64_t tiles, int slots, bool groups) { return tiles * (groups ? 12 : 64) <= slots; }
 // Arrivals: per merge record and kv head arrive_words words that the plan clears.  Word 0 counts
 // (and wraps to 0 with the last arrival), the others are the tree, one bit a node (set by the first of
-// two, cleared by the second).  They fill the end of the partial LSE array from its last word downwards, for which the planner
-// leaves rows of that array (hq >= hkv words each) unused.
+// two, cleared by the second).  They fill the end of the partial LSE array from its last word
+// downwards, for which the planner leaves rows of that array (hq >= hkv words each) unused.
 
 constexpr int kCuTilesInLds = 1024;
 constexpr int kValidateInPlan = 256;  // batches up to this have their page ids checked by plan_kernel
@@ -404,7 +418,6 @@ __global__ __launch_bounds__(256) void validate_pages_kernel(PlanArgs a) {
   if (__ballot(err) != 0 && lane == 0) {
     a.hdr->num_items = 0;
     a.hdr->num_merges = 0;
-   
     a.hdr->err = MC_ERR_RANGE;
   }
 }
@@ -988,11 +1001,12 @@ struct AttnArgs {
   const PlanHeader* hdr;
   const ItemRec* items;
   const MergeRec* merges;
-  float* part_lse;         // [partial row][hq], the arrival counts at its end
-  float* part_o;           // [partial row][hq][128]
+  float* part_lse;         // of every partial row (see MergeRec); the arrival words at its end
+  float* part_o;           // [partial row][128]
   int64_t page_stride;     // bytes
   int32_t num_pages, hkv, hq, batch, total_q;
   int32_t part_cap;        // rows of the partial arrays
+  int32_t behind;          // what merge_kernel combines (see MergeRec): kGroupsBehind, kTreesBehind
   float scale, scale_log2;  // softmax scale, and scale * log2(e)
 };
 
@@ -1046,7 +1060,7 @@ __device__ __forceinline__ void copy16_to_lds(const char* base, uint32_t lane_of
 // ---- partial rows ------------------------------------------------------------------------
 // They are written by one workgroup and read by another of the same launch, on any XCD: through
 // buffer instructions of device scope (sc1), which write to and read from the level all XCDs
-// share, so that no L2 has to be written back or invalidated as a whole.  Rows that group_merge_kernel
+// share, so that no L2 has to be written back or invalidated as a whole.  Rows that merge_kernel
 // reads go by plain ones (kLaunchScope): the launch's end makes them visible, and an L2 gathers the 16
 // bytes a lane that a row by row store of 32 rows is made of.
 typedef __amdgpu_buffer_rsrc_t buffer_rsrc;
@@ -1071,9 +1085,11 @@ __device__ __forceinline__ float load_part(buffer_rsrc r, uint32_t off) {
   return __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(r, off, 0, kScope));
 }
 
-// Chunks a merge record's last step combines: the prefix's and the tile's own, a tree's counting as one.
+// Chunks of a tile's own that a merge record's last step combines (a tree's count as one).
 template <int G>
-__device__ __forceinline__ int own_chunks(int nsplit, int ntok) { return ntok * G <= kFlatRows ? nsplit : 1; }
+__device__ __forceinline__ int own_chunks(bool trees, int nsplit, int ntok) {
+  return ntok * G <= kFlatRows || !trees ? nsplit : 1;
+}
 
 // What a workgroup was the last to arrive at, in LDS (the tiles are consumed): the merge records, the
 // first token of each among all whose rows are to be combined, and the record a token belongs to.
@@ -1099,14 +1115,15 @@ __device__ __forceinline__ void chunk_step(float lse, float& mx, float& den, flo
 // One kv head's rows of `tokens` tokens from their chunks: with L_c the chunk LSEs, LSE = log sum_c
 // exp(L_c) and O = sum_c exp(L_c - LSE) O_c, chunks in order: those of the group's prefix, then the tile's
 // own.  record(i, first) gives the merge record of token i and the first token of that record.  Of `blocks`
-// workgroups that share the rows this is number `block`.
+// workgroups that share the rows this is number `block`; trees: chunks of many rows have gone up a tree.
 // A chain of memory round trips and little else, run once by code that is not in the instruction
 // cache: half a wavefront takes a row, 16 bytes a lane; every lane forms the row's weights by itself
 // from LSEs it reads beside the rows (no exchange, no barrier); kRows rows x kChunks chunks are in
 // flight, and nothing but the loop stands under a condition.
 template <typename T, int G, int kScope, int kRows, int kChunks, typename Record>
 __device__ __forceinline__ void merge_rows(const AttnArgs& a, buffer_rsrc rs_o, buffer_rsrc rs_lse,
-                                           int hk, int tokens, int block, int blocks, Record&& record) {
+                                           int hk, int tokens, bool trees, int block, int blocks,
+                                           Record&& record) {
   const int rows = tokens * G, piece = threadIdx.x & 31;
   for (int r0 = (threadIdx.x >> 5) + block * kRows * (kThreads / 32); r0 < rows;
        r0 += blocks * kRows * (kThreads / 32)) {
@@ -1125,12 +1142,12 @@ __device__ __forceinline__ void merge_rows(const AttnArgs& a, buffer_rsrc rs_o, 
       const int tt = i - first;
       // row r of the chunk whose rows, of_rows of them, start at row0
       auto place = [&](uint32_t row0, int r, int of_rows) __attribute__((always_inline)) {
-        return row0 * 512u + (of_rows <= kFlatRows
+        return row0 * 512u + (of_rows <= kFlatRows || !trees
                                   ? r * 512u + piece * 16u
                                   : (piece >> 1) * of_rows * 32u + r * 32u + (piece & 1) * 16u);
       };
       g_nsplit[u] = m[4];
-      nch[u] = own_chunks<G>(m[2], m[1]) + m[4];
+      nch[u] = own_chunks<G>(trees, m[2], m[1]) + m[4];
       const uint32_t g0 = m[5] * a.hq + hk * m[6] * G, own0 = m[3] * a.hq + hk * m[1] * G;
       const int g_r = (m[7] + tt) * G + r % G, own_r = tt * G + r % G;
       g_row[u] = g0 + g_r;
@@ -1207,6 +1224,7 @@ __device__ __forceinline__ float max3(float a, float b, float c) {
 // What an item needs of its record.
 struct Item {
   int t0, t1, chunk, q_first, ntok, table_off, pidx_cap, merge, n_rec;   // n_rec: merge records there are
+  int behind;
   bool group;
 };
 
@@ -1218,9 +1236,10 @@ __device__ __forceinline__ uint32_t first_part_row(const AttnArgs& a, const Item
                   : (m[3] + it.chunk * m[1]) * a.hq + hk * m[1] * G;
 }
 
-// Whether an item's chunk is combined inside this launch; else group_merge_kernel does it behind it.
-__device__ __forceinline__ bool combined_here(const AttnArgs& a, const Item& it, const i32x8& m) {
-  return !(it.group || m[4] > 0) || groups_in_launch(a.batch, a.total_q);
+// Whether a chunk that is no tree's is combined inside this launch; else merge_kernel does it behind it.
+template <int G>
+__device__ __forceinline__ bool combined_here(const Item& it, const i32x8& m) {
+  return it.group || m[4] > 0 ? !(it.behind & kGroupsBehind) : it.ntok * G <= kFlatRows;
 }
 
 // Counts written rows - a chunk of few rows, a chunk of a prefix (at every member's record), or a tree's
@@ -1239,7 +1258,7 @@ __device__ __forceinline__ void arrive(const AttnArgs& a, const Item& it, int hk
   __syncthreads();
   // records of this item: one, or the group's members' (their tokens follow one another)
   if (tid < (it.group ? it.ntok : 1) && it.merge + tid < it.n_rec && mr[0] < it.q_first + it.ntok) {
-    const int n = own_chunks<G>(mr[2], mr[1]) + mr[4];
+    const int n = own_chunks<G>(true, mr[2], mr[1]) + mr[4];
     if (atomicInc(arrivals - ((int64_t)(it.merge + tid) * a.hkv + hk) * words, n - 1) == (unsigned)n - 1) {
       const int at = atomicAdd(&s_last, mr[1]);
       if (listed) {
@@ -1255,14 +1274,15 @@ __device__ __forceinline__ void arrive(const AttnArgs& a, const Item& it, int hk
   const int tokens = __builtin_amdgcn_readfirstlane(s_last);
   if (tokens == 0) return;
   if (listed)
-    merge_rows<T, G, kDeviceScope, 2, kListedAhead>(a, rs_o, rs_lse, hk, tokens, 0, 1, [&](int i, int& first) __attribute__((always_inline)) {
+    merge_rows<T, G, kDeviceScope, 2, kListedAhead>(
+        a, rs_o, rs_lse, hk, tokens, true, 0, 1, [&](int i, int& first) __attribute__((always_inline)) {
       const int k = list.rec_of[i];
       first = list.first[k];
       return *reinterpret_cast<const i32x8*>(list.rec[k]);
     });
   else
     merge_rows<T, G, kDeviceScope, 1, kMergeAhead>(
-        a, rs_o, rs_lse, hk, tokens, 0, 1, [&](int, int& first) __attribute__((always_inline)) { first = 0; return m; });
+        a, rs_o, rs_lse, hk, tokens, true, 0, 1, [&](int, int& first) __attribute__((always_inline)) { first = 0; return m; });
 }
 
 // max or sum over the four lanes l, l ^ 16, l ^ 32, l ^ 48: a swap of the wavefront's halves, then one
@@ -1461,7 +1481,7 @@ __device__ __forceinline__ void few_rows_item(const AttnArgs& a, const Item& it,
     }
     const float inv = fits ? 1.f / sum : 0.f, lse = fits ? mx * a.scale + __logf(sum) : -INFINITY;
     acc *= inv;
-    if (it.chunk >= 0 && !combined_here(a, it, m)) {
+    if (it.chunk >= 0 && !combined_here<G>(it, m)) {
       store_part<kLaunchScope>(rs_o, (part0 + r) * 512u + piece * 16u, acc);
       if (piece == 0) store_part<kLaunchScope>(rs_lse, (part0 + r) * 4u, lse);
     } else if (it.chunk >= 0) {
@@ -1474,7 +1494,7 @@ __device__ __forceinline__ void few_rows_item(const AttnArgs& a, const Item& it,
       if (piece == 0) a.lse[out_row] = lse;
     }
   }
-  if (it.chunk >= 0 && combined_here(a, it, m))
+  if (it.chunk >= 0 && combined_here<G>(it, m))
     arrive<T, G>(a, it, hk, rs_o, rs_lse, m, words, s_last, *reinterpret_cast<MergeList*>(lds));
 }
 
@@ -1522,6 +1542,8 @@ __global__ __launch_bounds__(kThreads, kCB == 1 ? 2 : 1) void attn_kernel(AttnAr
   const auto* rec = (const __attribute__((address_space(4))) i32x8*)(a.items + wi);
   i32x8 item = rec[0], item_b = rec[1];
   i32x8 hdr = *(const __attribute__((address_space(4))) i32x8*)a.hdr;
+  int behind = a.behind;
+  asm volatile("" : "+s"(behind));
   asm volatile("" ::"s"(a.pool_layer), "s"(a.begin), "s"(a.q), "s"(a.num_pages), "s"(a.total_q));
   asm volatile("" : "+s"(item), "+s"(item_b), "+s"(hdr));
   // the work list must come from a plan made for this very batch
@@ -1552,7 +1574,7 @@ __global__ __launch_bounds__(kThreads, kCB == 1 ? 2 : 1) void attn_kernel(AttnAr
   if (odd) return;
   // begin is read here, not taken from the plan (one plan may serve many decode steps)
   const int b = ((const_i32_ptr)a.begin)[seq];
-  const Item it = {t0, t1, chunk, q_first, ntok, table_off, pidx_cap, merge, hdr[6], group};
+  const Item it = {t0, t1, chunk, q_first, ntok, table_off, pidx_cap, merge, hdr[6], behind, group};
   if (kGate && ntok * G <= kFlatRows) {
     __shared__ float s_stat[2 * 4 * kFlatRows];   // maximum and sum per wavefront and row
     few_rows_item<T, G>(a, it, hk, b, row0, item_b, lds, s_stat, s_last);
@@ -2091,7 +2113,8 @@ __global__ __launch_bounds__(kThreads, kCB == 1 ? 2 : 1) void attn_kernel(AttnAr
       for (int i = 0; i < 16; ++i) o[i] = load_part4<kDeviceScope>(rs_o, at.byte + i * at.step);
     };
 
-    if (rows > kFlatRows && !group) {
+    const bool tree = rows > kFlatRows && !group && !(behind & kTreesBehind);
+    if (tree) {
       uint32_t* word0 = reinterpret_cast<uint32_t*>(a.part_lse) + (int64_t)a.part_cap * a.hq - 1 -
                         ((int64_t)merge * a.hkv + hk) * words - 1;
       int idx = chunk, count = m[2], node0 = 0;
@@ -2146,14 +2169,13 @@ __global__ __launch_bounds__(kThreads, kCB == 1 ? 2 : 1) void attn_kernel(AttnAr
         idx >>= 1;
       }
     }
-    if (rows <= kFlatRows || group || m[4] > 0) {
-      const bool flat = rows <= kFlatRows || group;
-      const uint32_t row0 = flat ? first_part_row<G>(a, it, hk, m) : chunk0;
-      if (!combined_here(a, it, m)) {
-        write_rows(row0, flat, std::integral_constant<int, kLaunchScope>{});
+    if (!tree || m[4] > 0) {
+      const uint32_t row0 = tree ? chunk0 : first_part_row<G>(a, it, hk, m);
+      if (!combined_here<G>(it, m)) {
+        write_rows(row0, !tree, std::integral_constant<int, kLaunchScope>{});
         return;
       }
-      write_rows(row0, flat, in_launch);
+      write_rows(row0, !tree, in_launch);
       arrive<T, G>(a, it, hk, rs_o, rs_lse, m, words, s_last, *reinterpret_cast<MergeList*>(lds));
       return;
     }
@@ -2201,31 +2223,36 @@ __global__ __launch_bounds__(kThreads, kCB == 1 ? 2 : 1) void attn_kernel(AttnAr
   }
 }
 
-// The members of shared-prefix groups that attn_kernel's launch does not combine: a workgroup per merge
-// record, kv head and 8 rows.  (It does nothing where the plan found no group.)
+// The chunks that attn_kernel's launch does not combine: a workgroup per merge record, 8 rows and kv head
+// (`blocks` of them share a record's rows), or as many in turn.  It does nothing where the plan found no
+// group or cut nothing, which takes the longer the more workgroups have to find that out.
 template <typename T, int G>
-__global__ __launch_bounds__(kThreads) void group_merge_kernel(AttnArgs a) {
+__global__ __launch_bounds__(kThreads) void merge_kernel(AttnArgs a, int blocks) {
   const i32x8 hdr = *(const __attribute__((address_space(4))) i32x8*)a.hdr;
-  const int group_rows = ((const_i32_ptr)a.hdr)[8];
-  if (hdr[0] != kPlanMagic || group_rows == 0 || hdr[4] != a.batch || hdr[5] != a.total_q) return;
+  const bool trees = !(a.behind & kTreesBehind);
+  const bool none = hdr[6] == 0 || (((const_i32_ptr)a.hdr)[8] == 0 && trees);
+  if (hdr[0] != kPlanMagic || none || hdr[4] != a.batch || hdr[5] != a.total_q) return;
   const buffer_rsrc rs_o = make_rsrc(a.part_o, (uint32_t)a.part_cap * a.hq * 512u);
   const buffer_rsrc rs_lse = make_rsrc(a.part_lse, (uint32_t)a.part_cap * a.hq * 4u);
-  for (int64_t w = blockIdx.x; w < (int64_t)hdr[6] * a.hkv; w += gridDim.x) {
-    const int rec = __builtin_amdgcn_readfirstlane((int)(w / a.hkv)), hk = (int)(w - (int64_t)rec * a.hkv);
+  const int64_t per_rec = (int64_t)a.hkv * blocks;
+  for (int64_t w = blockIdx.x; w < hdr[6] * per_rec; w += gridDim.x) {
+    const int rec = __builtin_amdgcn_readfirstlane((int)(w / per_rec)), at = (int)(w - rec * per_rec);
     const i32x8 m = *(const __attribute__((address_space(4))) i32x8*)(a.merges + rec);
-    if (m[4] == 0) continue;
-    auto one = [&](int, int& first) __attribute__((always_inline)) { first = 0; return m; };
-    merge_rows<T, G, kLaunchScope, 1, kMergeAhead>(a, rs_o, rs_lse, hk, m[1], blockIdx.y, gridDim.y, one);
+    if (!(m[4] > 0 ? a.behind & kGroupsBehind : !trees && m[1] * G > kFlatRows)) continue;
+    const int block = __builtin_amdgcn_readfirstlane(at / a.hkv), hk = at - block * a.hkv;
+    merge_rows<T, G, kLaunchScope, 1, kMergeAhead>(
+        a, rs_o, rs_lse, hk, m[1], trees, block, blocks,
+        [&](int, int& first) __attribute__((always_inline)) { first = 0; return m; });
   }
 }
 
 template <typename T>
-void launch_group_merge(int G, dim3 grid, hipStream_t hs, const AttnArgs& a) {
+void launch_merge(int G, dim3 grid, int blocks, hipStream_t hs, const AttnArgs& a) {
   switch (G) {
-    case 1: hipLaunchKernelGGL((group_merge_kernel<T, 1>), grid, dim3(kThreads), 0, hs, a); break;
-    case 2: hipLaunchKernelGGL((group_merge_kernel<T, 2>), grid, dim3(kThreads), 0, hs, a); break;
-    case 4: hipLaunchKernelGGL((group_merge_kernel<T, 4>), grid, dim3(kThreads), 0, hs, a); break;
-    default: hipLaunchKernelGGL((group_merge_kernel<T, 8>), grid, dim3(kThreads), 0, hs, a); break;
+    case 1: hipLaunchKernelGGL((merge_kernel<T, 1>), grid, dim3(kThreads), 0, hs, a, blocks); break;
+    case 2: hipLaunchKernelGGL((merge_kernel<T, 2>), grid, dim3(kThreads), 0, hs, a, blocks); break;
+    case 4: hipLaunchKernelGGL((merge_kernel<T, 4>), grid, dim3(kThreads), 0, hs, a, blocks); break;
+    default: hipLaunchKernelGGL((merge_kernel<T, 8>), grid, dim3(kThreads), 0, hs, a, blocks); break;
   }
 }
 
@@ -2412,6 +2439,11 @@ mc_status attn_impl(const mc_pool_desc* pool, int32_t layer, const void* q, int3
   a.hq = num_q_heads;
   a.batch = batch;
   a.total_q = total_q;
+  // (q tiles there are at least.  A batch of rows that are all few has no trees.)
+  const int64_t tiles = (int64_t)(w.max_tiles - batch) * pool->num_kv_heads;
+  const bool trees = w.part_cap > 0 && total_q > batch && (int64_t)total_q * G > kFlatRows;
+  a.behind = groups && !groups_in_launch(batch, total_q) ? kGroupsBehind : 0;
+  if (trees && trees_behind(tiles, slots, a.behind != 0)) a.behind |= kTreesBehind;
   a.scale = sm_scale > 0.f ? sm_scale : 1.0f / sqrtf((float)mc::kHeadDim);
   a.scale_log2 = a.scale * 1.4426950408889634f;
   dim3 grid((unsigned)blocks);
@@ -2427,15 +2459,13 @@ mc_status attn_impl(const mc_pool_desc* pool, int32_t layer, const void* q, int3
     st = pool->dtype == MC_F16 ? launch_attn<_Float16>(G, false, 2, grid, hs, a)
                                : launch_attn<__bf16>(G, false, 2, grid, hs, a);
   }
-  if (st != MC_OK || !groups || groups_in_launch(batch, total_q)) return st;
-  // the planner may have found shared prefixes: their members' chunks are combined (one workgroup a
-  // sequence and kv head if they all run at once, else a grid-stride walk)
-  const int64_t pairs = (int64_t)batch * pool->num_kv_heads;
-  const int rows = (total_q + batch - 1) / batch * G, per_block = kThreads / 32;
-  const dim3 mgrid((unsigned)(pairs < 4ll * slots ? pairs : 4ll * slots),
-                   (unsigned)std::min((rows + per_block - 1) / per_block, kBM / per_block));
-  if (pool->dtype == MC_F16) launch_group_merge<_Float16>(G, mgrid, hs, a);
-  else launch_group_merge<__bf16>(G, mgrid, hs, a);
+  if (st != MC_OK || a.behind == 0) return st;
+  const int rows = std::min((total_q + batch - 1) / batch * G, kBM), per_block = kThreads / 32;
+  const int row_blocks = (rows + per_block - 1) / per_block;
+  const int64_t all = (int64_t)w.max_tiles * row_blocks * pool->num_kv_heads;
+  const dim3 mgrid((unsigned)std::min<int64_t>(all, slots));
+  if (pool->dtype == MC_F16) launch_merge<_Float16>(G, mgrid, row_blocks, hs, a);
+  else launch_merge<__bf16>(G, mgrid, row_blocks, hs, a);
   return mc::launch_status();
 }
 

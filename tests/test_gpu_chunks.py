@@ -1,7 +1,7 @@
-"""Chunks of a cut KV range are combined inside the attention launch: rows that are counted (up to 16
-a q tile and kv head) and trees over two to many chunks, groups of both kinds, at the row counts where
-one becomes the other.  Launch after launch on one plan (the arrival words wrap), every launch the same
-bits whichever chunk comes last, and the oracle's result."""
+"""Chunks of a cut KV range are combined inside the attention launch - rows that are counted (up to 16
+a q tile and kv head), trees over two to many chunks, groups of both kinds, at the row counts where
+one becomes the other - or in a launch behind it.  Launch after launch on one plan (the arrival words
+wrap), every launch the same bits whichever chunk comes last, and the oracle's result."""
 import numpy as np
 import pytest
 
@@ -9,15 +9,15 @@ import mc_inputs as mi
 import oracle
 import paper_2412_12488_amd as mc
 import torch
-from gpu_harness import DEV, DevBatch, DevPool, bits, dev
+from gpu_harness import DEV, DevBatch, DevPool, bits, dev, oracle_rows
 from test_gpu_parity import LSE_TOL, O_TOL, fill_both, forked_decode_workload, small_workload
 
 pytestmark = pytest.mark.gpu
 
 
-def launches(w, n=6, q=None, begin=None, blank=(0x7fc1, float("nan"))):
+def launches(w, n=6, q=None, begin=(), blank=(0x7fc1, float("nan"))):
     """(out bits, lse) of n launches on one plan, the plan's header, and the oracle's pool.  The launches
-    take other q and begin if given, and find blank in out and lse."""
+    take other q if given, the first ones other begins, and find blank in out and lse."""
     pool = DevPool(w)
     pool.t.fill_(0x7fc1)
     opool = np.full(pool.elems, 0x7fc1, dtype=np.uint16)
@@ -28,19 +28,21 @@ def launches(w, n=6, q=None, begin=None, blank=(0x7fc1, float("nan"))):
     mc.mc_attn_plan(pool.desc, Hq, db.batch, db.total_q, db.cu_q, db.begin, db.page_table, db.cu_pages, ws, size)
     mc.mc_attn_plan_check(ws)
     q = dev(np.concatenate([w.q(s) for s in range(w.batch)]) if q is None else q)
-    begin = db.begin if begin is None else dev(np.array(begin, np.int32))
     got = []
-    for _ in range(n):
+    for i in range(n):
+        b = dev(np.array(begin[i], np.int32)) if i < len(begin) else db.begin
         out = torch.full((db.total_q, Hq, 128), blank[0], dtype=torch.int16, device=DEV)
         lse = torch.full((db.total_q, Hq), blank[1], dtype=torch.float32, device=DEV)
-        mc.mc_prefix_prefill_attn(pool.desc, 0, q, Hq, db.batch, db.total_q, db.cu_q, begin, db.page_table,
+        mc.mc_prefix_prefill_attn(pool.desc, 0, q, Hq, db.batch, db.total_q, db.cu_q, b, db.page_table,
                                   db.cu_pages, 0.0, out, lse, ws, size)
         got.append((out, lse))
     torch.cuda.synchronize()
     return got, ws[:64].view(torch.int32).cpu().numpy(), pool, opool
 
 
-def check(w, n=6):
+def check(w, n=6, rows=0):
+    """The plan's header, once all launches agree with each other and with the oracle (rows > 0: on as many
+    rows a sequence, any head)."""
     got, h, pool, opool = launches(w, n)
     out, lse = bits(got[0][0]), got[0][1].cpu().numpy()
     for o, l in got[1:]:
@@ -49,25 +51,36 @@ def check(w, n=6):
         at, q_len = int(w.cu_q[s]), int(w.n[s] - w.b[s])
         if q_len == 0:
             continue
-        ro, rl = oracle.attention(opool, pool.shape, 0, w.page_tables[s], w.q(s), w.num_q_heads, int(w.b[s]),
-                                  int(w.n[s]))
-        assert np.max(np.abs(oracle.decode(out[at:at + q_len], w.dtype) - ro)) <= O_TOL, s
-        assert np.max(np.abs(lse[at:at + q_len] - rl)) <= LSE_TOL, s
+        o, l = out[at:at + q_len], lse[at:at + q_len]
+        rr = hh = None
+        if rows:
+            rng = mi.rng_for(w.seed, s)
+            rr, hh = rng.integers(0, q_len, rows), rng.integers(0, w.num_q_heads, rows)
+            o, l = o[rr, hh], l[rr, hh]
+        ro, rl = oracle_rows(w, opool, pool.shape, 0, s, w.q(s), rr, hh)
+        assert np.max(np.abs(oracle.decode(o, w.dtype) - ro)) <= O_TOL, s
+        assert np.max(np.abs(l - rl)) <= LSE_TOL, s
     return h
 
 
 @pytest.mark.parametrize("dtype", [mi.BF16, mi.F16])
 @pytest.mark.parametrize("Hq,Hkv,new,keys", [
-    (32, 8, 4, 2100), (32, 8, 5, 2100),       # 16 rows: counted; 20: a tree (G = 4)
+    # one tile for each of eight kv heads, or fewer: 16 rows are counted, more combined behind the launch
+    (32, 8, 4, 2100), (32, 8, 5, 2100),       # 16 rows; 20 (G = 4)
     (64, 8, 2, 1100), (64, 8, 3, 1600),       # 16 rows, 24 (G = 8): two chunks, three
     (8, 8, 16, 2700), (8, 8, 17, 2700),       # 16 rows, 17 (G = 1): five chunks
-    (8, 8, 128, 3200), (8, 8, 129, 4300),     # a full tile; a tile and one row
-    (32, 8, 33, 1000), (16, 8, 40, 700),      # two tiles; one tile, two chunks (G = 2)
-    (8, 1, 20, 40000),                        # more chunks than one word of arrivals has nodes
+    (8, 8, 128, 3200), (16, 8, 40, 700),      # a full tile; two chunks (G = 2)
+    (8, 1, 20, 40000), (8, 1, 128, 1300),     # many chunks; eight tiles of one kv head
+    # more tiles: trees, a tile of 16 rows or fewer counted
+    (32, 8, 33, 1000), (32, 8, 36, 2100), (32, 8, 37, 2100),      # a tile and 4 rows, 16, 20
+    (64, 8, 18, 1600), (64, 8, 19, 2600),     # 16 rows, 24
+    (8, 8, 129, 4300), (8, 8, 144, 2700), (8, 8, 145, 3300),      # one row, 16, 17
+    (8, 1, 129, 1300), (16, 8, 81, 4500),     # nine tiles, the last of 8 rows; 17 tokens of two rows
+    (8, 1, 130, 40000),                       # more chunks than one word of arrivals has nodes
 ])
 def test_ranges_of_few_and_many_rows(dtype, Hq, Hkv, new, keys):
     w = small_workload(1200 + new, dtype, Hq, Hkv, [keys], [keys - new])
-    h = check(w)
+    h = check(w, rows=0 if new * keys < 1 << 20 else 512)
     assert h[6] == -(-new // (128 * Hkv // Hq)) and h[7] > 0, h[:9]     # every tile is cut
 
 
@@ -135,14 +148,14 @@ def test_a_row_that_is_not_a_number_is_written_as_such(dtype, Hq, Hkv, lens, new
 
 def test_a_row_that_is_not_a_number_beside_chunks_without_a_key():
     # a tree whose last chunks hold no key (a begin below the planned one), whichever of two comes first
-    w = small_workload(1290, mi.BF16, 32, 8, [4100, 4100], [4092, 4092])
+    w = small_workload(1290, mi.BF16, 32, 8, [4100, 4100], [4060, 4060])
     q = np.concatenate([w.q(s) for s in range(2)])
-    q[11, 9] = 0x7fc1
-    got, h, _, _ = launches(w, 6, q=q, begin=[700, 1900], blank=(0x1111, 7.0))
-    assert h[6] == 2, h[:9]
+    q[41, 9] = 0x7fc1
+    got, h, _, _ = launches(w, 6, q=q, begin=[[700, 1900]] * 6, blank=(0x1111, 7.0))
+    assert h[6] == 4, h[:9]
     for out, lse in got:
         o, l = oracle.decode(bits(out), mi.BF16), lse.cpu().numpy()
-        assert np.isnan(o[11, 9]).all() and np.isnan(l[11, 9])
+        assert np.isnan(o[41, 9]).all() and np.isnan(l[41, 9])
         assert np.isnan(o).sum() == 128 and np.isnan(l).sum() == 1
 
 
@@ -184,3 +197,39 @@ def test_trees_of_members_in_larger_batches(new):
     own = [0, 300, 2700, 40, 1300, 700, 90, 2000, 10, 550, 64]
     w = forks(1330 + new, mi.BF16, 32, 8, 1600, own, [new + i % 2 for i in range(len(own))])
     assert check(w)[8] > 0
+
+
+@pytest.mark.parametrize("dtype", [mi.BF16, mi.F16])
+@pytest.mark.parametrize("new", [8, 40, 500, 513])
+def test_chunks_without_a_key_and_the_plan_used_again(dtype, new):
+    # a begin so far below the planned one that the last chunks hold no key (behind the launch, a tree, the
+    # kernel without short tiles); then the planned begin on the same plan, whose arrival words have wrapped
+    # (whole q tiles, of 32 tokens: a multiple of that many)
+    w = small_workload(1340 + new, dtype, 32, 8, [4500 + new], [4500])
+    low = [[896], [2496], [32]]
+    got, h, pool, opool = launches(w, 5, begin=low)
+    assert h[6] == -(-new // 32) and h[7] > 0, h[:9]
+    rng = mi.rng_for(1340, new)
+    rr, hh = rng.integers(0, new, 256), rng.integers(0, 32, 256)
+    for (out, lse), (b,) in zip(got, low + [[4500]] * 2):
+        ro, rl = oracle.attention(opool, pool.shape, 0, w.page_tables[0], w.q(0), 32, b, b + new, sel_rows=rr,
+                                  sel_heads=hh)
+        assert np.max(np.abs(oracle.decode(bits(out)[rr, hh], dtype) - ro)) <= O_TOL, b
+        assert np.max(np.abs(lse.cpu().numpy()[rr, hh] - rl)) <= LSE_TOL, b
+
+
+@pytest.mark.parametrize("Hq,Hkv,new,keys", [(32, 8, 500, 5000), (32, 8, 513, 5013), (64, 8, 130, 3000),
+                                             (8, 8, 1025, 9000), (16, 8, 700, 2200)])
+def test_long_ranges_launch_after_launch(Hq, Hkv, new, keys):
+    # the kernel without short tiles: full tiles in trees, the last one counted where it has 16 rows or fewer
+    w = small_workload(1350 + new, mi.BF16, Hq, Hkv, [keys], [keys - new])
+    h = check(w, rows=512)
+    assert h[6] == -(-new // (128 * Hkv // Hq)), h[:9]
+
+
+@pytest.mark.parametrize("dtype", [mi.BF16, mi.F16])
+def test_the_remainder_round_launch_after_launch(dtype):
+    # 560 similar items for 512 slots: the 48 shortest are cut, three chunks each
+    w = small_workload(1360, dtype, 8, 1, [1280] * 35, [1024] * 35)
+    h = check(w, rows=16)
+    assert h[7] == 0 and h[9] > 1 and h[6] == 48, h[:10]
