@@ -570,6 +570,10 @@ __global__ __launch_bounds__(NT) void plan_kernel(PlanArgs a) {
   //     as one q tile - their tokens are neighbours in the q array, and every key of the prefix
   //     lies before every one of them, so no mask is involved - one K/V read for all of them,
   //     and their own remainders one by one; the parts are merged by LSE like any other chunks.
+  //     Prefix items hold the whole group's rows, or where they are combined in the launch (see MergeRec)
+  //     those of the members whose first tokens lie in the same kFlatRows rows of it: a slice.
+  const bool sliced = groups_in_launch(a.batch, a.total_q);
+  const int slice = max(kFlatRows * a.tile_tokens / kBM, 1);
   const bool try_groups = a.allow_groups && cu_in_lds && a.batch >= 2 && a.batch <= NT;
   if (t == 0) s_groups = 0;
   if (try_groups) {
@@ -670,6 +674,13 @@ __global__ __launch_bounds__(NT) void plan_kernel(PlanArgs a) {
       if (mine) {
         s_glead[t] = member ? near : -1;
         s_gp[t] = member ? s_gbase[near] : 0;
+        if (sliced) {      // from here on in s_common: the tokens of the slice this sequence leads, else 0
+          const int first = member ? s_cuq[near] : 0, id = (s_cuq[t] - first) / slice;
+          int end = t;
+          if (member && (t == near || (s_cuq[t - 1] - first) / slice != id))
+            do ++end; while (end <= s_glast[near] && (s_cuq[end] - first) / slice == id);
+          s_common[t] = s_cuq[end] - s_cuq[t];
+        }
       }
     }
     __syncthreads();
@@ -681,17 +692,6 @@ __global__ __launch_bounds__(NT) void plan_kernel(PlanArgs a) {
   // tiles its shared-prefix group covers, the group's new tokens if this tile leads one, and those of
   // the prefix items that the tile leads
   struct Tile { int s, row0, ntok, T, dmax, pt, gm, gi; };
-  // Prefix items hold the whole group's rows, or where they are combined in the launch (see MergeRec) those
-  // of the members whose first tokens lie in the same kFlatRows rows of it.
-  const bool sliced = groups_in_launch(a.batch, a.total_q);
-  const int slice = max(kFlatRows * a.tile_tokens / kBM, 1);
-  auto slice_tokens = [&](int lead, int sq) {     // of the slice that sequence sq leads, else 0
-    const int first = s_cuq[lead], id = (s_cuq[sq] - first) / slice;
-    if (sq > lead && (s_cuq[sq - 1] - first) / slice == id) return 0;
-    int end = sq + 1;
-    while (end <= s_glast[lead] && (s_cuq[end] - first) / slice == id) ++end;
-    return s_cuq[end] - s_cuq[sq];
-  };
   auto locate = [&](int i) {
     int lo = 0, hi = a.batch;
     while (hi - lo > 1) {
@@ -708,7 +708,7 @@ __global__ __launch_bounds__(NT) void plan_kernel(PlanArgs a) {
     x.dmax = ((b + x.row0) / kBN) & ~1;
     x.pt = groups ? s_gp[lo] : 0;
     x.gm = groups && s_glead[lo] == lo ? s_gsize[lo] : 0;
-    x.gi = !sliced ? x.gm : x.pt > 0 ? slice_tokens(s_glead[lo], lo) : 0;
+    x.gi = groups && sliced ? s_common[lo] : x.gm;
     return x;
   };
   // (a batch of no more tiles than threads: a thread's tile is the same in every step)
