@@ -994,16 +994,13 @@ struct AttnArgs {
   const char* q;
   char* out;
   float* lse;
-  const int32_t* cu_q;
   const int32_t* begin;
   const int32_t* page_table;
-  const int32_t* cu_pages;
   const PlanHeader* hdr;
   const ItemRec* items;
   const MergeRec* merges;
   float* part_lse;         // of every partial row (see MergeRec); the arrival words at its end
   float* part_o;           // [partial row][128]
-  int64_t page_stride;     // bytes
   int32_t num_pages, hkv, hq, batch, total_q;
   int32_t part_cap;        // rows of the partial arrays
   int32_t behind;          // what merge_kernel combines (see MergeRec): kGroupsBehind, kTreesBehind
@@ -2423,17 +2420,14 @@ mc_status attn_impl(const mc_pool_desc* pool, int32_t layer, const void* q, int3
   a.q = static_cast<const char*>(q);
   a.out = static_cast<char*>(out);
   a.lse = lse;
-  a.cu_q = cu_q;
   a.begin = begin;
   a.page_table = page_table;
-  a.cu_pages = cu_pages;
   a.hdr = reinterpret_cast<const PlanHeader*>(ws);
   a.items = reinterpret_cast<const ItemRec*>(ws + w.items);
   a.merges = reinterpret_cast<const MergeRec*>(ws + w.merges);
   a.part_lse = reinterpret_cast<float*>(ws + w.part_lse);
   a.part_o = reinterpret_cast<float*>(ws + w.part_o);
   a.part_cap = w.part_cap;
-  a.page_stride = mc::page_stride_bytes(pool);
   a.num_pages = pool->num_pages;
   a.hkv = pool->num_kv_heads;
   a.hq = num_q_heads;
@@ -2554,7 +2548,7 @@ mc_status mc_prefix_prefill_attn_noalloc(const mc_pool_desc* pool, int32_t layer
   int G = 0;
   mc_status st = check_attn_shape(pool, num_q_heads, batch, total_q, &G);
   if (st != MC_OK) return st;
-  // the work list alone must fit; what is left holds partial rows (32-byte item record, LSE
+  // the work list alone must fit; what is left holds partial rows (64-byte item record, LSE
   // and O per row and q head), fewer than the caller-workspace variant may ask for
   const int tile_tokens = kBM / G;
   const WorkspaceLayout fixed =
