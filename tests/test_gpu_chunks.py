@@ -107,7 +107,8 @@ def test_prefixes_of_few_and_many_rows(dtype, Hq, Hkv, members):
 @pytest.mark.parametrize("dtype", [mi.BF16, mi.F16])
 def test_members_with_trees_of_their_own(dtype):
     # forks that bring 5..8 new tokens (20..32 rows of a kv head) over own middle parts of up to five
-    # chunks: the members' own chunks are a tree, the prefix's are one
+    # chunks: these and the prefix's are combined in the launch behind it (a member's tree beside a prefix:
+    # test_trees_of_members_in_larger_batches)
     begins, new = [2048, 2300, 4700, 2048, 3300], [5, 6, 8, 4, 7]
     w = small_workload(1260, dtype, 32, 8, [b + n for b, n in zip(begins, new)], begins)
     for s in range(1, 5):
@@ -119,10 +120,12 @@ def test_members_with_trees_of_their_own(dtype):
 @pytest.mark.parametrize("dtype", [mi.BF16, mi.F16])
 @pytest.mark.parametrize("Hq,Hkv,lens,new,shared", [
     (32, 8, [1500, 900], [1, 1], 0),                                    # counted
-    (32, 8, [2100, 1600], [5, 7], 0),                                   # a tree
+    (32, 8, [2100, 1600], [5, 7], 0),                                   # behind the launch
+    (32, 8, [2100, 1600], [40, 37], 0),                                 # a tree
     (32, 8, [2300, 2200, 2150], [1, 1, 1], 2048),                       # a prefix, combined in the launch
     (32, 8, [2100 + 10 * i for i in range(12)], [1] * 12, 2048),        # and behind it
-    (32, 8, [2100, 2600, 3100], [5, 6, 8], 2048),                       # trees of members
+    (32, 8, [2100, 2600, 3100], [5, 6, 8], 2048),                       # members of more rows, behind it
+    (32, 8, [2100 + 300 * i for i in range(11)], [15] * 11, 2048),      # trees of members, read behind it
 ])
 def test_a_row_that_is_not_a_number_is_written_as_such(dtype, Hq, Hkv, lens, new, shared):
     w = small_workload(1280, dtype, Hq, Hkv, lens, [n - k for n, k in zip(lens, new)])
