@@ -170,11 +170,12 @@ constexpr int kMinSharedTiles = 8;    // a shared prefix shorter than 512 tokens
 // latency each, and every piece costs a partial row (fp32) for each of its rows, written and read.
 // Decode steps (at most one new token a sequence) have few rows: short pieces, 2 tiles as long as
 // a row then has no more than the kMergeAhead pieces that a merge requests early, else 4, if
-// they pay (short_pieces_pay).  Ranges of more tokens keep 8.  Append + attention + merge of a layer,
-// 32 / 8 heads, pieces of 8 / 4 / 2 tiles: decode of 1 x 1024 tokens 16.5 / 13.8 / 12.5 us, 1 x 1100
-// 16.5 / 13.8 / 13.1, 1 x 2048 16.7 / 14.1 / 13.6, 1 x 4096 17.4 / 15.6 / 15.8, 4 x 1024 17.6 / 15.1 /
-// 13.8, 4 x 2048 20.7 / 17.7 / 18.0 (between 17 and 32 tiles 2 would still be the better one, by 3 to
-// 5 %); prefill of 512 tokens 20.0 / 23.1 / 25.7, of 4 x 512 27.0 / 40.8 / 40.8.
+// they pay (short_pieces_pay).  Ranges of more tokens keep 8.  Append + attention of a layer, 32 / 8
+// heads, pieces of 8 / 4 / 2 tiles: decode of 1 x 1024 tokens 12.6 / 10.3 / 9.3 us, 1 x 1100 12.6 / 10.3 /
+// 10.1, 1 x 2048 12.8 / 10.5 / 10.6, 1 x 4096 13.0 / 11.9 / 13.8, 4 x 1024 13.2 / 11.2 / 10.6, 4 x 2048 15.4 /
+// 13.7 / 14.3; ranges of more tokens, 8 or whole / 4 (6 where that would be more items than run at once):
+// prefill of 512 17.8 / 17.5, 2 x 512 19.4 / 21.7, 4 x 512 26.2 / 31.3, 1024 25.1 / 26.2, 64 over 448 15.3 / 15.7;
+// 256 over 256, 8 / 8 heads, 17.1 / 16.5.
 constexpr int kMinChunkTiles = 8, kMinChunkTilesDecode = 4, kMinChunkTilesShort = 2;
 constexpr int kMergeAhead = 8;        // partial rows a merge of few rows requests beside their LSEs
 // ... and a merge of a shared prefix's rows, for which its pieces are so long that they and the member's own
@@ -358,25 +359,28 @@ __device__ __forceinline__ int block_inclusive_max_scan(int v, int* lds) {
 }
 
 // Whether pieces of L < kMinChunkTiles tiles gain more than they cost over pieces of kMinChunkTiles
-// (over whole ranges, if the longest has no more).  us of append + attention + merge of a layer with
-// pieces of 8 (whole) / of L tiles; heads q / kv:
-//   - All items have to run at once: the ones left over take a turn of their own.  334 items for 512
-//     slots, 64 x 64..500 tokens, 8 / 2: 16.8 / 15.5; 610 items, 128 x 64..900, 8 / 2: 21.9 / 24.6; 680
-//     items, 48 x 560..1400 of forks, 32 / 8: 28.7 / 31.7.  (The count is an estimate, up to a tenth
+// (over whole ranges, if the longest has no more).  us of append + attention of a layer with pieces of
+// 8 (whole) / of L tiles; heads q / kv:
+//   - All items have to run at once: the ones left over take a turn of their own.  616 items for 512
+//     slots, 32 x 64..900 tokens, 32 / 8, L = 4: 23.1 / 23.4.  (The count is an estimate, up to a tenth
 //     above the true one.)  An eighth more than the slots is made up for if the pieces are not the
-//     shortest nor many a row, and no group's merges grow: 536 items, 24 x 300..1000, 32 / 8: 22.7 / 21.8; 584, 32 x
-//     64..900: 22.4 / 22.8; 534, 100 forks of a 2048-token prompt, 8 / 2: 23.1 / 25.0.
-//   - Rows of more than 24 pieces: half the slots.  8 / 2 heads, 8192 tokens: 1 row 17.3 / 16.7, 4
-//     rows (256 items) 19.5 / 19.4, 8 rows (512) 23.4 / 24.7; 6000 tokens (24 pieces), 8 rows 21.0 / 20.5.
-//   - The merge reads every partial row: 8 heads, one of them kv, forks of a 4096-token prompt: 64 rows
-//     (9200 partial rows x heads) 22.0 / 21.2, 128 (18400) 23.5 / 24.7.
+//     shortest nor many a row, and no group's merges grow: 560 items, 24 x 300..1000, 32 / 8, which the
+//     estimate puts beyond that, L = 4: 24.2 / 24.0; 672 items, 48 forks of a 512-token prompt with 48..888
+//     of their own, 32 / 8, L = 6: 31.6 / 30.7.
+//   - Rows of more than 24 pieces: half the slots.  8 / 2 heads, 8192 tokens, L = 4: 1 row 13.6 / 12.8, 4
+//     rows (256 items) 16.1 / 16.7, 8 rows (512) 21.0 / 22.2; 6000 tokens (24 pieces), 8 rows (384) 18.5 / 19.6.
+//   - A merge reads every partial row: 8 heads, one of them kv, forks of a 4096-token prompt, L = 4: 64 rows
+//     21.5 / 20.4, 128 23.5 / 23.4.
 //   - Pieces of 6 differ from those of 8 in how well they fill the slots only, and add rows to a group's
-//     merges: 32 / 8 heads, 8 x 1024..4096 tokens (472 items) 29.2 / 28.3, 6 (368) 23.5 / 24.0; 8 / 2,
-//     128 forks of 2048 tokens 24.9 / 28.2.
-//   - Whole ranges have no merge: what is saved, longest - L tiles of latency, has to outweigh one, and
-//     the items that then read at once.  32 / 8 heads: 24 x 64..500 tokens 17.7 / 15.7, 16 x 320
-//     14.7 / 14.5, 20 x 320 15.2 / 15.8, 16 x 200 13.9 / 14.2; 8 / 1: 128 x 100..512 16.5 / 15.8,
-//     160 x 100..300 14.8 / 15.8.
+//     merges: 32 / 8 heads, 8 x 1024..4096 tokens (392 items) 23.3 / 23.1, 6 (328) 19.3 / 22.3; 8 / 2,
+//     128 forks of 2048 tokens 22.6 / 21.3, L = 4 20.8.
+//   - Whole ranges have nothing to combine: what is saved, longest - L tiles of latency, has to outweigh
+//     that, and the items that then read at once.  32 / 8 heads: 24 x 64..500 tokens, L = 4, 15.5 / 16.0, L = 2:
+//     16 x 320 12.5 / 13.4, 20 x 320 13.1 / 14.5, 16 x 200 11.4 / 12.5; 8 / 2: 64 x 64..500 13.7 / 13.9; 8 / 1:
+//     128 x 100..512 13.9 / 14.5, 160 x 100..300 12.5 / 13.8.
+// The lines were drawn where one wavefront walked an item's tiles and a launch combined the chunks, which
+// made whole ranges of up to 8 tiles up to 2 us slower than they are now; so short pieces are still
+// taken where they now lose a little (24 x 64..500, 16 x 320, 64 x 64..500, 128 x 100..512; 4 x 8192, 8 x 6000).
 // cost: tiles of all the ranges, at most 8 x slots / hkv.  No division: this is part of every step's
 // plan.  A q tile has kBM rows, so q heads are kv heads x kBM / tile_tokens.
 __device__ __forceinline__ bool short_pieces_pay(const PlanArgs& a, int L, int longest, bool groups, int tiles,
