@@ -373,7 +373,7 @@ def main():
                     help="time only the attention kernel on one workload and exit (for profiling): "
                          + ", ".join(ATTN_WORKLOADS))
     ap.add_argument("--decode-step", metavar="WORKLOAD", default=None,
-                    help="time only one decode step (append + plan + attention + merge), launched "
+                    help="time only one decode step (append + plan + attention), launched "
                          "call by call, from a HIP graph and with a plan made once, and exit")
     ap.add_argument("--values", choices=["normal", "zero"], default="normal",
                     help="with --attention-only: Q/K/V values, N(0,1) or all zeros")
