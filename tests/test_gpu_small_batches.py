@@ -169,3 +169,37 @@ def test_short_pieces_inside_a_shared_prefix(dtype, Hq, Hkv):
     h = plan_header(w)
     assert h["chunk_tiles"] == 2 and h["num_groups_rows"] == 4 * 4 + 7 * 3, h
     check_attention(w)
+
+
+# tables of fewer entries than a lane looks at, of one trip and several, mostly or partly not needed
+@pytest.mark.parametrize("need,slack", [([1], 0), ([3], 2), ([5, 0, 70], 1), ([1100], 0), ([40] * 17, 3),
+                                        ([9] * 40, 30), ([270] * 256, 1)])
+def test_page_ids_are_checked_where_a_token_needs_them(need, slack):
+    num_pages, B = 50, len(need)
+    rng = mi.rng_for(995 + B)
+    cu_pages = np.concatenate([[0], np.cumsum([n + slack for n in need])]).astype(np.int32)
+    table = np.where(np.arange(cu_pages[-1]) % 2, -1, num_pages).astype(np.int32)      # what no token needs
+    for s, n in enumerate(need):
+        table[cu_pages[s]:cu_pages[s] + n] = rng.integers(0, num_pages, n)
+    new = [int(n > 0) for n in need]
+    cu_q = dev(np.concatenate([[0], np.cumsum(new)]).astype(np.int32))
+    begin = dev(np.array([16 * n - 1 if n else 0 for n in need], np.int32))
+    pool = torch.zeros(num_pages * 2 * 8 * 16 * 128, dtype=torch.int16, device=DEV)
+    desc = mc.pool_desc(pool, 1, num_pages, 8, mc.MC_BF16)
+    size = mc.mc_attn_workspace_size(B, sum(new), 32, 8)
+    ws = torch.empty(size, dtype=torch.uint8, device=DEV)
+
+    def plan(t):
+        mc.mc_attn_plan(desc, 32, B, sum(new), cu_q, begin, dev(t), dev(cu_pages), ws, size)
+        mc.mc_attn_plan_check(ws)
+
+    plan(table)
+    for s, e in [(0, 0), (0, need[0] - 1), (B // 2, need[B // 2] // 2), (B - 1, need[-1] - 1)]:
+        if need[s] == 0:
+            continue
+        for bad in (-1, num_pages):
+            t = table.copy()
+            t[cu_pages[s] + e] = bad
+            with pytest.raises(mc.McError) as err:
+                plan(t)
+            assert err.value.status == mc.MC_ERR_RANGE, (s, e, bad)
