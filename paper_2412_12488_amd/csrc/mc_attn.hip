@@ -463,7 +463,8 @@ __global__ __launch_bounds__(NT) void plan_kernel(PlanArgs a) {
   __shared__ int s_groups;
   // remainder round: flags of the q tiles that are cut, the cost bucket at the boundary and how
   // many tiles of it are taken
-  __shared__ uint16_t s_owner[kSpreadItems];   // of items written one a thread: the tile, and per tile
+  __shared__ uint16_t s_owner[kSpreadItems], s_place[kSpreadItems];   // of items written one a thread: tile, place;
+                                               // and per tile
   __shared__ int s_first[NT], s_merge[NT];     // its first item and its merge record
   __shared__ uint8_t s_tailflag[kTailTilesMax];
   __shared__ int s_tail_bucket, s_tail_take, s_tail_taken;
@@ -920,7 +921,6 @@ __global__ __launch_bounds__(NT) void plan_kernel(PlanArgs a) {
   // another (a load and a store behind it each)
   const bool spread = one_each && tot_items > 0 && tot_items <= kSpreadItems;
   if (spread && t < total_tiles) {
-    for (int c = 0; c < n_items; ++c) s_owner[item_off + c] = (uint16_t)t;
     s_first[t] = item_off;
     s_merge[t] = merge_off;
   }
@@ -947,12 +947,24 @@ __global__ __launch_bounds__(NT) void plan_kernel(PlanArgs a) {
   //    by the tile's thread, 8 and 32 pieces of one decode row took 2.4 and 7.3 us, one a thread 1.1 and 1.2.
   //    With the page ids' look and without a sum that a bound replaces the plan of one row over 1000
   //    tokens takes 7.6 us instead of 10.0, over 8100 8.0 instead of 15.8, of 256 rows 14.4 instead of 19.4.)
-  auto put_item = [&](const Tile& x, int Li, int k, int merge) {
+  // Pieces of one length of decode steps lie tile by tile, so that a row's last piece combines them while others run
+  // (32 rows over 200..900 tokens, eight layers, 199 us, in the other order 206).  Else the first pieces of all tiles
+  // lie ahead of their second ones, so that a compute unit's two workgroups differ (16 decode rows beside a prefill of 600
+  // tokens 145, so 137; 500 new tokens over 2500 184, so 178).
+  const bool by_tile = a.total_q <= total_tiles;
+  struct Piece { int t0, t1, chunk; bool in_group; };
+  auto piece = [&](const Tile& x, int Li, int k) {
     const int ns = own_splits(x, Li);
-    const bool merged = ns > 1 || x.pt > 0, in_group = k >= ns;
-    const int c = in_group ? k - ns : k, from = in_group ? 0 : x.pt, end = in_group ? x.pt : x.T;
-    const int t0 = from + c * Li, ntok = in_group ? x.gi : x.ntok;
-    const int t1 = Li > 0 && (in_group ? t0 + Li < end : k + 1 < ns) ? t0 + Li : end;
+    const bool in_group = k >= ns;
+    const int c = in_group ? k - ns : k, t0 = (in_group ? 0 : x.pt) + c * Li, end = in_group ? x.pt : x.T;
+    return Piece{t0, Li > 0 && (in_group ? t0 + Li < end : k + 1 < ns) ? t0 + Li : end, c, in_group};
+  };
+  // its place in the list
+  auto place_of = [&](const Piece& p) {
+    return atomicAdd(&hist[p.in_group ? group_bucket(p.t1 - p.t0) : bucket(p.t1 - p.t0)], 1);
+  };
+  auto put_item = [&](const Tile& x, const Piece& p, bool merged, int merge, int at) {
+    const int t0 = p.t0, t1 = p.t1, ntok = p.in_group ? x.gi : x.ntok;
     const int sq0 = cu_in_lds ? s_cuq[x.s] : a.cu_q[x.s];
     const int sq_len = (cu_in_lds ? s_cuq[x.s + 1] : a.cu_q[x.s + 1]) - sq0;
     const int sb = cu_in_lds ? s_beg[x.s] : a.begin[x.s];
@@ -962,22 +974,23 @@ __global__ __launch_bounds__(NT) void plan_kernel(PlanArgs a) {
 #pragma unroll
     for (int i = 0; i < 8; ++i) it.ids[i] = a.page_table[tab + min(4 * t0 + i, cap)];
     it.seq = x.s;
-    it.row0 = in_group ? 0 : x.row0;
-    it.chunk = merged ? c : -1;
+    it.row0 = p.in_group ? 0 : x.row0;
+    it.chunk = merged ? p.chunk : -1;
     it.q_first = sq0 + it.row0;
     it.t0_ntok = (uint32_t)(t0 >> 1) | (uint32_t)(ntok - 1) << 24;
     // every tile of the item holds a validated entry, so the last one lies in tile t1 - 1 or beyond
-    it.t1_flags = (uint32_t)t1 | (uint32_t)min(cap - 4 * (t1 - 1), 3) << 26 | (in_group ? kItemGroup : 0);
+    it.t1_flags = (uint32_t)t1 | (uint32_t)min(cap - 4 * (t1 - 1), 3) << 26 | (p.in_group ? kItemGroup : 0);
     it.table_off = tab;
     it.merge = merged ? merge : -1;
-    a.items[atomicAdd(&hist[in_group ? group_bucket(t1 - t0) : bucket(t1 - t0)], 1)] = it;
+    a.items[at] = it;
   };
   for (int i = i_lo; i < i_hi; ++i) {
     const Tile x = tile(i);
     const int Li = chunk_len(i, x);
     const int ns = own_splits(x, Li), ng = grp_splits(x, Li);
-    const int merge = merge_off;
-    if (ns > 1 || x.pt > 0) {
+    const int merge = merge_off, n = ns + (x.gi ? ng : 0);
+    const bool merged = ns > 1 || x.pt > 0;
+    if (merged) {
       MergeRec m;
       m.q_row = (cu_in_lds ? s_cuq[x.s] : a.cu_q[x.s]) + x.row0;
       m.ntok = x.ntok;
@@ -990,19 +1003,27 @@ __global__ __launch_bounds__(NT) void plan_kernel(PlanArgs a) {
       a.merges[merge_off++] = m;
       own_off += ns * x.ntok;
     }
-    if (!spread)
-      for (int k = 0; k < ns + (x.gi ? ng : 0); ++k) put_item(x, Li, k, merge);
+    if (spread) {
+#pragma unroll 4
+      for (int k = 0; k < n; ++k) {
+        if (!by_tile) s_place[item_off + k] = (uint16_t)place_of(piece(x, Li, k));
+        s_owner[item_off + k] = (uint16_t)t;
+      }
+    } else {
+      for (int k = 0; k < n; ++k) {
+        const Piece p = piece(x, Li, k);
+        put_item(x, p, merged, merge, place_of(p));
+      }
+    }
   }
   if (spread) {
-    // (the first pieces of all tiles, then their second ones: neighbours in the launch then read the same keys;
-    // 500 new tokens over 4500, 32 / 8 heads: 0.7 us a layer less than tile by tile)
-    const int n = (tot_items + total_tiles - 1) / total_tiles, m = (tot_items + n - 1) / n;   // (a tile has an item)
-    for (int j = t; j < n * m; j += NT) {
-      const int c = j / m, k = (j - c * m) * n + c;
-      if (k >= tot_items) continue;
-      const int i = s_owner[k];
+    __syncthreads();
+    for (int j = t; j < tot_items; j += NT) {
+      const int i = s_owner[j];
       const Tile x = locate(i);
-      put_item(x, chunk_len(i, x), k - s_first[i], s_merge[i]);
+      const int Li = chunk_len(i, x);
+      const Piece p = piece(x, Li, j - s_first[i]);
+      put_item(x, p, own_splits(x, Li) > 1 || x.pt > 0, s_merge[i], by_tile ? place_of(p) : s_place[j]);
     }
   }
   if (t == 0) {
