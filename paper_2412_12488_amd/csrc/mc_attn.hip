@@ -7,7 +7,7 @@
 // Work
 //   * plan_kernel cuts the ragged batch into work items: a q tile (128 rows = TOK
 //     tokens x G query heads of one kv head's group, TOK = 128/G, token-major; 256
-//     rows when the KV ranges are long) over a range of 64-key KV tiles - the whole
+//     rows when the KV ranges are long, 32 or 16 when new tokens are few) over a range of 64-key KV tiles - the whole
 //     range, or a chunk of it when the batch alone would not fill the GPU (decode
 //     steps, short ranges over long contexts), or the prefix that neighbouring
 //     sequences with short new ranges share (Sec. 3.4; fork_sequence, Sec. 3.5).
@@ -18,7 +18,8 @@
 //     range write out/lse; the others write partial rows, which the last of a q
 //     tile's items to finish weighs together by their log-sum-exp (where that would
 //     take longer than a launch: merge_kernel).  Items of at most 16 rows (decode
-//     steps) go another way through the kernel, few_rows_item.
+//     steps; 32 where new tokens are few) go another way through the kernel,
+//     few_rows_item.
 // Kernel shape
 //   * the KV loop walks 64-key tiles (4 pages) through the page table; each page
 //     contributes one contiguous 4 KiB run of K and one of V for this kv head.
@@ -73,12 +74,13 @@ struct PlanHeader {
   int32_t tile_tokens;
   int32_t batch;
   int32_t total_q;
-  int32_t num_merges; // q tiles whose KV range was cut into several chunks
-  int32_t chunk_tiles;  // chunk length the planner settled on (KV tiles); 0 = nothing was cut
+  int32_t num_merges; // q tiles of kBM rows that were cut: into chunks of the KV range, or into tiles of fewer rows
+  int32_t chunk_tiles;  // the length (KV tiles) they were cut into, whole ranges of narrow tiles too; 0 = nothing was cut
   int32_t num_groups_rows;  // partial rows written by shared-prefix items (0 = no groups)
   int32_t tail_chunks;  // chunks per q tile of the remainder round (0 = not applied)
   int32_t arrive_words; // arrival words per merge record and kv head (see MergeRec)
-  int32_t pad[5];
+  int32_t num_records;  // merge records
+  int32_t pad[4];
 };
 static_assert(sizeof(PlanHeader) == 64, "header is 64 bytes");
 
@@ -112,8 +114,8 @@ constexpr uint32_t kItemGroup = 1u << 28;
 // share (g_off: the tile's first among them).  Partial rows are kept per chunk and kv head: the
 // R = ntok x G (of the prefix: g_stride x G) rows of chunk c and kv head h start at row
 // (part + c ntok) hq + h R (of the prefix: (g_part + c g_stride) hq + h R) of the partial arrays.
-//   * Chunks of up to kFlatRows rows (decode steps): every item writes its rows and counts itself; the
-//     last one reads all the others'.
+//   * Chunks of up to kFlatRows rows (decode steps; in launches that may have narrow q tiles kNarrowRows): every
+//     item writes its rows and counts itself; the last one reads all the others'.
 //   * Chunks of more rows: a binary tree over the chunks.  Of two neighbours the first to be done
 //     writes its rows and ends, the second reads them, combines, and goes on one level up: of n chunks n - 1
 //     are written and read (up to twice as many written, where neighbours miss each other), but not by one
@@ -131,7 +133,7 @@ struct MergeRec {
   int32_t g_nsplit, g_part, g_stride, g_off;
 };
 static_assert(sizeof(MergeRec) == 32, "merge record is 32 bytes");
-constexpr int kFlatRows = 16;
+constexpr int kFlatRows = 16, kNarrowRows = 32;   // (in launches that may have narrow q tiles: the latter)
 constexpr int kGroupsBehind = 1, kTreesBehind = 2;   // what is left to merge_kernel
 // Whether chunks of shared prefixes are combined inside the attention launch: host, plan and kernel agree
 // by the batch's numbers alone.  Few sequences, and no more new tokens than those (some may be idle), which
@@ -147,16 +149,13 @@ constexpr int kGroupsInLaunch = 8;
 __host__ __device__ constexpr bool groups_in_launch(int32_t batch, int32_t total_q) {
   return batch <= kGroupsInLaunch && total_q <= batch;
 }
-// Whether trees are left to merge_kernel: where the q tiles x kv heads are so few that a tile has many chunks,
-// whose levels follow one another, 2 to 3 us each.  The host does not know how many, and the launch costs 1.3
-// to 2.2 us where nothing was cut (up to 512 keys): a launch of its own only up to a 64th of the slots (8 of
-// 512).  Append + attention of a layer, by trees / behind, over 600, 1100, 1500, 3000, 6000 keys: 8
-// (32 / 8 heads, 16 new tokens) 16.6 / 17.8, 19.1 / 17.8, 19.1 / 18.7, 22.8 / 19.6, 28.6 / 21.3 us; 16 (64) 17.1 /
-// 19.5, 20.7 / 20.3, 21.6 / 22.4, 24.9 / 22.3, 30.5 / 25.0; 32 (128) 17.2 / 20.7, 21.8 / 21.6, 23.5 / 23.1, 27.5 /
-// 24.5, 40.6 / 35.2; 64 (256) 19.0 / 22.4, 22.2 / 23.9, 24.2 / 24.7, 34.5 / 34.5, 46.3 / 46.3.  Where groups bring
-// the launch anyway, up to a 12th (42): over 700, 1500, 5000 keys, 40 (4 x 40 tokens) 22.3 / 23.4, 27.1 / 25.2,
-// 47.2 / 41.1; 48 (12 x 16) 23.5 / 24.8, 35.7 / 35.4, 65.4 / 64.0; 80 (8 x 40) 24.1 / 27.3, 33.6 / 35.5, 59.0 / 60.9.
-inline bool trees_behind(int64_t tiles, int slots, bool groups) { return tiles * (groups ? 12 : 64) <= slots; }
+// Whether trees are left to merge_kernel, where groups may bring that launch anyway: if the q tiles x kv heads are so
+// few that a tile has many chunks, whose levels follow one another, 2 to 3 us each: up to a 12th of the slots (42).
+// Append + attention of a layer, by trees / behind, over 700, 1500, 5000 keys: 40 (4 x 40 tokens) 22.3 / 23.4, 27.1 /
+// 25.2, 47.2 / 41.1; 48 (12 x 16) 23.5 / 24.8, 35.7 / 35.4, 65.4 / 64.0; 80 (8 x 40) 24.1 / 27.3, 33.6 / 35.5, 59.0 /
+// 60.9.  (Without groups a launch for trees alone costs 3.5 to 4.6 us a layer.  It paid up to a 64th of the slots,
+// where narrow q tiles, whose chunks are counted, have taken the trees' place.)
+inline bool trees_behind(int64_t tiles, int slots) { return tiles * 12 <= slots; }
 // Arrivals: per merge record and kv head arrive_words words that the plan clears.  Word 0 counts
 // (and wraps to 0 with the last arrival), the others are the tree, one bit a node (set by the first of
 // two, cleared by the second).  They fill the end of the partial LSE array from its last word
@@ -178,6 +177,11 @@ constexpr int kMinSharedTiles = 8;    // a shared prefix shorter than 512 tokens
 // prefill of 512 17.8 / 17.5, 2 x 512 19.4 / 21.7, 4 x 512 26.2 / 31.3, 1024 25.1 / 26.2, 64 over 448 15.3 / 15.7;
 // 256 over 256, 8 / 8 heads, 17.1 / 16.5.
 constexpr int kMinChunkTiles = 8, kMinChunkTilesDecode = 4, kMinChunkTilesShort = 2;
+constexpr int kNarrowBatch = 16;      // sequences of a batch that may have narrow tiles
+constexpr int kNarrowPieces = 16;     // pieces of a narrow tile
+// Narrow tiles of ranges up to this are not cut.  16 rows, whole / pieces of 4, us a layer: 32 tokens over 512 15.3 /
+// 16.9, over 1024 (17 tiles) 19.7 / 17.9.
+constexpr int kWholeNarrow = 12;
 constexpr int kMergeAhead = 8;        // partial rows a merge of few rows requests beside their LSEs
 // ... and a merge of a shared prefix's rows, for which its pieces are so long that they and the member's own
 // one are no more, up to pieces of as many tiles.  Append + attention of a layer, 32 / 8 heads, pieces of 4 / 6 /
@@ -260,7 +264,7 @@ struct PlanArgs {
   int32_t* cu_tiles;
   ItemRec* items;
   MergeRec* merges;
-  int32_t batch, total_q, tile_tokens, num_pages, max_tiles, max_items, part_cap;
+  int32_t batch, total_q, tile_tokens, num_pages, max_tiles, max_items, max_merges, part_cap;
   uint32_t* arrivals_end;  // one past the last arrival word (see MergeRec)
   int32_t hq, hkv, slots;   // q and kv heads; workgroups the GPU runs at a time
   int32_t allow_groups; // look for decode rows of neighbouring sequences that share a prefix
@@ -411,6 +415,55 @@ __device__ __forceinline__ bool short_pieces_pay(const PlanArgs& a, int L, int l
   return longest > kMinChunkTiles || whole <= min(8 + 64 * (saved - 1), (1 + 2 * saved) * a.tile_tokens);
 }
 
+// The header of a plan that the attention has nothing to do for.
+__device__ __forceinline__ void refuse_plan(PlanHeader* h) {
+  h->err = MC_ERR_RANGE;
+  h->num_items = h->num_merges = h->num_records = 0;
+  h->magic = kPlanMagic;
+}
+
+// The rows of a q tile of a batch of few sequences and few new tokens: kBM, or kNarrowRows or half as many, whose
+// items few_rows_item walks with all four wavefronts.  n: the batch's tiles of kBM rows, of kNarrowRows, of half as
+// many, and the KV tiles that the latter two look at.
+// A workgroup alone on its compute unit takes 1.07 us for a KV tile and 128 rows, 0.54 us for 32 or for 16 (each
+// wavefront walks every fourth half tile).  So narrow tiles have less than half the rate, but need no tree of
+// chunks (2 to 3 us a level) and no launch behind, and fill the compute units where q tiles of 128 rows are few.  Two
+// workgroups a compute unit take 1.34 us: what the L2s hand out, 15 TB/s, is the bound then, so there are never
+// more narrow items than compute units.
+// us a layer of four (append, attention, their share of the plan), whole tiles (cut) / 32 rows / 16 rows, 32 / 8
+// heads, tokens over keys cached:
+//   - up to 18 KV tiles, uncut: 64 over 512 19.1 / 17.9 / 13.9; 128 over 1024 23.9 / 20.2 / 19.4; 256 over 512 20.4 /
+//     17.9 / -, over 1024 24.1 / 22.8 / -;
+//   - 16 rows up to 16 tiles a compute unit, if every tile can be cut at least once: 8 over 4096 22.0 / 25.0 / 17.7,
+//     over 16000 30.4 / 33.4 / 24.9; 32 over 1024 21.5 / 18.2 / 15.4, over 4096 25.0 / 21.7 / 22.8, over 8192 28.2 /
+//     26.3 / 33; 64 over 2048 27.0 / 22.0 / 23.0;
+//   - 32 rows up to 24 tiles a compute unit: 64 over 4096 31.0 / 26.2; 128 over 2048 28.1 / 26.3, over 4096 (32 tiles)
+//     33.6 / 35.1; 256 over 2048 (34) 31.0 / 31.4;
+//   - up to a 64th of the slots of (q tile, kv head) pairs always, because whole tiles have many chunks there: 32 over
+//     8192 28.2 / 26.3, over 16000 34.6 / 35.6.
+__device__ __forceinline__ int narrow_rows(const PlanArgs& a, const int (&n)[5], int longest) {
+  if (n[2] <= n[0]) return kBM;                  // no tile holds more rows than that
+  const int units = a.slots / 2;
+  auto one_each = [&](int tiles) {
+    return tiles <= a.max_items && tiles <= a.max_merges && (long long)tiles * a.hkv <= units;
+  };
+  if (one_each(n[2]) && (longest <= 18 || (one_each(2 * n[2]) && (long long)n[4] * a.hkv <= 16 * units)))
+    return kNarrowRows / 2;
+  if (one_each(n[1]) && ((long long)n[3] * a.hkv <= 24 * units || 64ll * n[0] * a.hkv <= a.slots)) return kNarrowRows;
+  return kBM;
+}
+
+// The length of the pieces these are cut into, so that there are no more than compute units: as many equal ones a
+// tile, or by the sum of the tiles' lengths.  Nor are there more than the launch's grid has room for, or more than
+// kNarrowPieces a tile, which its last item combines (32 pieces of 32 rows: 17 us).
+__device__ __forceinline__ int narrow_pieces(const PlanArgs& a, int tiles, int cost, int longest) {
+  const int units = a.slots / 2, items = tiles * a.hkv;
+  const int equal = (longest + units / items - 1) / (units / items);
+  const int sum = units > items ? (int)(((long long)cost * a.hkv + units - items - 1) / (units - items)) : longest;
+  const int room = a.max_items > tiles ? (cost + a.max_items - tiles - 1) / (a.max_items - tiles) : longest;
+  return max(max(min(equal, sum), room), (longest + kNarrowPieces - 1) / kNarrowPieces);
+}
+
 // Page ids of every needed table entry, for batches too large for the planner's one workgroup
 // to walk: one wavefront per sequence, many workgroups.  Runs after plan_kernel and, on a bad
 // id, turns its verdict into MC_ERR_RANGE with an empty work list.  (Sequences whose offsets
@@ -434,9 +487,7 @@ __global__ __launch_bounds__(256) void validate_pages_kernel(PlanArgs a) {
       if (pg[u] < 0 || pg[u] >= a.num_pages) err = 1;
   }
   if (__ballot(err) != 0 && lane == 0) {
-    a.hdr->num_items = 0;
-    a.hdr->num_merges = 0;
-    a.hdr->err = MC_ERR_RANGE;
+    refuse_plan(a.hdr);
   }
 }
 
@@ -447,11 +498,11 @@ __global__ __launch_bounds__(256) void validate_pages_kernel(PlanArgs a) {
 // the launch is made of short items.
 // NT threads: 1024, or 256 for small batches, whose many block-wide steps then cost a quarter
 // of the wavefronts to synchronise.
-template <int NT>
+template <int NT, bool kMayNarrow>
 __global__ __launch_bounds__(NT) void plan_kernel(PlanArgs a) {
   __shared__ int scan[5 * NT / 64];   // wavefront totals of the block scans and sums
   __shared__ int hist[kBuckets];
-  __shared__ int s_err, s_maxcost, s_table_end, s_pages, s_suspect;
+  __shared__ int s_err, s_maxcost, s_table_end, s_pages, s_suspect, s_sums[5];
   // per-sequence arrays of batches that fit: the searches and tile look-ups below stay in LDS
   __shared__ int s_cu[kCuTilesInLds + 1], s_cuq[kCuTilesInLds + 1], s_beg[kCuTilesInLds],
       s_cup[kCuTilesInLds + 1];
@@ -506,6 +557,10 @@ __global__ __launch_bounds__(NT) void plan_kernel(PlanArgs a) {
   }
   // 1. validate, count tiles per sequence (contiguous chunk of sequences per thread)
   int my_tiles = 0, err = 0, maxcost = 1, my_pages = 0, table_end = 0;
+  // (kMayNarrow) the same in tiles of kNarrowRows rows and of half as many, and the KV tiles
+  // that these have to look at
+  const int narrow_tokens = a.tile_tokens * kNarrowRows / kBM;
+  int narrow_tiles[2] = {0, 0}, narrow_visits[2] = {0, 0};
   if (t == 0 && (cuq(0) != 0 || cuq(a.batch) != a.total_q || cup(0) < 0)) err = 1;
   for (int s = s_lo; s < s_hi; ++s) {
     const int q = cuq(s + 1) - cuq(s), b = beg(s);
@@ -518,7 +573,31 @@ __global__ __launch_bounds__(NT) void plan_kernel(PlanArgs a) {
     my_pages += need;            // (of all sequences no more than cu_pages[batch])
     table_end = max(table_end, cup(s) + need);
     my_tiles += (q + a.tile_tokens - 1) / a.tile_tokens;
+    if constexpr (kMayNarrow) {
+      const int visits = (int)min((end - q / 2 + kBN - 1) / kBN, (int64_t)1 << 12);
+#pragma unroll
+      for (int k = 0; k < 2; ++k) {
+        const int tiles = min((q + (narrow_tokens >> k) - 1) / (narrow_tokens >> k), 1 << 12);
+        narrow_tiles[k] += tiles;
+        narrow_visits[k] += tiles * visits;       // (at most 2^24 for each of 16 sequences)
+      }
+    }
     maxcost = max(maxcost, (int)((end + kBN - 1) / kBN));
+  }
+  // In the small variant all sequences are the first wavefront's, a thread each: it sums the tiles before them here,
+  // ahead of the barrier that there is.
+  constexpr bool kFirstWave = NT == kPlanThreadsSmall;
+  constexpr int kSums = kMayNarrow ? 5 : 1;
+  int before[kSums] = {my_tiles};
+  if constexpr (kMayNarrow)
+    for (int k = 0; k < 2; ++k) { before[1 + k] = narrow_tiles[k]; before[3 + k] = narrow_visits[k]; }
+  if (kFirstWave && t < 64) {
+#pragma unroll
+    for (int k = 0; k < kSums; ++k) {
+      const int incl = wave_inclusive_sum(before[k]);
+      before[k] = incl - before[k];
+      if (t == 63) s_sums[k] = incl;
+    }
   }
   // (one LDS atomic per wavefront, not per thread: 1024 atomics on one address take microseconds)
   if (__ballot(err != 0) != 0 && (t & 63) == 0) atomicOr(&s_err, 1);
@@ -532,7 +611,7 @@ __global__ __launch_bounds__(NT) void plan_kernel(PlanArgs a) {
   }
   __syncthreads();
   if (s_err) {
-    if (t == 0) { a.hdr->err = MC_ERR_RANGE; a.hdr->num_items = 0; a.hdr->num_merges = 0; a.hdr->magic = kPlanMagic; }
+    if (t == 0) refuse_plan(a.hdr);
     return;
   }
   // 2. page ids of every needed table entry.  Small batches (their offsets sit in LDS) look at the table as it lies
@@ -558,26 +637,6 @@ __global__ __launch_bounds__(NT) void plan_kernel(PlanArgs a) {
   for (int k = 0; k < kFlatLoads; ++k)
     flat_ids[k] = ids_here && !suspect ? flat_load(t + k * NT) : i32x4u{0, 0, 0, 0};
   // (batches beyond that: validate_pages_kernel, launched after this kernel, on many workgroups)
-  // 3. exclusive scan of tiles per sequence
-  int total_tiles;
-  int base = block_exclusive_scan<NT>(my_tiles, scan, &total_tiles);
-  for (int s = s_lo; s < s_hi; ++s) {
-    a.cu_tiles[s] = base;
-    if (cu_in_lds) s_cu[s] = base;
-    const int q = cuq(s + 1) - cuq(s);
-    base += (q + a.tile_tokens - 1) / a.tile_tokens;
-  }
-  if (t == 0) {
-    a.cu_tiles[a.batch] = total_tiles;
-    if (cu_in_lds) s_cu[a.batch] = total_tiles;
-  }
-  __threadfence_block();
-  __syncthreads();
-  if (total_tiles > a.max_tiles) {
-    if (t == 0) { a.hdr->err = MC_ERR_RANGE; a.hdr->num_items = 0; a.hdr->num_merges = 0; a.hdr->magic = kPlanMagic; }
-    return;
-  }
-
   // 3b. shared-prefix groups (Sec. 3.4, fork_sequence in Sec. 3.5: sequences may share the pages of a common
   //     prefix).  The new tokens of neighbouring sequences with short new ranges (decode rows,
   //     or a few tokens each) whose tables start with the same pages attend that prefix together
@@ -701,6 +760,41 @@ __global__ __launch_bounds__(NT) void plan_kernel(PlanArgs a) {
   }
   bool groups = try_groups && s_groups != 0;
 
+  // 3. exclusive scan of tiles per sequence
+  //     Tiles of fewer rows where even these are no more than a workgroup a compute unit: narrow_rows.
+  int total_tiles, base, whole_tiles;
+  bool narrow = false;
+  if constexpr (kMayNarrow) {
+    const int all[5] = {s_sums[0], s_sums[1], s_sums[2], s_sums[3], s_sums[4]};
+    const int rows = wide || groups ? kBM : narrow_rows(a, all, s_maxcost);
+    const int k = rows == kBM ? 0 : rows == kNarrowRows ? 1 : 2;
+    base = k == 0 ? before[0] : k == 1 ? before[1] : before[2];
+    total_tiles = k == 0 ? all[0] : k == 1 ? all[1] : all[2];
+    narrow = k > 0;
+    whole_tiles = all[0];
+    if (narrow) a.tile_tokens = narrow_tokens >> (k - 1);
+  } else {
+    if constexpr (kFirstWave) { base = before[0]; total_tiles = s_sums[0]; }
+    else base = block_exclusive_scan<NT>(my_tiles, scan, &total_tiles);
+    whole_tiles = total_tiles;
+  }
+  for (int s = s_lo; s < s_hi; ++s) {
+    a.cu_tiles[s] = base;
+    if (cu_in_lds) s_cu[s] = base;
+    const int q = cuq(s + 1) - cuq(s);
+    base += (q + a.tile_tokens - 1) / a.tile_tokens;
+  }
+  if (t == 0) {
+    a.cu_tiles[a.batch] = total_tiles;
+    if (cu_in_lds) s_cu[a.batch] = total_tiles;
+  }
+  __threadfence_block();
+  __syncthreads();
+  if (total_tiles > (narrow ? a.max_items : a.max_tiles)) {
+    if (t == 0) refuse_plan(a.hdr);
+    return;
+  }
+
   // q tile i: its sequence, first row, token count, KV tiles, the last even tile index at which
   // a chunk may start (every row must see at least the first key of every chunk), the prefix
   // tiles its shared-prefix group covers, the group's new tokens if this tile leads one, and those of
@@ -763,9 +857,10 @@ __global__ __launch_bounds__(NT) void plan_kernel(PlanArgs a) {
     cost = (long long)total_tiles * s_maxcost <= INT32_MAX ? block_sum_int<NT>((int)cost, scan)
                                                              : block_sum<NT>(cost, scan);
     const long long room = (long long)kItemsPerSlot * a.slots, heads = cost * a.hkv + room - 1;
-    const long long want = heads <= INT32_MAX ? (int)heads / (int)room : heads / room;
+    long long want = heads <= INT32_MAX ? (int)heads / (int)room : heads / room;
+    if (kMayNarrow && narrow) want = narrow_pieces(a, total_tiles, (int)min(cost, 1ll << 30), s_maxcost);
     // short pieces: only if no sequence has two new tokens (as many q tiles as new tokens)
-    int shortest = kMinChunkTiles;
+    int shortest = narrow ? kMinChunkTilesDecode : kMinChunkTiles;
     if (a.total_q <= total_tiles && want < kMinChunkTiles) {
       shortest = s_maxcost <= kMinChunkTilesShort * kMergeAhead ? kMinChunkTilesShort : kMinChunkTilesDecode;
       shortest = max(shortest, ((int)want + 1) & ~1);
@@ -781,7 +876,8 @@ __global__ __launch_bounds__(NT) void plan_kernel(PlanArgs a) {
     }
     L = (L + 1) & ~1;
     for (;;) {
-      if (L >= s_maxcost) { L = 0; break; }   // nothing is long enough to be cut
+      // (nothing is long enough to be cut)
+      if (L >= s_maxcost || (narrow && s_maxcost <= kWholeNarrow)) { L = 0; break; }
       // (each tile has at most s_maxcost / L + 1 chunks of its own, and as many of a prefix its tokens)
       const long long most = (long long)(groups ? 2 : 1) * (s_maxcost / L + 1) * a.total_q +
                              (long long)total_tiles * arrive_rows(L);
@@ -811,7 +907,7 @@ __global__ __launch_bounds__(NT) void plan_kernel(PlanArgs a) {
     const int rem = (int)(n % a.slots);
     const int rem_tiles = rem / a.hkv;
     const int c = rem > 0 ? min(8, (a.slots + rem - 1) / rem) : 0;
-    if (L == 0 && !groups && !wide && total_tiles <= kTailTilesMax && n >= a.slots &&
+    if (L == 0 && !groups && !wide && !narrow && total_tiles <= kTailTilesMax && n >= a.slots &&
         n < (int64_t)kRoundsWanted * a.slots && rem_tiles >= 1 && 10 * rem <= 7 * a.slots && c >= 2 &&
         (int64_t)rem_tiles * (a.tile_tokens * c + arrive_rows(0)) <= a.part_cap) {
       if (t == 0) { s_tail_bucket = kBuckets; s_tail_take = 0; s_tail_taken = 0; }
@@ -926,8 +1022,8 @@ __global__ __launch_bounds__(NT) void plan_kernel(PlanArgs a) {
   }
   __syncthreads();
   if (s_err || tot_items > a.max_items || tot_own + tot_grp + (int64_t)tot_merge * arrive_rows(L) > a.part_cap ||
-      tot_merge > a.max_tiles) {   // a page id, or what cannot happen
-    if (t == 0) { a.hdr->err = MC_ERR_RANGE; a.hdr->num_items = 0; a.hdr->num_merges = 0; a.hdr->magic = kPlanMagic; }
+      tot_merge > a.max_merges) {   // a page id, or what cannot happen
+    if (t == 0) refuse_plan(a.hdr);
     return;
   }
   // where each group's partial rows start (after all the tiles' own): its members need it
@@ -1029,8 +1125,9 @@ __global__ __launch_bounds__(NT) void plan_kernel(PlanArgs a) {
   if (t == 0) {
     a.hdr->err = MC_OK;
     a.hdr->num_items = tot_items;
-    a.hdr->num_merges = tot_merge;
-    a.hdr->chunk_tiles = L;
+    a.hdr->num_merges = narrow ? whole_tiles : tot_merge;
+    a.hdr->chunk_tiles = narrow && L == 0 ? (s_maxcost + 1) & ~1 : L;
+    a.hdr->num_records = tot_merge;
     a.hdr->tile_tokens = a.tile_tokens;
     a.hdr->batch = a.batch;
     a.hdr->total_q = a.total_q;
@@ -1105,6 +1202,7 @@ struct AttnArgs {
   float* part_o;           // [partial row][128]
   int32_t num_pages, hkv, hq, batch, total_q;
   int32_t part_cap;        // rows of the partial arrays
+  int32_t flat_rows;       // rows up to which chunks are no tree's (merge_kernel)
   int32_t behind;          // what merge_kernel combines (see MergeRec): kGroupsBehind, kTreesBehind
   float scale, scale_log2;  // softmax scale, and scale * log2(e)
 };
@@ -1186,8 +1284,8 @@ __device__ __forceinline__ float load_part(buffer_rsrc r, uint32_t off) {
 
 // Chunks of a tile's own that a merge record's last step combines (a tree's count as one).
 template <int G>
-__device__ __forceinline__ int own_chunks(bool trees, int nsplit, int ntok) {
-  return ntok * G <= kFlatRows || !trees ? nsplit : 1;
+__device__ __forceinline__ int own_chunks(int flat, bool trees, int nsplit, int ntok) {
+  return ntok * G <= flat || !trees ? nsplit : 1;
 }
 
 // What a workgroup was the last to arrive at, in LDS (the tiles are consumed): the merge records, the
@@ -1221,7 +1319,7 @@ __device__ __forceinline__ void chunk_step(float lse, float& mx, float& den, flo
 // flight, and nothing but the loop stands under a condition.
 template <typename T, int G, int kScope, int kRows, int kChunks, typename Record>
 __device__ __forceinline__ void merge_rows(const AttnArgs& a, buffer_rsrc rs_o, buffer_rsrc rs_lse,
-                                           int hk, int tokens, bool trees, int block, int blocks,
+                                           int hk, int tokens, int flat, bool trees, int block, int blocks,
                                            Record&& record) {
   const int rows = tokens * G, piece = threadIdx.x & 31;
   for (int r0 = (threadIdx.x >> 5) + block * kRows * (kThreads / 32); r0 < rows;
@@ -1241,12 +1339,12 @@ __device__ __forceinline__ void merge_rows(const AttnArgs& a, buffer_rsrc rs_o, 
       const int tt = i - first;
       // row r of the chunk whose rows, of_rows of them, start at row0
       auto place = [&](uint32_t row0, int r, int of_rows) __attribute__((always_inline)) {
-        return row0 * 512u + (of_rows <= kFlatRows || !trees
+        return row0 * 512u + (of_rows <= flat || !trees
                                   ? r * 512u + piece * 16u
                                   : (piece >> 1) * of_rows * 32u + r * 32u + (piece & 1) * 16u);
       };
       g_nsplit[u] = m[4];
-      nch[u] = own_chunks<G>(trees, m[2], m[1]) + m[4];
+      nch[u] = own_chunks<G>(flat, trees, m[2], m[1]) + m[4];
       const uint32_t g0 = m[5] * a.hq + hk * m[6] * G, own0 = m[3] * a.hq + hk * m[1] * G;
       const int g_r = (m[7] + tt) * G + r % G, own_r = tt * G + r % G;
       g_row[u] = g0 + g_r;
@@ -1336,20 +1434,20 @@ __device__ __forceinline__ uint32_t first_part_row(const AttnArgs& a, const Item
 }
 
 // Whether a chunk that is no tree's is combined inside this launch; else merge_kernel does it behind it.
-template <int G>
+template <int G, int kFlat>
 __device__ __forceinline__ bool combined_here(const Item& it, const i32x8& m) {
-  return it.group || m[4] > 0 ? !(it.behind & kGroupsBehind) : it.ntok * G <= kFlatRows;
+  return it.group || m[4] > 0 ? !(it.behind & kGroupsBehind) : it.ntok * G <= kFlat;
 }
 
 // Counts written rows - a chunk of few rows, a chunk of a prefix (at every member's record), or a tree's
 // result - and, if they were the last there, combines the record's chunks.  s_last: 0, and published;
 // list: free LDS.
-template <typename T, int G>
+template <typename T, int G, int kFlat, int kRows>
 __device__ __forceinline__ void arrive(const AttnArgs& a, const Item& it, int hk, buffer_rsrc rs_o,
                                        buffer_rsrc rs_lse, const i32x8& m, int words, int& s_last,
                                        MergeList& list) {
   const int tid = threadIdx.x;
-  const bool listed = it.group || it.ntok * G > kFlatRows;
+  const bool listed = it.group || it.ntok * G > kFlat;
   uint32_t* arrivals = reinterpret_cast<uint32_t*>(a.part_lse) + (int64_t)a.part_cap * a.hq - 1;
   i32x8 mr = m;
   if (it.group) mr = *reinterpret_cast<const i32x8*>(a.merges + min(it.merge + tid, it.n_rec - 1));
@@ -1357,7 +1455,7 @@ __device__ __forceinline__ void arrive(const AttnArgs& a, const Item& it, int hk
   __syncthreads();
   // records of this item: one, or the group's members' (their tokens follow one another)
   if (tid < (it.group ? it.ntok : 1) && it.merge + tid < it.n_rec && mr[0] < it.q_first + it.ntok) {
-    const int n = own_chunks<G>(true, mr[2], mr[1]) + mr[4];
+    const int n = own_chunks<G>(kFlat, true, mr[2], mr[1]) + mr[4];
     if (atomicInc(arrivals - ((int64_t)(it.merge + tid) * a.hkv + hk) * words, n - 1) == (unsigned)n - 1) {
       const int at = atomicAdd(&s_last, mr[1]);
       if (listed) {
@@ -1374,14 +1472,14 @@ __device__ __forceinline__ void arrive(const AttnArgs& a, const Item& it, int hk
   if (tokens == 0) return;
   if (listed)
     merge_rows<T, G, kDeviceScope, 2, kListedAhead>(
-        a, rs_o, rs_lse, hk, tokens, true, 0, 1, [&](int i, int& first) __attribute__((always_inline)) {
+        a, rs_o, rs_lse, hk, tokens, kFlat, true, 0, 1, [&](int i, int& first) __attribute__((always_inline)) {
       const int k = list.rec_of[i];
       first = list.first[k];
       return *reinterpret_cast<const i32x8*>(list.rec[k]);
     });
   else
-    merge_rows<T, G, kDeviceScope, 1, kMergeAhead>(
-        a, rs_o, rs_lse, hk, tokens, true, 0, 1, [&](int, int& first) __attribute__((always_inline)) { first = 0; return m; });
+    merge_rows<T, G, kDeviceScope, kRows, kMergeAhead>(
+        a, rs_o, rs_lse, hk, tokens, kFlat, true, 0, 1, [&](int, int& first) __attribute__((always_inline)) { first = 0; return m; });
 }
 
 // max or sum over the four lanes l, l ^ 16, l ^ 32, l ^ 48: a swap of the wavefront's halves, then one
@@ -1396,9 +1494,10 @@ __device__ __forceinline__ float across_rows(float x, Op&& op) {
   return op(__builtin_bit_cast(float, lo), __builtin_bit_cast(float, hi));
 }
 
-// An item of at most kFlatRows rows.  All four wavefronts hold those rows and take half tiles (32
-// keys, 2 pages) in turn, each by itself: K straight into registers, V through its own 16 KiB of LDS,
-// no barrier until their sums are put together at the end.  v_mfma_f32_16x16x32: S^T = K Q^T (A = 16
+// An item of at most 16 rows, or of two blocks of 16 which share every K and V fragment (kRB = 2).  All four
+// wavefronts hold those rows and take half tiles (32 keys, 2 pages) in turn, each by itself: K straight into
+// registers, V through its own 16 KiB of LDS, no barrier until their sums are put together at the end.
+// v_mfma_f32_16x16x32: S^T = K Q^T (A = 16
 // keys, lane l: key l % 16, d 8 (l / 16) ..), a lane then has one row (l % 16) and 8 of the 32 keys;
 // O^T += V^T P^T with P^T straight from S^T: operand slot 8 g + j is key 4 g + j of the first 16 keys
 // (j < 4) or of the second, for both operands (g = l / 16).
@@ -1414,9 +1513,12 @@ __device__ __forceinline__ float across_rows(float x, Op&& op) {
 // of 64 forks of a 2048-token prompt, 32 / 8, four layers 196.1 -> 200.3, 200.1; of 64 rows over 1024..4096
 // beside a prefill, two layers 328 -> 329, 336; of eight rows over 1024..4096, 64 / 8, eight layers 207.0 ->
 // 205.0, 205.4.
+// kNarrow: ranges of few new tokens, a workgroup a compute unit at most, their keys in the L2s: bound by latency, so V
+// is requested beside K there (256 tokens over 256, 8 / 8 heads, 11.8 -> 11.3 us a layer; 128 over 1024, 32 / 8,
+// 19.5 -> 19.0).
 // A layer (append and attention) of one row over 1000 keys, 32 / 8 heads, 12.9 -> 10.5 us; of eight rows
 // over 1024..4096, 64 / 8 heads, 27.7 -> 25.5; 256 rows, bound by the reads, the same.
-template <typename T, int G>
+template <typename T, int G, int kRB, bool kNarrow>
 __device__ __forceinline__ void few_rows_item(const AttnArgs& a, const Item& it, int hk, int b, int row0,
                                               const i32x8& ids, char* lds, float* stat, int& s_last) {
   typedef typename Mfma<T>::vec8 vec8;
@@ -1434,7 +1536,7 @@ __device__ __forceinline__ void few_rows_item(const AttnArgs& a, const Item& it,
   // K: key l16 of each page, chunks 4 kk + g4; V: 4 rows an instruction, swizzled as tiles are
   const uint32_t k_off = l16 * kRowBytes + g4 * 16;
   const uint32_t v_off = g4 * kRowBytes + ((l16 ^ (g4 << 2)) << 4) + (uint32_t)a.hkv * kHeadPageBytes;
-  vec8 kf[2][4], q[4];
+  vec8 kf[2][4], q[kRB][4];
   auto request_v = [&](int32_t id0, int32_t id1, int buf) __attribute__((always_inline)) {
     const char* page[2] = {page_base(id0), page_base(id1)};
 #pragma unroll
@@ -1460,12 +1562,17 @@ __device__ __forceinline__ void few_rows_item(const AttnArgs& a, const Item& it,
     request_v(id0, id1, 0);
     request_k(id0, id1);
   }
-  // the row of this lane (one that does not exist reads the last one's q)
-  const int my_row = min(l16, rows - 1), tt = my_row / G;
-  const char* q_row = a.q + ((int64_t)(it.q_first + tt) * a.hq + hk * G + my_row % G) * kRowBytes;
+  // this lane's row of each block (one that does not exist reads the last one's q)
+  int tt[kRB];
 #pragma unroll
-  for (int kk = 0; kk < 4; ++kk)
-    q[kk] = __builtin_bit_cast(vec8, *reinterpret_cast<const u32x4*>(q_row + kk * 64 + g4 * 16));
+  for (int rb = 0; rb < kRB; ++rb) {
+    const int my_row = min(16 * rb + l16, rows - 1);
+    tt[rb] = my_row / G;
+    const char* q_row = a.q + ((int64_t)(it.q_first + tt[rb]) * a.hq + hk * G + my_row % G) * kRowBytes;
+#pragma unroll
+    for (int kk = 0; kk < 4; ++kk)
+      q[rb][kk] = __builtin_bit_cast(vec8, *reinterpret_cast<const u32x4*>(q_row + kk * 64 + g4 * 16));
+  }
 
   // positions: as in attn_kernel
   const int first_pos = it.group ? it.t1 * kBN : b + row0;
@@ -1473,39 +1580,48 @@ __device__ __forceinline__ void few_rows_item(const AttnArgs& a, const Item& it,
   const bool fits = b >= 0 && kv_len > kBN * it.t0;
   const int n_halves = fits ? (kv_len + kHalf - 1) / kHalf : 0;
   const int n_full = (first_pos + 1) / kHalf;
-  const int my_pos = first_pos + tt;
   const float c2 = a.scale_log2;
 
-  f32x4 o[8];
+  f32x4 o[kRB][8];
+  float m_run[kRB], l_run[kRB];     // the row's running maximum (raw); this lane's part of its sum
 #pragma unroll
-  for (int i = 0; i < 8; ++i) o[i] = f32x4{0.f, 0.f, 0.f, 0.f};
-  float m_run = -INFINITY, l_run = 0.f;     // the row's running maximum (raw); this lane's part of its sum
+  for (int rb = 0; rb < kRB; ++rb) {
+#pragma unroll
+    for (int i = 0; i < 8; ++i) o[rb][i] = f32x4{0.f, 0.f, 0.f, 0.f};
+    m_run[rb] = -INFINITY;
+    l_run[rb] = 0.f;
+  }
   int buf = 0;
   for (; h < n_halves; h += 4, buf ^= 1) {
-    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     const bool more = h + 4 < n_halves;
-    if (more) request_v(next0, next1, buf ^ 1);
+    if constexpr (!kNarrow) {
+      asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+      if (more) request_v(next0, next1, buf ^ 1);
+    }
     // (K and q pass through the wait: the compiler, which counts its own loads but not the copies, would
     // else wait for them once more ahead of S)
+    // (the other V buffer has been read)
+    if constexpr (kNarrow) asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
     asm volatile("s_waitcnt vmcnt(0)"
                  : "+v"(kf[0][0]), "+v"(kf[0][1]), "+v"(kf[0][2]), "+v"(kf[0][3]), "+v"(kf[1][0]), "+v"(kf[1][1]),
-                   "+v"(kf[1][2]), "+v"(kf[1][3]), "+v"(q[0]), "+v"(q[1]), "+v"(q[2]), "+v"(q[3])
+                   "+v"(kf[1][2]), "+v"(kf[1][3]), "+v"(q[0][0]), "+v"(q[0][1]), "+v"(q[0][2]), "+v"(q[0][3]),
+                   "+v"(q[kRB - 1][0]), "+v"(q[kRB - 1][1]), "+v"(q[kRB - 1][2]), "+v"(q[kRB - 1][3])
                  :
                  : "memory");
-    f32x4 s[2] = {{0.f, 0.f, 0.f, 0.f}, {0.f, 0.f, 0.f, 0.f}};
+    f32x4 s[kRB][2];
+#pragma unroll
+    for (int rb = 0; rb < kRB; ++rb) s[rb][0] = s[rb][1] = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
     for (int kk = 0; kk < 4; ++kk)
 #pragma unroll
-      for (int p = 0; p < 2; ++p) s[p] = Mfma<T>::run16(kf[p][kk], q[kk], s[p]);
+      for (int p = 0; p < 2; ++p)
+#pragma unroll
+        for (int rb = 0; rb < kRB; ++rb) s[rb][p] = Mfma<T>::run16(kf[p][kk], q[rb][kk], s[rb][p]);
     if (more) {
+      if constexpr (kNarrow) request_v(next0, next1, buf ^ 1);
       request_k(next0, next1);
       next0 = id_of(h + 8, 0);
       next1 = id_of(h + 8, 1);
-    }
-    if (h >= n_full) {
-#pragma unroll
-      for (int i = 0; i < 8; ++i)
-        if (h * kHalf + 16 * (i >> 2) + 4 * g4 + (i & 3) > my_pos) s[i >> 2][i & 3] = -INFINITY;
     }
     const uint32_t v_buf = lds_own + buf * kHalfBytes;
     if (kv_len < (h + 1) * kHalf) {      // V rows of keys past the range: 0 x NaN would poison O
@@ -1516,18 +1632,29 @@ __device__ __forceinline__ void few_rows_item(const AttnArgs& a, const Item& it,
         if (4 * i + g4 >= valid)
           *reinterpret_cast<u32x4 __attribute__((address_space(3)))*>((size_t)(v_buf + i * 1024 + lane * 16)) = zero;
     }
-    float mx = fmaxf(fmaxf(fmaxf(s[0][0], s[0][1]), fmaxf(s[0][2], s[0][3])),
-                     fmaxf(fmaxf(s[1][0], s[1][1]), fmaxf(s[1][2], s[1][3])));
-    mx = fmaxf(m_run, across_rows(mx, [](float x, float y) { return fmaxf(x, y); }));
-    const float ref = mx > -INFINITY ? mx : 0.f, mc2 = ref * c2;      // (no key seen yet: no maximum)
-    const float alpha = __builtin_amdgcn_exp2f((m_run - ref) * c2);
-    m_run = mx;
-    float p[8];
+    float alpha[kRB];
+    u32x4 pw[kRB];
 #pragma unroll
-    for (int i = 0; i < 8; ++i) p[i] = __builtin_amdgcn_exp2f(__builtin_fmaf(s[i >> 2][i & 3], c2, -mc2));
-    l_run = __builtin_fmaf(l_run, alpha, ((p[0] + p[1]) + (p[2] + p[3])) + ((p[4] + p[5]) + (p[6] + p[7])));
-    const u32x4 pw = {Mfma<T>::pack2(p[0], p[1]), Mfma<T>::pack2(p[2], p[3]), Mfma<T>::pack2(p[4], p[5]),
-                      Mfma<T>::pack2(p[6], p[7])};
+    for (int rb = 0; rb < kRB; ++rb) {
+      if (h >= n_full) {
+#pragma unroll
+        for (int i = 0; i < 8; ++i)
+          if (h * kHalf + 16 * (i >> 2) + 4 * g4 + (i & 3) > first_pos + tt[rb]) s[rb][i >> 2][i & 3] = -INFINITY;
+      }
+      const f32x4 &s0 = s[rb][0], &s1 = s[rb][1];
+      float mx = fmaxf(fmaxf(fmaxf(s0[0], s0[1]), fmaxf(s0[2], s0[3])), fmaxf(fmaxf(s1[0], s1[1]), fmaxf(s1[2], s1[3])));
+      mx = fmaxf(m_run[rb], across_rows(mx, [](float x, float y) { return fmaxf(x, y); }));
+      const float ref = mx > -INFINITY ? mx : 0.f, mc2 = ref * c2;      // (no key seen yet: no maximum)
+      alpha[rb] = __builtin_amdgcn_exp2f((m_run[rb] - ref) * c2);
+      m_run[rb] = mx;
+      float p[8];
+#pragma unroll
+      for (int i = 0; i < 8; ++i) p[i] = __builtin_amdgcn_exp2f(__builtin_fmaf(s[rb][i >> 2][i & 3], c2, -mc2));
+      l_run[rb] = __builtin_fmaf(l_run[rb], alpha[rb],
+                                 ((p[0] + p[1]) + (p[2] + p[3])) + ((p[4] + p[5]) + (p[6] + p[7])));
+      pw[rb] = u32x4{Mfma<T>::pack2(p[0], p[1]), Mfma<T>::pack2(p[2], p[3]), Mfma<T>::pack2(p[4], p[5]),
+                     Mfma<T>::pack2(p[6], p[7])};
+    }
 #pragma unroll
     for (int i = 0; i < 8; ++i) {
       const int key = 4 * g4 + (l16 >> 2), at = 2 * i + ((l16 & 3) >> 1), sub = (l16 & 1) * 8;
@@ -1535,8 +1662,11 @@ __device__ __forceinline__ void few_rows_item(const AttnArgs& a, const Item& it,
       const s16x4 hi =
           __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4_ptr)(size_t)(v_buf + v_swz(key + 16, at) + sub));
       const vec8 vf = __builtin_bit_cast(vec8, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
-      o[i] *= alpha;
-      o[i] = Mfma<T>::run16(vf, __builtin_bit_cast(vec8, pw), o[i]);
+#pragma unroll
+      for (int rb = 0; rb < kRB; ++rb) {
+        o[rb][i] *= alpha[rb];
+        o[rb][i] = Mfma<T>::run16(vf, __builtin_bit_cast(vec8, pw[rb]), o[rb][i]);
+      }
     }
   }
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // (a half tile past the range may be under way)
@@ -1544,22 +1674,29 @@ __device__ __forceinline__ void few_rows_item(const AttnArgs& a, const Item& it,
 
   // ---- the four wavefronts' sums: O by rows of 32 pieces of 16 bytes (piece 4 i + g4: d = 16 i + 4 g4
   //      + {0..3}; the swizzle spreads the rows over the banks), each in its own LDS
-  l_run = across_rows(l_run, [](float x, float y) { return x + y; });
-  if (l16 < rows) {
+  constexpr int kRows = 16 * kRB;
 #pragma unroll
-    for (int i = 0; i < 8; ++i)
-      *reinterpret_cast<f32x4*>(lds + wave * (2 * kHalfBytes) + l16 * 512 + (((4 * i + g4) ^ l16) << 4)) = o[i];
-  }
-  if (lane < 16) {
-    stat[wave * 16 + lane] = m_run;
-    stat[64 + wave * 16 + lane] = l_run;
+  for (int rb = 0; rb < kRB; ++rb) {
+    const int r = 16 * rb + l16;
+    l_run[rb] = across_rows(l_run[rb], [](float x, float y) { return x + y; });
+    if (r < rows) {
+#pragma unroll
+      for (int i = 0; i < 8; ++i)
+        *reinterpret_cast<f32x4*>(lds + wave * (2 * kHalfBytes) + r * 512 + (((4 * i + g4) ^ r) << 4)) = o[rb][i];
+    }
+    if (lane < 16) {
+      stat[wave * kRows + r] = m_run[rb];
+      stat[(4 + wave) * kRows + r] = l_run[rb];
+    }
   }
   __syncthreads();
   const buffer_rsrc rs_o = make_rsrc(a.part_o, (uint32_t)a.part_cap * a.hq * 512u);
   const buffer_rsrc rs_lse = make_rsrc(a.part_lse, (uint32_t)a.part_cap * a.hq * 4u);
   i32x8 m = {0, 0, 0, 0, 0, 0, 0, 0};
   int words = 0;
-  if (it.chunk >= 0) {
+  constexpr int kFlat = kNarrow ? kNarrowRows : kFlatRows;
+  const bool chunk = it.chunk >= 0;
+  if (chunk) {
     m = *(const __attribute__((address_space(4))) i32x8*)(a.merges + it.merge);
     words = ((const_i32_ptr)a.hdr)[10];
   }
@@ -1568,22 +1705,22 @@ __device__ __forceinline__ void few_rows_item(const AttnArgs& a, const Item& it,
     const int piece = tid & 31;
     float mx = -INFINITY;
 #pragma unroll
-    for (int w = 0; w < 4; ++w) mx = fmaxf(mx, stat[w * 16 + r]);
+    for (int w = 0; w < 4; ++w) mx = fmaxf(mx, stat[w * kRows + r]);
     const float ref = mx > -INFINITY ? mx : 0.f;
     float sum = 0.f;
     f32x4 acc = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
     for (int w = 0; w < 4; ++w) {
-      const float f = __builtin_amdgcn_exp2f((stat[w * 16 + r] - ref) * c2);
-      sum = __builtin_fmaf(stat[64 + w * 16 + r], f, sum);
+      const float f = __builtin_amdgcn_exp2f((stat[w * kRows + r] - ref) * c2);
+      sum = __builtin_fmaf(stat[(4 + w) * kRows + r], f, sum);
       acc += f * *reinterpret_cast<const f32x4*>(lds + w * (2 * kHalfBytes) + r * 512 + ((piece ^ r) << 4));
     }
     const float inv = fits ? 1.f / sum : 0.f, lse = fits ? mx * a.scale + __logf(sum) : -INFINITY;
     acc *= inv;
-    if (it.chunk >= 0 && !combined_here<G>(it, m)) {
+    if (chunk && !combined_here<G, kFlat>(it, m)) {
       store_part<kLaunchScope>(rs_o, (part0 + r) * 512u + piece * 16u, acc);
       if (piece == 0) store_part<kLaunchScope>(rs_lse, (part0 + r) * 4u, lse);
-    } else if (it.chunk >= 0) {
+    } else if (chunk) {
       store_part<kDeviceScope>(rs_o, (part0 + r) * 512u + piece * 16u, acc);
       if (piece == 0) store_part<kDeviceScope>(rs_lse, (part0 + r) * 4u, lse);
     } else {
@@ -1593,9 +1730,13 @@ __device__ __forceinline__ void few_rows_item(const AttnArgs& a, const Item& it,
       if (piece == 0) a.lse[out_row] = lse;
     }
   }
-  if (it.chunk >= 0 && combined_here<G>(it, m))
-    arrive<T, G>(a, it, hk, rs_o, rs_lse, m, words, s_last, *reinterpret_cast<MergeList*>(lds));
+  if (chunk && combined_here<G, kFlat>(it, m))
+    arrive<T, G, kFlat, kRB>(a, it, hk, rs_o, rs_lse, m, words, s_last, *reinterpret_cast<MergeList*>(lds));
 }
+
+// Kinds of the kernel (kMode): plain; for batches with many short q tiles (decode steps); for batches whose q tiles
+// may be narrow.
+constexpr int kPlain = 0, kGated = 1, kNarrowTiles = 2;
 
 // Pipeline of one workgroup.  A KV tile (64 keys, 4 pages) is the unit of the V staging
 // and of the workgroup barrier; a half tile (32 keys, 2 pages) is the unit of the K staging and
@@ -1609,13 +1750,15 @@ __device__ __forceinline__ void few_rows_item(const AttnArgs& a, const Item& it,
 // The two score register sets swap roles every half step, so a tile starts and ends with the
 // same set and nothing is copied.  Each step of a phase is one MFMA, at most one LDS fragment
 // fetch (4 MFMAs ahead of its use) and a slice of the VALU work; the order is pinned.
-// kGate: wavefronts none of whose rows exists skip the arithmetic.  Worth it for batches with
+// kGated: wavefronts none of whose rows exists skip the arithmetic.  Worth it for batches with
 // many short q tiles (decode steps); the plain variant is ~2 % faster when all tiles are full.
 // kCB: blocks of 32 rows per wavefront.  1: q tiles of 128 rows, two workgroups per compute
 // unit.  2: q tiles of 256 rows, one workgroup per compute unit with twice the registers: every
 // K and V fragment read from LDS feeds two MFMAs, every tile copied to LDS serves twice the rows.
-template <typename T, int G, bool kGate, int kCB>
+template <typename T, int G, int kMode, int kCB>
 __global__ __launch_bounds__(kThreads, kCB == 1 ? 2 : 1) void attn_kernel(AttnArgs a) {
+  constexpr bool kGate = kMode == kGated, kNarrow = kMode == kNarrowTiles;
+  constexpr int kFlat = kNarrow ? kNarrowRows : kFlatRows;
   constexpr int kWaveRows = 32 * kCB;       // rows per wavefront
   constexpr int TOK = kBM * kCB / G;        // tokens per q tile
   constexpr int kHalf = kBN / 2;
@@ -1644,9 +1787,13 @@ __global__ __launch_bounds__(kThreads, kCB == 1 ? 2 : 1) void attn_kernel(AttnAr
   int behind = a.behind;
   asm volatile("" : "+s"(behind));
   asm volatile("" ::"s"(a.pool_layer), "s"(a.begin), "s"(a.q), "s"(a.num_pages), "s"(a.total_q));
-  asm volatile("" : "+s"(item), "+s"(item_b), "+s"(hdr));
+  int n_rec = 0;
+  if (kNarrow) n_rec = ((const_i32_ptr)a.hdr)[11];
+  asm volatile("" : "+s"(item), "+s"(item_b), "+s"(hdr), "+s"(n_rec));
+  if (!kNarrow) n_rec = hdr[6];                // as many as q tiles that were cut
   // the work list must come from a plan made for this very batch
-  const bool ours = (hdr[0] == kPlanMagic) & (wi < hdr[2]) & (hdr[3] == TOK) & (hdr[4] == a.batch) &
+  const bool narrow = kNarrow && (hdr[3] == kNarrowRows / G || hdr[3] == kNarrowRows / 2 / G);
+  const bool ours = (hdr[0] == kPlanMagic) & (wi < hdr[2]) & (narrow | (hdr[3] == TOK)) & (hdr[4] == a.batch) &
                     (hdr[5] == a.total_q);
   if (!ours) return;
 
@@ -1666,17 +1813,23 @@ __global__ __launch_bounds__(kThreads, kCB == 1 ? 2 : 1) void attn_kernel(AttnAr
   const int pidx_cap = 4 * (t1 - 1) + (int)((uint32_t)item[3] >> 26 & 3);
   const int merge = item[7];                         // merge record, if chunk >= 0
   // a record that cannot come from the planner (a workspace written over by something else)
-  const bool odd = ((unsigned)seq >= (unsigned)a.batch) | (row0 < 0) | (t1 <= t0) | (ntok > TOK) |
+  const bool odd = ((unsigned)seq >= (unsigned)a.batch) | (row0 < 0) | (t1 <= t0) | (ntok > (narrow ? hdr[3] : TOK)) |
                    (q_first < 0) | ((int64_t)q_first + ntok > a.total_q) | (table_off < 0) |
-                   ((chunk >= 0) & ((unsigned)merge >= (unsigned)hdr[6])) |
-                   (group & (chunk < 0)) | (kCB != 1 & chunk >= 0);   // (ranges of wide q tiles are never cut)
+                   ((chunk >= 0) & ((unsigned)merge >= (unsigned)n_rec)) |
+                   (group & (chunk < 0)) | ((kCB != 1) & (chunk >= 0));   // (ranges of wide q tiles are never cut)
   if (odd) return;
   // begin is read here, not taken from the plan (one plan may serve many decode steps)
   const int b = ((const_i32_ptr)a.begin)[seq];
-  const Item it = {t0, t1, chunk, q_first, ntok, table_off, pidx_cap, merge, hdr[6], behind, group};
+  const Item it = {t0, t1, chunk, q_first, ntok, table_off, pidx_cap, merge, n_rec, behind, group};
   if (kGate && ntok * G <= kFlatRows) {
     __shared__ float s_stat[2 * 4 * kFlatRows];   // maximum and sum per wavefront and row
-    few_rows_item<T, G>(a, it, hk, b, row0, item_b, lds, s_stat, s_last);
+    few_rows_item<T, G, 1, false>(a, it, hk, b, row0, item_b, lds, s_stat, s_last);
+    return;
+  }
+  if (kNarrow && ntok * G <= kNarrowRows) {
+    __shared__ float s_stat[2 * 4 * kNarrowRows];
+    if (ntok * G <= kNarrowRows / 2) few_rows_item<T, G, 1, true>(a, it, hk, b, row0, item_b, lds, s_stat, s_last);
+    else few_rows_item<T, G, 2, true>(a, it, hk, b, row0, item_b, lds, s_stat, s_last);
     return;
   }
 
@@ -2212,7 +2365,7 @@ __global__ __launch_bounds__(kThreads, kCB == 1 ? 2 : 1) void attn_kernel(AttnAr
       for (int i = 0; i < 16; ++i) o[i] = load_part4<kDeviceScope>(rs_o, at.byte + i * at.step);
     };
 
-    const bool tree = rows > kFlatRows && !group && !(behind & kTreesBehind);
+    const bool tree = rows > kFlat && !group && !(behind & kTreesBehind);
     if (tree) {
       uint32_t* word0 = reinterpret_cast<uint32_t*>(a.part_lse) + (int64_t)a.part_cap * a.hq - 1 -
                         ((int64_t)merge * a.hkv + hk) * words - 1;
@@ -2270,12 +2423,12 @@ __global__ __launch_bounds__(kThreads, kCB == 1 ? 2 : 1) void attn_kernel(AttnAr
     }
     if (!tree || m[4] > 0) {
       const uint32_t row0 = tree ? chunk0 : first_part_row<G>(a, it, hk, m);
-      if (!combined_here<G>(it, m)) {
+      if (!combined_here<G, kFlat>(it, m)) {
         write_rows(row0, !tree, std::integral_constant<int, kLaunchScope>{});
         return;
       }
       write_rows(row0, !tree, in_launch);
-      arrive<T, G>(a, it, hk, rs_o, rs_lse, m, words, s_last, *reinterpret_cast<MergeList*>(lds));
+      arrive<T, G, kFlat, kNarrow ? 2 : 1>(a, it, hk, rs_o, rs_lse, m, words, s_last, *reinterpret_cast<MergeList*>(lds));
       return;
     }
   }
@@ -2329,18 +2482,19 @@ template <typename T, int G>
 __global__ __launch_bounds__(kThreads) void merge_kernel(AttnArgs a, int blocks) {
   const i32x8 hdr = *(const __attribute__((address_space(4))) i32x8*)a.hdr;
   const bool trees = !(a.behind & kTreesBehind);
-  const bool none = hdr[6] == 0 || (((const_i32_ptr)a.hdr)[8] == 0 && trees);
+  const int records = ((const_i32_ptr)a.hdr)[11];
+  const bool none = records == 0 || (((const_i32_ptr)a.hdr)[8] == 0 && trees);
   if (hdr[0] != kPlanMagic || none || hdr[4] != a.batch || hdr[5] != a.total_q) return;
   const buffer_rsrc rs_o = make_rsrc(a.part_o, (uint32_t)a.part_cap * a.hq * 512u);
   const buffer_rsrc rs_lse = make_rsrc(a.part_lse, (uint32_t)a.part_cap * a.hq * 4u);
   const int64_t per_rec = (int64_t)a.hkv * blocks;
-  for (int64_t w = blockIdx.x; w < hdr[6] * per_rec; w += gridDim.x) {
+  for (int64_t w = blockIdx.x; w < records * per_rec; w += gridDim.x) {
     const int rec = __builtin_amdgcn_readfirstlane((int)(w / per_rec)), at = (int)(w - rec * per_rec);
     const i32x8 m = *(const __attribute__((address_space(4))) i32x8*)(a.merges + rec);
-    if (!(m[4] > 0 ? a.behind & kGroupsBehind : !trees && m[1] * G > kFlatRows)) continue;
+    if (!(m[4] > 0 ? a.behind & kGroupsBehind : !trees && m[1] * G > a.flat_rows)) continue;
     const int block = __builtin_amdgcn_readfirstlane(at / a.hkv), hk = at - block * a.hkv;
     merge_rows<T, G, kLaunchScope, 1, kMergeAhead>(
-        a, rs_o, rs_lse, hk, m[1], trees, block, blocks,
+        a, rs_o, rs_lse, hk, m[1], a.flat_rows, trees, block, blocks,
         [&](int, int& first) __attribute__((always_inline)) { first = 0; return m; });
   }
 }
@@ -2355,22 +2509,26 @@ void launch_merge(int G, dim3 grid, int blocks, hipStream_t hs, const AttnArgs& 
   }
 }
 
-template <typename T, bool kGate, int kCB>
+template <typename T, int kMode, int kCB>
 mc_status launch_attn_g(int G, dim3 grid, hipStream_t hs, const AttnArgs& a) {
   switch (G) {
-    case 1: hipLaunchKernelGGL((attn_kernel<T, 1, kGate, kCB>), grid, dim3(kThreads), 0, hs, a); break;
-    case 2: hipLaunchKernelGGL((attn_kernel<T, 2, kGate, kCB>), grid, dim3(kThreads), 0, hs, a); break;
-    case 4: hipLaunchKernelGGL((attn_kernel<T, 4, kGate, kCB>), grid, dim3(kThreads), 0, hs, a); break;
-    case 8: hipLaunchKernelGGL((attn_kernel<T, 8, kGate, kCB>), grid, dim3(kThreads), 0, hs, a); break;
+    case 1: hipLaunchKernelGGL((attn_kernel<T, 1, kMode, kCB>), grid, dim3(kThreads), 0, hs, a); break;
+    case 2: hipLaunchKernelGGL((attn_kernel<T, 2, kMode, kCB>), grid, dim3(kThreads), 0, hs, a); break;
+    case 4: hipLaunchKernelGGL((attn_kernel<T, 4, kMode, kCB>), grid, dim3(kThreads), 0, hs, a); break;
+    case 8: hipLaunchKernelGGL((attn_kernel<T, 8, kMode, kCB>), grid, dim3(kThreads), 0, hs, a); break;
     default: return MC_ERR_UNSUPPORTED;
   }
   return mc::launch_status();
 }
 
 template <typename T>
-mc_status launch_attn(int G, bool gate, int row_blocks, dim3 grid, hipStream_t hs, const AttnArgs& a) {
-  if (row_blocks == 2) return launch_attn_g<T, false, 2>(G, grid, hs, a);
-  return gate ? launch_attn_g<T, true, 1>(G, grid, hs, a) : launch_attn_g<T, false, 1>(G, grid, hs, a);
+mc_status launch_attn(int G, int mode, int row_blocks, dim3 grid, hipStream_t hs, const AttnArgs& a) {
+  if (row_blocks == 2) return launch_attn_g<T, kPlain, 2>(G, grid, hs, a);
+  switch (mode) {
+    case kNarrowTiles: return launch_attn_g<T, kNarrowTiles, 1>(G, grid, hs, a);
+    case kGated: return launch_attn_g<T, kGated, 1>(G, grid, hs, a);
+    default: return launch_attn_g<T, kPlain, 1>(G, grid, hs, a);
+  }
 }
 
 // Workgroups of the attention kernel the current GPU runs at a time: two per compute unit
@@ -2398,6 +2556,14 @@ int device_slots(int row_blocks = 1) {
 // slot; the number of q tiles is at least total_q / tile_tokens, which the host knows.
 bool may_cut(const WorkspaceLayout& w, int hkv, int slots) {
   return w.part_cap > 0 && (int64_t)(w.max_tiles - w.batch) * hkv < (int64_t)kRoundsWanted * slots;
+}
+
+// Whether the planner may take q tiles of fewer rows (narrow_rows): at most a workgroup of kNarrowRows rows a compute
+// unit, few sequences, and more new tokens than those.  By the batch's sizes, because planner and attention kernel
+// are others then: with these paths, which they never take, the others took 0.2 to 0.4 us longer a launch (one
+// decode row, eight layers, 81.7 -> 84.1 us).
+bool may_narrow(int32_t batch, int32_t total_q, int G, int hkv, int slots) {
+  return batch <= kNarrowBatch && total_q > batch && (int64_t)total_q * G * hkv <= (int64_t)kNarrowRows * (slots / 2);
 }
 
 // Shared-prefix groups are made of sequences with one new token each: worth looking for only
@@ -2457,7 +2623,6 @@ mc_status plan_impl(const mc_pool_desc* pool, int32_t num_q_heads, int32_t batch
   a.hdr = reinterpret_cast<PlanHeader*>(ws);
   a.cu_tiles = reinterpret_cast<int32_t*>(ws + w.cu_tiles);
   a.items = reinterpret_cast<ItemRec*>(ws + w.items);
-  a.merges = reinterpret_cast<MergeRec*>(ws + w.merges);
   a.arrivals_end = reinterpret_cast<uint32_t*>(ws + w.part_lse) + (size_t)w.part_cap * num_q_heads;
   a.batch = batch;
   a.total_q = total_q;
@@ -2473,19 +2638,21 @@ mc_status plan_impl(const mc_pool_desc* pool, int32_t num_q_heads, int32_t batch
   a.slots_wide = device_slots(2);
   a.allow_groups = may_group(w, total_q, tile_tokens);
   a.max_items = item_bound(w, a.hkv, a.slots, a.allow_groups);
+  a.merges = reinterpret_cast<MergeRec*>(a.items + a.max_items);
+  a.max_merges = (int32_t)((ws + w.part_lse - (char*)a.merges) / sizeof(MergeRec));
   a.part_cap = w.part_cap;
   a.ahead = ahead_tokens;
   // (few sequences only: the page-id checks and the table comparisons of shared prefixes go
   // a wavefront per sequence or pair and want the wavefronts of the large workgroup)
-  if (batch <= 16 && w.max_tiles <= 8 * kPlanThreadsSmall)
-    hipLaunchKernelGGL(plan_kernel<kPlanThreadsSmall>, dim3(1), dim3(kPlanThreadsSmall), 0,
-                       static_cast<hipStream_t>(stream), a);
+  hipStream_t hs = static_cast<hipStream_t>(stream);
+  if (may_narrow(batch, total_q, G, a.hkv, a.slots))
+    hipLaunchKernelGGL((plan_kernel<kPlanThreadsSmall, true>), dim3(1), dim3(kPlanThreadsSmall), 0, hs, a);
+  else if (batch <= 16 && w.max_tiles <= 8 * kPlanThreadsSmall)
+    hipLaunchKernelGGL((plan_kernel<kPlanThreadsSmall, false>), dim3(1), dim3(kPlanThreadsSmall), 0, hs, a);
   else
-    hipLaunchKernelGGL(plan_kernel<kPlanThreads>, dim3(1), dim3(kPlanThreads), 0,
-                       static_cast<hipStream_t>(stream), a);
+    hipLaunchKernelGGL((plan_kernel<kPlanThreads, false>), dim3(1), dim3(kPlanThreads), 0, hs, a);
   if (batch > kValidateInPlan)
-    hipLaunchKernelGGL(validate_pages_kernel, dim3((batch + 3) / 4), dim3(256), 0,
-                       static_cast<hipStream_t>(stream), a);
+    hipLaunchKernelGGL(validate_pages_kernel, dim3((batch + 3) / 4), dim3(256), 0, hs, a);
   return mc::launch_status();
 }
 
@@ -2513,8 +2680,8 @@ mc_status attn_impl(const mc_pool_desc* pool, int32_t layer, const void* q, int3
   const int slots = device_slots(1);
   if (slots <= 0) return MC_ERR_HIP;
   const bool groups = may_group(w, total_q, tile_tokens);
-  const int64_t blocks =
-      (int64_t)item_bound(w, pool->num_kv_heads, slots, groups) * pool->num_kv_heads;
+  const int32_t max_items = item_bound(w, pool->num_kv_heads, slots, groups);
+  const int64_t blocks = (int64_t)max_items * pool->num_kv_heads;
   if (blocks > 0x7fffffffll) return MC_ERR_UNSUPPORTED;
   char* ws = static_cast<char*>(workspace);
   AttnArgs a;
@@ -2526,7 +2693,7 @@ mc_status attn_impl(const mc_pool_desc* pool, int32_t layer, const void* q, int3
   a.page_table = page_table;
   a.hdr = reinterpret_cast<const PlanHeader*>(ws);
   a.items = reinterpret_cast<const ItemRec*>(ws + w.items);
-  a.merges = reinterpret_cast<const MergeRec*>(ws + w.merges);
+  a.merges = reinterpret_cast<const MergeRec*>(a.items + max_items);
   a.part_lse = reinterpret_cast<float*>(ws + w.part_lse);
   a.part_o = reinterpret_cast<float*>(ws + w.part_o);
   a.part_cap = w.part_cap;
@@ -2539,21 +2706,24 @@ mc_status attn_impl(const mc_pool_desc* pool, int32_t layer, const void* q, int3
   const int64_t tiles = (int64_t)(w.max_tiles - batch) * pool->num_kv_heads;
   const bool trees = w.part_cap > 0 && total_q > batch && (int64_t)total_q * G > kFlatRows;
   a.behind = groups && !groups_in_launch(batch, total_q) ? kGroupsBehind : 0;
-  if (trees && trees_behind(tiles, slots, a.behind != 0)) a.behind |= kTreesBehind;
+  if (trees && a.behind != 0 && trees_behind(tiles, slots)) a.behind |= kTreesBehind;
   a.scale = sm_scale > 0.f ? sm_scale : 1.0f / sqrtf((float)mc::kHeadDim);
   a.scale_log2 = a.scale * 1.4426950408889634f;
   dim3 grid((unsigned)blocks);
   hipStream_t hs = static_cast<hipStream_t>(stream);
   // many sequences for the number of q tiles: a good share of the tiles is short
-  const bool gate = 4ll * batch >= w.max_tiles - batch;
-  st = pool->dtype == MC_F16 ? launch_attn<_Float16>(G, gate, 1, grid, hs, a)
-                             : launch_attn<__bf16>(G, gate, 1, grid, hs, a);
+  const int mode = may_narrow(batch, total_q, G, pool->num_kv_heads, slots) ? kNarrowTiles
+                   : 4ll * batch >= w.max_tiles - batch                     ? kGated
+                                                                            : kPlain;
+  a.flat_rows = mode == kNarrowTiles ? kNarrowRows : kFlatRows;
+  st = pool->dtype == MC_F16 ? launch_attn<_Float16>(G, mode, 1, grid, hs, a)
+                             : launch_attn<__bf16>(G, mode, 1, grid, hs, a);
   if (st == MC_OK && wide_tiles_allowed(batch, total_q, G, pool->num_kv_heads)) {
     // the plan may be one of wide q tiles (fewer items than the grid's bound, which holds for
     // either width): that kernel, too; the one the plan was not made for finds the other tile
     // size in the header and returns
-    st = pool->dtype == MC_F16 ? launch_attn<_Float16>(G, false, 2, grid, hs, a)
-                               : launch_attn<__bf16>(G, false, 2, grid, hs, a);
+    st = pool->dtype == MC_F16 ? launch_attn<_Float16>(G, kPlain, 2, grid, hs, a)
+                               : launch_attn<__bf16>(G, kPlain, 2, grid, hs, a);
   }
   if (st != MC_OK || a.behind == 0) return st;
   const int rows = std::min((total_q + batch - 1) / batch * G, kBM), per_block = kThreads / 32;

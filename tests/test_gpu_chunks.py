@@ -236,3 +236,20 @@ def test_the_remainder_round_launch_after_launch(dtype):
     w = small_workload(1360, dtype, 8, 1, [1280] * 35, [1024] * 35)
     h = check(w, rows=16)
     assert h[7] == 0 and h[9] > 1 and h[6] == 48, h[:10]
+
+
+# per line: the tokens of a q tile that the planner takes, on both sides of each bound with 512 workgroup slots
+@pytest.mark.parametrize("dtype", [mi.BF16, mi.F16])
+@pytest.mark.parametrize("Hq,Hkv,new,cached,tokens", [
+    (8, 8, [256], [256], 16), (32, 8, [128], [1024], 4), (32, 8, [128], [1025], 8),  # 18 KV tiles; 19, not to be cut
+    (32, 8, [129], [64], 8), (32, 8, [256], [512], 8), (32, 8, [257], [512], 32),    # 256 workgroups, or more
+    (64, 8, [3], [6000], 2), (8, 1, [130], [1100], 2), (16, 8, [40], [650], 8),      # 16 rows, cut and uncut
+    (64, 8, [8], [8100], 2), (64, 8, [8], [8300], 4),                                # 16 tiles a unit, or more
+    (32, 8, [64], [6000], 8), (32, 8, [64], [6200], 32), (32, 8, [20], [17000], 8),  # 24, or more, or few pairs
+    (32, 8, [5, 17, 64, 1, 0, 33], [100, 3000, 200, 2000, 70, 0], 8),                # ragged
+    (8, 8, [17, 3, 31, 32, 1], [0, 15, 700, 2500, 5], 16),
+    (64, 8, [3] * 16, [40 * i for i in range(16)], 2), (64, 8, [3] * 17, [40 * i for i in range(17)], 16),
+])
+def test_narrow_q_tiles(dtype, Hq, Hkv, new, cached, tokens):
+    w = small_workload(1370 + sum(new), dtype, Hq, Hkv, [n + c for n, c in zip(new, cached)], cached)
+    assert check(w, 3, rows=0 if max(cached) < 4000 else 64)[3] == tokens
