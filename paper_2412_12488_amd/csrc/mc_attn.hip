@@ -74,13 +74,12 @@ struct PlanHeader {
   int32_t tile_tokens;
   int32_t batch;
   int32_t total_q;
-  int32_t num_merges; // q tiles of kBM rows that were cut: into chunks of the KV range, or into tiles of fewer rows
-  int32_t chunk_tiles;  // the length (KV tiles) they were cut into, whole ranges of narrow tiles too; 0 = nothing was cut
+  int32_t num_merges; // merge records: q tiles whose KV range was cut into several chunks
+  int32_t chunk_tiles;  // chunk length the planner settled on (KV tiles); 0 = nothing was cut
   int32_t num_groups_rows;  // partial rows written by shared-prefix items (0 = no groups)
   int32_t tail_chunks;  // chunks per q tile of the remainder round (0 = not applied)
   int32_t arrive_words; // arrival words per merge record and kv head (see MergeRec)
-  int32_t num_records;  // merge records
-  int32_t pad[4];
+  int32_t pad[5];
 };
 static_assert(sizeof(PlanHeader) == 64, "header is 64 bytes");
 
@@ -418,7 +417,7 @@ __device__ __forceinline__ bool short_pieces_pay(const PlanArgs& a, int L, int l
 // The header of a plan that the attention has nothing to do for.
 __device__ __forceinline__ void refuse_plan(PlanHeader* h) {
   h->err = MC_ERR_RANGE;
-  h->num_items = h->num_merges = h->num_records = 0;
+  h->num_items = h->num_merges = 0;
   h->magic = kPlanMagic;
 }
 
@@ -762,7 +761,7 @@ __global__ __launch_bounds__(NT) void plan_kernel(PlanArgs a) {
 
   // 3. exclusive scan of tiles per sequence
   //     Tiles of fewer rows where even these are no more than a workgroup a compute unit: narrow_rows.
-  int total_tiles, base, whole_tiles;
+  int total_tiles, base;
   bool narrow = false;
   if constexpr (kMayNarrow) {
     const int all[5] = {s_sums[0], s_sums[1], s_sums[2], s_sums[3], s_sums[4]};
@@ -771,12 +770,10 @@ __global__ __launch_bounds__(NT) void plan_kernel(PlanArgs a) {
     base = k == 0 ? before[0] : k == 1 ? before[1] : before[2];
     total_tiles = k == 0 ? all[0] : k == 1 ? all[1] : all[2];
     narrow = k > 0;
-    whole_tiles = all[0];
     if (narrow) a.tile_tokens = narrow_tokens >> (k - 1);
   } else {
     if constexpr (kFirstWave) { base = before[0]; total_tiles = s_sums[0]; }
     else base = block_exclusive_scan<NT>(my_tiles, scan, &total_tiles);
-    whole_tiles = total_tiles;
   }
   for (int s = s_lo; s < s_hi; ++s) {
     a.cu_tiles[s] = base;
@@ -1125,9 +1122,8 @@ __global__ __launch_bounds__(NT) void plan_kernel(PlanArgs a) {
   if (t == 0) {
     a.hdr->err = MC_OK;
     a.hdr->num_items = tot_items;
-    a.hdr->num_merges = narrow ? whole_tiles : tot_merge;
-    a.hdr->chunk_tiles = narrow && L == 0 ? (s_maxcost + 1) & ~1 : L;
-    a.hdr->num_records = tot_merge;
+    a.hdr->num_merges = tot_merge;
+    a.hdr->chunk_tiles = L;
     a.hdr->tile_tokens = a.tile_tokens;
     a.hdr->batch = a.batch;
     a.hdr->total_q = a.total_q;
@@ -1787,10 +1783,7 @@ __global__ __launch_bounds__(kThreads, kCB == 1 ? 2 : 1) void attn_kernel(AttnAr
   int behind = a.behind;
   asm volatile("" : "+s"(behind));
   asm volatile("" ::"s"(a.pool_layer), "s"(a.begin), "s"(a.q), "s"(a.num_pages), "s"(a.total_q));
-  int n_rec = 0;
-  if (kNarrow) n_rec = ((const_i32_ptr)a.hdr)[11];
-  asm volatile("" : "+s"(item), "+s"(item_b), "+s"(hdr), "+s"(n_rec));
-  if (!kNarrow) n_rec = hdr[6];                // as many as q tiles that were cut
+  asm volatile("" : "+s"(item), "+s"(item_b), "+s"(hdr));
   // the work list must come from a plan made for this very batch
   const bool narrow = kNarrow && (hdr[3] == kNarrowRows / G || hdr[3] == kNarrowRows / 2 / G);
   const bool ours = (hdr[0] == kPlanMagic) & (wi < hdr[2]) & (narrow | (hdr[3] == TOK)) & (hdr[4] == a.batch) &
@@ -1815,12 +1808,12 @@ __global__ __launch_bounds__(kThreads, kCB == 1 ? 2 : 1) void attn_kernel(AttnAr
   // a record that cannot come from the planner (a workspace written over by something else)
   const bool odd = ((unsigned)seq >= (unsigned)a.batch) | (row0 < 0) | (t1 <= t0) | (ntok > (narrow ? hdr[3] : TOK)) |
                    (q_first < 0) | ((int64_t)q_first + ntok > a.total_q) | (table_off < 0) |
-                   ((chunk >= 0) & ((unsigned)merge >= (unsigned)n_rec)) |
+                   ((chunk >= 0) & ((unsigned)merge >= (unsigned)hdr[6])) |
                    (group & (chunk < 0)) | ((kCB != 1) & (chunk >= 0));   // (ranges of wide q tiles are never cut)
   if (odd) return;
   // begin is read here, not taken from the plan (one plan may serve many decode steps)
   const int b = ((const_i32_ptr)a.begin)[seq];
-  const Item it = {t0, t1, chunk, q_first, ntok, table_off, pidx_cap, merge, n_rec, behind, group};
+  const Item it = {t0, t1, chunk, q_first, ntok, table_off, pidx_cap, merge, hdr[6], behind, group};
   if (kGate && ntok * G <= kFlatRows) {
     __shared__ float s_stat[2 * 4 * kFlatRows];   // maximum and sum per wavefront and row
     few_rows_item<T, G, 1, false>(a, it, hk, b, row0, item_b, lds, s_stat, s_last);
@@ -2482,13 +2475,12 @@ template <typename T, int G>
 __global__ __launch_bounds__(kThreads) void merge_kernel(AttnArgs a, int blocks) {
   const i32x8 hdr = *(const __attribute__((address_space(4))) i32x8*)a.hdr;
   const bool trees = !(a.behind & kTreesBehind);
-  const int records = ((const_i32_ptr)a.hdr)[11];
-  const bool none = records == 0 || (((const_i32_ptr)a.hdr)[8] == 0 && trees);
+  const bool none = hdr[6] == 0 || (((const_i32_ptr)a.hdr)[8] == 0 && trees);
   if (hdr[0] != kPlanMagic || none || hdr[4] != a.batch || hdr[5] != a.total_q) return;
   const buffer_rsrc rs_o = make_rsrc(a.part_o, (uint32_t)a.part_cap * a.hq * 512u);
   const buffer_rsrc rs_lse = make_rsrc(a.part_lse, (uint32_t)a.part_cap * a.hq * 4u);
   const int64_t per_rec = (int64_t)a.hkv * blocks;
-  for (int64_t w = blockIdx.x; w < records * per_rec; w += gridDim.x) {
+  for (int64_t w = blockIdx.x; w < hdr[6] * per_rec; w += gridDim.x) {
     const int rec = __builtin_amdgcn_readfirstlane((int)(w / per_rec)), at = (int)(w - rec * per_rec);
     const i32x8 m = *(const __attribute__((address_space(4))) i32x8*)(a.merges + rec);
     if (!(m[4] > 0 ? a.behind & kGroupsBehind : !trees && m[1] * G > a.flat_rows)) continue;

@@ -1,6 +1,6 @@
 """Chunks of a cut KV range are combined inside the attention launch - rows that are counted (up to 16
-a q tile and kv head), trees over two to many chunks, groups of both kinds, at the row counts where
-one becomes the other - or in a launch behind it.  Launch after launch on one plan (the arrival words
+a q tile and kv head, 32 of narrow q tiles), trees over two to many chunks, groups of both kinds, at the
+row counts where one becomes the other - or in a launch behind it.  Launch after launch on one plan (the arrival words
 wrap), every launch the same bits whichever chunk comes last, and the oracle's result."""
 import numpy as np
 import pytest
@@ -63,9 +63,34 @@ def check(w, n=6, rows=0):
     return h
 
 
+# per line: the tokens of a q tile, and how many of them are cut, with 512 workgroup slots
+@pytest.mark.parametrize("dtype", [mi.BF16, mi.F16])
+@pytest.mark.parametrize("Hq,Hkv,new,keys,tokens,cut", [
+    # whole q tiles: 16 rows, counted (G = 4, 8, 1); a tree of more chunks than one word of arrivals has nodes
+    (32, 8, 4, 2100, 32, 1), (64, 8, 2, 1100, 16, 1), (8, 8, 16, 2700, 128, 1), (8, 1, 130, 40000, 16, 9),
+    # narrow ones of 16 rows, the last of 4 rows or 8, a row, as many as the others; many pieces a tile
+    (32, 8, 5, 2100, 4, 2), (64, 8, 3, 1600, 2, 2), (8, 8, 17, 2700, 16, 2), (8, 8, 128, 3200, 16, 8),
+    (32, 8, 33, 1000, 4, 9), (32, 8, 36, 2100, 4, 9), (32, 8, 37, 2100, 4, 10), (64, 8, 18, 1600, 2, 9),
+    (64, 8, 19, 2600, 2, 10), (8, 8, 144, 2700, 16, 9), (8, 8, 145, 3300, 16, 10), (8, 1, 128, 1300, 2, 64),
+    (8, 1, 129, 1300, 2, 65),
+    # of 32 rows: the last of one row, of two; uncut; many pieces
+    (8, 8, 129, 4300, 32, 5), (16, 8, 81, 4500, 16, 6), (16, 8, 40, 700, 8, 0), (8, 1, 20, 40000, 4, 5),
+])
+def test_ranges_of_few_and_many_rows(dtype, Hq, Hkv, new, keys, tokens, cut):
+    w = small_workload(1200 + new, dtype, Hq, Hkv, [keys], [keys - new])
+    h = check(w, rows=0 if new * keys < 1 << 20 else 512)
+    assert (h[3], h[6]) == (tokens, cut) and (h[7] > 0) == (cut > 0), h[:9]
+
+
+def beside_others(Hq, lens, begins):
+    """lens and begins with three short ranges behind, too many tokens in all for narrow q tiles."""
+    n = {8: 400, 16: 180, 32: 90, 64: 45}[Hq]
+    return lens + [n + 60, n + 7, n], begins + [60, 7, 0]
+
+
 @pytest.mark.parametrize("dtype", [mi.BF16, mi.F16])
 @pytest.mark.parametrize("Hq,Hkv,new,keys", [
-    # one tile for each of eight kv heads, or fewer: 16 rows are counted, more combined behind the launch
+    # one tile for each of eight kv heads, or fewer: 16 rows are counted, more go up a tree
     (32, 8, 4, 2100), (32, 8, 5, 2100),       # 16 rows; 20 (G = 4)
     (64, 8, 2, 1100), (64, 8, 3, 1600),       # 16 rows, 24 (G = 8): two chunks, three
     (8, 8, 16, 2700), (8, 8, 17, 2700),       # 16 rows, 17 (G = 1): five chunks
@@ -78,10 +103,12 @@ def check(w, n=6, rows=0):
     (8, 1, 129, 1300), (16, 8, 81, 4500),     # nine tiles, the last of 8 rows; 17 tokens of two rows
     (8, 1, 130, 40000),                       # more chunks than one word of arrivals has nodes
 ])
-def test_ranges_of_few_and_many_rows(dtype, Hq, Hkv, new, keys):
-    w = small_workload(1200 + new, dtype, Hq, Hkv, [keys], [keys - new])
-    h = check(w, rows=0 if new * keys < 1 << 20 else 512)
-    assert h[6] == -(-new // (128 * Hkv // Hq)) and h[7] > 0, h[:9]     # every tile is cut
+def test_whole_tiles_of_few_and_many_rows(dtype, Hq, Hkv, new, keys):
+    lens, begins = beside_others(Hq, [keys], [keys - new])
+    w = small_workload(1400 + new, dtype, Hq, Hkv, lens, begins)
+    h = check(w, rows=256)
+    tokens = 128 * Hkv // Hq
+    assert (h[3], h[6]) == (tokens, -(-new // tokens)) and h[7] >= 8, h[:9]     # every tile of the first is cut
 
 
 @pytest.mark.parametrize("Hq,Hkv", [(32, 8), (8, 8), (64, 8)])
@@ -116,18 +143,20 @@ def test_members_with_trees_of_their_own(dtype):
     assert check(w)[8] > 0
 
 
-# per line: where the chunks of the row of NaN come together
+# per line: where the chunks of the row of NaN come together; the tokens of a q tile, how many are cut
 @pytest.mark.parametrize("dtype", [mi.BF16, mi.F16])
-@pytest.mark.parametrize("Hq,Hkv,lens,new,shared", [
-    (32, 8, [1500, 900], [1, 1], 0),                                    # counted
-    (32, 8, [2100, 1600], [5, 7], 0),                                   # behind the launch
-    (32, 8, [2100, 1600], [40, 37], 0),                                 # a tree
-    (32, 8, [2300, 2200, 2150], [1, 1, 1], 2048),                       # a prefix, combined in the launch
-    (32, 8, [2100 + 10 * i for i in range(12)], [1] * 12, 2048),        # and behind it
-    (32, 8, [2100, 2600, 3100], [5, 6, 8], 2048),                       # members of more rows, behind it
-    (32, 8, [2100 + 300 * i for i in range(11)], [15] * 11, 2048),      # trees of members, read behind it
+@pytest.mark.parametrize("Hq,Hkv,lens,new,shared,tokens,cut", [
+    (32, 8, [1500, 900], [1, 1], 0, 32, 2),                                    # counted
+    (32, 8, [2100, 1600], [5, 7], 0, 4, 4),                                    # counted, narrow tiles of 16 rows
+    (32, 8, [2100, 1600], [40, 37], 0, 8, 10),                                 # and of 32
+    (32, 8, [2100, 1600, 400, 90, 300], [5, 7, 90, 90, 90], 0, 32, 2),         # trees of 20 and 28 rows
+    (32, 8, [2100, 1600, 400, 90, 300], [40, 37, 90, 90, 90], 0, 32, 4),       # of 128 and 32, and of 20
+    (32, 8, [2300, 2200, 2150], [1, 1, 1], 2048, 32, 3),                       # a prefix, combined in the launch
+    (32, 8, [2100 + 10 * i for i in range(12)], [1] * 12, 2048, 32, 12),       # and behind it
+    (32, 8, [2100, 2600, 3100], [5, 6, 8], 2048, 32, 3),                       # members of more rows, behind it
+    (32, 8, [2100 + 300 * i for i in range(11)], [15] * 11, 2048, 32, 11),     # trees of members, read behind it
 ])
-def test_a_row_that_is_not_a_number_is_written_as_such(dtype, Hq, Hkv, lens, new, shared):
+def test_a_row_that_is_not_a_number_is_written_as_such(dtype, Hq, Hkv, lens, new, shared, tokens, cut):
     w = small_workload(1280, dtype, Hq, Hkv, lens, [n - k for n, k in zip(lens, new)])
     for s in range(1, len(lens) if shared else 0):
         w.share_prefix(s, 0, shared)
@@ -135,7 +164,7 @@ def test_a_row_that_is_not_a_number_is_written_as_such(dtype, Hq, Hkv, lens, new
     token, head = int(w.cu_q[1]), 9
     q[token, head] = 0x7fc1
     got, h, pool, opool = launches(w, 3, q=q, blank=(0x1111, 7.0))
-    assert h[6] >= w.batch and (h[8] > 0) == (shared > 0), h[:9]
+    assert (h[3], h[6]) == (tokens, cut) and (h[8] > 0) == (shared > 0), h[:9]
     for out, lse in got:
         o, l = oracle.decode(bits(out), dtype), lse.cpu().numpy()
         assert np.isnan(o[token, head]).all() and np.isnan(l[token, head])
@@ -149,13 +178,18 @@ def test_a_row_that_is_not_a_number_is_written_as_such(dtype, Hq, Hkv, lens, new
             assert np.max(np.abs(l[at:at + n] - rl)) <= LSE_TOL, s
 
 
-def test_a_row_that_is_not_a_number_beside_chunks_without_a_key():
-    # a tree whose last chunks hold no key (a begin below the planned one), whichever of two comes first
-    w = small_workload(1290, mi.BF16, 32, 8, [4100, 4100], [4060, 4060])
-    q = np.concatenate([w.q(s) for s in range(2)])
+# per line: narrow tiles of 32 rows, counted; trees
+@pytest.mark.parametrize("others,tokens,cut", [(False, 8, 10), (True, 32, 4)])
+def test_a_row_that_is_not_a_number_beside_chunks_without_a_key(others, tokens, cut):
+    # the last chunks of both ranges hold no key (a begin below the planned one), whichever of two comes first
+    lens, begins = [4100, 4100], [4060, 4060]
+    if others:
+        lens, begins = beside_others(32, lens, begins)
+    w = small_workload(1290, mi.BF16, 32, 8, lens, begins)
+    q = np.concatenate([w.q(s) for s in range(w.batch)])
     q[41, 9] = 0x7fc1
-    got, h, _, _ = launches(w, 6, q=q, begin=[[700, 1900]] * 6, blank=(0x1111, 7.0))
-    assert h[6] == 4, h[:9]
+    got, h, _, _ = launches(w, 6, q=q, begin=[[700, 1900] + begins[2:]] * 6, blank=(0x1111, 7.0))
+    assert (h[3], h[6]) == (tokens, cut), h[:9]
     for out, lse in got:
         o, l = oracle.decode(bits(out), mi.BF16), lse.cpu().numpy()
         assert np.isnan(o[41, 9]).all() and np.isnan(l[41, 9])
@@ -203,15 +237,15 @@ def test_trees_of_members_in_larger_batches(new):
 
 
 @pytest.mark.parametrize("dtype", [mi.BF16, mi.F16])
-@pytest.mark.parametrize("new", [8, 40, 500, 513])
-def test_chunks_without_a_key_and_the_plan_used_again(dtype, new):
-    # a begin so far below the planned one that the last chunks hold no key (behind the launch, a tree, the
-    # kernel without short tiles); then the planned begin on the same plan, whose arrival words have wrapped
-    # (whole q tiles, of 32 tokens: a multiple of that many)
+@pytest.mark.parametrize("new,tokens,cut", [(8, 4, 2), (40, 8, 5), (500, 32, 16), (513, 32, 17)])
+def test_chunks_without_a_key_and_the_plan_used_again(dtype, new, tokens, cut):
+    # a begin so far below the planned one that the last chunks hold no key (counted, of narrow tiles of 16 rows
+    # and 32; trees in the kernel without short tiles); then the planned begin on the same plan, whose arrival
+    # words have wrapped (whole tiles are of 32 tokens: begins are a multiple of that many)
     w = small_workload(1340 + new, dtype, 32, 8, [4500 + new], [4500])
     low = [[896], [2496], [32]]
     got, h, pool, opool = launches(w, 5, begin=low)
-    assert h[6] == -(-new // 32) and h[7] > 0, h[:9]
+    assert (h[3], h[6]) == (tokens, cut) and h[7] > 0, h[:9]
     rng = mi.rng_for(1340, new)
     rr, hh = rng.integers(0, new, 256), rng.integers(0, 32, 256)
     for (out, lse), (b,) in zip(got, low + [[4500]] * 2):
