@@ -69,7 +69,7 @@ constexpr int32_t kPlanMagic = 0x6d63706c;
 
 struct PlanHeader {
   int32_t magic;
-  int32_t err;        // mc_status found on the device by the plan kernel
+  int32_t heads;      // head_counts of the plan
   int32_t num_items;  // work items (q tile x KV chunk) in the work list
   int32_t tile_tokens;
   int32_t batch;
@@ -79,9 +79,15 @@ struct PlanHeader {
   int32_t num_groups_rows;  // partial rows written by shared-prefix items (0 = no groups)
   int32_t tail_chunks;  // chunks per q tile of the remainder round (0 = not applied)
   int32_t arrive_words; // arrival words per merge record and kv head (see MergeRec)
-  int32_t pad[5];
+  int32_t err;        // mc_status found on the device by the plan kernel
+  int32_t pad[4];
 };
 static_assert(sizeof(PlanHeader) == 64, "header is 64 bytes");
+
+// Both head counts in one word: where merge records, partial rows and arrivals lie follows from them, so a
+// plan made for others is not this batch's, even where its q tiles hold as many tokens (16 are 128 rows of 8
+// q heads a kv head, and 16 rows of one).
+__host__ __device__ constexpr int32_t head_counts(int32_t hkv, int32_t G) { return (int32_t)((uint32_t)hkv * 16 + G); }
 
 // One work item: q tile (seq, row0) over the KV tiles [t0, t1) of its sequence.  t0 is even.
 // chunk < 0: the item covers the tile's whole KV range and writes out/lse itself.  Otherwise it is
@@ -1121,6 +1127,7 @@ __global__ __launch_bounds__(NT) void plan_kernel(PlanArgs a) {
   }
   if (t == 0) {
     a.hdr->err = MC_OK;
+    a.hdr->heads = head_counts(a.hkv, a.hq / a.hkv);
     a.hdr->num_items = tot_items;
     a.hdr->num_merges = tot_merge;
     a.hdr->chunk_tiles = L;
@@ -1786,7 +1793,7 @@ __global__ __launch_bounds__(kThreads, kCB == 1 ? 2 : 1) void attn_kernel(AttnAr
   asm volatile("" : "+s"(item), "+s"(item_b), "+s"(hdr));
   // the work list must come from a plan made for this very batch
   const bool narrow = kNarrow && (hdr[3] == kNarrowRows / G || hdr[3] == kNarrowRows / 2 / G);
-  const bool ours = (hdr[0] == kPlanMagic) & (wi < hdr[2]) & (narrow | (hdr[3] == TOK)) & (hdr[4] == a.batch) &
+  const bool ours = (hdr[0] == kPlanMagic) & (hdr[1] == head_counts(a.hkv, G)) & (wi < hdr[2]) & (narrow | (hdr[3] == TOK)) & (hdr[4] == a.batch) &
                     (hdr[5] == a.total_q);
   if (!ours) return;
 
@@ -2476,7 +2483,7 @@ __global__ __launch_bounds__(kThreads) void merge_kernel(AttnArgs a, int blocks)
   const i32x8 hdr = *(const __attribute__((address_space(4))) i32x8*)a.hdr;
   const bool trees = !(a.behind & kTreesBehind);
   const bool none = hdr[6] == 0 || (((const_i32_ptr)a.hdr)[8] == 0 && trees);
-  if (hdr[0] != kPlanMagic || none || hdr[4] != a.batch || hdr[5] != a.total_q) return;
+  if (hdr[0] != kPlanMagic || hdr[1] != head_counts(a.hkv, G) || none || hdr[4] != a.batch || hdr[5] != a.total_q) return;
   const buffer_rsrc rs_o = make_rsrc(a.part_o, (uint32_t)a.part_cap * a.hq * 512u);
   const buffer_rsrc rs_lse = make_rsrc(a.part_lse, (uint32_t)a.part_cap * a.hq * 4u);
   const int64_t per_rec = (int64_t)a.hkv * blocks;

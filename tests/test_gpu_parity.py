@@ -954,6 +954,31 @@ def test_one_plan_with_forks_and_a_prefill_range_up_to_a_tile_edge():
             lo += qlen[s]
 
 
+# per line: heads of the plan and of the call.  Each pair of plans has q tiles of as many tokens for both
+@pytest.mark.parametrize("planned,called,new,cached", [
+    ((64, 8), (32, 8), 8, 8300),       # 32 rows of 8 q heads a kv head; 16 rows of 4
+    ((8, 8), (64, 8), 128, 3000),      # 16 rows of 1; 128 of 8
+    ((8, 8), (32, 8), 256, 2500),      # 32 rows of 1; 128 of 4
+    ((32, 8), (16, 4), 40, 4500),      # the same tiles, other heads
+])
+def test_a_plan_for_other_heads_writes_nothing(planned, called, new, cached):
+    w = small_workload(735, mi.BF16, *planned, [cached + new], [cached])
+    pool, db = DevPool(w), DevBatch(w)
+    size = max(mc.mc_attn_workspace_size(1, new, *heads) for heads in (planned, called))
+    ws = torch.zeros(size, dtype=torch.uint8, device=DEV)
+    mc.mc_attn_plan(pool.desc, planned[0], 1, new, db.cu_q, db.begin, db.page_table, db.cu_pages, ws, size)
+    mc.mc_attn_plan_check(ws)
+    assert ws[:64].view(torch.int32)[6] > 0              # q tiles that are cut
+    desc = mc.pool_desc(pool.t, 1, pool.num_pages, called[1], mi.BF16)
+    out = torch.full((new, called[0], 128), 0x7fc1, dtype=torch.int16, device=DEV)
+    lse = torch.full((new, called[0]), 7.0, dtype=torch.float32, device=DEV)
+    q = torch.zeros_like(out)
+    mc.mc_prefix_prefill_attn(desc, 0, q, called[0], 1, new, db.cu_q, db.begin, db.page_table, db.cu_pages, 0.0,
+                              out, lse, ws, size)
+    torch.cuda.synchronize()
+    assert bool((out == 0x7fc1).all()) and bool((lse == 7.0).all())
+
+
 def test_a_begin_that_no_longer_fits_the_plan_writes_nothing():
     """The attention call reads begin itself.  A value the plan was not made for - negative, or
     far below the planned one - must neither fault nor read outside the sequence's table: rows of
