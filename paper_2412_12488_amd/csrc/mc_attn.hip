@@ -119,8 +119,8 @@ constexpr uint32_t kItemGroup = 1u << 28;
 // share (g_off: the tile's first among them).  Partial rows are kept per chunk and kv head: the
 // R = ntok x G (of the prefix: g_stride x G) rows of chunk c and kv head h start at row
 // (part + c ntok) hq + h R (of the prefix: (g_part + c g_stride) hq + h R) of the partial arrays.
-//   * Chunks of up to kFlatRows rows (decode steps; in launches that may have narrow q tiles kNarrowRows): every
-//     item writes its rows and counts itself; the last one reads all the others'.
+//   * Chunks of up to kFlatRows rows (decode steps), of narrow q tiles of up to kNarrowRows: every item
+//     writes its rows and counts itself; the last one reads all the others'.
 //   * Chunks of more rows: a binary tree over the chunks.  Of two neighbours the first to be done
 //     writes its rows and ends, the second reads them, combines, and goes on one level up: of n chunks n - 1
 //     are written and read (up to twice as many written, where neighbours miss each other), but not by one
@@ -138,7 +138,7 @@ struct MergeRec {
   int32_t g_nsplit, g_part, g_stride, g_off;
 };
 static_assert(sizeof(MergeRec) == 32, "merge record is 32 bytes");
-constexpr int kFlatRows = 16, kNarrowRows = 32;   // (in launches that may have narrow q tiles: the latter)
+constexpr int kFlatRows = 16, kNarrowRows = 32;
 constexpr int kGroupsBehind = 1, kTreesBehind = 2;   // what is left to merge_kernel
 // Whether chunks of shared prefixes are combined inside the attention launch: host, plan and kernel agree
 // by the batch's numbers alone.  Few sequences, and no more new tokens than those (some may be idle), which
@@ -1205,7 +1205,6 @@ struct AttnArgs {
   float* part_o;           // [partial row][128]
   int32_t num_pages, hkv, hq, batch, total_q;
   int32_t part_cap;        // rows of the partial arrays
-  int32_t flat_rows;       // rows up to which chunks are no tree's (merge_kernel)
   int32_t behind;          // what merge_kernel combines (see MergeRec): kGroupsBehind, kTreesBehind
   float scale, scale_log2;  // softmax scale, and scale * log2(e)
 };
@@ -1516,14 +1515,16 @@ __device__ __forceinline__ float across_rows(float x, Op&& op) {
 // of 64 forks of a 2048-token prompt, 32 / 8, four layers 196.1 -> 200.3, 200.1; of 64 rows over 1024..4096
 // beside a prefill, two layers 328 -> 329, 336; of eight rows over 1024..4096, 64 / 8, eight layers 207.0 ->
 // 205.0, 205.4.
-// kNarrow: ranges of few new tokens, a workgroup a compute unit at most, their keys in the L2s: bound by latency, so V
-// is requested beside K there (256 tokens over 256, 8 / 8 heads, 11.8 -> 11.3 us a layer; 128 over 1024, 32 / 8,
-// 19.5 -> 19.0).
+// beside: items of a plan of narrow q tiles, a workgroup a compute unit at most, their keys in the L2s: bound by
+// latency, so V is requested beside K there (256 tokens over 256, 8 / 8 heads, 11.8 -> 11.3 us a layer; 128 over 1024,
+// 32 / 8, 19.5 -> 19.0).  Not for the decode rows of plans of whole tiles, which the launch that may have narrow ones
+// runs as well (kNarrow; eight rows over 16000 beside 128 new tokens, 8 / 1 heads, 31.1 us a layer, 28.4 with V ahead).
 // A layer (append and attention) of one row over 1000 keys, 32 / 8 heads, 12.9 -> 10.5 us; of eight rows
 // over 1024..4096, 64 / 8 heads, 27.7 -> 25.5; 256 rows, bound by the reads, the same.
 template <typename T, int G, int kRB, bool kNarrow>
 __device__ __forceinline__ void few_rows_item(const AttnArgs& a, const Item& it, int hk, int b, int row0,
-                                              const i32x8& ids, char* lds, float* stat, int& s_last) {
+                                              const i32x8& ids, char* lds, float* stat, int& s_last,
+                                              bool beside) {
   typedef typename Mfma<T>::vec8 vec8;
   constexpr int kHalf = kBN / 2, kHalfBytes = kHalf * kRowBytes;
   const int tid = threadIdx.x, lane = tid & 63, l16 = lane & 15, g4 = lane >> 4;
@@ -1597,14 +1598,13 @@ __device__ __forceinline__ void few_rows_item(const AttnArgs& a, const Item& it,
   int buf = 0;
   for (; h < n_halves; h += 4, buf ^= 1) {
     const bool more = h + 4 < n_halves;
-    if constexpr (!kNarrow) {
+    if constexpr (kNarrow) asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");   // the other V buffer has been read
+    if (!beside) {
       asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
       if (more) request_v(next0, next1, buf ^ 1);
     }
     // (K and q pass through the wait: the compiler, which counts its own loads but not the copies, would
     // else wait for them once more ahead of S)
-    // (the other V buffer has been read)
-    if constexpr (kNarrow) asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
     asm volatile("s_waitcnt vmcnt(0)"
                  : "+v"(kf[0][0]), "+v"(kf[0][1]), "+v"(kf[0][2]), "+v"(kf[0][3]), "+v"(kf[1][0]), "+v"(kf[1][1]),
                    "+v"(kf[1][2]), "+v"(kf[1][3]), "+v"(q[0][0]), "+v"(q[0][1]), "+v"(q[0][2]), "+v"(q[0][3]),
@@ -1621,7 +1621,7 @@ __device__ __forceinline__ void few_rows_item(const AttnArgs& a, const Item& it,
 #pragma unroll
         for (int rb = 0; rb < kRB; ++rb) s[rb][p] = Mfma<T>::run16(kf[p][kk], q[rb][kk], s[rb][p]);
     if (more) {
-      if constexpr (kNarrow) request_v(next0, next1, buf ^ 1);
+      if (beside) request_v(next0, next1, buf ^ 1);
       request_k(next0, next1);
       next0 = id_of(h + 8, 0);
       next1 = id_of(h + 8, 1);
@@ -1755,13 +1755,14 @@ constexpr int kPlain = 0, kGated = 1, kNarrowTiles = 2;
 // fetch (4 MFMAs ahead of its use) and a slice of the VALU work; the order is pinned.
 // kGated: wavefronts none of whose rows exists skip the arithmetic.  Worth it for batches with
 // many short q tiles (decode steps); the plain variant is ~2 % faster when all tiles are full.
+// kNarrowTiles, where the plan is of whole tiles: as kGated (16 sequences of 40 new tokens over 3000, 8 / 8 heads, 56.6
+// us a layer without, 55.3 with; one of 256 over 1500, 32 / 8, 27.1, 27.2).
 // kCB: blocks of 32 rows per wavefront.  1: q tiles of 128 rows, two workgroups per compute
 // unit.  2: q tiles of 256 rows, one workgroup per compute unit with twice the registers: every
 // K and V fragment read from LDS feeds two MFMAs, every tile copied to LDS serves twice the rows.
 template <typename T, int G, int kMode, int kCB>
 __global__ __launch_bounds__(kThreads, kCB == 1 ? 2 : 1) void attn_kernel(AttnArgs a) {
-  constexpr bool kGate = kMode == kGated, kNarrow = kMode == kNarrowTiles;
-  constexpr int kFlat = kNarrow ? kNarrowRows : kFlatRows;
+  constexpr bool kGate = kMode != kPlain, kNarrow = kMode == kNarrowTiles;
   constexpr int kWaveRows = 32 * kCB;       // rows per wavefront
   constexpr int TOK = kBM * kCB / G;        // tokens per q tile
   constexpr int kHalf = kBN / 2;
@@ -1793,8 +1794,8 @@ __global__ __launch_bounds__(kThreads, kCB == 1 ? 2 : 1) void attn_kernel(AttnAr
   asm volatile("" : "+s"(item), "+s"(item_b), "+s"(hdr));
   // the work list must come from a plan made for this very batch
   const bool narrow = kNarrow && (hdr[3] == kNarrowRows / G || hdr[3] == kNarrowRows / 2 / G);
-  const bool ours = (hdr[0] == kPlanMagic) & (hdr[1] == head_counts(a.hkv, G)) & (wi < hdr[2]) & (narrow | (hdr[3] == TOK)) & (hdr[4] == a.batch) &
-                    (hdr[5] == a.total_q);
+  const bool ours = (hdr[0] == kPlanMagic) & (hdr[1] == head_counts(a.hkv, G)) & (wi < hdr[2]) &
+                    (narrow | (hdr[3] == TOK)) & (hdr[4] == a.batch) & (hdr[5] == a.total_q);
   if (!ours) return;
 
   const int tid = threadIdx.x, lane = tid & 63;
@@ -1821,15 +1822,17 @@ __global__ __launch_bounds__(kThreads, kCB == 1 ? 2 : 1) void attn_kernel(AttnAr
   // begin is read here, not taken from the plan (one plan may serve many decode steps)
   const int b = ((const_i32_ptr)a.begin)[seq];
   const Item it = {t0, t1, chunk, q_first, ntok, table_off, pidx_cap, merge, hdr[6], behind, group};
-  if (kGate && ntok * G <= kFlatRows) {
+  if (kMode == kGated && ntok * G <= kFlatRows) {
     __shared__ float s_stat[2 * 4 * kFlatRows];   // maximum and sum per wavefront and row
-    few_rows_item<T, G, 1, false>(a, it, hk, b, row0, item_b, lds, s_stat, s_last);
+    few_rows_item<T, G, 1, false>(a, it, hk, b, row0, item_b, lds, s_stat, s_last, false);
     return;
   }
-  if (kNarrow && ntok * G <= kNarrowRows) {
+  // (a prefix's items are few: with 32 rows they go that way beside whole tiles, too.  8 forks of 1024 tokens beside 100 new
+  // ones, 32 / 8 heads, 23.0 us a layer, so 20.8.)
+  if (kNarrow && (narrow | (ntok * G <= (group ? kNarrowRows : kFlatRows)))) {
     __shared__ float s_stat[2 * 4 * kNarrowRows];
-    if (ntok * G <= kNarrowRows / 2) few_rows_item<T, G, 1, true>(a, it, hk, b, row0, item_b, lds, s_stat, s_last);
-    else few_rows_item<T, G, 2, true>(a, it, hk, b, row0, item_b, lds, s_stat, s_last);
+    if (ntok * G <= kFlatRows) few_rows_item<T, G, 1, true>(a, it, hk, b, row0, item_b, lds, s_stat, s_last, narrow);
+    else few_rows_item<T, G, 2, true>(a, it, hk, b, row0, item_b, lds, s_stat, s_last, true);
     return;
   }
 
@@ -2365,7 +2368,7 @@ __global__ __launch_bounds__(kThreads, kCB == 1 ? 2 : 1) void attn_kernel(AttnAr
       for (int i = 0; i < 16; ++i) o[i] = load_part4<kDeviceScope>(rs_o, at.byte + i * at.step);
     };
 
-    const bool tree = rows > kFlat && !group && !(behind & kTreesBehind);
+    const bool tree = rows > kFlatRows && !group && !(behind & kTreesBehind);
     if (tree) {
       uint32_t* word0 = reinterpret_cast<uint32_t*>(a.part_lse) + (int64_t)a.part_cap * a.hq - 1 -
                         ((int64_t)merge * a.hkv + hk) * words - 1;
@@ -2423,13 +2426,16 @@ __global__ __launch_bounds__(kThreads, kCB == 1 ? 2 : 1) void attn_kernel(AttnAr
     }
     if (!tree || m[4] > 0) {
       const uint32_t row0 = tree ? chunk0 : first_part_row<G>(a, it, hk, m);
-      if (!combined_here<G, kFlat>(it, m)) {
+      // (launches that may have narrow tiles never combine a prefix's chunks; 16 rows went another way above)
+      if (kNarrow || !combined_here<G, kFlatRows>(it, m)) {
         write_rows(row0, !tree, std::integral_constant<int, kLaunchScope>{});
         return;
       }
-      write_rows(row0, !tree, in_launch);
-      arrive<T, G, kFlat, kNarrow ? 2 : 1>(a, it, hk, rs_o, rs_lse, m, words, s_last, *reinterpret_cast<MergeList*>(lds));
-      return;
+      if constexpr (!kNarrow) {
+        write_rows(row0, !tree, in_launch);
+        arrive<T, G, kFlatRows, 1>(a, it, hk, rs_o, rs_lse, m, words, s_last, *reinterpret_cast<MergeList*>(lds));
+        return;
+      }
     }
   }
   if (kGate && !wave_active) return;
@@ -2482,7 +2488,8 @@ template <typename T, int G>
 __global__ __launch_bounds__(kThreads) void merge_kernel(AttnArgs a, int blocks) {
   const i32x8 hdr = *(const __attribute__((address_space(4))) i32x8*)a.hdr;
   const bool trees = !(a.behind & kTreesBehind);
-  const bool none = hdr[6] == 0 || (((const_i32_ptr)a.hdr)[8] == 0 && trees);
+  // (chunks of narrow q tiles are counted in the launch)
+  const bool none = hdr[6] == 0 || (((const_i32_ptr)a.hdr)[8] == 0 && (trees || hdr[3] * G < kBM));
   if (hdr[0] != kPlanMagic || hdr[1] != head_counts(a.hkv, G) || none || hdr[4] != a.batch || hdr[5] != a.total_q) return;
   const buffer_rsrc rs_o = make_rsrc(a.part_o, (uint32_t)a.part_cap * a.hq * 512u);
   const buffer_rsrc rs_lse = make_rsrc(a.part_lse, (uint32_t)a.part_cap * a.hq * 4u);
@@ -2490,10 +2497,10 @@ __global__ __launch_bounds__(kThreads) void merge_kernel(AttnArgs a, int blocks)
   for (int64_t w = blockIdx.x; w < hdr[6] * per_rec; w += gridDim.x) {
     const int rec = __builtin_amdgcn_readfirstlane((int)(w / per_rec)), at = (int)(w - rec * per_rec);
     const i32x8 m = *(const __attribute__((address_space(4))) i32x8*)(a.merges + rec);
-    if (!(m[4] > 0 ? a.behind & kGroupsBehind : !trees && m[1] * G > a.flat_rows)) continue;
+    if (!(m[4] > 0 ? a.behind & kGroupsBehind : !trees && m[1] * G > kFlatRows)) continue;
     const int block = __builtin_amdgcn_readfirstlane(at / a.hkv), hk = at - block * a.hkv;
     merge_rows<T, G, kLaunchScope, 1, kMergeAhead>(
-        a, rs_o, rs_lse, hk, m[1], a.flat_rows, trees, block, blocks,
+        a, rs_o, rs_lse, hk, m[1], kFlatRows, trees, block, blocks,
         [&](int, int& first) __attribute__((always_inline)) { first = 0; return m; });
   }
 }
@@ -2714,7 +2721,6 @@ mc_status attn_impl(const mc_pool_desc* pool, int32_t layer, const void* q, int3
   const int mode = may_narrow(batch, total_q, G, pool->num_kv_heads, slots) ? kNarrowTiles
                    : 4ll * batch >= w.max_tiles - batch                     ? kGated
                                                                             : kPlain;
-  a.flat_rows = mode == kNarrowTiles ? kNarrowRows : kFlatRows;
   st = pool->dtype == MC_F16 ? launch_attn<_Float16>(G, mode, 1, grid, hs, a)
                              : launch_attn<__bf16>(G, mode, 1, grid, hs, a);
   if (st == MC_OK && wide_tiles_allowed(batch, total_q, G, pool->num_kv_heads)) {

@@ -287,3 +287,23 @@ def test_the_remainder_round_launch_after_launch(dtype):
 def test_narrow_q_tiles(dtype, Hq, Hkv, new, cached, tokens):
     w = small_workload(1370 + sum(new), dtype, Hq, Hkv, [n + c for n, c in zip(new, cached)], cached)
     assert check(w, 3, rows=0 if max(cached) < 4000 else 64)[3] == tokens
+
+
+# batches that may have narrow q tiles and keep whole ones: decode rows counted, 17 to 32 rows and more in trees, wavefronts
+# without a row; a shared prefix, whose members are combined behind the launch
+@pytest.mark.parametrize("dtype", [mi.BF16, mi.F16])
+@pytest.mark.parametrize("Hq,Hkv,new,cached,shared", [
+    (16, 8, [16, 3, 9, 14, 1, 16, 11, 16, 8, 2, 16, 16, 12, 16, 0, 16], 4000, 0),     # 2 to 32 rows
+    (64, 8, [5, 1, 4, 2, 8, 5, 7, 3, 5, 6, 1, 5, 5, 5, 5, 5], 4000, 0),               # 8 to 64
+    (8, 8, [40, 60, 96, 17, 33, 128, 1, 16], 6000, 0),                                # one to four wavefronts
+    (32, 8, [1] * 8 + [100], 1100, 1024), (32, 8, [5, 4, 1, 8, 3], 1100, 1024),       # 32 rows of the prefix; 84
+    (64, 8, [1, 1, 1, 1, 30], 1100, 1024), (8, 8, [17, 8, 1, 5, 200], 1100, 1024), (16, 8, [1] * 9 + [100], 1100, 1024),
+])
+def test_whole_tiles_where_narrow_ones_are_possible(dtype, Hq, Hkv, new, cached, shared):
+    cached = [cached + 70 * i for i in range(len(new))]
+    w = small_workload(1500 + sum(new), dtype, Hq, Hkv, [n + c for n, c in zip(new, cached)], cached)
+    for s in range(1, len(new) if shared else 0):
+        w.share_prefix(s, 0, shared)
+    assert sum(new) * Hq <= 32 * 256
+    h = check(w, 3, rows=32)
+    assert h[3] == 128 * Hkv // Hq and h[6] >= len(new) - 2 and (h[8] > 0) == (shared > 0), h[:9]
