@@ -183,7 +183,6 @@ constexpr int kMinSharedTiles = 8;    // a shared prefix shorter than 512 tokens
 // 256 over 256, 8 / 8 heads, 17.1 / 16.5.
 constexpr int kMinChunkTiles = 8, kMinChunkTilesDecode = 4, kMinChunkTilesShort = 2;
 constexpr int kNarrowBatch = 16;      // sequences of a batch that may have narrow tiles
-constexpr int kNarrowPieces = 16;     // pieces of a narrow tile
 // Narrow tiles of ranges up to this are not cut.  16 rows, whole / pieces of 4, us a layer: 32 tokens over 512 15.3 /
 // 16.9, over 1024 (17 tiles) 19.7 / 17.9.
 constexpr int kWholeNarrow = 12;
@@ -428,45 +427,71 @@ __device__ __forceinline__ void refuse_plan(PlanHeader* h) {
 }
 
 // The rows of a q tile of a batch of few sequences and few new tokens: kBM, or kNarrowRows or half as many, whose
-// items few_rows_item walks with all four wavefronts.  n: the batch's tiles of kBM rows, of kNarrowRows, of half as
-// many, and the KV tiles that the latter two look at.
+// items few_rows_item walks with all four wavefronts, cut into pieces of `pieces` KV tiles.  tiles: the batch's tiles of
+// kBM rows, of kNarrowRows, of half as many; visits: the KV tiles they look at, as if all of a sequence's tiles lay
+// in its middle; longest: KV tiles of the longest range; many: of the longest of more than kFlatRows rows (0: none).
 // A workgroup alone on its compute unit takes 1.07 us for a KV tile and 128 rows, 0.54 us for 32 or for 16 (each
 // wavefront walks every fourth half tile).  So narrow tiles have less than half the rate, but need no tree of
 // chunks (2 to 3 us a level) and no launch behind, and fill the compute units where q tiles of 128 rows are few.  Two
 // workgroups a compute unit take 1.34 us: what the L2s hand out, 15 TB/s, is the bound then, so there are never
 // more narrow items than compute units.
-// us a layer of four (append, attention, their share of the plan), whole tiles (cut) / 32 rows / 16 rows, 32 / 8
-// heads, tokens over keys cached:
-//   - up to 18 KV tiles, uncut: 64 over 512 19.1 / 17.9 / 13.9; 128 over 1024 23.9 / 20.2 / 19.4; 256 over 512 20.4 /
-//     17.9 / -, over 1024 24.1 / 22.8 / -;
-//   - 16 rows up to 16 tiles a compute unit, if every tile can be cut at least once: 8 over 4096 22.0 / 25.0 / 17.7,
-//     over 16000 30.4 / 33.4 / 24.9; 32 over 1024 21.5 / 18.2 / 15.4, over 4096 25.0 / 21.7 / 22.8, over 8192 28.2 /
-//     26.3 / 33; 64 over 2048 27.0 / 22.0 / 23.0;
-//   - 32 rows up to 24 tiles a compute unit: 64 over 4096 31.0 / 26.2; 128 over 2048 28.1 / 26.3, over 4096 (32 tiles)
-//     33.6 / 35.1; 256 over 2048 (34) 31.0 / 31.4;
-//   - up to a 64th of the slots of (q tile, kv head) pairs always, because whole tiles have many chunks there: 32 over
-//     8192 28.2 / 26.3, over 16000 34.6 / 35.6.
-__device__ __forceinline__ int narrow_rows(const PlanArgs& a, const int (&n)[5], int longest) {
-  if (n[2] <= n[0]) return kBM;                  // no tile holds more rows than that
-  const int units = a.slots / 2;
-  auto one_each = [&](int tiles) {
-    return tiles <= a.max_items && tiles <= a.max_merges && (long long)tiles * a.hkv <= units;
-  };
-  if (one_each(n[2]) && (longest <= 18 || (one_each(2 * n[2]) && (long long)n[4] * a.hkv <= 16 * units)))
-    return kNarrowRows / 2;
-  if (one_each(n[1]) && ((long long)n[3] * a.hkv <= 24 * units || 64ll * n[0] * a.hkv <= a.slots)) return kNarrowRows;
-  return kBM;
-}
-
-// The length of the pieces these are cut into, so that there are no more than compute units: as many equal ones a
-// tile, or by the sum of the tiles' lengths.  Nor are there more than the launch's grid has room for, or more than
-// kNarrowPieces a tile, which its last item combines (32 pieces of 32 rows: 17 us).
-__device__ __forceinline__ int narrow_pieces(const PlanArgs& a, int tiles, int cost, int longest) {
-  const int units = a.slots / 2, items = tiles * a.hkv;
-  const int equal = (longest + units / items - 1) / (units / items);
-  const int sum = units > items ? (int)(((long long)cost * a.hkv + units - items - 1) / (units - items)) : longest;
-  const int room = a.max_items > tiles ? (cost + a.max_items - tiles - 1) / (a.max_items - tiles) : longest;
-  return max(max(min(equal, sum), room), (longest + kNarrowPieces - 1) / kNarrowPieces);
+// Narrow tiles are taken as follows (us a layer of four: append, attention, their share of the plan; 32 / 8 heads
+// unless named; tokens over keys cached).
+//   - 16 rows up to 18 KV tiles, uncut, or up to 16 a compute unit if every tile can be cut at least once.  Whole
+//     tiles / 32 rows / 16 rows: 64 over 512 19.1 / 17.9 / 13.9; 128 over 1024 23.9 / 20.2 / 19.4; 8 over 4096 22.0 /
+//     25.0 / 17.7, over 16000 30.4 / 33.4 / 24.9; 32 over 1024 21.5 / 18.2 / 15.4, over 4096 25.0 / 21.7 / 22.8, over
+//     8192 28.2 / 26.3 / 33; 64 over 2048 27.0 / 22.0 / 23.0.
+//   - 32 rows up to 24 KV tiles a compute unit.  64 over 4096 31.0 / 26.2; 128 over 4096 (32 tiles) 33.6 / 35.1.
+//   - Both only if whole tiles would not be done sooner.  Estimates, in the time of a narrow item's KV tile: narrow ones
+//     take the longest piece, and 9 (32 rows) or 5 more if pieces have to be combined.  Whole ones are cut into
+//     pieces of 8 KV tiles or more, two for a KV tile of many rows and 5 for a level of their tree (2 with up to 64
+//     rows); one for a KV tile of few rows, and 5 to combine those.  That counts where lengths differ: narrow
+//     pieces have one length for all ranges, and one workgroup a compute unit leaves few of them.  Whole / narrow: 15
+//     rows over 500..4096 beside 800 tokens, 8 / 2 heads, 26.0 / 44.9; 8 rows over 4000 beside 100 tokens over 900
+//     45.0 / 61.7; 4 rows over 300..1100 beside 200 tokens 18.7 / 20.1, over 600..1500 beside 100 18.9 / 17.3.  One
+//     range: 128 over 2300 28.6 / 27.3, over 2700 29.2 / 29.6; 256 over 1100 24.5 / 23.5, over 1250 24.8 / 24.7; 64 over
+//     3000, 64 / 8 heads, 28.5 / 29.8.
+//   - Always up to a 64th of the slots of (q tile, kv head) pairs if the longest range has many rows: whole tiles have
+//     many chunks there, and their trees take longer.  Whole with trees / with a launch behind / narrow: 32 over 8192
+//     35.5 / 28.3 / 26.4, over 16000 45.9 / 34.7 / 35.9; 128 over 32000, 8 / 1 heads, 55.4 / 43.3 / 51.3.  (The launch
+//     behind costs 3.5 where ranges are shorter, and the host does not see how long they are.)
+// Pieces: as many equal ones a tile as there are compute units for, or by the sum of the lengths, no more than the
+// launch's grid has room for.  A tile's last item combines them, 0.5 us for each of 32 rows and half of that for 16,
+// eight at a time (nine take as long as 16): so 16 at most, or 8 where those are no more than 4 KV tiles longer (20
+// over 9000: 9 of 16 tiles 28.6, 8 of 18 26.4); of 16 rows 32 in long ranges of few tiles (8 over 32000, 8 / 1 heads,
+// 31.8 -> 27.5; with more tiles, 16 over 32000, 32.9 -> 35.8).
+// Every line of the planner runs once, from memory, and its length is its time: both sizes are weighed at once, 16 rows
+// in odd lanes and 32 in even ones, in floats, and neither the lengths' exact sum nor paths that such a batch cannot
+// take are in its planner.  (A form in integers, once a size, made a plan 2.4 us longer than the two rules by sums
+// alone did; this makes it 1 us shorter.)
+__device__ __forceinline__ int narrow_rows(const PlanArgs& a, const int* tiles, const int* visits, int longest, int many,
+                                           int& pieces) {
+  const bool half = threadIdx.x & 1;             // 16 rows in odd lanes, 32 in even ones
+  const int n0 = tiles[0], n = tiles[1 + half], units = a.slots / 2, items = n * a.hkv;
+  const float all = (float)visits[1 + half] * a.hkv, range = longest;
+  auto over = [](float x, float y) { return x * __builtin_amdgcn_rcpf(y); };
+  const bool few_pairs = 64 * n0 * a.hkv <= a.slots;
+  const bool fits = tiles[2] > n0 && items <= units && n <= min(a.max_items, a.max_merges) && longest <= 1 << 20 &&
+                    (half ? longest <= 18 || (2 * items <= units && all <= 16 * units) : all <= 24 * units || few_pairs);
+  float L = over(range, floorf(over(units + 0.5f, items)));
+  L = fminf(L, over(all, units - items));
+  L = fmaxf(L, over(range, half && longest > 256 && 64 * items <= units ? 32 : 16));
+  const float eight = ceilf(range * 0.125f);
+  L = eight - L > 4 ? L : fmaxf(L, eight);
+  const int most = visits[1 + half] + n * (a.total_q / (2 * kBN) + 1);      // KV tiles, from below the diagonal
+  L = ceilf(fmaxf(fmaxf(L, kMinChunkTilesDecode), over(most, a.max_items - n) * 1.001f));
+  const bool cut = L < range && longest > kWholeNarrow;
+  const float narrow = cut ? L + (!half && many > L ? 9 : 5) : range;
+  const float per = fmaxf(kMinChunkTiles, over((float)visits[0] * a.hkv, a.slots));
+  float whole = fminf(2 * many, 2 * per);
+  if (many > per)
+    whole += (a.total_q * kBM <= 64 * n0 * a.tile_tokens ? 2 : 5) * ceilf(__log2f(over(many, per)) - 0.01f);
+  if (longest > many) whole = fmaxf(whole, fminf(range, per + 5));
+  const unsigned long long pays = __ballot(fits && ((few_pairs && longest == many) || narrow <= whole));
+  if ((pays & 3) == 0) return kBM;
+  const int lane = (pays & 2) != 0;
+  pieces = __builtin_amdgcn_readlane((int)fminf(L, range), lane);
+  return kNarrowRows >> lane;
 }
 
 // Page ids of every needed table entry, for batches too large for the planner's one workgroup
@@ -507,7 +532,7 @@ template <int NT, bool kMayNarrow>
 __global__ __launch_bounds__(NT) void plan_kernel(PlanArgs a) {
   __shared__ int scan[5 * NT / 64];   // wavefront totals of the block scans and sums
   __shared__ int hist[kBuckets];
-  __shared__ int s_err, s_maxcost, s_table_end, s_pages, s_suspect, s_sums[5];
+  __shared__ int s_err, s_maxcost, s_table_end, s_pages, s_suspect, s_sums[6], s_many;
   // per-sequence arrays of batches that fit: the searches and tile look-ups below stay in LDS
   __shared__ int s_cu[kCuTilesInLds + 1], s_cuq[kCuTilesInLds + 1], s_beg[kCuTilesInLds],
       s_cup[kCuTilesInLds + 1];
@@ -546,7 +571,7 @@ __global__ __launch_bounds__(NT) void plan_kernel(PlanArgs a) {
   // 0. q tile width: wide tiles when a new token sees kWideMinKeys keys on average.  Their ranges are not
   //    cut: the host allows them where there are four a compute unit of a 256-unit GPU.
   bool wide = false;
-  if (a.wide_tile_tokens > 0) {
+  if (!kMayNarrow && a.wide_tile_tokens > 0) {
     long long keys = 0, rows = 0;
     for (int s = s_lo; s < s_hi; ++s) {
       const long long q = cuq(s + 1) - cuq(s), b = beg(s);
@@ -562,10 +587,10 @@ __global__ __launch_bounds__(NT) void plan_kernel(PlanArgs a) {
   }
   // 1. validate, count tiles per sequence (contiguous chunk of sequences per thread)
   int my_tiles = 0, err = 0, maxcost = 1, my_pages = 0, table_end = 0;
-  // (kMayNarrow) the same in tiles of kNarrowRows rows and of half as many, and the KV tiles
-  // that these have to look at
+  // (kMayNarrow) the same in tiles of kNarrowRows rows and of half as many, the KV tiles that all three have to look
+  // at, and the longest range of more than kFlatRows rows
   const int narrow_tokens = a.tile_tokens * kNarrowRows / kBM;
-  int narrow_tiles[2] = {0, 0}, narrow_visits[2] = {0, 0};
+  int narrow_tiles[2] = {0, 0}, visits[3] = {0, 0, 0}, many = 0;
   if (t == 0 && (cuq(0) != 0 || cuq(a.batch) != a.total_q || cup(0) < 0)) err = 1;
   for (int s = s_lo; s < s_hi; ++s) {
     const int q = cuq(s + 1) - cuq(s), b = beg(s);
@@ -579,29 +604,38 @@ __global__ __launch_bounds__(NT) void plan_kernel(PlanArgs a) {
     table_end = max(table_end, cup(s) + need);
     my_tiles += (q + a.tile_tokens - 1) / a.tile_tokens;
     if constexpr (kMayNarrow) {
-      const int visits = (int)min((end - q / 2 + kBN - 1) / kBN, (int64_t)1 << 12);
+      // (q tiles have 2^i tokens, and no more than 2^10 have few enough rows, over 2^20 KV tiles: narrow_rows)
+      const int mean = (int)min((end - q / 2 + kBN - 1) / kBN, (int64_t)1 << 20), shift = __builtin_ctz(a.tile_tokens);
 #pragma unroll
       for (int k = 0; k < 2; ++k) {
-        const int tiles = min((q + (narrow_tokens >> k) - 1) / (narrow_tokens >> k), 1 << 12);
-        narrow_tiles[k] += tiles;
-        narrow_visits[k] += tiles * visits;       // (at most 2^24 for each of 16 sequences)
+        narrow_tiles[k] = (q + (narrow_tokens >> k) - 1) >> (shift - 2 - k);
+        visits[1 + k] = narrow_tiles[k] * mean;
       }
+      visits[0] = ((q + a.tile_tokens - 1) >> shift) * mean;
     }
-    maxcost = max(maxcost, (int)((end + kBN - 1) / kBN));
+    const int T = (int)((end + kBN - 1) / kBN);
+    if (q > narrow_tokens / 2) many = max(many, T);
+    maxcost = max(maxcost, T);
   }
   // In the small variant all sequences are the first wavefront's, a thread each: it sums the tiles before them here,
   // ahead of the barrier that there is.
   constexpr bool kFirstWave = NT == kPlanThreadsSmall;
-  constexpr int kSums = kMayNarrow ? 5 : 1;
+  constexpr int kSums = kMayNarrow ? 6 : 1;
   int before[kSums] = {my_tiles};
-  if constexpr (kMayNarrow)
-    for (int k = 0; k < 2; ++k) { before[1 + k] = narrow_tiles[k]; before[3 + k] = narrow_visits[k]; }
+  if constexpr (kMayNarrow) {
+    for (int k = 0; k < 2; ++k) before[1 + k] = narrow_tiles[k];
+    for (int k = 0; k < 3; ++k) before[3 + k] = visits[k];
+  }
   if (kFirstWave && t < 64) {
 #pragma unroll
     for (int k = 0; k < kSums; ++k) {
       const int incl = wave_inclusive_sum(before[k]);
       before[k] = incl - before[k];
       if (t == 63) s_sums[k] = incl;
+    }
+    if constexpr (kMayNarrow) {
+      many = wave_inclusive_max(many);
+      if (t == 63) s_many = many;
     }
   }
   // (one LDS atomic per wavefront, not per thread: 1024 atomics on one address take microseconds)
@@ -650,7 +684,7 @@ __global__ __launch_bounds__(NT) void plan_kernel(PlanArgs a) {
   //     and their own remainders one by one; the parts are merged by LSE like any other chunks.
   //     Prefix items hold the whole group's rows, or where they are combined in the launch (see MergeRec)
   //     those of the members whose first tokens lie in the same kFlatRows rows of it: a slice.
-  const bool sliced = groups_in_launch(a.batch, a.total_q);
+  const bool sliced = !kMayNarrow && groups_in_launch(a.batch, a.total_q);
   const int slice = max(kFlatRows * a.tile_tokens / kBM, 1);
   const bool try_groups = a.allow_groups && cu_in_lds && a.batch >= 2 && a.batch <= NT;
   if (t == 0) s_groups = 0;
@@ -769,12 +803,12 @@ __global__ __launch_bounds__(NT) void plan_kernel(PlanArgs a) {
   //     Tiles of fewer rows where even these are no more than a workgroup a compute unit: narrow_rows.
   int total_tiles, base;
   bool narrow = false;
+  int pieces = 0;
   if constexpr (kMayNarrow) {
-    const int all[5] = {s_sums[0], s_sums[1], s_sums[2], s_sums[3], s_sums[4]};
-    const int rows = wide || groups ? kBM : narrow_rows(a, all, s_maxcost);
+    const int rows = groups ? kBM : narrow_rows(a, s_sums, s_sums + 3, s_maxcost, s_many, pieces);
     const int k = rows == kBM ? 0 : rows == kNarrowRows ? 1 : 2;
     base = k == 0 ? before[0] : k == 1 ? before[1] : before[2];
-    total_tiles = k == 0 ? all[0] : k == 1 ? all[1] : all[2];
+    total_tiles = s_sums[k];
     narrow = k > 0;
     if (narrow) a.tile_tokens = narrow_tokens >> (k - 1);
   } else {
@@ -851,7 +885,9 @@ __global__ __launch_bounds__(NT) void plan_kernel(PlanArgs a) {
   //    below the shortest piece of this kind of batch, doubled until the partial rows fit the
   //    workspace.
   int L = 0;
-  if (!wide && (int64_t)total_tiles * a.hkv < (int64_t)kRoundsWanted * a.slots) {
+  if (kMayNarrow && narrow) {
+    L = s_maxcost > kWholeNarrow ? (pieces + 1) & ~1 : s_maxcost;
+  } else if (!wide && (int64_t)total_tiles * a.hkv < (int64_t)kRoundsWanted * a.slots) {
     long long cost = 0;
     for (int i = t; i < total_tiles; i += NT) {
       const Tile x = tile(i);
@@ -860,10 +896,9 @@ __global__ __launch_bounds__(NT) void plan_kernel(PlanArgs a) {
     cost = (long long)total_tiles * s_maxcost <= INT32_MAX ? block_sum_int<NT>((int)cost, scan)
                                                              : block_sum<NT>(cost, scan);
     const long long room = (long long)kItemsPerSlot * a.slots, heads = cost * a.hkv + room - 1;
-    long long want = heads <= INT32_MAX ? (int)heads / (int)room : heads / room;
-    if (kMayNarrow && narrow) want = narrow_pieces(a, total_tiles, (int)min(cost, 1ll << 30), s_maxcost);
+    const long long want = heads <= INT32_MAX ? (int)heads / (int)room : heads / room;
     // short pieces: only if no sequence has two new tokens (as many q tiles as new tokens)
-    int shortest = narrow ? kMinChunkTilesDecode : kMinChunkTiles;
+    int shortest = kMinChunkTiles;
     if (a.total_q <= total_tiles && want < kMinChunkTiles) {
       shortest = s_maxcost <= kMinChunkTilesShort * kMergeAhead ? kMinChunkTilesShort : kMinChunkTilesDecode;
       shortest = max(shortest, ((int)want + 1) & ~1);
@@ -878,15 +913,14 @@ __global__ __launch_bounds__(NT) void plan_kernel(PlanArgs a) {
       L = max(L, min((longest + kListedAhead - 2) / (kListedAhead - 1), kListedAhead));
     }
     L = (L + 1) & ~1;
-    for (;;) {
-      // (nothing is long enough to be cut)
-      if (L >= s_maxcost || (narrow && s_maxcost <= kWholeNarrow)) { L = 0; break; }
-      // (each tile has at most s_maxcost / L + 1 chunks of its own, and as many of a prefix its tokens)
-      const long long most = (long long)(groups ? 2 : 1) * (s_maxcost / L + 1) * a.total_q +
-                             (long long)total_tiles * arrive_rows(L);
-      if (most <= a.part_cap || total_part_rows(L) <= a.part_cap) break;
-      L *= 2;
-    }
+  }
+  while (L > 0) {
+    if (L >= s_maxcost) { L = 0; break; }   // nothing is long enough to be cut
+    // (each tile has at most s_maxcost / L + 1 chunks of its own, and as many of a prefix its tokens)
+    const long long most = (long long)(groups ? 2 : 1) * (s_maxcost / L + 1) * a.total_q +
+                           (long long)total_tiles * arrive_rows(L);
+    if (most <= a.part_cap || total_part_rows(L) <= a.part_cap) break;
+    L *= 2;
   }
   // without cuts the groups still need partial rows: no room, no groups
   if (L == 0 && groups && total_part_rows(0) > a.part_cap) {

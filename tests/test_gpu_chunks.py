@@ -283,10 +283,26 @@ def test_the_remainder_round_launch_after_launch(dtype):
     (32, 8, [5, 17, 64, 1, 0, 33], [100, 3000, 200, 2000, 70, 0], 8),                # ragged
     (8, 8, [17, 3, 31, 32, 1], [0, 15, 700, 2500, 5], 16),
     (64, 8, [3] * 16, [40 * i for i in range(16)], 2), (64, 8, [3] * 17, [40 * i for i in range(17)], 16),
+    # whole tiles sooner done, or narrow ones: one range; ranges beside longer decode rows
+    (32, 8, [128], [2300], 8), (32, 8, [128], [2700], 32), (32, 8, [256], [1100], 8), (32, 8, [256], [1500], 32),
+    (32, 8, [1] * 8 + [100], [4000] * 8 + [900], 32), (8, 2, [1] * 15 + [800], [500 + 240 * i for i in range(15)] + [0], 32),
+    (32, 8, [1] * 4 + [200], [300, 600, 900, 1100, 0], 32), (32, 8, [1] * 4 + [100], [600, 900, 1200, 1500, 0], 8),
+    (8, 1, [1] * 4 + [300], [2100, 2300, 2400, 2600, 0], 4),
 ])
 def test_narrow_q_tiles(dtype, Hq, Hkv, new, cached, tokens):
     w = small_workload(1370 + sum(new), dtype, Hq, Hkv, [n + c for n, c in zip(new, cached)], cached)
     assert check(w, 3, rows=0 if max(cached) < 4000 else 64)[3] == tokens
+
+
+@pytest.mark.parametrize("Hq,Hkv,new,cached,tiles", [
+    (32, 8, 32, 16000, 32), (32, 8, 20, 9000, 18), (32, 8, 24, 12000, 20),     # eight pieces; not nine; ten
+    (8, 1, 16, 32000, 32), (8, 1, 8, 32000, 16),                               # 16 at most; 32 of few tiles of 16 rows
+    (32, 8, 64, 4700, 20), (32, 8, 37, 600, 0),                                # four; uncut
+])
+def test_pieces_of_narrow_q_tiles(Hq, Hkv, new, cached, tiles):
+    w = small_workload(1390 + new, mi.BF16, Hq, Hkv, [new + cached], [cached])
+    h = check(w, 3, rows=64)
+    assert h[3] < 128 * Hkv // Hq and h[7] == tiles, h[:9]
 
 
 # batches that may have narrow q tiles and keep whole ones: decode rows counted, 17 to 32 rows and more in trees, wavefronts
