@@ -1238,6 +1238,7 @@ struct AttnArgs {
   float* part_lse;         // of every partial row (see MergeRec); the arrival words at its end
   float* part_o;           // [partial row][128]
   int32_t num_pages, hkv, hq, batch, total_q;
+  int32_t units;           // compute units
   int32_t part_cap;        // rows of the partial arrays
   int32_t behind;          // what merge_kernel combines (see MergeRec): kGroupsBehind, kTreesBehind
   float scale, scale_log2;  // softmax scale, and scale * log2(e)
@@ -1549,10 +1550,11 @@ __device__ __forceinline__ float across_rows(float x, Op&& op) {
 // of 64 forks of a 2048-token prompt, 32 / 8, four layers 196.1 -> 200.3, 200.1; of 64 rows over 1024..4096
 // beside a prefill, two layers 328 -> 329, 336; of eight rows over 1024..4096, 64 / 8, eight layers 207.0 ->
 // 205.0, 205.4.
-// beside: items of a plan of narrow q tiles, a workgroup a compute unit at most, their keys in the L2s: bound by
-// latency, so V is requested beside K there (256 tokens over 256, 8 / 8 heads, 11.8 -> 11.3 us a layer; 128 over 1024,
-// 32 / 8, 19.5 -> 19.0).  Not for the decode rows of plans of whole tiles, which the launch that may have narrow ones
-// runs as well (kNarrow; eight rows over 16000 beside 128 new tokens, 8 / 1 heads, 31.1 us a layer, 28.4 with V ahead).
+// beside: a workgroup a compute unit at most, as in plans of narrow q tiles, their keys in the L2s: bound by latency, so
+// V is requested beside K there (256 tokens over 256, 8 / 8 heads, 11.8 -> 11.3 us a layer; 128 over 1024, 32 / 8, 19.5 ->
+// 19.0; 16 over 300, 8 / 8, a whole tile, 11.9 -> 11.5).  Only in the launch that may have narrow tiles (kNarrow), and not for
+// the decode rows of plans of more items, which it runs as well (eight rows over 16000 beside 128 new tokens, 8 / 1 heads,
+// 31.1 us a layer, 28.4 with V ahead).
 // A layer (append and attention) of one row over 1000 keys, 32 / 8 heads, 12.9 -> 10.5 us; of eight rows
 // over 1024..4096, 64 / 8 heads, 27.7 -> 25.5; 256 rows, bound by the reads, the same.
 template <typename T, int G, int kRB, bool kNarrow>
@@ -1865,7 +1867,8 @@ __global__ __launch_bounds__(kThreads, kCB == 1 ? 2 : 1) void attn_kernel(AttnAr
   // ones, 32 / 8 heads, 23.0 us a layer, so 20.8.)
   if (kNarrow && (narrow | (ntok * G <= (group ? kNarrowRows : kFlatRows)))) {
     __shared__ float s_stat[2 * 4 * kNarrowRows];
-    if (ntok * G <= kFlatRows) few_rows_item<T, G, 1, true>(a, it, hk, b, row0, item_b, lds, s_stat, s_last, narrow);
+    if (ntok * G <= kFlatRows) few_rows_item<T, G, 1, true>(a, it, hk, b, row0, item_b, lds, s_stat, s_last,
+                                                                 narrow | (hdr[2] * a.hkv <= a.units));
     else few_rows_item<T, G, 2, true>(a, it, hk, b, row0, item_b, lds, s_stat, s_last, true);
     return;
   }
@@ -2737,6 +2740,7 @@ mc_status attn_impl(const mc_pool_desc* pool, int32_t layer, const void* q, int3
   a.part_lse = reinterpret_cast<float*>(ws + w.part_lse);
   a.part_o = reinterpret_cast<float*>(ws + w.part_o);
   a.part_cap = w.part_cap;
+  a.units = slots / 2;
   a.num_pages = pool->num_pages;
   a.hkv = pool->num_kv_heads;
   a.hq = num_q_heads;
