@@ -1,7 +1,7 @@
 """Chunks of a cut KV range are combined inside the attention launch - rows that are counted (up to 16
 a q tile and kv head, 32 of narrow q tiles), trees over two to many chunks, groups of both kinds, at the
-row counts where one becomes the other - or in a launch behind it.  Launch after launch on one plan (the arrival words
-wrap), every launch the same bits whichever chunk comes last, and the oracle's result."""
+row counts where one becomes the other - or in a launch behind it.  Launch after launch on one plan (the
+arrival words wrap), every launch the same bits whichever chunk comes last, and the oracle's result."""
 import numpy as np
 import pytest
 
@@ -323,3 +323,43 @@ def test_whole_tiles_where_narrow_ones_are_possible(dtype, Hq, Hkv, new, cached,
     assert sum(new) * Hq <= 32 * 256
     h = check(w, 3, rows=32)
     assert h[3] == 128 * Hkv // Hq and h[6] >= len(new) - 2 and (h[8] > 0) == (shared > 0), h[:9]
+
+
+# a plan made ahead: per line the tile's tokens, and whether it is cut.  The ranges step over the end of a 64-key tile, so
+# that a last piece (a last KV tile) holds no key at first and some later
+@pytest.mark.parametrize("dtype", [mi.BF16, mi.F16])
+@pytest.mark.parametrize("Hq,Hkv,new,cached,tokens,cut", [
+    (32, 8, [9], [1020], 4, True), (32, 8, [40], [250], 4, False),          # 16 rows
+    (32, 8, [128], [2040], 8, True), (32, 8, [200], [500], 8, False),       # 32
+    (64, 8, [3, 8, 1, 5], [700, 1275, 2000, 60], 2, True),                  # ragged
+])
+def test_narrow_q_tiles_planned_ahead(dtype, Hq, Hkv, new, cached, tokens, cut):
+    ahead, B, tq = 70, len(new), sum(new)
+    final = [n + c + ahead for n, c in zip(new, cached)]
+    w = small_workload(1600 + tq, dtype, Hq, Hkv, final, cached)
+    pool = DevPool(w)
+    pool.t.fill_(0x7fc1)
+    opool = np.full(pool.elems, 0x7fc1, dtype=np.uint16)
+    fill_both(w, pool, opool)
+    cu_q = dev(np.concatenate([[0], np.cumsum(new)]).astype(np.int32))
+    db = DevBatch(w)
+    size = mc.mc_attn_workspace_size(B, tq, Hq, Hkv)
+    ws = torch.full((size,), 0xff, dtype=torch.uint8, device=DEV)
+    mc.mc_attn_plan_ahead(pool.desc, Hq, B, tq, cu_q, db.begin, db.page_table, db.cu_pages, ahead, ws, size)
+    mc.mc_attn_plan_check(ws)
+    h = ws[:64].view(torch.int32).cpu().numpy()
+    assert h[3] == tokens and (h[7] > 0) == cut, h[:9]
+    q = np.concatenate([w.q(s)[:n] for s, n in enumerate(new)])
+    for step in (0, 1, 27, 63, 64, ahead):
+        begin = [c + step for c in cached]
+        out = torch.full((tq, Hq, 128), 0x7fc1, dtype=torch.int16, device=DEV)
+        lse = torch.full((tq, Hq), float("nan"), dtype=torch.float32, device=DEV)
+        mc.mc_prefix_prefill_attn(pool.desc, 0, dev(q), Hq, B, tq, cu_q, dev(np.array(begin, np.int32)), db.page_table,
+                                  db.cu_pages, 0.0, out, lse, ws, size)
+        torch.cuda.synchronize()
+        at = 0
+        for s, (n, b) in enumerate(zip(new, begin)):
+            ro, rl = oracle.attention(opool, pool.shape, 0, w.page_tables[s], q[at:at + n], Hq, b, b + n)
+            assert np.max(np.abs(oracle.decode(bits(out[at:at + n]), dtype) - ro)) <= O_TOL, (step, s)
+            assert np.max(np.abs(lse[at:at + n].cpu().numpy() - rl)) <= LSE_TOL, (step, s)
+            at += n

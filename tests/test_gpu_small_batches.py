@@ -175,10 +175,50 @@ def test_short_pieces_inside_a_shared_prefix(dtype, Hq, Hkv):
 @pytest.mark.parametrize("need,slack", [([1], 0), ([3], 2), ([5, 0, 70], 1), ([1100], 0), ([40] * 17, 3),
                                         ([9] * 40, 30), ([270] * 256, 1)])
 def test_page_ids_are_checked_where_a_token_needs_them(need, slack):
+    plan, table, cu_pages, num_pages = planned_tables(need, slack, valid_slack=False)
+    plan(table)
+    for s, e in [(0, 0), (0, need[0] - 1), (len(need) // 2, need[len(need) // 2] // 2), (len(need) - 1, need[-1] - 1)]:
+        if need[s] == 0:
+            continue
+        for bad in (-1, num_pages):
+            refused(plan, table, cu_pages[s] + e, bad)
+
+
+# every id is in range but one, so the look at the table as it lies has to find it: entries that are requested early (16 of
+# 256 threads, 4 of 1024), in later trips of as many, in the last four, and behind a trip's edges
+@pytest.mark.parametrize("need,slack", [([9000], 0), ([4097], 0), ([33000, 7], 0), ([1000] * 17, 0), ([600] * 20, 2),
+                                        ([150, 0, 90] * 30, 0), ([130] * 255 + [4099], 0)])
+def test_a_single_page_id_out_of_range_is_found(need, slack):
+    plan, table, cu_pages, num_pages = planned_tables(need, slack, valid_slack=True)
+    plan(table)
+    early = 4096                          # 4 entries x 4 x 256 threads, x 1 x 1024
+    edges = [0, 1, 3, 4, 1023, 1024, early - 1, early, early + 1]
+    trip = 4 * 4 * (256 if len(need) <= 16 else 1024)
+    edges += [early + k * trip + d for k in (1, 2) for d in (-4, -1, 0)]
+    last = len(table) - slack
+    edges += [last - 1, last - 2, last - 3, last - 4, last - 5, last // 2]
+    needed = np.concatenate([np.arange(cu_pages[s], cu_pages[s] + n) for s, n in enumerate(need)])
+    for at in sorted(set(edges) & set(needed.tolist())):
+        refused(plan, table, at, (-1, num_pages)[at % 2])
+
+
+def refused(plan, table, at, bad):
+    t = table.copy()
+    t[at] = bad
+    with pytest.raises(mc.McError) as err:
+        plan(t)
+    assert err.value.status == mc.MC_ERR_RANGE, (at, bad)
+
+
+def planned_tables(need, slack, valid_slack):
+    """plan(table) for one decode row over all entries a sequence needs, such a table with slack more entries a
+    sequence, its cu_pages, and the pool's pages."""
     num_pages, B = 50, len(need)
     rng = mi.rng_for(995 + B)
     cu_pages = np.concatenate([[0], np.cumsum([n + slack for n in need])]).astype(np.int32)
     table = np.where(np.arange(cu_pages[-1]) % 2, -1, num_pages).astype(np.int32)      # what no token needs
+    if valid_slack:
+        table[:] = rng.integers(0, num_pages, len(table))
     for s, n in enumerate(need):
         table[cu_pages[s]:cu_pages[s] + n] = rng.integers(0, num_pages, n)
     new = [int(n > 0) for n in need]
@@ -193,13 +233,4 @@ def test_page_ids_are_checked_where_a_token_needs_them(need, slack):
         mc.mc_attn_plan(desc, 32, B, sum(new), cu_q, begin, dev(t), dev(cu_pages), ws, size)
         mc.mc_attn_plan_check(ws)
 
-    plan(table)
-    for s, e in [(0, 0), (0, need[0] - 1), (B // 2, need[B // 2] // 2), (B - 1, need[-1] - 1)]:
-        if need[s] == 0:
-            continue
-        for bad in (-1, num_pages):
-            t = table.copy()
-            t[cu_pages[s] + e] = bad
-            with pytest.raises(mc.McError) as err:
-                plan(t)
-            assert err.value.status == mc.MC_ERR_RANGE, (s, e, bad)
+    return plan, table, cu_pages, num_pages
