@@ -1051,8 +1051,13 @@ __global__ __launch_bounds__(NT) void plan_kernel(PlanArgs a) {
   int item_off = offs[0], own_off = offs[1], grp_off = offs[2], merge_off = offs[3];
   for (int i = 0, off = offs[4]; i < kPer; ++i) { hist[t * kPer + i] = off; off += local[i]; }
   // a batch of no more tiles than threads: its items are written one a thread, not those of a tile one after
-  // another (a load and a store behind it each)
-  const bool spread = one_each && tot_items > 0 && tot_items <= kSpreadItems;
+  // another (a load and a store behind it each), if a tile has more than four, or for decode steps' order (below).
+  // Fewer are written sooner by the tile's thread (187 tiles of up to four pieces, one range, plan 13.7 -> 10.8 us) and lie
+  // better: neighbours in the launch are of other tiles (13 rows beside a prefill of 2000 tokens, 32 / 8 heads, 48.9
+  // us a layer, so 47.0; one range of 8 / 1 heads 109.2, 104.6).
+  const bool by_tile = a.total_q <= total_tiles;
+  const bool spread = one_each && tot_items > total_tiles && tot_items <= kSpreadItems &&
+                      (by_tile || s_maxcost > 4 * L);
   if (spread && t < total_tiles) {
     s_first[t] = item_off;
     s_merge[t] = merge_off;
@@ -1080,11 +1085,10 @@ __global__ __launch_bounds__(NT) void plan_kernel(PlanArgs a) {
   //    by the tile's thread, 8 and 32 pieces of one decode row took 2.4 and 7.3 us, one a thread 1.1 and 1.2.
   //    With the page ids' look and without a sum that a bound replaces the plan of one row over 1000
   //    tokens takes 7.6 us instead of 10.0, over 8100 8.0 instead of 15.8, of 256 rows 14.4 instead of 19.4.)
-  // Pieces of one length of decode steps lie tile by tile, so that a row's last piece combines them while others run
-  // (32 rows over 200..900 tokens, eight layers, 199 us, in the other order 206).  Else the first pieces of all tiles
-  // lie ahead of their second ones, so that a compute unit's two workgroups differ (16 decode rows beside a prefill of 600
-  // tokens 145, so 137; 500 new tokens over 2500 184, so 178).
-  const bool by_tile = a.total_q <= total_tiles;
+  // Pieces of one length of decode steps lie tile by tile (by_tile), so that a row's last piece combines them while
+  // others run (32 rows over 200..900 tokens, eight layers, 199 us, in the other order 206).  Else the first pieces of
+  // all tiles lie ahead of their second ones, so that a compute unit's two workgroups differ (16 decode rows beside a
+  // prefill of 600 tokens 145, so 137; 500 new tokens over 2500 184, so 178).
   struct Piece { int t0, t1, chunk; bool in_group; };
   auto piece = [&](const Tile& x, int Li, int k) {
     const int ns = own_splits(x, Li);
