@@ -532,7 +532,7 @@ template <int NT, bool kMayNarrow>
 __global__ __launch_bounds__(NT) void plan_kernel(PlanArgs a) {
   __shared__ int scan[5 * NT / 64];   // wavefront totals of the block scans and sums
   __shared__ int hist[kBuckets];
-  __shared__ int s_err, s_maxcost, s_table_end, s_pages, s_suspect, s_sums[6], s_many;
+  __shared__ int s_err, s_maxcost, s_table_end, s_pages, s_suspect, s_sums[6], s_many, s_alike;
   // per-sequence arrays of batches that fit: the searches and tile look-ups below stay in LDS
   __shared__ int s_cu[kCuTilesInLds + 1], s_cuq[kCuTilesInLds + 1], s_beg[kCuTilesInLds],
       s_cup[kCuTilesInLds + 1];
@@ -550,7 +550,7 @@ __global__ __launch_bounds__(NT) void plan_kernel(PlanArgs a) {
   __shared__ uint8_t s_tailflag[kTailTilesMax];
   __shared__ int s_tail_bucket, s_tail_take, s_tail_taken;
   const int t = threadIdx.x;
-  if (t == 0) { s_err = 0; s_maxcost = 1; s_table_end = s_pages = s_suspect = 0; }
+  if (t == 0) { s_err = 0; s_maxcost = 1; s_table_end = s_pages = s_suspect = s_alike = 0; }
   for (int i = t; i < kBuckets; i += NT) hist[i] = 0;
   const bool cu_in_lds = a.batch <= kCuTilesInLds;
   if (cu_in_lds) {
@@ -675,6 +675,16 @@ __global__ __launch_bounds__(NT) void plan_kernel(PlanArgs a) {
 #pragma unroll
   for (int k = 0; k < kFlatLoads; ++k)
     flat_ids[k] = ids_here && !suspect ? flat_load(t + k * NT) : i32x4u{0, 0, 0, 0};
+  auto look_at_rest = [&]() {
+    for (int i = t + kFlatLoads * NT; ids_here && !suspect && 4ll * i < table_n; i += kFlatTrip * NT) {
+      i32x4u more[kFlatTrip];
+#pragma unroll
+      for (int k = 0; k < kFlatTrip; ++k) more[k] = flat_load(i + k * NT);
+#pragma unroll
+      for (int k = 0; k < kFlatTrip; ++k) suspect |= bad_id(more[k]);
+    }
+  };
+  bool looked = false;
   // (batches beyond that: validate_pages_kernel, launched after this kernel, on many workgroups)
   // 3b. shared-prefix groups (Sec. 3.4, fork_sequence in Sec. 3.5: sequences may share the pages of a common
   //     prefix).  The new tokens of neighbouring sequences with short new ranges (decode rows,
@@ -687,24 +697,31 @@ __global__ __launch_bounds__(NT) void plan_kernel(PlanArgs a) {
   const bool sliced = !kMayNarrow && groups_in_launch(a.batch, a.total_q);
   const int slice = max(kFlatRows * a.tile_tokens / kBM, 1);
   const bool try_groups = a.allow_groups && cu_in_lds && a.batch >= 2 && a.batch <= NT;
+  constexpr int kMinPages = kMinSharedTiles * kBN / kPage;
+  // a sequence can be a member if its new range leaves room for another token in a q tile
+  auto is_short = [&](int sq) {
+    const int q = s_cuq[sq + 1] - s_cuq[sq];
+    return q >= 1 && q < a.tile_tokens;
+  };
   if (t == 0) s_groups = 0;
   if (try_groups) {
     for (int i = t; i < a.batch; i += NT) { s_common[i] = 0; s_gp[i] = 0; s_glead[i] = -1; s_gsize[i] = 0; }
     __syncthreads();
     // pages in common between s and s+1, among the whole pages cached by both.  First every
     // pair at once, one thread each: unrelated sequences differ in their first page and are
-    // done (s_common = 1 marks a pair that is not).  Then 16 lanes a remaining pair.
-    constexpr int kMinPages = kMinSharedTiles * kBN / kPage;
-    // a sequence can be a member if its new range leaves room for another token in a q tile
-    auto is_short = [&](int sq) {
-      const int q = s_cuq[sq + 1] - s_cuq[sq];
-      return q >= 1 && q < a.tile_tokens;
-    };
+    // done (s_common = 1 marks a pair that is not).  Then 16 lanes a remaining pair, behind the look at the rest of
+    // the table, which asks for all of it at once, where a pair's lanes walk it, a memory latency for every 128 entries
+    // (plan of 99 forks of 4000 tokens 34.2 us when every sequence's ids were looked at ahead, 38 when all of them were
+    // behind, now 30.6; of 64 of 2048 26.9, 24.0, 22.6).
     if (t + 1 < a.batch && is_short(t) && is_short(t + 1) &&
         min(s_beg[t], s_beg[t + 1]) / kPage >= kMinPages &&
         a.page_table[s_cup[t]] == a.page_table[s_cup[t + 1]])
-      s_common[t] = 1;
+      s_common[t] = s_alike = 1;
     __syncthreads();
+    looked = s_alike != 0;
+  }
+  if (looked) {
+    look_at_rest();
     // (16 lanes a pair, eight entries a lane and table in flight: the pairs of 64 sequences in one turn)
     for (int sq = t >> 4; sq + 1 < a.batch; sq += NT >> 4) {
       if (s_common[sq] == 0) continue;
@@ -1002,13 +1019,7 @@ __global__ __launch_bounds__(NT) void plan_kernel(PlanArgs a) {
   if (!suspect) {
 #pragma unroll
     for (int k = 0; k < kFlatLoads; ++k) suspect |= bad_id(flat_ids[k]);
-    for (int i = t + kFlatLoads * NT; ids_here && 4ll * i < table_n; i += kFlatTrip * NT) {
-      i32x4u more[kFlatTrip];
-#pragma unroll
-      for (int k = 0; k < kFlatTrip; ++k) more[k] = flat_load(i + k * NT);
-#pragma unroll
-      for (int k = 0; k < kFlatTrip; ++k) suspect |= bad_id(more[k]);
-    }
+    if (!looked) look_at_rest();
   }
   if (__ballot(suspect) != 0 && (t & 63) == 0) s_suspect = 1;
   __syncthreads();

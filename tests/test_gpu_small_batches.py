@@ -186,10 +186,14 @@ def test_page_ids_are_checked_where_a_token_needs_them(need, slack):
 
 # every id is in range but one, so the look at the table as it lies has to find it: entries that are requested early (16 of
 # 256 threads, 4 of 1024), in later trips of as many, in the last four, and behind a trip's edges
-@pytest.mark.parametrize("need,slack", [([9000], 0), ([4097], 0), ([33000, 7], 0), ([1000] * 17, 0), ([600] * 20, 2),
-                                        ([150, 0, 90] * 30, 0), ([130] * 255 + [4099], 0)])
-def test_a_single_page_id_out_of_range_is_found(need, slack):
+@pytest.mark.parametrize("need,slack,shared", [([9000], 0, 0), ([4097], 0, 0), ([33000, 7], 0, 0), ([1000] * 17, 0, 0),
+                                               ([600] * 20, 2, 0), ([150, 0, 90] * 30, 0, 0), ([130] * 255 + [4099], 0, 0),
+                                               ([700] * 16, 0, 600), ([300] * 40 + [9, 0] * 5 + [2500] * 4, 0, 250)])
+def test_a_single_page_id_out_of_range_is_found(need, slack, shared):
     plan, table, cu_pages, num_pages = planned_tables(need, slack, valid_slack=True)
+    for s, n in enumerate(need):          # forks: found by their tables before the items are counted
+        if n >= shared:
+            table[cu_pages[s]:cu_pages[s] + shared] = table[:shared]
     plan(table)
     early = 4096                          # 4 entries x 4 x 256 threads, x 1 x 1024
     edges = [0, 1, 3, 4, 1023, 1024, early - 1, early, early + 1]
