@@ -211,7 +211,7 @@ inline size_t round64(size_t x) { return (x + 63) & ~size_t(63); }
 // says so in the plan's header; the host only rules the wide tiles out where the batch cannot
 // want them - fewer than 4096 new tokens per sequence on average, or fewer wide tiles than four
 // per compute unit of a 256-unit GPU - and otherwise launches both kernels, of which the one
-// the plan was not made for returns at once.  The workspace is laid out for the narrow tiles
+// the plan was not made for returns at once.  The workspace is laid out for the tiles of 128 rows
 // (more of them), which holds either plan.
 inline bool wide_tiles_allowed(int32_t batch, int32_t total_q, int G, int num_kv_heads) {
 #ifdef MC_WIDE_TILES
@@ -430,10 +430,10 @@ __device__ __forceinline__ void refuse_plan(PlanHeader* h) {
 // items few_rows_item walks with all four wavefronts, cut into pieces of `pieces` KV tiles.  tiles: the batch's tiles of
 // kBM rows, of kNarrowRows, of half as many; visits: the KV tiles they look at, as if all of a sequence's tiles lay
 // in its middle; longest: KV tiles of the longest range; many: of the longest of more than kFlatRows rows (0: none).
-// A workgroup alone on its compute unit takes 1.07 us for a KV tile and 128 rows, 0.54 us for 32 or for 16 (each
-// wavefront walks every fourth half tile).  So narrow tiles have less than half the rate, but need no tree of
-// chunks (2 to 3 us a level) and no launch behind, and fill the compute units where q tiles of 128 rows are few.  Two
-// workgroups a compute unit take 1.34 us: what the L2s hand out, 15 TB/s, is the bound then, so there are never
+// A workgroup alone on its compute unit takes 0.74 us for a KV tile and 128 rows, 0.56 us for 32 and 0.60 for 16 (each
+// wavefront walks every fourth half tile).  So narrow tiles have a third of the rate, but need no tree of
+// chunks (2 to 3 us a level) and no launch behind, and fill the compute units where q tiles of 128 rows are few.  On
+// all units that is 15 TB/s, what the L2s hand out, and two workgroups a unit take 1.08 and 1.04 us: there are never
 // more narrow items than compute units.
 // Narrow tiles are taken as follows (us a layer of four: append, attention, their share of the plan; 32 / 8 heads
 // unless named; tokens over keys cached).
@@ -442,15 +442,16 @@ __device__ __forceinline__ void refuse_plan(PlanHeader* h) {
 //     25.0 / 17.7, over 16000 30.4 / 33.4 / 24.9; 32 over 1024 21.5 / 18.2 / 15.4, over 4096 25.0 / 21.7 / 22.8, over
 //     8192 28.2 / 26.3 / 33; 64 over 2048 27.0 / 22.0 / 23.0.
 //   - 32 rows up to 24 KV tiles a compute unit.  64 over 4096 31.0 / 26.2; 128 over 4096 (32 tiles) 33.6 / 35.1.
-//   - Both only if whole tiles would not be done sooner.  Estimates, in the time of a narrow item's KV tile: narrow ones
-//     take the longest piece, and 9 (32 rows) or 5 more if pieces have to be combined.  Whole ones are cut into
-//     pieces of 8 KV tiles or more, two for a KV tile of many rows and 5 for a level of their tree (2 with up to 64
-//     rows); one for a KV tile of few rows, and 5 to combine those.  That counts where lengths differ: narrow
-//     pieces have one length for all ranges, and one workgroup a compute unit leaves few of them.  Whole / narrow: 15
-//     rows over 500..4096 beside 800 tokens, 8 / 2 heads, 26.0 / 44.9; 8 rows over 4000 beside 100 tokens over 900
-//     45.0 / 61.7; 4 rows over 300..1100 beside 200 tokens 18.7 / 20.1, over 600..1500 beside 100 18.9 / 17.3.  One
-//     range: 128 over 2300 28.6 / 27.3, over 2700 29.2 / 29.6; 256 over 1100 24.5 / 23.5, over 1250 24.8 / 24.7; 64 over
-//     3000, 64 / 8 heads, 28.5 / 29.8.
+//   - Both only if whole tiles would not be done sooner.  Estimates, in the time of a narrow item's KV tile, with the
+//     weights that part the figures below (and more like them, 64 / 8 to 8 / 1 heads, 5 to 1000 tokens): narrow ones
+//     take the longest piece, and 9 (32 rows) or 5 more if pieces have to be combined.  Whole ones are cut into pieces
+//     of 8 KV tiles or more, two for a KV tile of many rows and 5 for a level of their tree (2 with up to 64 rows); one
+//     for a KV tile of few rows, and 5 to combine those.  That counts where lengths differ: narrow pieces have one
+//     length for all ranges, and one workgroup a compute unit leaves few of them.  Whole / narrow: 15 rows over
+//     500..4096 beside 800 tokens, 8 / 2 heads, 26.0 / 44.9; 8 rows over 4000 beside 100 tokens over 900 45.0 / 61.7; 4
+//     rows over 300..1100 beside 200 tokens 18.7 / 20.1, over 600..1500 beside 100 18.9 / 17.3.  One range: 128 over
+//     2300 28.6 / 27.3, over 2700 29.2 / 29.6; 256 over 1100 24.5 / 23.5, over 1250 24.8 / 24.7; 64 over 3000, 64 / 8
+//     heads, 28.5 / 29.8.
 //   - Always up to a 64th of the slots of (q tile, kv head) pairs if the longest range has many rows: whole tiles have
 //     many chunks there, and their trees take longer.  Whole with trees / with a launch behind / narrow: 32 over 8192
 //     35.5 / 28.3 / 26.4, over 16000 45.9 / 34.7 / 35.9; 128 over 32000, 8 / 1 heads, 55.4 / 43.3 / 51.3.  (The launch
@@ -542,11 +543,11 @@ __global__ __launch_bounds__(NT) void plan_kernel(PlanArgs a) {
   __shared__ int s_common[kCuTilesInLds], s_gp[kCuTilesInLds], s_glead[kCuTilesInLds],
       s_gsize[kCuTilesInLds], s_gbase[kCuTilesInLds], s_glast[kCuTilesInLds];
   __shared__ int s_groups;
+  // of items written one a thread: tile and place in the list; of a tile: its first item and its merge record
+  __shared__ uint16_t s_owner[kSpreadItems], s_place[kSpreadItems];
+  __shared__ int s_first[NT], s_merge[NT];
   // remainder round: flags of the q tiles that are cut, the cost bucket at the boundary and how
   // many tiles of it are taken
-  __shared__ uint16_t s_owner[kSpreadItems], s_place[kSpreadItems];   // of items written one a thread: tile, place;
-                                               // and per tile
-  __shared__ int s_first[NT], s_merge[NT];     // its first item and its merge record
   __shared__ uint8_t s_tailflag[kTailTilesMax];
   __shared__ int s_tail_bucket, s_tail_take, s_tail_taken;
   const int t = threadIdx.x;
@@ -2619,7 +2620,8 @@ bool may_cut(const WorkspaceLayout& w, int hkv, int slots) {
 // Whether the planner may take q tiles of fewer rows (narrow_rows): at most a workgroup of kNarrowRows rows a compute
 // unit, few sequences, and more new tokens than those.  By the batch's sizes, because planner and attention kernel
 // are others then: with these paths, which they never take, the others took 0.2 to 0.4 us longer a launch (one
-// decode row, eight layers, 81.7 -> 84.1 us).
+// decode row, eight layers, 81.7 -> 84.1 us).  A batch that may have narrow tiles and keeps whole ones pays that (one
+// range of 256 tokens over 1500, 32 / 8 heads, 26.3 -> 26.8 us a layer).
 bool may_narrow(int32_t batch, int32_t total_q, int G, int hkv, int slots) {
   return batch <= kNarrowBatch && total_q > batch && (int64_t)total_q * G * hkv <= (int64_t)kNarrowRows * (slots / 2);
 }
