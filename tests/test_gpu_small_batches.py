@@ -175,13 +175,34 @@ def test_short_pieces_inside_a_shared_prefix(dtype, Hq, Hkv):
 @pytest.mark.parametrize("need,slack", [([1], 0), ([3], 2), ([5, 0, 70], 1), ([1100], 0), ([40] * 17, 3),
                                         ([9] * 40, 30), ([270] * 256, 1)])
 def test_page_ids_are_checked_where_a_token_needs_them(need, slack):
-    plan, table, cu_pages, num_pages = planned_tables(need, slack, valid_slack=False)
+    num_pages, B = 50, len(need)
+    rng = mi.rng_for(995 + B)
+    cu_pages = np.concatenate([[0], np.cumsum([n + slack for n in need])]).astype(np.int32)
+    table = np.where(np.arange(cu_pages[-1]) % 2, -1, num_pages).astype(np.int32)      # what no token needs
+    for s, n in enumerate(need):
+        table[cu_pages[s]:cu_pages[s] + n] = rng.integers(0, num_pages, n)
+    new = [int(n > 0) for n in need]
+    cu_q = dev(np.concatenate([[0], np.cumsum(new)]).astype(np.int32))
+    begin = dev(np.array([16 * n - 1 if n else 0 for n in need], np.int32))
+    pool = torch.zeros(num_pages * 2 * 8 * 16 * 128, dtype=torch.int16, device=DEV)
+    desc = mc.pool_desc(pool, 1, num_pages, 8, mc.MC_BF16)
+    size = mc.mc_attn_workspace_size(B, sum(new), 32, 8)
+    ws = torch.empty(size, dtype=torch.uint8, device=DEV)
+
+    def plan(t):
+        mc.mc_attn_plan(desc, 32, B, sum(new), cu_q, begin, dev(t), dev(cu_pages), ws, size)
+        mc.mc_attn_plan_check(ws)
+
     plan(table)
-    for s, e in [(0, 0), (0, need[0] - 1), (len(need) // 2, need[len(need) // 2] // 2), (len(need) - 1, need[-1] - 1)]:
+    for s, e in [(0, 0), (0, need[0] - 1), (B // 2, need[B // 2] // 2), (B - 1, need[-1] - 1)]:
         if need[s] == 0:
             continue
         for bad in (-1, num_pages):
-            refused(plan, table, cu_pages[s] + e, bad)
+            t = table.copy()
+            t[cu_pages[s] + e] = bad
+            with pytest.raises(mc.McError) as err:
+                plan(t)
+            assert err.value.status == mc.MC_ERR_RANGE, (s, e, bad)
 
 
 # every id is in range but one, so the look at the table as it lies has to find it: entries that are requested early (16 of
@@ -190,7 +211,7 @@ def test_page_ids_are_checked_where_a_token_needs_them(need, slack):
                                                ([600] * 20, 2, 0), ([150, 0, 90] * 30, 0, 0), ([130] * 255 + [4099], 0, 0),
                                                ([700] * 16, 0, 600), ([300] * 40 + [9, 0] * 5 + [2500] * 4, 0, 250)])
 def test_a_single_page_id_out_of_range_is_found(need, slack, shared):
-    plan, table, cu_pages, num_pages = planned_tables(need, slack, valid_slack=True)
+    plan, table, cu_pages, num_pages = planned_tables(need, slack)
     for s, n in enumerate(need):          # forks: found by their tables before the items are counted
         if n >= shared:
             table[cu_pages[s]:cu_pages[s] + shared] = table[:shared]
@@ -214,17 +235,13 @@ def refused(plan, table, at, bad):
     assert err.value.status == mc.MC_ERR_RANGE, (at, bad)
 
 
-def planned_tables(need, slack, valid_slack):
+def planned_tables(need, slack):
     """plan(table) for one decode row over all entries a sequence needs, such a table with slack more entries a
-    sequence, its cu_pages, and the pool's pages."""
+    sequence, all in range, its cu_pages, and the pool's pages."""
     num_pages, B = 50, len(need)
-    rng = mi.rng_for(995 + B)
+    rng = mi.rng_for(997 + B)
     cu_pages = np.concatenate([[0], np.cumsum([n + slack for n in need])]).astype(np.int32)
-    table = np.where(np.arange(cu_pages[-1]) % 2, -1, num_pages).astype(np.int32)      # what no token needs
-    if valid_slack:
-        table[:] = rng.integers(0, num_pages, len(table))
-    for s, n in enumerate(need):
-        table[cu_pages[s]:cu_pages[s] + n] = rng.integers(0, num_pages, n)
+    table = rng.integers(0, num_pages, cu_pages[-1]).astype(np.int32)
     new = [int(n > 0) for n in need]
     cu_q = dev(np.concatenate([[0], np.cumsum(new)]).astype(np.int32))
     begin = dev(np.array([16 * n - 1 if n else 0 for n in need], np.int32))
